@@ -126,7 +126,10 @@ typedef struct {
                                library's schedule, -1 = off, k > 0 = every k
                                K-steps of 4 dimensions. FP64 MFMA: one check
                                after half the K-steps for d <= 16, every k
-                               (default 4) K-steps beyond; FP64 VALU: every
+                               (default 4) K-steps beyond, or, where the count
+                               keeps a hit list (5 <= d <= 64 with enough
+                               candidates), the bounding boxes of 16-point
+                               tiles instead (any value but -1); FP64 VALU: every
                                4k (default 4) dimensions for d > 8 (the d <= 8
                                forms keep the query rows in registers and run
                                without checks) */
@@ -151,9 +154,9 @@ typedef struct {
                                column), with 1 for the point itself: about
                                half the distance tiles. For count-only use
                                (selfjoin_count, selfjoin_core_points): the
-                               count then records no in-masks, so a following
-                               selfjoin_pairs / selfjoin_knn evaluates its
-                               tiles again (full stencil). The batched form
+                               count then records no in-masks and no hit list,
+                               so a following selfjoin_pairs / selfjoin_knn
+                               evaluates its tiles again. The batched form
                                (selfjoin_batch_build) takes it for every
                                problem: no in-mask buffer, and
                                selfjoin_batch_pairs re-runs the tiles. The
@@ -186,7 +189,8 @@ typedef struct {
                             recorded in-masks expanded, or the tiles re-run
                             in emission form); 0 for count */
     int64_t tiles_pruned; /* 16 x 16 tiles left before their last K-step
-                            because every value's partial distance already
+                            because every value's partial distance (or the
+                            distance of the bounding boxes) already
                             exceeded the threshold (the short-circuit of
                             Section III-B, see sj_opts.short_circuit): FP64
                             MFMA against eps^2 + Delta (prefix norms at the

@@ -7,7 +7,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libselfjoin.so")
-SOURCES = ["sj_api.hip", "sj_build.hip", "sj_refine.hip", "sj_lowp.hip", "sj_batch.hip", "sj_probe.hip"]
+SOURCES = ["sj_api.hip", "sj_build.hip", "sj_refine.hip", "sj_lowp.hip", "sj_hits.hip", "sj_batch.hip", "sj_probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -27,14 +27,30 @@ FLAGS = [
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source into libselfjoin.so; always recompiles."""
-    tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [HIPCC] + FLAGS + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", tmp]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
-    if verbose:
-        print(res.stderr)
+    """Compile every source (one hipcc each, side by side) and link them into
+    libselfjoin.so; always recompiles."""
+    tag = ".tmp%d" % os.getpid()
+    tmp = LIB + tag
+    objs = [os.path.join(CSRC, s + tag + ".o") for s in SOURCES]
+    compile_flags = [f for f in FLAGS if f != "-shared"]
+    try:
+        runs = [subprocess.Popen([HIPCC] + compile_flags + ["-c", os.path.join(CSRC, s), "-o", o],
+                                 stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+                for s, o in zip(SOURCES, objs)]
+        outs = [r.communicate()[0] for r in runs]
+        for s, r, text in zip(SOURCES, runs, outs):
+            if r.returncode != 0:
+                raise RuntimeError("hipcc failed on " + s + ":\n" + text)
+        link = [HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared"] + objs + ["-o", tmp]
+        res = subprocess.run(link, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc link failed:\n" + res.stdout + res.stderr)
+        if verbose:
+            print("".join(outs) + res.stderr)
+    finally:
+        for o in objs:
+            if os.path.exists(o):
+                os.remove(o)
     os.replace(tmp, LIB)
     return LIB
 

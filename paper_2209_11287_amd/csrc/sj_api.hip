@@ -22,8 +22,15 @@ thread_local std::string g_err;
 __global__ void k_set_i32(int32_t *p, int32_t v) { *p = v; }
 
 // The count's total (the last entry of the offsets' exclusive scan) beside
-// its counters, so that one copy brings both to the host.
-__global__ void k_total_to_ctr(const int64_t *total, DevCounters *ctr) { ctr->spare[1] = (unsigned long long)*total; }
+// its counters, so that one copy brings both to the host, and with a hit list
+// the entries reserved in its fullest region.
+__global__ void k_total_to_ctr(const int64_t *total, const unsigned long long *cursor, DevCounters *ctr) {
+    ctr->spare[1] = (unsigned long long)*total;
+    if (!cursor) return;
+    unsigned long long m = 0;
+    for (int r = 0; r < kHitRegions; ++r) m = max(m, cursor[r * kHitCursorStride]);
+    ctr->spare[0] = m;
+}
 
 // Core flags in the input order and their number (one counter atomic per
 // block).
@@ -297,19 +304,23 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     const bool sym = fp64 && g.sym != 0;
     g.masks_valid = false;
     g.lp_masks_valid = false;
-    ro.record_lp = is_lowp(path) && !g.lean;
-    if (fp64 && !sym && !g.lean && !g.masks && g.tiles > 0 && g.tiles * 32 <= kMaskBudget)
+    g.hits_valid = false;
+    ro.hits = hits_usable(g, path) && (!g.lean || g.lean_hits);
+    ro.record_hits = ro.hits && !sym && !g.lean;
+    ro.record_lp = is_lowp(path) && !g.lean && !ro.hits;
+    if (fp64 && !ro.hits && !sym && !g.lean && !g.masks && g.tiles > 0 && g.tiles * 32 <= kMaskBudget)
         g.masks = dev_alloc_n<unsigned long long>((size_t)g.tiles * 4, s);
-    ro.masks = fp64 && !sym ? g.masks : nullptr;
+    ro.masks = fp64 && !sym && !ro.hits ? g.masks : nullptr;
     ro.sym = sym;
-    if (sym && g.n > 0) fill_zero(g.cnt, (size_t)g.n * sizeof(int32_t), s);
-    hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(1), 0, s, g.cnt + g.n, 0);
+    if (sym && !ro.hits && g.n > 0) fill_zero(g.cnt, (size_t)g.n * sizeof(int32_t), s);
+    if (!ro.hits) hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(1), 0, s, g.cnt + g.n, 0);
     SJ_HIP(hipGetLastError());
     if (g.n > 0) refine_count(g, path, g.cnt, ro, s);
     else fill_zero(g.ctr, sizeof(DevCounters), s);
     exclusive_scan_i32_to_i64(g.cnt, g.off, g.n + 1, s);
     // the total and the counters: one copy, one sync
-    hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, g.ctr);
+    const bool listed = ro.record_hits && g.hits;
+    hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, listed ? g.hit_cursor : nullptr, g.ctr);
     SJ_HIP(hipGetLastError());
     DevCounters hctr{};
     SJ_HIP(hipMemcpyAsync(&hctr, g.ctr, sizeof hctr, hipMemcpyDeviceToHost, s));
@@ -318,6 +329,11 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     g.total = total;
     g.masks_valid = ro.masks != nullptr;
     g.lp_masks_valid = ro.record_lp && g.lp_masks != nullptr;
+    if (listed) {
+        g.hit_most = hctr.spare[0];
+        g.hits_valid = g.hit_most <= g.hit_cap;
+        g.hits_lowp = is_lowp(path);
+    }
     g.count_path = path;
     cr.ran = true;
     cr.hc = read_counters(hctr);
@@ -758,6 +774,7 @@ sj_status selfjoin_count_noalloc(const double *points, int64_t n, int32_t d, dou
     AllocScope scope(&arena);
     Grid g;
     g.lean = true;
+    g.lean_hits = need + hits_lean_bytes(n, d) <= kScratchBytes;
     build_grid(g, points, n, d, eps, 0, s);
     const sj_path run = path_for(g, path);
     CountRun cr;

@@ -52,8 +52,7 @@ __global__ void k_fill_u8(unsigned char *p, size_t bytes, unsigned char v) {
     for (; i < bytes; i += stride) p[i] = v;
 }
 
-// Zeroes up to eight segments (4-byte aligned, whole 4-byte words) in one
-// launch: the build's small pads and counters.
+// Segments of fill_zero_many.
 struct FillList {
     uint32_t *p[8];
     unsigned long long words[8];
@@ -64,22 +63,6 @@ __global__ void k_fill_many(FillList L) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (int k = 0; k < L.n; ++k)
         for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < L.words[k]; i += stride) L.p[k][i] = 0u;
-}
-
-static void fill_zero_many(std::initializer_list<std::pair<void *, size_t>> segs, hipStream_t s) {
-    FillList L{};
-    size_t most = 0;
-    for (const auto &sg : segs) {
-        if (!sg.first || !sg.second) continue;
-        L.p[L.n] = static_cast<uint32_t *>(sg.first);
-        L.words[L.n] = sg.second / 4;
-        most = std::max(most, sg.second / 4);
-        ++L.n;
-    }
-    if (!L.n) return;
-    const unsigned blocks = (unsigned)std::min<size_t>((most + kThreads - 1) / kThreads, 1024);
-    hipLaunchKernelGGL(k_fill_many, dim3(blocks), dim3(kThreads), 0, s, L);
-    SJ_HIP(hipGetLastError());
 }
 
 // What the host reads back after the grid build's device work: the table
@@ -1255,6 +1238,22 @@ void fill_zero(void *p, size_t bytes, hipStream_t s) {
     SJ_HIP(hipGetLastError());
 }
 
+void fill_zero_many(std::initializer_list<std::pair<void *, size_t>> segs, hipStream_t s) {
+    FillList L{};
+    size_t most = 0;
+    for (const auto &sg : segs) {
+        if (!sg.first || !sg.second) continue;
+        L.p[L.n] = static_cast<uint32_t *>(sg.first);
+        L.words[L.n] = sg.second / 4;
+        most = std::max(most, sg.second / 4);
+        ++L.n;
+    }
+    if (!L.n) return;
+    const unsigned blocks = (unsigned)std::min<size_t>((most + kThreads - 1) / kThreads, 1024);
+    hipLaunchKernelGGL(k_fill_many, dim3(blocks), dim3(kThreads), 0, s, L);
+    SJ_HIP(hipGetLastError());
+}
+
 // Stable sort of (key, value) pairs by the low `bits` key bits. On return
 // *key_a / *val_a point at the sorted arrays (buffers may be swapped).
 void radix_sort_pairs(unsigned long long **key_a, int32_t **val_a, unsigned long long *key_b, int32_t *val_b,
@@ -1318,6 +1317,9 @@ void free_grid(Grid &g, hipStream_t s) {
     g.lp_masks = nullptr;
     g.lp_groups = -1;
     g.lp_masks_valid = false;
+    hits_free_list(g, s);
+    if (g.hit_index) dev_free(g.hit_index, s);
+    g.hit_index = nullptr;
 }
 
 // Host-side reading of the grid geometry; identical arithmetic to the

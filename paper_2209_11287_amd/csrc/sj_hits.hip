@@ -1,0 +1,1065 @@
+// Hit-list count for d = 5 .. 64 (FP64, FP32 and split-BF16 MFMA tiles).
+//
+// At higher d a point has few neighbours among many candidates (the grid
+// indexes at most four dimensions), so nearly every 16 x 16 tile is empty and
+// the time goes into the tiles themselves. This count evaluates about half of
+// them, drops those that cannot hold a pair before their rows are read, and
+// records the few pairs it finds instead of a mask bit per candidate:
+//
+//  - Half of the tiles. Each unordered pair of block items (up to 64
+//    consecutive rows of one grid line) meets in one place only: block a takes
+//    block b > a when a + b is even, b < a when a + b is odd (so every block
+//    takes about half of its neighbours, wherever it lies in the order), and
+//    of its own rows the pairs (q, c > q). A pair within eps is a candidate of
+//    both of its points, so either side may evaluate it.
+//  - Box filter. Every work item (up to 16 consecutive rows) has a bounding
+//    box over all d dimensions; an item whose box is more than eps from the
+//    block's box has no pair with it. In clustered data the grid's candidates
+//    are mostly other clusters: on a 1M-point mixture of 100 clusters in 64
+//    dimensions the lists hold 77k candidates a point, its cluster 10k.
+//  - Hit list. A pair within eps is appended to a list (i, c) of sorted
+//    indices and counted for both points; the pairs call sorts the list by
+//    point. The lists of a 1M-point set with 50 neighbours a point take 0.2
+//    GB, where a bit per candidate takes 10 GB.
+//
+// Measured, count + pairs of one join (MI355X): Gaussian mixture of 1M points
+// and 50 neighbours, d = 16: count kernel 9.3 -> 4.2 ms, pairs 0.95 -> 1.6 ms;
+// d = 64: count 144 -> 16.2 ms (10.7 ms of it FP64 MFMA). Index-free count of
+// 65536 points, d = 16: 4.29 -> 1.46 ms (0.88 ms of MFMA). Uniform, 2M points,
+// d = 5: 8.7 -> 3.9 ms. Of the tile loop's time about 85 % is MFMA; the rest of
+// the kernel is the walk (box tests between barriers) and the hits.
+//
+// The box test is safe in FP32: boxes hold the centred coordinates times a
+// power of two that puts eps in [1, 2), rounded outward and widened by one more
+// step (which covers the rounding of the centring), a gap is one subtraction,
+// and the threshold carries a relative margin of 1e-4 against at most
+// 3 (d + 2) 2^-24 of the sum.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cfloat>
+#include <cmath>
+#include <cstring>
+
+#include "sj_internal.h"
+
+namespace sj {
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
+constexpr int kRound = kThreads;    // candidate items tested per round
+constexpr int kSurv = 2 * kRound;   // surviving items held for the tile loop
+constexpr int kHitChunk = 256;      // list entries a wave reserves at a time
+constexpr int kWaveBin = 1024;      // neighbours of a point that one wave orders in LDS
+constexpr int kBigBits = 1 << 18;   // list positions per bitmap window of the larger ones
+
+typedef double double4_t __attribute__((ext_vector_type(4)));
+
+struct HitGrid {
+    const double *xs, *xa, *nrm;
+    const int32_t *perm;
+    const Item *items;
+    const Range *ranges;
+    const int32_t *blocks;       // first item of each block item, plus item_base
+    const int32_t *item_block;   // block of each item
+    const int2 *span;            // per block and range: candidate items [x, y)
+    const float *blo, *bhi;      // boxes: [dimension][item], dimensions padded to a multiple of 4
+    int64_t bstride;             // items per dimension of blo / bhi
+    int32_t d, dp, da, nranges, nitems, nblocks, item_base;
+    int32_t boxes;               // 0: no box test (short_circuit = -1)
+    float thr;                   // box test: squared gap sum that drops an item (scaled units)
+    double eps2;
+};
+
+struct HitOut {
+    int32_t *cnt;                // per-point counts (sorted order), zeroed before the launch
+    DevCounters *ctr;
+    int2 *hits;                  // kHitRegions regions of `cap` entries, or null: count only
+    unsigned long long *cursor;  // entries reserved in each region, kHitCursorStride apart
+    unsigned long long cap;
+};
+
+__device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The oracle's chain: ascending dimensions from +0.0, fl(a - b) then fma.
+__device__ __forceinline__ double exact_d2(const double *__restrict__ a, const double *__restrict__ b, int d) {
+    double acc = 0.0;
+    for (int t = 0; t < d; ++t) {
+        const double delta = __dsub_rn(a[t], b[t]);
+        acc = __fma_rn(delta, delta, acc);
+    }
+    return acc;
+}
+
+// Chunks of 16 consecutive blocks (which share candidates) dealt round-robin
+// to the 8 XCDs; hardware block b runs on XCD b % 8.
+__device__ __forceinline__ int xcd_block(int b, int nb) {
+    constexpr int kChunk = 16;
+    const int full = nb / (8 * kChunk) * (8 * kChunk);
+    if (b >= full) return b;
+    const int x = b & 7, k = b >> 3;
+    return ((k / kChunk) * 8 + x) * kChunk + (k % kChunk);
+}
+
+__device__ __forceinline__ unsigned lane_rank(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
+__device__ __forceinline__ int64_t readlane_i64(int64_t v, int lane) {
+    const int lo = __builtin_amdgcn_readlane((int)(v & 0xffffffff), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// ------------------------------------------------------------------ index --
+__device__ __forceinline__ float below(float v) { return nextafterf(v, -INFINITY); }
+__device__ __forceinline__ float above(float v) { return nextafterf(v, INFINITY); }
+
+// First item in [a, b) whose end (END) or begin lies past x.
+template <bool END>
+__device__ __forceinline__ int first_item(const Item *__restrict__ items, int a, int b, int x) {
+    while (a < b) {
+        const int m = a + (b - a) / 2;
+        if ((END ? items[m].qend : items[m].qbegin + 1) > x) b = m;
+        else a = m + 1;
+    }
+    return a;
+}
+
+// The index of the count, in one launch. Blocks [0, nbox): boxes of 16 work
+// items each, one wave per item at a time, lane t the column t of its rows
+// (whole rows read), then whole runs of 16 items stored per dimension. The
+// blocks after them: the candidate items of each block item and range (the
+// items that hold a row of the range; an item lies in one line, so no item
+// appears twice), and the block of each item.
+__global__ __launch_bounds__(kThreads) void k_hit_index(HitGrid G, double sc, unsigned nbox, float *__restrict__ blo,
+                                                        float *__restrict__ bhi, int2 *__restrict__ span,
+                                                        int32_t *__restrict__ item_block) {
+    __shared__ float lo[kHitMaxD][17], hi[kHitMaxD][17];
+    if (blockIdx.x >= nbox) {  // whole block
+        const int64_t t = (int64_t)(blockIdx.x - nbox) * kThreads + threadIdx.x;
+        if (t >= (int64_t)G.nblocks * G.nranges) return;
+        const int b = (int)(t / G.nranges), o = (int)(t - (int64_t)b * G.nranges);
+        const int ib = G.blocks[b] - G.item_base, ie = G.blocks[b + 1] - G.item_base;
+        if (o == 0)
+            for (int i = ib; i < ie; ++i) item_block[i] = b;
+        const Range r = G.ranges[(int64_t)ib * G.nranges + o];
+        int2 s = make_int2(0, 0);
+        if (r.end > r.begin) {
+            s.x = first_item<true>(G.items, 0, G.nitems, r.begin);
+            s.y = first_item<false>(G.items, s.x, G.nitems, r.end);
+        }
+        span[t] = s;
+        return;
+    }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int i0 = blockIdx.x * 16;
+    for (int u = wv; u < 16; u += kWaves) {
+        float l = -FLT_MAX, h = INFINITY;  // a padded dimension bounds nothing
+        if (i0 + u < G.nitems && lane < G.d) {
+            const Item I = G.items[i0 + u];
+            double mn = INFINITY, mx = -INFINITY;
+#pragma unroll 4
+            for (int r = I.qbegin; r < I.qend; ++r) {
+                const double v = G.xa[(int64_t)r * G.da + lane];
+                mn = fmin(mn, v);
+                mx = fmax(mx, v);
+            }
+            l = below(__double2float_rd(mn * sc));
+            h = above(__double2float_ru(mx * sc));
+        }
+        lo[lane][u] = l;
+        hi[lane][u] = h;
+    }
+    __syncthreads();
+    const int dims = (G.d + 3) & ~3;
+    for (int e = threadIdx.x; e < 16 * dims; e += kThreads) {
+        const int t = e >> 4, u = e & 15;
+        if (i0 + u < G.nitems) {
+            blo[(int64_t)t * G.bstride + i0 + u] = lo[t][u];
+            bhi[(int64_t)t * G.bstride + i0 + u] = hi[t][u];
+        }
+    }
+}
+
+// ------------------------------------------------------------- tile parts --
+// What the tile loop of a block shares, whatever the tile's precision.
+struct BlockShared {
+    int2 surv[kSurv];     // surviving items: first row, rows | own block << 8
+    int pre[28], first[28];
+    int wcount[kWaves];
+    int cntq[64];         // pairs of the block's rows as query
+    float alo[kHitMaxD], ahi[kHitMaxD];
+};
+
+// Walks a block's candidate items, kRound at a time, and keeps those of the
+// block's half whose boxes are near enough. State is block-uniform except
+// `dropped` (per thread).
+struct Walk {
+    int total, pos, step;
+    unsigned dropped;
+};
+
+__device__ __forceinline__ Walk walk_init(const HitGrid &G, BlockShared &S, int bi, int ib, int ie, int seg, int nseg) {
+    const int tid = threadIdx.x;
+    Walk W;
+    if (tid < 64) {
+        int2 s = make_int2(0, 0);
+        if (tid < G.nranges) s = G.span[(int64_t)bi * G.nranges + tid];
+        const int len = s.y - s.x;
+        int incl = len;
+        for (int o = 1; o < 32; o <<= 1) {
+            const int y = __shfl_up(incl, o);
+            if (tid >= o) incl += y;
+        }
+        if (tid < 28) {
+            S.pre[tid] = tid < G.nranges ? incl - len : INT_MAX;
+            S.first[tid] = s.x - (incl - len);
+        }
+        if (tid == 31) S.wcount[0] = incl;  // lanes past the ranges add nothing
+    }
+    if (tid < 64) S.cntq[tid] = 0;
+    const int dims = (G.d + 3) & ~3;
+    if (tid < dims) {
+        float l = INFINITY, h = -INFINITY;
+        for (int i = ib; i < ie; ++i) {
+            l = fminf(l, G.blo[(int64_t)tid * G.bstride + i]);
+            h = fmaxf(h, G.bhi[(int64_t)tid * G.bstride + i]);
+        }
+        S.alo[tid] = l;
+        S.ahi[tid] = h;
+    }
+    __syncthreads();
+    W.total = S.wcount[0];
+    W.pos = seg * kRound;
+    W.step = nseg * kRound;
+    W.dropped = 0;
+    __syncthreads();
+    return W;
+}
+
+// Refills the survivor list (at least kRound entries unless the walk ends);
+// returns their number. Every thread of the block calls it.
+__device__ __forceinline__ int walk_fill(const HitGrid &G, BlockShared &S, Walk &W, int bi, int nt) {
+    const int tid = threadIdx.x, wv = tid >> 6;
+    int have = 0;
+    while (W.pos < W.total && have < kRound) {
+        const int p = W.pos + tid;
+        bool ok = false;
+        int2 ent = make_int2(0, 0);
+        if (p < W.total) {
+            int o = 0;
+#pragma unroll
+            for (int st = 16; st > 0; st >>= 1)
+                if (o + st < 28 && S.pre[o + st] <= p) o += st;
+            const int it = S.first[o] + p;
+            const int b = G.item_block[it];
+            ok = b == bi || ((bi < b) == (((bi + b) & 1) == 0));
+            if (ok) {
+                const Item I = G.items[it];
+                ent = make_int2(I.qbegin, (I.qend - I.qbegin) | (b == bi ? 256 : 0));
+                if (G.boxes && b != bi) {
+                    float s = 0.f;
+                    for (int t = 0; t < G.d; t += 4) {
+                        float l[4], h[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            l[u] = G.blo[(int64_t)(t + u) * G.bstride + it];
+                            h[u] = G.bhi[(int64_t)(t + u) * G.bstride + it];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const float g = fmaxf(fmaxf(l[u] - S.ahi[t + u], S.alo[t + u] - h[u]), 0.f);
+                            s = fmaf(g, g, s);
+                        }
+                        if (s > G.thr) {
+                            ok = false;
+                            W.dropped += nt;
+                            break;
+                        }
+                    }
+                }
+            }
+        }
+        const unsigned long long m = __ballot(ok);
+        if ((tid & 63) == 0) S.wcount[wv] = __popcll(m);
+        __syncthreads();
+        int base = have;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wv) base += S.wcount[w];
+            have += S.wcount[w];
+        }
+        if (ok) S.surv[base + lane_rank(m)] = ent;
+        __syncthreads();
+        W.pos += W.step;
+    }
+    return have;
+}
+
+// A wave's run of reserved list entries.
+struct HitRun {
+    unsigned long long at;  // next entry (index into the region)
+    int left;               // entries left
+};
+
+__device__ __forceinline__ void hit_pad(const HitOut &R, HitRun &H, int region, int lane) {
+    for (int e = lane; e < H.left; e += 64)
+        if (H.at + e < R.cap) R.hits[region * R.cap + H.at + e] = make_int2(-1, -1);
+}
+
+// Appends (q, c) for the lanes of m. Past the region's capacity the entries
+// are only counted by the cursor (the list is then not valid).
+__device__ __forceinline__ void hit_push(const HitOut &R, HitRun &H, int region, unsigned long long m, bool mine,
+                                         int q, int c, int lane) {
+    const int k = __popcll(m);
+    if (k > H.left) {
+        hit_pad(R, H, region, lane);
+        unsigned long long a = 0;
+        if (lane == 0) a = atomicAdd(R.cursor + region * kHitCursorStride, (unsigned long long)kHitChunk);
+        H.at = ((unsigned long long)(unsigned)uniform_i32((int)(a >> 32)) << 32) | (unsigned)uniform_i32((int)a);
+        H.left = kHitChunk;
+    }
+    if (mine) {
+        const unsigned long long e = H.at + lane_rank(m);
+        if (e < R.cap) R.hits[region * R.cap + e] = make_int2(q, c);
+    }
+    H.at += k;
+    H.left -= k;
+}
+
+// ------------------------------------------------------------------- FP64 --
+// One wave runs the block's (up to) four 16-row query tiles against one
+// candidate item at a time: its B operand is loaded straight into registers
+// (one item ahead), the A operand (-2 q, zero past d) of all four tiles sits in
+// LDS, so a candidate row is read once per 64 queries, nothing in the loop
+// waits on another wave, and the four tiles' chains are independent. Bound by
+// the FP64 matrix unit: KS MFMAs of 64 cycles per tile against about 30 vector
+// instructions. K order: two K-steps share one 16-byte load of the row (lane g
+// holds dimensions 8p + 2g and 8p + 2g + 1 of K-step pair p), a last single
+// K-step dimension 4 (KS - 1) + g.
+// The accumulator starts at |q|^2 (+inf for absent rows), so D = |q|^2 - 2 q.c
+// and a value is in iff D <= eps^2 - |c|^2; the band of +-Delta around it goes
+// to the exact chain (the sum of the same terms as in k_m64, in another order,
+// which its Delta covers).
+template <int KS>
+struct HitTile {
+    double b[KS];
+    double nc;
+    int c, n;  // the lane's column: its row; rows of the item | own << 8
+};
+
+template <int KS>
+__device__ __forceinline__ void hit_load(HitTile<KS> &T, int2 e, const HitGrid &G, int g, int j) {
+    const int n = e.y & 255;
+    T.n = e.y;
+    T.c = e.x + min(j, n - 1);
+    const double *__restrict__ row = G.xa + (int64_t)T.c * G.da;
+#pragma unroll
+    for (int p = 0; p < KS / 2; ++p) {
+        const double2 v = *reinterpret_cast<const double2 *>(row + 8 * p + 2 * g);
+        T.b[2 * p] = v.x;
+        T.b[2 * p + 1] = v.y;
+    }
+    if (KS & 1) T.b[KS - 1] = row[4 * (KS - 1) + g];
+    T.nc = G.nrm[T.c];
+}
+
+// The high word of a double as a float: the same order (sign, exponent,
+// leading mantissa bits), so x <= y implies high(x) <= high(y); infinities
+// become NaN, below nothing. FP64 compares would contend with the MFMAs for
+// the FP64 pipe; this test only has to let every candidate value through.
+__device__ __forceinline__ float high(double v) { return __int_as_float(__double2hiint(v)); }
+__device__ __forceinline__ float low4(const double4_t &v) {
+    return fminf(fminf(high(v[0]), high(v[1])), fminf(high(v[2]), high(v[3])));
+}
+
+template <int KS>
+constexpr int hit_k(int s, int g) {
+    return (s == KS - 1 && (KS & 1)) ? 4 * s + g : 8 * (s >> 1) + 2 * g + (s & 1);
+}
+
+template <int KS>
+__global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64(HitGrid G, HitOut R, double delta, int nseg) {
+    __shared__ double A[4 * KS * 64];
+    __shared__ double4_t qn[4 * 4];  // [tile][row group g]: |q|^2 of rows g + 4r
+    __shared__ BlockShared S;
+    const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i32(tid >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    const int bi = lb / nseg, seg = lb - bi * nseg;
+    const int ib = uniform_i32(G.blocks[bi] - G.item_base), ie = uniform_i32(G.blocks[bi + 1] - G.item_base);
+    const int nt = ie - ib;
+    // the block's rows are consecutive: only the last item can be short
+    const int q0 = uniform_i32(G.items[ib].qbegin);
+    const int nrows = uniform_i32(G.items[ie - 1].qend) - q0;
+    for (int e = tid; e < nt * KS * 64; e += kThreads) {
+        const int ln = e & 63, s = (e >> 6) % KS, t = (e >> 6) / KS;
+        const int row = 16 * t + (ln & 15), k = hit_k<KS>(s, ln >> 4);
+        A[e] = (row < nrows && k < G.d) ? -2.0 * G.xa[(int64_t)(q0 + row) * G.da + k] : 0.0;
+    }
+    if (tid < 64) {
+        const int t = tid >> 4, gg = (tid >> 2) & 3, r = tid & 3, row = 16 * t + gg + 4 * r;
+        reinterpret_cast<double *>(qn)[tid] = row < nrows ? G.nrm[q0 + row] : INFINITY;
+    }
+    Walk W = walk_init(G, S, bi, ib, ie, seg, nseg);
+    HitRun H{0, 0};
+    const int region = (blockIdx.x ^ (blockIdx.x >> 4)) & (kHitRegions - 1);
+    unsigned long long band = 0, band_in = 0;  // wave-uniform
+    const double clo = G.eps2 - delta, chi = G.eps2 + delta;
+    // the pairs of tile t (values acc; some value may be at or below its threshold)
+    auto record = [&](const HitTile<KS> &T, const double4_t &acc, int t, bool valid, bool own) {
+        const double hi = valid ? chi - T.nc : -INFINITY, lo = valid ? clo - T.nc : -INFINITY;
+        int mine = 0;  // pairs of the lane's candidate in this tile
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            unsigned long long w = __ballot(acc[r] <= hi);
+            const int q = q0 + 16 * t + g + 4 * r;
+            if (own) w &= __ballot(T.c > q);  // own block: each pair once
+            if (w == 0ull) continue;
+            const unsigned long long bm = w & ~__ballot(acc[r] <= lo);
+            if (__builtin_expect(bm != 0ull, 0)) {  // rare: the exact chain on the original coordinates
+                bool ok = false;
+                if (__builtin_amdgcn_inverse_ballot_w64(bm))
+                    ok = exact_d2(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)T.c * G.dp, G.d) <= G.eps2;
+                const unsigned long long okm = __ballot(ok);
+                band += (unsigned long long)__popcll(bm);
+                band_in += (unsigned long long)__popcll(okm);
+                w = (w & ~bm) | okm;
+                if (w == 0ull) continue;
+            }
+            const bool hit = __builtin_amdgcn_inverse_ballot_w64(w);
+            if (hit) {
+                ++mine;
+                atomicAdd(&S.cntq[16 * t + g + 4 * r], 1);
+            }
+            if (R.hits) hit_push(R, H, region, w, hit, q, T.c, lane);
+        }
+        if (mine) atomicAdd(R.cnt + T.c, mine);
+    };
+    auto run = [&](const HitTile<KS> &T) {
+        const int tn = uniform_i32(T.n);
+        const bool own = tn > 255, valid = j < (tn & 255);
+        const float thr = high(valid ? chi - T.nc : -INFINITY);
+        const double *a = A + lane;
+        for (int t = 0; t < nt; ++t) {
+            double4_t acc = qn[4 * t + g];
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(t * KS + s) * 64], T.b[s], acc, 0, 0, 0);
+            if (__ballot(low4(acc) <= thr)) record(T, acc, t, valid, own);
+        }
+    };
+    for (;;) {
+        const int ns = walk_fill(G, S, W, bi, nt);
+        if (ns == 0) break;
+        HitTile<KS> T0, T1;
+        if (wv < ns) hit_load<KS>(T0, S.surv[wv], G, g, j);
+        for (int e = wv; e < ns; e += 2 * kWaves) {
+            // past the end the loads repeat the last item (the same count on every path)
+            hit_load<KS>(T1, S.surv[min(e + kWaves, ns - 1)], G, g, j);
+            run(T0);
+            if (e + kWaves >= ns) break;
+            hit_load<KS>(T0, S.surv[min(e + 2 * kWaves, ns - 1)], G, g, j);
+            run(T1);
+        }
+        __syncthreads();
+    }
+    if (R.hits) hit_pad(R, H, region, lane);
+    __syncthreads();
+    // the rows' counts as query, and the point itself (once per row)
+    if (tid < nrows) {
+        const int v = S.cntq[tid] + (seg == 0 ? 1 : 0);
+        if (v) atomicAdd(R.cnt + q0 + tid, v);
+    }
+    unsigned long long dr = W.dropped;
+    for (int sh = 32; sh > 0; sh >>= 1) dr += __shfl_xor(dr, sh);
+    if (lane == 0) {
+        if (dr) atomicAdd(&R.ctr->pruned, dr);
+        if (band) {
+            atomicAdd(&R.ctr->rechecked, band);
+            atomicAdd(&R.ctr->rechecked_in, band_in);
+        }
+    }
+}
+
+// --------------------------------------------------------------- hit list --
+// From the list to the bins. Point i's bin holds its other neighbours,
+// [off[i], off[i + 1] - 1), in any order. Both points of a pair are anywhere in
+// the set, so placing the pairs one by one costs two returning atomics and two
+// scattered stores a pair (1.6 ms for 25M pairs of a 1M-point set). Instead the
+// points are cut into buckets of 2^sh consecutive ones (at most kBuckets; a
+// bucket's share of the bins is known from off): k_hit_part deals the pairs to
+// the buckets, a slab of the list at a time with one reservation per slab and
+// bucket, and k_hit_place then orders each bucket by point with LDS counters,
+// its stores staying inside the bucket's own stretch of the bins.
+constexpr int kBuckets = 4096;
+constexpr int kPartThreads = 512;
+constexpr int kPartItems = 16;
+constexpr int kSlab = kPartThreads * kPartItems;
+
+__global__ __launch_bounds__(kPartThreads) void k_hit_part(const int2 *__restrict__ hits,
+                                                           const unsigned long long *__restrict__ cursor,
+                                                           unsigned long long cap, const int64_t *__restrict__ off,
+                                                           int sh, int nbuckets, unsigned *__restrict__ fill,
+                                                           uint2 *__restrict__ part) {
+    __shared__ unsigned slot[kBuckets];
+    const int2 *h = hits + blockIdx.y * cap;
+    const int64_t n = (int64_t)min(cursor[blockIdx.y * kHitCursorStride], cap);
+    const int tid = threadIdx.x;
+    for (int64_t s0 = (int64_t)blockIdx.x * kSlab; s0 < n; s0 += (int64_t)gridDim.x * kSlab) {
+        for (int b = tid; b < nbuckets; b += kPartThreads) slot[b] = 0;
+        __syncthreads();
+        int2 p[kPartItems];
+        unsigned rank[kPartItems];  // ranks within the slab's share of the two buckets (each below 2^14 + 1)
+#pragma unroll
+        for (int k = 0; k < kPartItems; ++k) {
+            const int64_t e = s0 + k * kPartThreads + tid;
+            p[k] = e < n ? h[e] : make_int2(-1, -1);
+        }
+#pragma unroll
+        for (int k = 0; k < kPartItems; ++k)
+            if (p[k].x >= 0) {
+                const unsigned r = atomicAdd(&slot[p[k].x >> sh], 1u);
+                rank[k] = r | (atomicAdd(&slot[p[k].y >> sh], 1u) << 16);
+            }
+        __syncthreads();
+        for (int b = tid; b < nbuckets; b += kPartThreads) {
+            const unsigned c = slot[b];
+            const int64_t first = (int64_t)b << sh;
+            if (c) slot[b] = (unsigned)(off[first] - first) + atomicAdd(fill + b, c);
+        }
+        __syncthreads();
+        const unsigned mask = (1u << sh) - 1u;
+#pragma unroll
+        for (int k = 0; k < kPartItems; ++k)
+            if (p[k].x >= 0) {
+                part[slot[p[k].x >> sh] + (rank[k] & 0xffffu)] = make_uint2((unsigned)p[k].x & mask, (unsigned)p[k].y);
+                part[slot[p[k].y >> sh] + (rank[k] >> 16)] = make_uint2((unsigned)p[k].y & mask, (unsigned)p[k].x);
+            }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_hit_place(const uint2 *__restrict__ part,
+                                                        const int64_t *__restrict__ off, int64_t n, int sh,
+                                                        int32_t *__restrict__ bin) {
+    extern __shared__ unsigned at[];  // next free place of each point, from the bucket's first
+    const int64_t p0 = (int64_t)blockIdx.x << sh, p1 = min(n, p0 + (int64_t(1) << sh));
+    const int64_t o0 = off[p0];
+    for (int64_t i = p0 + threadIdx.x; i < p1; i += kThreads) at[i - p0] = (unsigned)(off[i] - o0);
+    __syncthreads();
+    const int64_t m = off[p1] - o0 - (p1 - p0);
+    const uint2 *src = part + (o0 - p0);
+    int32_t *dst = bin + o0;
+#pragma unroll 4
+    for (int64_t e = threadIdx.x; e < m; e += kThreads) {
+        const uint2 v = src[e];
+        dst[atomicAdd(&at[v.x], 1u)] = (int32_t)v.y;
+    }
+}
+
+// The pairs placed one by one, for lists too long for 32-bit bucket places.
+__global__ __launch_bounds__(kThreads) void k_hit_bin(const int2 *__restrict__ hits,
+                                                      const unsigned long long *__restrict__ cursor,
+                                                      unsigned long long cap, const int64_t *__restrict__ off,
+                                                      int32_t *__restrict__ fill, int32_t *__restrict__ bin) {
+    const int2 *h = hits + blockIdx.y * cap;
+    const int64_t n = (int64_t)min(cursor[blockIdx.y * kHitCursorStride], cap);
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        const int2 p = h[e];
+        if (p.x < 0) continue;
+        bin[off[p.x] + atomicAdd(fill + p.x, 1)] = p.y;
+        bin[off[p.y] + atomicAdd(fill + p.y, 1)] = p.x;
+    }
+}
+
+// Position of a candidate row in an item's list (its ranges in order): the
+// ranges sorted by row are the ranges in the order of their line keys (the
+// base-3 digits of the range index reversed), so a binary search over them
+// finds the row's range. sb / sd: per sorted slot u < 27 the begin of the last
+// non-empty range up to u, and its list position minus its begin.
+struct ListMap {
+    int sb[32], sd[32];
+};
+
+__device__ __forceinline__ void list_map(const HitGrid &G, int it, int lane, ListMap &M) {
+    int rb = 0, len = 0;
+    if (lane < G.nranges) {
+        const Range r = G.ranges[(int64_t)it * G.nranges + lane];
+        rb = r.begin;
+        len = max(0, r.end - r.begin);
+    }
+    int incl = len;
+    for (int o = 1; o < 32; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    const int dl = incl - len - rb;
+    // slot u holds range o(u): the base-3 digits reversed
+    int u = lane, o = 0;
+    for (int m = G.nranges; m > 1; m /= 3) {
+        o = o * 3 + u % 3;
+        u /= 3;
+    }
+    int src = lane < G.nranges ? o : 0;
+    const int rbs = __shfl(rb, src), dls = __shfl(dl, src), lens = __shfl(len, src);
+    int x = (lane < G.nranges && lens > 0) ? lane : -1;  // last non-empty slot so far
+    for (int s = 1; s < 32; s <<= 1) {
+        const int y = __shfl_up(x, s);
+        if (lane >= s) x = max(x, y);
+    }
+    const int fb = __shfl(rbs, max(x, 0)), fd = __shfl(dls, max(x, 0));
+    if (lane < 32) {
+        M.sb[lane] = lane >= G.nranges ? INT_MAX : (x >= 0 ? fb : INT_MIN);
+        M.sd[lane] = fd;
+    }
+}
+
+__device__ __forceinline__ int list_pos(const ListMap &M, int c) {
+    int o = 0;
+#pragma unroll
+    for (int st = 16; st > 0; st >>= 1)
+        if (M.sb[o + st] <= c) o += st;
+    return c + M.sd[o];
+}
+
+// Pairs of the points [qlo, qhi), one wave per work item: a point's bin and
+// the point itself, ordered by list position (the candidate order), each
+// neighbour's rank being the number of smaller positions (compared against all
+// of them from LDS, four to a read). Points with more than kWaveBin
+// neighbours go to k_hit_emit_big.
+struct EmitOut {
+    const int64_t *off;
+    const int32_t *bin;
+    int64_t base;
+    int32_t qlo, qhi, item_lo, item_hi;
+    int2 *pairs;
+    double *d2;
+    int32_t *big;  // [0]: number, then (point, item) of the larger ones
+    int32_t per;   // queries of an item that one wave takes (a power of two up to 16)
+};
+
+__global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
+    __shared__ ListMap maps[kWaves];
+    __shared__ uint4 keys[kWaves][kWaveBin / 4 + 1];
+    const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
+    const int64_t w = (int64_t)blockIdx.x * kWaves + wv;
+    const int parts = kTileQ / E.per;
+    const int it = (int)(E.item_lo + w / parts), part = (int)(w % parts);
+    if (it >= E.item_hi) return;
+    ListMap &M = maps[wv];
+    const Item I = G.items[it];
+    const int qb = max(I.qbegin + part * E.per, E.qlo), nq = min(min(I.qend, I.qbegin + (part + 1) * E.per), E.qhi) - qb;
+    if (nq <= 0) return;
+    // lane i: offset and input index of query qb + i; the offset of the end
+    // in the lane after the last
+    const int64_t offs = E.off[qb + min(lane, nq)];
+    const int32_t pqs = G.perm[qb + min(lane, nq - 1)];
+    const int64_t o_first = readlane_i64(offs, 0);
+    int nxt = E.bin[o_first + min((int64_t)lane, readlane_i64(offs, 1) - o_first - 1)];
+    list_map(G, it, lane, M);
+    unsigned *ks = reinterpret_cast<unsigned *>(keys[wv]);
+    auto settle = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    settle();
+    auto rank_of = [&](unsigned k, int m) {
+        int rank = 0;
+#pragma unroll 4
+        for (int f = 0; f < (m + 3) >> 2; ++f) {
+            const uint4 o = keys[wv][f];
+            rank += (o.x < k) + (o.y < k) + (o.z < k) + (o.w < k);
+        }
+        return rank;
+    };
+    auto put = [&](int64_t at, int32_t pq, int q, int c, int32_t pc) {
+        E.pairs[at] = make_int2(pq, pc);
+        if (E.d2) E.d2[at] = exact_d2(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)c * G.dp, G.d);
+    };
+    for (int i = 0; i < nq; ++i) {
+        const int q = qb + i;
+        const int64_t o0 = readlane_i64(offs, i), m64 = readlane_i64(offs, i + 1) - o0;  // the point itself included
+        const int cur = nxt;
+        if (i + 1 < nq) {  // the next query's neighbours, in flight during this one
+            const int64_t o1 = o0 + m64;
+            nxt = E.bin[o1 + min((int64_t)lane, readlane_i64(offs, i + 2) - o1 - 1)];
+        }
+        const int32_t pq = __builtin_amdgcn_readlane(pqs, i);
+        if (m64 > kWaveBin) {
+            if (lane == 0) {
+                const int s = atomicAdd(E.big, 1);
+                E.big[2 + 2 * s] = q;
+                E.big[3 + 2 * s] = it;
+            }
+            continue;
+        }
+        const int m = (int)m64;
+        settle();
+        if (m <= 64) {
+            const int c = lane < m - 1 ? cur : q;
+            const int32_t pc = G.perm[c];
+            const unsigned k = (unsigned)list_pos(M, c);
+            ks[lane] = lane < m ? k : 0xffffffffu;
+            settle();
+            const int rank = rank_of(k, m);
+            if (lane < m) put(o0 - E.base + rank, pq, q, c, pc);
+        } else {
+            for (int e = lane; e < ((m + 3) & ~3); e += 64) {
+                unsigned k = 0xffffffffu;
+                if (e < m) k = (unsigned)list_pos(M, e < m - 1 ? E.bin[o0 + e] : q);
+                ks[e] = k;
+            }
+            settle();
+            for (int e = lane; e < m; e += 64) {
+                const int c = e < m - 1 ? E.bin[o0 + e] : q;
+                put(o0 - E.base + rank_of(ks[e], m), pq, q, c, G.perm[c]);
+            }
+        }
+    }
+}
+
+// Points with many neighbours: one block per point, the list positions of
+// the neighbours as bits of an LDS window, which then leave in order.
+__global__ __launch_bounds__(kThreads) void k_hit_emit_big(HitGrid G, EmitOut E) {
+    __shared__ ListMap M;
+    __shared__ unsigned bits[kBigBits / 32];
+    __shared__ int wsum[kWaves];
+    __shared__ int total_pos;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int nbig = E.big[0];
+    for (int s = blockIdx.x; s < nbig; s += gridDim.x) {
+        const int q = E.big[2 + 2 * s], it = E.big[3 + 2 * s];
+        __syncthreads();
+        if (tid < 64) list_map(G, it, lane, M);
+        if (tid == 0) {
+            int t = 0;
+            for (int o = 0; o < G.nranges; ++o) {
+                const Range r = G.ranges[(int64_t)it * G.nranges + o];
+                t += max(0, r.end - r.begin);
+            }
+            total_pos = t;
+        }
+        __syncthreads();
+        const int64_t o0 = E.off[q], m = E.off[q + 1] - o0;
+        const int32_t pq = G.perm[q];
+        int64_t at = o0 - E.base;
+        for (int64_t w0 = 0; w0 < total_pos; w0 += kBigBits) {
+            for (int e = tid; e < kBigBits / 32; e += kThreads) bits[e] = 0;
+            __syncthreads();
+            for (int64_t e = tid; e < m; e += kThreads) {
+                const int c = e < m - 1 ? E.bin[o0 + e] : q;
+                const int64_t p = (int64_t)list_pos(M, c) - w0;
+                if (p >= 0 && p < kBigBits) atomicOr(&bits[p >> 5], 1u << (p & 31));
+            }
+            __syncthreads();
+            for (int b0 = 0; b0 < kBigBits / 32; b0 += kThreads) {
+                unsigned v = bits[b0 + tid];
+                const int c0 = __popc(v);
+                int incl = c0;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int y = __shfl_up(incl, o);
+                    if (lane >= o) incl += y;
+                }
+                if (lane == 63) wsum[wv] = incl;
+                __syncthreads();
+                int pre = incl - c0, all = 0;
+                for (int w = 0; w < kWaves; ++w) {
+                    if (w < wv) pre += wsum[w];
+                    all += wsum[w];
+                }
+                int64_t o = at + pre;
+                while (v) {
+                    const int bit = __builtin_ctz(v);
+                    v &= v - 1;
+                    const int64_t p = w0 + 32 * (int64_t)(b0 + tid) + bit;
+                    // back to the row: the range holding list position p
+                    int64_t left = p;
+                    int c = 0;
+                    for (int r = 0; r < G.nranges; ++r) {
+                        const Range x = G.ranges[(int64_t)it * G.nranges + r];
+                        const int len = max(0, x.end - x.begin);
+                        if (left < len) {
+                            c = x.begin + (int)left;
+                            break;
+                        }
+                        left -= len;
+                    }
+                    E.pairs[o] = make_int2(pq, G.perm[c]);
+                    if (E.d2) E.d2[o] = exact_d2(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)c * G.dp, G.d);
+                    ++o;
+                }
+                at += all;
+                __syncthreads();
+            }
+        }
+    }
+}
+
+HitGrid hit_grid(const Grid &g) {
+    HitGrid G{};
+    G.xs = g.xs;
+    G.xa = g.xa;
+    G.nrm = g.nrm;
+    G.perm = g.perm;
+    G.items = g.item;
+    G.ranges = g.ranges;
+    G.blocks = g.blocks;
+    G.item_block = g.hit_item_block;
+    G.span = g.hit_span;
+    G.blo = g.hit_blo;
+    G.bhi = g.hit_bhi;
+    G.bstride = g.items;
+    G.d = g.d;
+    G.dp = g.dp;
+    G.da = g.da;
+    G.nranges = g.nranges;
+    G.nitems = (int32_t)g.items;
+    G.nblocks = (int32_t)g.nblocks;
+    G.item_base = g.item_base;
+    G.boxes = g.sc != -1;
+    const double sc = std::ldexp(1.0, -std::ilogb(g.eps));
+    G.thr = (float)(g.eps2 * sc * sc * (1.0 + 1e-4));
+    G.eps2 = g.eps2;
+    return G;
+}
+
+size_t align_up(size_t b) { return (b + 255) & ~size_t(255); }
+
+// Bytes of the index that hit_prepare adds to a grid.
+size_t hit_index_bytes(int64_t items, int64_t nblocks, int nranges, int d) {
+    const size_t dims = (size_t)((d + 3) & ~3);
+    return 2 * align_up(dims * items * sizeof(float)) + align_up(items * sizeof(int32_t)) +
+           align_up((size_t)nblocks * nranges * sizeof(int2));
+}
+
+}  // namespace
+
+// The grids and paths this count takes: block items with one candidate list
+// (d > 4), d <= 64 (whole rows in a wave's lanes; more dimensions stay on the
+// per-wave tiles), work items at least half full (an item is a tile here, and
+// lines with few points leave most of its columns empty: the packed lists of
+// k_m64 / k_lowp then have fewer tiles), enough tile work (candidate pairs x
+// K-steps) to pay for the index and for ordering the list, some 60 us of
+// launches (n = 5000, d = 16, 1.8e6: join 411 us without, 440 with; index-free
+// n = 2048, d = 8, 8.4e6: 315 and 333; n = 5000, d = 6, 2.3e7: 530 and 493;
+// n = 30000, d = 5, 1.3e8: 559 and 514; n = 9001, d = 23 index-free, 4.9e8: 1169
+// and 502), eps far enough from the ends of the range for the boxes'
+// power-of-two scale.
+bool hits_usable(const Grid &g, sj_path path) {
+    return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && path == SJ_FP64_MFMA &&
+           g.n >= 8 * g.items && (double)g.cand_items * (g.da >> 2) >= 0x1p24 && g.eps >= 0x1p-500 &&
+           g.eps <= 0x1p500;
+}
+
+size_t hits_lean_bytes(int64_t n, int32_t d) {
+    if (d <= 4 || d > kHitMaxD || n == 0) return 0;
+    const int64_t items = n / 8;  // hits_usable
+    return hit_index_bytes(items, items, 27, d) + 8 * 256;
+}
+
+void hits_prepare(Grid &g, hipStream_t s) {
+    if (g.hit_index) return;
+    const size_t dims = (size_t)((g.d + 3) & ~3);
+    char *p = static_cast<char *>(dev_alloc(hit_index_bytes(g.items, g.nblocks, g.nranges, g.d), s));
+    g.hit_index = p;
+    g.hit_blo = reinterpret_cast<float *>(p);
+    p += align_up(dims * g.items * sizeof(float));
+    g.hit_bhi = reinterpret_cast<float *>(p);
+    p += align_up(dims * g.items * sizeof(float));
+    g.hit_item_block = reinterpret_cast<int32_t *>(p);
+    p += align_up(g.items * sizeof(int32_t));
+    g.hit_span = reinterpret_cast<int2 *>(p);
+    const double sc = std::ldexp(1.0, -std::ilogb(g.eps));
+    const unsigned nbox = (unsigned)((g.items + 15) / 16);
+    const int64_t t = g.nblocks * g.nranges;
+    hipLaunchKernelGGL(k_hit_index, dim3(nbox + (unsigned)((t + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
+                       hit_grid(g), sc, nbox, g.hit_blo, g.hit_bhi, g.hit_span, g.hit_item_block);
+    SJ_HIP(hipGetLastError());
+}
+
+void hits_free_list(Grid &g, hipStream_t s) {
+    if (g.hits) dev_free(g.hits, s);
+    if (g.hit_cursor) dev_free(g.hit_cursor, s);
+    if (g.hit_bin) dev_free(g.hit_bin, s);
+    g.hits = nullptr;
+    g.hit_cursor = nullptr;
+    g.hit_bin = nullptr;
+    g.hit_cap = 0;
+    g.hits_valid = false;
+}
+
+// Entries per region for `most` of them in the fullest (0: a first guess of
+// 256 pairs a point, of which half are listed), or 0 when the list would
+// exceed the budget.
+static unsigned long long region_cap(const Grid &g, unsigned long long most) {
+    const unsigned long long waves = (unsigned long long)g.nblocks * kWaves;
+    if (!most) most = (128ull * (unsigned long long)g.n + waves * kHitChunk) / kHitRegions + 16 * kHitChunk;
+    most = (most + kHitChunk - 1) / kHitChunk * kHitChunk;
+    return most * kHitRegions * sizeof(int2) <= (unsigned long long)kMaskBudget ? most : 0;
+}
+
+// Enqueues the count: counts into cnt (n + 1 entries, zeroed here), pairs into
+// the grid's list when `record`; ro.ctr zeroed here unless it already counts. most: entries per region
+// that a former run of this count reserved (0: not known).
+void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
+                RefineOut &ro, hipStream_t s) {
+    (void)path;
+    hits_prepare(g, s);
+    g.hits_valid = false;
+    HitOut R{};
+    R.cnt = cnt;
+    R.ctr = ro.ctr;
+    if (record) {  // (a former list is dropped)
+        const unsigned long long cap = region_cap(g, most);
+        if (g.hit_bin) dev_free(g.hit_bin, s);
+        g.hit_bin = nullptr;
+        if (cap > g.hit_cap) {
+            hits_free_list(g, s);
+            g.hits = dev_alloc_n<int2>((size_t)(cap * kHitRegions), s);
+            g.hit_cap = cap;
+        }
+        if (g.hits) {
+            if (!g.hit_cursor) g.hit_cursor = dev_alloc_n<unsigned long long>(kHitRegions * kHitCursorStride, s);
+            R.hits = g.hits;
+            R.cursor = g.hit_cursor;
+            R.cap = g.hit_cap;
+        }
+    }
+    fill_zero_many({{cnt, ((size_t)g.n + 1) * sizeof(int32_t)},
+                    {R.cursor, R.cursor ? kHitRegions * kHitCursorStride * sizeof(unsigned long long) : 0},
+                    {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
+                   s);
+    const HitGrid G = hit_grid(g);
+    // few blocks: their walks are split so that the chip is filled
+    const int nseg = (int)std::max<int64_t>(1, std::min<int64_t>(16, 4096 / g.nblocks));
+    const dim3 grid((unsigned)(g.nblocks * nseg));
+    ro.kt.start(ro.timed, s);
+    const double delta = fp64_mfma_delta(g);
+    ro.band_rel = g.eps2 > 0 ? delta / g.eps2 : 0.0;
+    switch (g.da >> 2) {
+#define SJ_HIT(KSV)                                                                                    \
+    case KSV:                                                                                          \
+        hipLaunchKernelGGL(k_hit_f64<KSV>, grid, dim3(kThreads), 0, s, G, R, delta, nseg);             \
+        break
+        SJ_HIT(2);
+        SJ_HIT(3);
+        SJ_HIT(4);
+        SJ_HIT(5);
+        SJ_HIT(6);
+        SJ_HIT(7);
+        SJ_HIT(8);
+        SJ_HIT(9);
+        SJ_HIT(10);
+        SJ_HIT(11);
+        SJ_HIT(12);
+        SJ_HIT(13);
+        SJ_HIT(14);
+        SJ_HIT(15);
+        SJ_HIT(16);
+#undef SJ_HIT
+        default: throw Unsupported{"hit-list count: d out of range"};
+    }
+    SJ_HIP(hipGetLastError());
+    ro.kt.stop(s);
+}
+
+// A list for a pairs call whose count kept none (half-stencil option, a count
+// on another path, or a list that outgrew its first guess): the count run
+// again, its counts dropped. False when the list would exceed the budget.
+bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
+    unsigned long long most = g.hit_most;
+    for (int tries = 0; tries < 2; ++tries) {
+        if (!region_cap(g, most)) return false;
+        int32_t *cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
+        RefineOut again;
+        again.ctr = ro.ctr;
+        hits_count(g, path, cnt, true, most, true, again, s);
+        dev_free(cnt, s);
+        if (!g.hits) return false;
+        unsigned long long cur[kHitRegions * kHitCursorStride];
+        SJ_HIP(hipMemcpyAsync(cur, g.hit_cursor, sizeof cur, hipMemcpyDeviceToHost, s));
+        SJ_HIP(hipStreamSynchronize(s));
+        ro.band_rel = again.band_rel;
+        most = 0;
+        for (int r = 0; r < kHitRegions; ++r) most = std::max(most, cur[r * kHitCursorStride]);
+        g.hit_most = most;
+        if (most <= g.hit_cap) {
+            g.hits_valid = true;
+            g.hits_lowp = is_lowp(path);
+            return true;
+        }
+    }
+    return false;
+}
+
+// Pairs of the chunk from the list (valid): the bins are made on the first
+// call and kept for the chunks that follow.
+void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, bool zero_ctr,
+                RefineOut &ro, hipStream_t s) {
+    ro.kt.start(ro.timed, s);
+    int sh = 6;
+    while ((g.n >> sh) >= kBuckets) ++sh;
+    const int nbuckets = (int)((g.n + (int64_t(1) << sh) - 1) >> sh);
+    const int64_t entries = g.total - g.n;  // each listed pair twice
+    const bool parts = sh <= 13 && entries * (int64_t)sizeof(uint2) <= kMaskBudget;
+    const size_t nfill = g.hit_bin ? 0 : parts ? (size_t)nbuckets : (size_t)g.n;
+    // more than kWaveBin neighbours: at most written / kWaveBin points
+    const size_t nbig = (size_t)(p.written / kWaveBin) + 1;
+    int32_t *work = dev_alloc_n<int32_t>(2 + 2 * nbig + nfill, s);
+    int32_t *fill = work + 2 + 2 * nbig;
+    fill_zero_many({{work, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}, {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
+                   s);
+    if (!g.hit_bin) {
+        g.hit_bin = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(g.total, 1), s);
+        if (parts) {
+            uint2 *part = dev_alloc_n<uint2>((size_t)std::max<int64_t>(entries, 1), s);
+            const int64_t slabs = (int64_t)(g.hit_most + kSlab - 1) / kSlab;
+            hipLaunchKernelGGL(k_hit_part, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(slabs, 128)), kHitRegions),
+                               dim3(kPartThreads), 0, s, g.hits, g.hit_cursor, g.hit_cap, g.off, sh, nbuckets,
+                               reinterpret_cast<unsigned *>(fill), part);
+            SJ_HIP(hipGetLastError());
+            hipLaunchKernelGGL(k_hit_place, dim3((unsigned)nbuckets), dim3(kThreads), sizeof(unsigned) << sh, s, part,
+                               g.off, g.n, sh, g.hit_bin);
+            SJ_HIP(hipGetLastError());
+            dev_free(part, s);
+        } else {
+            hipLaunchKernelGGL(k_hit_bin, dim3(256, kHitRegions), dim3(kThreads), 0, s, g.hits, g.hit_cursor,
+                               g.hit_cap, g.off, fill, g.hit_bin);
+            SJ_HIP(hipGetLastError());
+        }
+    }
+    const int nitems = (int)(p.item_hi - p.item_lo);
+    if (nitems > 0) {
+        EmitOut E{};
+        E.off = g.off;
+        E.bin = g.hit_bin;
+        E.base = p.base;
+        E.qlo = (int32_t)qlo;
+        E.qhi = (int32_t)p.next;
+        E.item_lo = (int32_t)p.item_lo;
+        E.item_hi = (int32_t)p.item_hi;
+        E.pairs = reinterpret_cast<int2 *>(pairs);
+        E.d2 = d2;
+        E.big = work;
+        const HitGrid G = hit_grid(g);
+        // a wave's queries run one after the other: few items are spread over more waves
+        E.per = kTileQ;
+        while (E.per > 1 && (int64_t)nitems * (kTileQ / E.per) < 16384) E.per /= 2;
+        const int64_t waves = (int64_t)nitems * (kTileQ / E.per);
+        hipLaunchKernelGGL(k_hit_emit, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, G, E);
+        SJ_HIP(hipGetLastError());
+        if (p.written > kWaveBin) {
+            hipLaunchKernelGGL(k_hit_emit_big, dim3((unsigned)std::min<size_t>(nbig, 1024)), dim3(kThreads), 0, s, G, E);
+            SJ_HIP(hipGetLastError());
+        }
+    }
+    dev_free(work, s);
+    ro.kt.stop(s);
+}
+
+}  // namespace sj

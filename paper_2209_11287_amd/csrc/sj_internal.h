@@ -5,7 +5,9 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <initializer_list>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/selfjoin.h"
@@ -22,6 +24,9 @@ constexpr int kRowPad = 64;        // extra zeroed rows after every point array
 constexpr int kBlockItems = 4;     // work items per block item (low-precision paths)
 constexpr int kLpMaxD = 64;        // largest d of the low-precision paths
 constexpr int64_t kMaskBudget = int64_t(16) << 30;  // largest in-mask buffer (bytes)
+constexpr int kHitMaxD = 64;       // largest d of the hit-list count
+constexpr int kHitRegions = 16;    // regions of a hit list, each with its own cursor
+constexpr int kHitCursorStride = 16;  // cursors 128 bytes apart
 constexpr int64_t kLeanLineTable = int64_t(1) << 20;  // largest dense line table of a lean build
 
 // Thread-local error text.
@@ -222,6 +227,22 @@ struct Grid {
     int64_t lp_groups = -1;      // -1 until the layout is computed
     unsigned long long *lp_masks = nullptr;
     bool lp_masks_valid = false;
+    // hit-list count (sj_hits.hip): its index (boxes and candidate items,
+    // slices of hit_index, made on the first such count), and the list of the
+    // pairs it found, kHitRegions regions of hit_cap entries; hit_bin = the
+    // list by point, made by the first pairs call after a count
+    void *hit_index = nullptr;
+    float *hit_blo = nullptr, *hit_bhi = nullptr;
+    int32_t *hit_item_block = nullptr;
+    int2 *hit_span = nullptr;
+    int2 *hits = nullptr;
+    unsigned long long *hit_cursor = nullptr;
+    unsigned long long hit_cap = 0;
+    unsigned long long hit_most = 0;  // entries the last recording count reserved in its fullest region
+    int32_t *hit_bin = nullptr;
+    bool hits_valid = false;
+    bool hits_lowp = false;      // the list comes from a low-precision path's count
+    bool lean_hits = false;      // lean: the scratch also holds the hit index
     double *dev_nmax = nullptr;  // device copy of nmax
 
     // cached per-query counts (sorted order) and their exclusive prefix sums
@@ -267,6 +288,10 @@ int64_t grid_cref(Grid &g, hipStream_t s);
 // Zero fill by kernel (usable under stream capture, unlike a memset node).
 void fill_zero(void *p, size_t bytes, hipStream_t s);
 
+// Zeroes up to eight segments (4-byte aligned, whole 4-byte words) in one
+// launch.
+void fill_zero_many(std::initializer_list<std::pair<void *, size_t>> segs, hipStream_t s);
+
 // Scans and sort (sj_build.hip).
 void exclusive_scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, hipStream_t s);
 void radix_sort_pairs(unsigned long long **key_a, int32_t **val_a, unsigned long long *key_b, int32_t *val_b,
@@ -310,6 +335,8 @@ struct RefineOut {
     KernelTimer kt;          // those events
     DevCounters *ctr = nullptr;            // device counters (zeroed by the launcher)
     unsigned long long *masks = nullptr;   // per-tile in-masks to record (FP64 count), nullable
+    bool hits = false;         // run the hit-list count
+    bool record_hits = false;  // and keep its list
     bool record_lp = false;  // low-precision count: record its in-masks (layout and buffer on the grid)
     double band_rel = 0;     // largest band half-width / eps^2
     int64_t cand_eval = 0;
@@ -377,6 +404,16 @@ void lowp_count(Grid &g, sj_path path, int32_t *cnt_sorted, RefineOut &ro, hipSt
 void lowp_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2,
                 RefineOut &ro, hipStream_t s);
 void lowp_measure(Grid &g, sj_path path, double *max_err, double *max_band, int64_t *viol, hipStream_t s);
+
+// Hit-list count (sj_hits.hip).
+bool hits_usable(const Grid &g, sj_path path);
+size_t hits_lean_bytes(int64_t n, int32_t d);
+void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
+                RefineOut &ro, hipStream_t s);
+bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s);
+void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, bool zero_ctr, RefineOut &ro,
+                hipStream_t s);
+void hits_free_list(Grid &g, hipStream_t s);
 
 }  // namespace sj
 

@@ -1976,14 +1976,22 @@ void launch_sym_cand(const Grid &g, unsigned long long *acc, hipStream_t s) {
 // land in ro.ctr (device, zeroed here), read back by the caller with the
 // total.
 void refine_count(Grid &g, sj_path path, int32_t *cnt_sorted, RefineOut &ro, hipStream_t s) {
+    const bool sym = ro.sym && (path == SJ_FP64_VALU || path == SJ_FP64_MFMA);
+    ro.cand_eval = g.cand_items;
+    if (ro.hits) {
+        if (sym) {
+            fill_zero(ro.ctr, sizeof(DevCounters), s);
+            launch_sym_cand(g, &ro.ctr->spare[0], s);
+        }
+        hits_count(g, path, cnt_sorted, ro.record_hits, 0, !sym, ro, s);
+        return;
+    }
     fill_zero(ro.ctr, sizeof(DevCounters), s);
     RefOut R{};
     R.cnt = cnt_sorted;
     R.ctr = ro.ctr;
     R.item_lo = 0;
     R.masks = ro.masks;
-    const bool sym = ro.sym && (path == SJ_FP64_VALU || path == SJ_FP64_MFMA);
-    ro.cand_eval = g.cand_items;
     if (sym) launch_sym_cand(g, &ro.ctr->spare[0], s);
     if (path == SJ_FP64_VALU) {
         ro.kt.start(ro.timed, s);
@@ -2097,8 +2105,12 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
     R.pairs = pairs;
     R.d2 = d2;
     R.item_lo = (int32_t)p.item_lo;
-    fill_zero(ro.ctr, sizeof(DevCounters), s);
     R.ctr = ro.ctr;
+    if (g.hits_valid && g.hits_lowp == is_lowp(path)) {
+        hits_pairs(g, p, qlo, pairs, d2, true, ro, s);
+        return;
+    }
+    fill_zero(ro.ctr, sizeof(DevCounters), s);
     const int nitems = (int)(p.item_hi - p.item_lo);
     if ((path == SJ_FP64_VALU || path == SJ_FP64_MFMA) && g.masks_valid && g.masks) {
         ro.kt.start(ro.timed, s);
@@ -2113,6 +2125,8 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
             SJ_HIP(hipGetLastError());
         }
         ro.kt.stop(s);
+    } else if (hits_usable(g, path) && hits_ensure(g, path, ro, s)) {
+        hits_pairs(g, p, qlo, pairs, d2, false, ro, s);
     } else if (path == SJ_FP64_VALU) {
         ro.kt.start(ro.timed, s);
         launch_v64<MODE_EMIT>(g, R, nitems, s);

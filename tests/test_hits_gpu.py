@@ -1,0 +1,85 @@
+"""Hit-list count (d = 5 .. 64): pair lists in the order that the mask
+expansion of the vector-ALU path gives (query order, then candidate order),
+counts and distances, on every K-step count and its neighbours, ragged last
+items, split walks, points whose bins are longer than a wave's and a block's
+window, and a list that outgrows its first guess."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import gpu_join, log
+from workloads import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+PATHS = ["fp64_mfma"]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2209_11287_amd as p
+    p.load()
+    yield
+
+
+def _eps(X, s):
+    Y = X[:2000]
+    d2 = ((X[:64, None, :] - Y[None]) ** 2).sum(2).ravel()
+    return float(np.sqrt(np.partition(d2, int(64 + 64 * s * len(Y) / len(X)))[int(64 + 64 * s * len(Y) / len(X))]))
+
+
+def _same(X, eps, path, capacity=None, **kw):
+    import oracle
+    log(f"[hits] path={path} n={X.shape[0]} d={X.shape[1]} eps={eps} capacity={capacity} {kw}")
+    a = gpu_join(X, eps, path, want_d2=True, capacity=capacity, **kw)
+    b = gpu_join(X, eps, "fp64_valu", want_d2=True, **kw)  # masks, exact chain
+    total, pp, _, _ = oracle.grid_count(X, eps)
+    assert a["total"] == b["total"] == total
+    assert np.array_equal(a["per_point"], pp)
+    assert np.array_equal(a["pairs"], b["pairs"])
+    assert np.array_equal(a["d2"], b["d2"])
+    return a
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("d", [5, 7, 8, 9, 12, 13, 16, 17, 20, 25, 31, 32, 36, 41, 47, 48, 53, 60, 63, 64])
+def test_every_k_step_count(path, d):
+    X = gen.gaussian_mixture(9007, d, clusters=6, seed=d)
+    eps = _eps(X, 30)
+    _same(X, eps, path)
+    _same(X, eps, path, index_dims=1, short_circuit=-1)  # long lines, no box test
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("n", [2800, 2944, 2945, 2959, 2960, 2961, 3007, 3009])
+def test_ragged_ends_and_smallest_work(path, n):
+    # around whole blocks of 64 and tiles of 16 points; 2800 stays on the
+    # per-wave tiles (less work than this count takes)
+    X = gen.make("uniform", n, 6, seed=n)
+    _same(X, 0.2, path, index_dims=-1)
+
+
+@pytest.mark.parametrize("path", PATHS)
+def test_chunks_and_skewed_points(path):
+    X = gen.make("expo", 20011, 5, seed=3)
+    _same(X, _eps(X, 40), path, capacity=50021)
+
+
+@pytest.mark.parametrize("path", PATHS)
+def test_long_bins_and_list_growth(path):
+    # 1500 points at one place (more neighbours than a wave orders), a
+    # spread set around them; then a set in which all 3000 points pair (the
+    # list outgrows its first guess and the pairs call makes it again)
+    rng = np.random.default_rng(2)
+    X = np.concatenate([np.full((1500, 8), 0.25), rng.random((9000, 8))])[rng.permutation(10500)]
+    _same(X, 0.3, path)
+    _same(rng.random((3000, 6)) * 1e-3, 1.0, path)
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("scale", [2.0 ** -400, 1e100])
+def test_units_far_from_one(path, scale):
+    X = gen.gaussian_mixture(6001, 9, clusters=4, seed=4) * scale
+    _same(X, _eps(X / scale, 25) * scale, path)
