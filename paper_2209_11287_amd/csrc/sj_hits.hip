@@ -40,8 +40,10 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "sj_internal.h"
+#include "sj_lowp.h"
 
 namespace sj {
 
@@ -56,6 +58,10 @@ constexpr int kWaveBin = 1024;      // neighbours of a point that one wave order
 constexpr int kBigBits = 1 << 18;   // list positions per bitmap window of the larger ones
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef short short8_t __attribute__((ext_vector_type(8)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 struct HitGrid {
     const double *xs, *xa, *nrm;
@@ -69,6 +75,7 @@ struct HitGrid {
     int64_t bstride;             // items per dimension of blo / bhi
     int32_t d, dp, da, nranges, nitems, nblocks, item_base;
     int32_t boxes;               // 0: no box test (short_circuit = -1)
+    double sc, eps_s, eps2_s;    // low precision: the tiles' power-of-two scale, scaled eps and eps^2
     float thr;                   // box test: squared gap sum that drops an item (scaled units)
     double eps2;
 };
@@ -330,6 +337,130 @@ __device__ __forceinline__ void hit_push(const HitOut &R, HitRun &H, int region,
     H.left -= k;
 }
 
+// A wave's share of the counters and of the list.
+struct HitCtx {
+    HitRun run;
+    int region;
+    unsigned long long band, band_in;  // wave-uniform
+    int2 *wait;   // low precision: the wave's band pairs (row of the block, candidate), in LDS
+    int waiting;  // their number (below kBandRun before a tile)
+};
+constexpr int kBandRun = 64;
+
+// The chain of exact_d2 on padded rows (zero from d to dp, a multiple of 4:
+// those steps add +0.0), 16 dimensions' loads in flight at a time.
+__device__ __forceinline__ double exact_d2_rows(const double *__restrict__ a, const double *__restrict__ b, int dp) {
+    double acc = 0.0;
+    for (int t0 = 0; t0 < dp; t0 += 16) {
+        double2 x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int t = min(t0 + 2 * u, dp - 2);
+            x[u] = *reinterpret_cast<const double2 *>(a + t);
+            y[u] = *reinterpret_cast<const double2 *>(b + t);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (t0 + 2 * u >= dp) break;
+            const double d0 = __dsub_rn(x[u].x, y[u].x), d1 = __dsub_rn(x[u].y, y[u].y);
+            acc = __fma_rn(d0, d0, acc);
+            acc = __fma_rn(d1, d1, acc);
+        }
+    }
+    return acc;
+}
+
+// Decides the first min(waiting, 64) of the wave's band pairs, one to a lane.
+__device__ __forceinline__ void band_flush(const HitGrid &G, const HitOut &R, BlockShared &S, HitCtx &C, int q0,
+                                           int lane) {
+    const int n = min(C.waiting, 64);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int2 p = C.wait[min(lane, n - 1)];
+    const int2 more = C.wait[64 + lane];
+    const bool hit = lane < n && exact_d2_rows(G.xs + (int64_t)(q0 + p.x) * G.dp, G.xs + (int64_t)p.y * G.dp, G.dp) <=
+                                     G.eps2;
+    const unsigned long long w = __ballot(hit);
+    C.band += (unsigned long long)n;
+    C.band_in += (unsigned long long)__popcll(w);
+    if (w) {
+        if (hit) {
+            atomicAdd(&S.cntq[p.x], 1);
+            atomicAdd(R.cnt + p.y, 1);
+        }
+        if (R.hits) hit_push(R, C.run, C.region, w, hit, q0 + p.x, p.y, lane);
+    }
+    C.wait[lane] = more;  // those past the first 64 move up
+    C.waiting -= n;
+}
+
+// The pairs of one tile: bit l of w[r] = the value of lane l's register r, row
+// row0 + RS r of the block against candidate c, may be within eps; of in[r] =
+// it is (the band between them is decided by the exact chain on the original
+// coordinates: at once where the band is all but empty, else (DEFER) 64 pairs at
+// a time, a pair to a lane, since the chain is a serial one over whole rows).
+// own: a tile of the block's own rows, each pair once.
+template <int RS, bool DEFER>
+__device__ __forceinline__ void hit_record(const HitGrid &G, const HitOut &R, BlockShared &S, HitCtx &C,
+                                           const unsigned long long wm[4], const unsigned long long in[4], int q0,
+                                           int row0, int c, bool own, int lane) {
+    int mine = 0;  // pairs of the lane's candidate in this tile
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        unsigned long long w = wm[r];
+        const int q = q0 + row0 + RS * r;
+        if (own) w &= __ballot(c > q);
+        if (w == 0ull) continue;
+        const unsigned long long bm = w & ~in[r];
+        if (DEFER && bm != 0ull) {
+            if (__builtin_amdgcn_inverse_ballot_w64(bm)) C.wait[C.waiting + lane_rank(bm)] = make_int2(row0 + RS * r, c);
+            C.waiting += __popcll(bm);
+            if (C.waiting >= kBandRun) band_flush(G, R, S, C, q0, lane);
+            w &= ~bm;
+            if (w == 0ull) continue;
+        } else if (__builtin_expect(bm != 0ull, 0)) {
+            bool ok = false;
+            if (__builtin_amdgcn_inverse_ballot_w64(bm))
+                ok = exact_d2(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)c * G.dp, G.d) <= G.eps2;
+            const unsigned long long okm = __ballot(ok);
+            C.band += (unsigned long long)__popcll(bm);
+            C.band_in += (unsigned long long)__popcll(okm);
+            w = (w & ~bm) | okm;
+            if (w == 0ull) continue;
+        }
+        const bool hit = __builtin_amdgcn_inverse_ballot_w64(w);
+        if (hit) {
+            ++mine;
+            atomicAdd(&S.cntq[row0 + RS * r], 1);
+        }
+        if (R.hits) hit_push(R, C.run, C.region, w, hit, q, c, lane);
+    }
+    if (mine) atomicAdd(R.cnt + c, mine);
+}
+
+// The end of a block: the list's last entries, the rows' counts as query (and
+// the point itself, once per row), the counters.
+__device__ __forceinline__ void hit_finish(const HitOut &R, BlockShared &S, HitCtx &C, const Walk &W, int q0, int nrows,
+                                           int seg, bool count_dropped) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (R.hits) hit_pad(R, C.run, C.region, lane);
+    __syncthreads();
+    if (tid < nrows) {
+        const int v = S.cntq[tid] + (seg == 0 ? 1 : 0);
+        if (v) atomicAdd(R.cnt + q0 + tid, v);
+    }
+    unsigned long long dr = count_dropped ? W.dropped : 0;
+    for (int sh = 32; sh > 0; sh >>= 1) dr += __shfl_xor(dr, sh);
+    if (lane == 0) {
+        if (dr) atomicAdd(&R.ctr->pruned, dr);
+        if (C.band) {
+            atomicAdd(&R.ctr->rechecked, C.band);
+            atomicAdd(&R.ctr->rechecked_in, C.band_in);
+        }
+    }
+}
+
 // ------------------------------------------------------------------- FP64 --
 // One wave runs the block's (up to) four 16-row query tiles against one
 // candidate item at a time: its B operand is loaded straight into registers
@@ -405,39 +536,17 @@ __global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64(HitGrid G
         reinterpret_cast<double *>(qn)[tid] = row < nrows ? G.nrm[q0 + row] : INFINITY;
     }
     Walk W = walk_init(G, S, bi, ib, ie, seg, nseg);
-    HitRun H{0, 0};
-    const int region = (blockIdx.x ^ (blockIdx.x >> 4)) & (kHitRegions - 1);
-    unsigned long long band = 0, band_in = 0;  // wave-uniform
+    HitCtx C{{0, 0}, (int)((blockIdx.x ^ (blockIdx.x >> 4)) & (kHitRegions - 1)), 0, 0, nullptr, 0};
     const double clo = G.eps2 - delta, chi = G.eps2 + delta;
-    // the pairs of tile t (values acc; some value may be at or below its threshold)
     auto record = [&](const HitTile<KS> &T, const double4_t &acc, int t, bool valid, bool own) {
         const double hi = valid ? chi - T.nc : -INFINITY, lo = valid ? clo - T.nc : -INFINITY;
-        int mine = 0;  // pairs of the lane's candidate in this tile
+        unsigned long long w[4], in[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            unsigned long long w = __ballot(acc[r] <= hi);
-            const int q = q0 + 16 * t + g + 4 * r;
-            if (own) w &= __ballot(T.c > q);  // own block: each pair once
-            if (w == 0ull) continue;
-            const unsigned long long bm = w & ~__ballot(acc[r] <= lo);
-            if (__builtin_expect(bm != 0ull, 0)) {  // rare: the exact chain on the original coordinates
-                bool ok = false;
-                if (__builtin_amdgcn_inverse_ballot_w64(bm))
-                    ok = exact_d2(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)T.c * G.dp, G.d) <= G.eps2;
-                const unsigned long long okm = __ballot(ok);
-                band += (unsigned long long)__popcll(bm);
-                band_in += (unsigned long long)__popcll(okm);
-                w = (w & ~bm) | okm;
-                if (w == 0ull) continue;
-            }
-            const bool hit = __builtin_amdgcn_inverse_ballot_w64(w);
-            if (hit) {
-                ++mine;
-                atomicAdd(&S.cntq[16 * t + g + 4 * r], 1);
-            }
-            if (R.hits) hit_push(R, H, region, w, hit, q, T.c, lane);
+            w[r] = __ballot(acc[r] <= hi);
+            in[r] = __ballot(acc[r] <= lo);
         }
-        if (mine) atomicAdd(R.cnt + T.c, mine);
+        hit_record<4, false>(G, R, S, C, w, in, q0, 16 * t + g, T.c, own, lane);
     };
     auto run = [&](const HitTile<KS> &T) {
         const int tn = uniform_i32(T.n);
@@ -467,22 +576,203 @@ __global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64(HitGrid G
         }
         __syncthreads();
     }
-    if (R.hits) hit_pad(R, H, region, lane);
+    hit_finish(R, S, C, W, q0, nrows, seg, true);
+}
+
+// ---------------------------------------------------------- low precision --
+// FP32 and split-BF16 tiles (rounding, band and test of k_lowp, sj_lowp.hip):
+// rows centred on the block's first query, scaled and rounded; D = |c'|^2 -
+// 2 q'.c' with the candidate norm (FP64, rounded once) in the accumulator and a
+// threshold pair per row. A wave rounds a candidate item in its own registers,
+// straight from the FP64 rows, and runs the block's four query tiles against
+// it: five FP64 and a few FP32 operations per coordinate for 64 queries, and no
+// staging of tiles through LDS, which bounded the block kernels (two barriers
+// per 64 candidates, every rounded value written and read back). FP32 is then
+// bound by its MFMAs (32 cycles per K-step of 4 and tile), split BF16 by the
+// rounding (about 700 cycles per item at d = 64 against 384 of MFMA). Gaussian
+// mixture, 1M points: FP32, d = 32 21.7 -> 5.5 ms; split BF16, d = 64 86 -> 9.2 ms
+// (33 ms with the band pairs rechecked one by one where they were met).
+// K order: FP32 as in the FP64 tiles; split BF16 lane g holds dimensions
+// 32 s + 8 g .. + 7.
+template <int PREC, int KS>
+struct LpTile {
+    static constexpr int NB = PREC == PREC_F32 ? KS : 8 * KS;  // coordinates per lane
+    double b[NB];
+    int c, n;
+};
+
+// Dimension of the lane's coordinate u.
+template <int PREC, int KS>
+__device__ __forceinline__ int lp_k(int u, int g) {
+    if (PREC == PREC_F32) return hit_k<KS>(u, g);
+    return 32 * (u >> 3) + 8 * g + (u & 7);
+}
+
+template <int PREC, int KS>
+__device__ __forceinline__ void lp_load(LpTile<PREC, KS> &T, int2 e, const HitGrid &G, int g, int j) {
+    T.n = e.y;
+    T.c = e.x + min(j, (e.y & 255) - 1);
+    const double *__restrict__ row = G.xs + (int64_t)T.c * G.dp;
+#pragma unroll
+    for (int u = 0; u + 1 < LpTile<PREC, KS>::NB; u += 2) {
+        const int k = lp_k<PREC, KS>(u, g);
+        // rows are zero from d to dp (a multiple of 4); past dp nothing is read
+        double2 v = make_double2(0.0, 0.0);
+        if (PREC == PREC_F32 || k < G.dp) v = *reinterpret_cast<const double2 *>(row + k);
+        T.b[u] = v.x;
+        T.b[u + 1] = v.y;
+    }
+    if (PREC == PREC_F32 && (KS & 1)) T.b[KS - 1] = row[4 * (KS - 1) + g];
+}
+
+// Two values to BF16 (round to nearest even), the first in the low half.
+__device__ __forceinline__ unsigned bf16_pair(float a, float b) {
+    const bf16x2_t v = __builtin_convertvector((float2_t){a, b}, bf16x2_t);
+    return __builtin_bit_cast(unsigned, v);
+}
+
+template <int PREC, int KS>
+__global__ __launch_bounds__(kThreads, PREC == PREC_F32 ? (KS <= 8 ? 4 : 3) : (KS == 1 ? 4 : 3)) void k_hit_lp(
+    HitGrid G, HitOut R, int nseg) {
+    using Tile = LpTile<PREC, KS>;
+    constexpr int NB = Tile::NB;
+    constexpr int NP = PREC == PREC_F32 ? 1 : 2;  // parts of an operand (hi, lo)
+    // A operand of lane l: FP32 one float per K-step, split BF16 eight halves (hi parts, then lo parts)
+    __shared__ uint4 Abuf[PREC == PREC_F32 ? KS * 64 : NP * 4 * KS * 64];
+    __shared__ double xr[64];
+    __shared__ int2 wait[kWaves][2 * kBandRun];
+    __shared__ float4_t thi[16], tlo[16];  // [tile][row group g]: thresholds of rows 4g + r
+    __shared__ BlockShared S;
+    const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i32(tid >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    const int bi = lb / nseg, seg = lb - bi * nseg;
+    const int ib = uniform_i32(G.blocks[bi] - G.item_base), ie = uniform_i32(G.blocks[bi + 1] - G.item_base);
+    const int nt = ie - ib;
+    const int q0 = uniform_i32(G.items[ib].qbegin);
+    const int nrows = uniform_i32(G.items[ie - 1].qend) - q0;
+    if (tid < 64) xr[tid] = tid < G.dp ? G.xs[(int64_t)q0 * G.dp + tid] : 0.0;
     __syncthreads();
-    // the rows' counts as query, and the point itself (once per row)
-    if (tid < nrows) {
-        const int v = S.cntq[tid] + (seg == 0 ? 1 : 0);
-        if (v) atomicAdd(R.cnt + q0 + tid, v);
-    }
-    unsigned long long dr = W.dropped;
-    for (int sh = 32; sh > 0; sh >>= 1) dr += __shfl_xor(dr, sh);
-    if (lane == 0) {
-        if (dr) atomicAdd(&R.ctr->pruned, dr);
-        if (band) {
-            atomicAdd(&R.ctr->rechecked, band);
-            atomicAdd(&R.ctr->rechecked_in, band_in);
+    // wave t rounds query tile t (rows 16 t + j) as the tile loop rounds candidates
+    {
+        const int row = 16 * wv + j;
+        double nn = 0.0;
+        const double *__restrict__ q = G.xs + (int64_t)(q0 + min(row, nrows - 1)) * G.dp;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int k = lp_k<PREC, KS>(u, g);
+            unsigned bits = 0;
+            double y = 0.0;
+            if (row < nrows && k < G.d) y = round_in<PREC>(__dsub_rn(q[k], xr[k]) * G.sc, bits);
+            nn = __fma_rn(y, y, nn);
+            if constexpr (PREC == PREC_F32) {
+                reinterpret_cast<float *>(Abuf)[(wv * KS + u) * 64 + lane] = -2.0f * __uint_as_float(bits);
+            } else {  // -2 hi and -2 lo are exact
+                unsigned short *h = reinterpret_cast<unsigned short *>(Abuf + (wv * KS + (u >> 3)) * 64 + lane);
+                unsigned short *l = reinterpret_cast<unsigned short *>(Abuf + ((4 + wv) * KS + (u >> 3)) * 64 + lane);
+                h[u & 7] = f32_to_bf16(-2.0f * bf16_to_f32((unsigned short)(bits & 0xffffu)));
+                l[u & 7] = f32_to_bf16(-2.0f * bf16_to_f32((unsigned short)(bits >> 16)));
+            }
         }
+        nn += __shfl_xor(nn, 16);
+        nn += __shfl_xor(nn, 32);  // |q'|^2 of row j in every lane of its column
+        double dl = 0.0;
+        if (g == 0) {
+            const int K = PREC == PREC_F32 ? 4 * KS : 32 * KS;
+            dl = lp_delta<PREC>(nn, G.eps_s, G.eps2_s, G.d, K);
+            const double thr = G.eps2_s - nn;
+            const bool ok = row < nrows;
+            reinterpret_cast<float *>(thi)[16 * wv + j] = ok ? (float)(thr + dl) : -INFINITY;
+            reinterpret_cast<float *>(tlo)[16 * wv + j] = ok ? (float)(thr - dl) : -INFINITY;
+            if (!ok) dl = 0.0;
+        }
+        for (int sh = 8; sh > 0; sh >>= 1) dl = fmax(dl, __shfl_xor(dl, sh));
+        if (lane == 0 && seg == 0) atomicMax(&R.ctr->max_delta, (unsigned long long)__double_as_longlong(dl));
     }
+    Walk W = walk_init(G, S, bi, ib, ie, seg, nseg);
+    HitCtx C{{0, 0}, (int)((blockIdx.x ^ (blockIdx.x >> 4)) & (kHitRegions - 1)), 0, 0, wait[wv], 0};
+
+    auto run = [&](const Tile &T) {
+        const int tn = uniform_i32(T.n);
+        const bool own = tn > 255, valid = j < (tn & 255);
+        // round the candidate: y = (x - r) sc in FP64, then as round_in
+        float f[NB];
+        double np = 0.0;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) f[u] = (float)(__dsub_rn(T.b[u], xr[lp_k<PREC, KS>(u, g)]) * G.sc);
+        short8_t bh[PREC == PREC_F32 ? 1 : KS], bl[PREC == PREC_F32 ? 1 : KS];
+        if constexpr (PREC == PREC_F32) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) np = __fma_rn((double)f[u], (double)f[u], np);
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                uint4 h, l;
+                unsigned *hw = reinterpret_cast<unsigned *>(&h), *lw = reinterpret_cast<unsigned *>(&l);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float f0 = f[8 * s + 2 * e], f1 = f[8 * s + 2 * e + 1];
+                    const unsigned hp = bf16_pair(f0, f1);
+                    const float h0 = __uint_as_float(hp << 16), h1 = __uint_as_float(hp & 0xffff0000u);
+                    const unsigned lp = bf16_pair(f0 - h0, f1 - h1);  // differences exact
+                    // hi + lo is a multiple of f's last place not above it by more than one: exact in FP32
+                    const double v0 = (double)(h0 + __uint_as_float(lp << 16));
+                    const double v1 = (double)(h1 + __uint_as_float(lp & 0xffff0000u));
+                    np = __fma_rn(v0, v0, np);
+                    np = __fma_rn(v1, v1, np);
+                    hw[e] = hp;
+                    lw[e] = lp;
+                }
+                bh[s] = __builtin_bit_cast(short8_t, h);
+                bl[s] = __builtin_bit_cast(short8_t, l);
+            }
+        }
+        np += __shfl_xor(np, 16);
+        np += __shfl_xor(np, 32);
+        const float nc = valid ? (float)np : INFINITY;
+        for (int t = 0; t < nt; ++t) {
+            float4_t acc = (float4_t){nc, nc, nc, nc};
+            const float4_t hi = thi[4 * t + g];
+            if constexpr (PREC == PREC_F32) {
+                const float *a = reinterpret_cast<const float *>(Abuf) + t * KS * 64 + lane;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s * 64], f[s], acc, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const short8_t ah = __builtin_bit_cast(short8_t, Abuf[(t * KS + s) * 64 + lane]);
+                    const short8_t al = __builtin_bit_cast(short8_t, Abuf[((4 + t) * KS + s) * 64 + lane]);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[s], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[s], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[s], acc, 0, 0, 0);
+                }
+            }
+            unsigned long long w[4], in[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[r] = __ballot(acc[r] <= hi[r]);
+            if ((w[0] | w[1] | w[2] | w[3]) == 0ull) continue;
+            const float4_t lo = tlo[4 * t + g];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) in[r] = __ballot(acc[r] <= lo[r]);
+            hit_record<1, true>(G, R, S, C, w, in, q0, 16 * t + 4 * g, T.c, own, lane);
+        }
+    };
+    for (;;) {
+        const int ns = walk_fill(G, S, W, bi, nt);
+        if (ns == 0) break;
+        Tile T0, T1;
+        if (wv < ns) lp_load(T0, S.surv[wv], G, g, j);
+        for (int e = wv; e < ns; e += 2 * kWaves) {
+            lp_load(T1, S.surv[min(e + kWaves, ns - 1)], G, g, j);
+            run(T0);
+            if (e + kWaves >= ns) break;
+            lp_load(T0, S.surv[min(e + 2 * kWaves, ns - 1)], G, g, j);
+            run(T1);
+        }
+        __syncthreads();
+    }
+    if (C.waiting) band_flush(G, R, S, C, q0, lane);
+    hit_finish(R, S, C, W, q0, nrows, seg, false);  // tiles_pruned is 0 on these paths
 }
 
 // --------------------------------------------------------------- hit list --
@@ -585,7 +875,8 @@ struct ListMap {
     int sb[32], sd[32];
 };
 
-__device__ __forceinline__ void list_map(const HitGrid &G, int it, int lane, ListMap &M) {
+// Returns the list's length.
+__device__ __forceinline__ int list_map(const HitGrid &G, int it, int lane, ListMap &M) {
     int rb = 0, len = 0;
     if (lane < G.nranges) {
         const Range r = G.ranges[(int64_t)it * G.nranges + lane];
@@ -616,6 +907,7 @@ __device__ __forceinline__ void list_map(const HitGrid &G, int it, int lane, Lis
         M.sb[lane] = lane >= G.nranges ? INT_MAX : (x >= 0 ? fb : INT_MIN);
         M.sd[lane] = fd;
     }
+    return __builtin_amdgcn_readlane(incl, 31);
 }
 
 __device__ __forceinline__ int list_pos(const ListMap &M, int c) {
@@ -626,11 +918,18 @@ __device__ __forceinline__ int list_pos(const ListMap &M, int c) {
     return c + M.sd[o];
 }
 
-// Pairs of the points [qlo, qhi), one wave per work item: a point's bin and
-// the point itself, ordered by list position (the candidate order), each
-// neighbour's rank being the number of smaller positions (compared against all
-// of them from LDS, four to a read). Points with more than kWaveBin
-// neighbours go to k_hit_emit_big.
+// Pairs of the points [qlo, qhi), one wave per work item (or a part of one): a
+// point's bin and the point itself, ordered by list position (the candidate
+// order). A neighbour's rank is found in one of two ways, whichever takes fewer
+// instructions: the number of smaller positions, compared against all of them
+// from LDS, four to a read (few neighbours in a long list); or a bitmap of the
+// list positions in LDS, kWinBits of them at a time, with the number of bits
+// before each word (many neighbours: 21M pairs of a skewed set of 216408 points
+// in 5 dimensions took 1.21 ms by comparison alone, the dense points having
+// hundreds of neighbours). Points with more than kWaveBin neighbours go to
+// k_hit_emit_big.
+constexpr int kWinBits = 32768;
+
 struct EmitOut {
     const int64_t *off;
     const int32_t *bin;
@@ -644,7 +943,8 @@ struct EmitOut {
 
 __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
     __shared__ ListMap maps[kWaves];
-    __shared__ uint4 keys[kWaves][kWaveBin / 4 + 1];
+    __shared__ uint4 keys[kWaves][kWaveBin / 4 + 1];  // positions, or the bitmap
+    __shared__ unsigned short before[kWaves][kWinBits / 32];
     const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
     const int64_t w = (int64_t)blockIdx.x * kWaves + wv;
     const int parts = kTileQ / E.per;
@@ -660,7 +960,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
     const int32_t pqs = G.perm[qb + min(lane, nq - 1)];
     const int64_t o_first = readlane_i64(offs, 0);
     int nxt = E.bin[o_first + min((int64_t)lane, readlane_i64(offs, 1) - o_first - 1)];
-    list_map(G, it, lane, M);
+    const int total = list_map(G, it, lane, M);
     unsigned *ks = reinterpret_cast<unsigned *>(keys[wv]);
     auto settle = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -679,7 +979,46 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
     };
     auto put = [&](int64_t at, int32_t pq, int q, int c, int32_t pc) {
         E.pairs[at] = make_int2(pq, pc);
-        if (E.d2) E.d2[at] = exact_d2(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)c * G.dp, G.d);
+        if (E.d2) E.d2[at] = exact_d2_rows(G.xs + (int64_t)q * G.dp, G.xs + (int64_t)c * G.dp, G.dp);
+    };
+    // pairs of one query by bitmap; neighbour e of m is cur (m <= 64) or from the bin
+    const int nwin = (total + kWinBits - 1) / kWinBits;
+    auto by_bitmap = [&](int64_t o0, int m, int q, int32_t pq, int cur) {
+        int at = 0;  // pairs of the windows before
+        for (int w = 0; w < nwin; ++w) {
+            const int w0 = w * kWinBits, words = (min(total - w0, kWinBits) + 31) >> 5;
+            const int per = (words + 63) >> 6;  // words per lane, consecutive
+            for (int u = 0; u < per; ++u) ks[u * 64 + lane] = 0;
+            settle();
+            for (int e = lane; e < m; e += 64) {
+                const int p = list_pos(M, e == m - 1 ? q : m <= 64 ? cur : E.bin[o0 + e]) - w0;
+                if (p >= 0 && p < kWinBits) atomicOr(ks + (p >> 5), 1u << (p & 31));
+            }
+            settle();
+            int sum = 0;
+            for (int u = 0; u < per; ++u) {
+                before[wv][lane * per + u] = (unsigned short)sum;
+                sum += __popc(ks[lane * per + u]);
+            }
+            int incl = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(incl, o);
+                if (lane >= o) incl += y;
+            }
+            const int excl = incl - sum;
+            for (int u = 0; u < per; ++u) before[wv][lane * per + u] += (unsigned short)excl;
+            settle();
+            for (int e = lane; e < m; e += 64) {
+                const int c = e == m - 1 ? q : m <= 64 ? cur : E.bin[o0 + e];
+                const int p = list_pos(M, c) - w0;
+                if (p >= 0 && p < kWinBits) {
+                    const int rank = before[wv][p >> 5] + __popc(ks[p >> 5] & ((1u << (p & 31)) - 1u));
+                    put(o0 - E.base + at + rank, pq, q, c, G.perm[c]);
+                }
+            }
+            at += __builtin_amdgcn_readlane(incl, 63);
+            settle();
+        }
     };
     for (int i = 0; i < nq; ++i) {
         const int q = qb + i;
@@ -700,7 +1039,15 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
         }
         const int m = (int)m64;
         settle();
-        if (m <= 64) {
+        // instructions of the two ways, about: 9 per read of four positions
+        // and 64 neighbours; per window 70, 10 per word of a lane and 40 per 64
+        // neighbours
+        const int chunks = (m + 63) >> 6;
+        const int by_rank = 9 * ((m + 3) >> 2) * chunks;
+        const int by_bits = nwin * (70 + 40 * chunks) + 10 * ((total + 2047) >> 11);
+        if (by_bits < by_rank) {
+            by_bitmap(o0, m, q, pq, cur);
+        } else if (m <= 64) {
             const int c = lane < m - 1 ? cur : q;
             const int32_t pc = G.perm[c];
             const unsigned k = (unsigned)list_pos(M, c);
@@ -800,6 +1147,17 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit_big(HitGrid G, EmitOut E)
     }
 }
 
+// Calls f with the compile-time K-step count `ks` (LO .. HI).
+template <int LO, int HI, typename F>
+void by_k_steps(int ks, F f) {
+    if constexpr (LO > HI) {
+        throw Unsupported{"hit-list count: d out of range"};
+    } else {
+        if (ks == LO) f(std::integral_constant<int, LO>{});
+        else by_k_steps<LO + 1, HI>(ks, f);
+    }
+}
+
 HitGrid hit_grid(const Grid &g) {
     HitGrid G{};
     G.xs = g.xs;
@@ -823,7 +1181,10 @@ HitGrid hit_grid(const Grid &g) {
     G.item_base = g.item_base;
     G.boxes = g.sc != -1;
     const double sc = std::ldexp(1.0, -std::ilogb(g.eps));
-    G.thr = (float)(g.eps2 * sc * sc * (1.0 + 1e-4));
+    G.sc = sc;
+    G.eps_s = g.eps * sc;
+    G.eps2_s = g.eps2 * sc * sc;
+    G.thr = (float)(G.eps2_s * (1.0 + 1e-4));
     G.eps2 = g.eps2;
     return G;
 }
@@ -851,7 +1212,7 @@ size_t hit_index_bytes(int64_t items, int64_t nblocks, int nranges, int d) {
 // and 502), eps far enough from the ends of the range for the boxes'
 // power-of-two scale.
 bool hits_usable(const Grid &g, sj_path path) {
-    return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && path == SJ_FP64_MFMA &&
+    return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && (path == SJ_FP64_MFMA || path == SJ_FP32_MFMA || path == SJ_BF16X3_MFMA) &&
            g.n >= 8 * g.items && (double)g.cand_items * (g.da >> 2) >= 0x1p24 && g.eps >= 0x1p-500 &&
            g.eps <= 0x1p500;
 }
@@ -908,7 +1269,6 @@ static unsigned long long region_cap(const Grid &g, unsigned long long most) {
 // that a former run of this count reserved (0: not known).
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
                 RefineOut &ro, hipStream_t s) {
-    (void)path;
     hits_prepare(g, s);
     g.hits_valid = false;
     HitOut R{};
@@ -939,30 +1299,20 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
     const int nseg = (int)std::max<int64_t>(1, std::min<int64_t>(16, 4096 / g.nblocks));
     const dim3 grid((unsigned)(g.nblocks * nseg));
     ro.kt.start(ro.timed, s);
-    const double delta = fp64_mfma_delta(g);
-    ro.band_rel = g.eps2 > 0 ? delta / g.eps2 : 0.0;
-    switch (g.da >> 2) {
-#define SJ_HIT(KSV)                                                                                    \
-    case KSV:                                                                                          \
-        hipLaunchKernelGGL(k_hit_f64<KSV>, grid, dim3(kThreads), 0, s, G, R, delta, nseg);             \
-        break
-        SJ_HIT(2);
-        SJ_HIT(3);
-        SJ_HIT(4);
-        SJ_HIT(5);
-        SJ_HIT(6);
-        SJ_HIT(7);
-        SJ_HIT(8);
-        SJ_HIT(9);
-        SJ_HIT(10);
-        SJ_HIT(11);
-        SJ_HIT(12);
-        SJ_HIT(13);
-        SJ_HIT(14);
-        SJ_HIT(15);
-        SJ_HIT(16);
-#undef SJ_HIT
-        default: throw Unsupported{"hit-list count: d out of range"};
+    if (path == SJ_FP64_MFMA) {
+        const double delta = fp64_mfma_delta(g);
+        ro.band_rel = g.eps2 > 0 ? delta / g.eps2 : 0.0;
+        by_k_steps<2, 16>(g.da >> 2, [&](auto ks) {
+            hipLaunchKernelGGL(k_hit_f64<decltype(ks)::value>, grid, dim3(kThreads), 0, s, G, R, delta, nseg);
+        });
+    } else if (path == SJ_FP32_MFMA) {
+        by_k_steps<2, 16>(g.dp >> 2, [&](auto ks) {
+            hipLaunchKernelGGL((k_hit_lp<PREC_F32, decltype(ks)::value>), grid, dim3(kThreads), 0, s, G, R, nseg);
+        });
+    } else {
+        by_k_steps<1, 2>((g.d + 31) / 32, [&](auto ks) {
+            hipLaunchKernelGGL((k_hit_lp<PREC_BF16X3, decltype(ks)::value>), grid, dim3(kThreads), 0, s, G, R, nseg);
+        });
     }
     SJ_HIP(hipGetLastError());
     ro.kt.stop(s);

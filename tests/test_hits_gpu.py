@@ -11,7 +11,7 @@ from workloads import generators as gen
 
 pytestmark = pytest.mark.gpu
 
-PATHS = ["fp64_mfma"]
+PATHS = ["fp64_mfma", "fp32_mfma", "bf16x3_mfma"]
 
 
 @pytest.fixture(scope="module", autouse=True)
