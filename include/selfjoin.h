@@ -346,7 +346,10 @@ sj_status selfjoin_count_noalloc(const double *points, int64_t n, int32_t d, dou
  * and the pairs launch are each captured into a HIP graph on first use and
  * replayed. The count pass records every problem's in-masks (up to 64 GiB;
  * beyond, the pairs launch re-runs the tiles), so the pairs launch is one
- * kernel that expands them. With opts->tune, the tuner picks per d the
+ * kernel that expands them. On SJ_FP64_MFMA the problems with 5 <= d <= 64
+ * (when they hold enough candidates together) are counted on half of their
+ * tiles instead, one launch per number of K-steps beside the graph, and their
+ * pairs go to one list (up to 64 GiB) that the pairs call orders. With opts->tune, the tuner picks per d the
  * index_dims and the short-circuit setting (timing the FP64 MFMA count on the
  * largest problem of that d; cached in tune_cache), and on the first count
  * the schedule of the tile kernels: persistent grids of the resident waves

@@ -21,49 +21,77 @@ namespace sj {
 
 namespace {
 
-// Sort key of each work item: its problem's d in the high bits (items of one
-// tile form together), then descending cost (candidate tiles x K-steps);
-// value = global item index.
-__global__ void k_item_cost(const Item *__restrict__ items, const Range *__restrict__ ranges, int nitems,
-                            int nranges, int ksteps, int d, bool sym, int64_t base, unsigned long long *__restrict__ key,
-                            int32_t *__restrict__ val) {
-    const int it = blockIdx.x * blockDim.x + threadIdx.x;
-    if (it >= nitems) return;
+// Last problem p with base[p] <= x.
+__device__ __forceinline__ int problem_of(const int64_t *__restrict__ base, int B, int64_t x) {
+    int lo = 0, hi = B;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (base[mid] <= x) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+__device__ __forceinline__ unsigned long long cost_key(int form, unsigned long long c) {
+    const unsigned long long cap = 0xffffffffull;
+    return ((unsigned long long)form << 32) | (cap - (c < cap ? c : cap));
+}
+
+// Sort key of each work item of the batch, all problems in one launch (a
+// launch each took 1.5 ms for 256 problems): its problem's tile form in the high
+// bits (form[p]: the problems the hit-list count takes after the others, then
+// d), then descending cost (candidate tiles x K-steps); value = global item
+// index.
+__global__ void k_item_cost(const BProb *__restrict__ probs, const int64_t *__restrict__ item_base,
+                            const int32_t *__restrict__ form, int B, int64_t total, bool sym,
+                            unsigned long long *__restrict__ key, int32_t *__restrict__ val) {
+    const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gi >= total) return;
+    const int p = problem_of(item_base, B, gi);
+    const DevGrid &G = probs[p].G;
+    const int64_t it = gi - item_base[p];
     // half stencil: the ranges as the count cuts them (from the first query on)
-    const int32_t cut = sym ? items[it].qbegin : INT32_MIN;
+    const int32_t cut = sym ? G.items[it].qbegin : INT32_MIN;
     unsigned long long c = 0;
-    for (int o = 0; o < nranges; ++o) {
-        const Range r = ranges[(int64_t)it * nranges + o];
+    for (int o = 0; o < G.nranges; ++o) {
+        const Range r = G.ranges[it * G.nranges + o];
         const int32_t b = max(r.begin, cut);
         c += (unsigned long long)(r.end > b ? (r.end - b + 15) / 16 : 0);
     }
-    c *= (unsigned long long)(ksteps > 0 ? ksteps : 1);
-    const unsigned long long cap = 0xffffffffull;
-    key[base + it] = ((unsigned long long)d << 32) | (cap - (c < cap ? c : cap));
-    val[base + it] = (int32_t)(base + it);
+    key[gi] = cost_key(form[p], c * (unsigned long long)(G.da >> 2));
+    val[gi] = (int32_t)gi;
 }
 
-// Sort key of each block item of a problem counted with LDS-shared tiles
+// Sort key of each block item of the problems counted with LDS-shared tiles
 // (FP64 MFMA, d = 5 .. 16): d in the high bits, then descending cost (its
 // list's tiles x K-steps x items; half stencil: the list cut at the block's
 // first query); value = global block index.
-__global__ void k_block_cost(const int32_t *__restrict__ blocks, int item_base, const Item *__restrict__ items,
-                             const Range *__restrict__ ranges, int nranges, int nb, int ksteps, int d, bool sym,
-                             int64_t base, unsigned long long *__restrict__ key, int32_t *__restrict__ val) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    const int it0 = blocks[b] - item_base, ni = blocks[b + 1] - blocks[b];
-    const int32_t cut = sym ? items[it0].qbegin : INT32_MIN;
+__global__ void k_block_cost(const BProb *__restrict__ probs, const int64_t *__restrict__ block_base, int B,
+                             int64_t total, bool sym, unsigned long long *__restrict__ key,
+                             int32_t *__restrict__ val) {
+    const int64_t gb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gb >= total) return;
+    const int p = problem_of(block_base, B, gb);
+    const DevGrid &G = probs[p].G;
+    const int b = (int)(gb - block_base[p]);
+    const int64_t it0 = G.blocks[b] - G.item_base;
+    const int ni = G.blocks[b + 1] - G.blocks[b];
+    const int32_t cut = sym ? G.items[it0].qbegin : INT32_MIN;
     unsigned long long c = 0;
-    for (int o = 0; o < nranges; ++o) {
-        const Range r = ranges[(int64_t)it0 * nranges + o];
+    for (int o = 0; o < G.nranges; ++o) {
+        const Range r = G.ranges[it0 * G.nranges + o];
         const int32_t rb = max(r.begin, cut);
         c += (unsigned long long)(r.end > rb ? r.end - rb : 0);
     }
-    c = (c + 15) / 16 * (unsigned long long)ksteps * (unsigned long long)ni;
-    const unsigned long long cap = 0xffffffffull;
-    key[base + b] = ((unsigned long long)d << 32) | (cap - (c < cap ? c : cap));
-    val[base + b] = (int32_t)(base + b);
+    key[gb] = cost_key(G.d, (c + 15) / 16 * (unsigned long long)(G.da >> 2) * (unsigned long long)ni);
+    val[gb] = (int32_t)gb;
+}
+
+// One problem's offsets from those of many: out[i] = off[i] - off[0].
+__global__ void k_copy_offsets(const int64_t *__restrict__ off, int64_t n, int64_t *__restrict__ out) {
+    const int64_t base = off[0];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = off[i] - base;
 }
 
 // Tuned choices, per path, d and size class: index_dims and the
@@ -110,6 +138,7 @@ float time_count(const double *pts, int64_t n, int d, double eps, int k, int sc,
         int32_t *cnt = dev_alloc_n<int32_t>((size_t)n + 1, s);
         RefineOut ro;
         ro.timed = true;
+        ro.hits = hits_usable(g, SJ_FP64_MFMA);
         ro.ctr = dev_alloc_n<DevCounters>(1, s);
         refine_count(g, SJ_FP64_MFMA, cnt, ro, s);  // warm
         ro.kt.ms();
@@ -166,7 +195,18 @@ struct Batch {
     std::vector<BProb> probs;
     int64_t *totals_dev = nullptr;
     std::vector<int64_t> totals;
-    unsigned long long *masks = nullptr;  // every problem's in-masks (or null: pairs re-run the tiles)
+    unsigned long long *masks = nullptr;  // in-masks (or null: pairs re-run the tiles)
+    int64_t mask_tiles = 0;               // their tile slots
+    std::vector<int64_t> tile_base;       // first tile slot of each problem, all problems together (segmented
+                                          // builds: tile_off counts from there), else 0
+    HitBatch hb;                          // the hit-list count of the problems it takes (FP64 MFMA)
+    std::vector<char> in_hb;              // those problems
+    bool hits_counted = false;            // the last count ran it
+    int32_t *rest = nullptr;              // the other problems' indices
+    int nrest = 0;
+    int64_t rest_items = 0;               // their items (the first of the queue)
+    int32_t *cnt_all = nullptr;           // per-query counts and offsets of every problem
+    int64_t *off_all = nullptr;
     bool segmented = false;               // grids from one segmented build (their arrays in `owned`)
     std::vector<void *> owned;
     bool masks_valid = false;
@@ -182,7 +222,7 @@ struct Batch {
     hipGraphExec_t pexec[2] = {nullptr, nullptr};
     hipStream_t pgraph_stream[2] = {nullptr, nullptr};
     int32_t *pgraph_pairs[2] = {nullptr, nullptr};
-    bool pgraph_masks[2] = {false, false};
+    int pgraph_mode[2] = {-1, -1};
 };
 
 constexpr int64_t kBatchMaskBudget = int64_t(64) << 30;  // largest in-mask buffer of a batch (bytes)
@@ -195,21 +235,17 @@ void batch_free(Batch &b, hipStream_t s) {
     }
     for (Grid *g : b.grids) {
         if (!g) continue;
-        if (g->cnt) {
-            dev_free(g->cnt, s);
-            g->cnt = nullptr;
-        }
-        if (g->off) {
-            dev_free(g->off, s);
-            g->off = nullptr;
-        }
+        g->cnt = nullptr;  // slices of cnt_all, off_all
+        g->off = nullptr;
         free_grid(*g, s);
         delete g;
     }
     b.grids.clear();
     for (void *p : b.owned) dev_free(p, s);
     b.owned.clear();
-    void *bufs[] = {b.item_base_dev, b.queue, b.ctr, b.probs_dev, b.totals_dev, b.masks, b.bqueue, b.block_base_dev};
+    hit_batch_free(b.hb, s);
+    void *bufs[] = {b.item_base_dev, b.queue,  b.ctr,            b.probs_dev, b.totals_dev, b.masks,
+                    b.bqueue,        b.block_base_dev, b.rest, b.cnt_all,   b.off_all};
     for (void *p : bufs)
         if (p) dev_free(p, s);
     b.bqueue = nullptr;
@@ -220,6 +256,9 @@ void batch_free(Batch &b, hipStream_t s) {
     b.probs_dev = nullptr;
     b.totals_dev = nullptr;
     b.masks = nullptr;
+    b.rest = nullptr;
+    b.cnt_all = nullptr;
+    b.off_all = nullptr;
 }
 
 void batch_build(Batch &b, int B, const double *const *points, const int64_t *n, const int32_t *d, const double *eps,
@@ -265,8 +304,9 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
         }
     }
     b.item_base.assign(B + 1, 0);
+    int64_t rows = 0;
     int64_t mask_tiles = 0;
-    std::vector<int64_t> tile_base(B + 1, 0);
+    b.tile_base.assign(B + 1, 0);
     // every problem's grid in one segmented build (tile slots counted over
     // all problems together), else one build per problem
     std::vector<SegInput> sin(B);
@@ -284,13 +324,44 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
             build_grid(*b.grids[i], points[i], n[i], d[i], eps[i], b.kdims[i], s);
         }
         Grid &g = *b.grids[i];
-        g.cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
-        g.off = dev_alloc_n<int64_t>((size_t)g.n + 1, s);
+        rows += g.n + 1;
         b.item_base[i + 1] = b.item_base[i] + g.items;
         b.max_n = std::max(b.max_n, g.n);
-        tile_base[i] = b.segmented ? 0 : mask_tiles;
+        b.tile_base[i] = b.segmented ? mask_tiles : 0;
         mask_tiles += g.tiles;
     }
+    b.cnt_all = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(rows, 1), s);
+    b.off_all = dev_alloc_n<int64_t>((size_t)std::max<int64_t>(rows, 1), s);
+    for (int64_t i = 0, at = 0; i < B; ++i) {
+        b.grids[i]->cnt = b.cnt_all + at;
+        b.grids[i]->off = b.off_all + at;
+        at += b.grids[i]->n + 1;
+    }
+    hit_batch_build(b.hb, b.grids, s);
+    b.in_hb.assign(B, 0);
+    for (int i : b.hb.probs) b.in_hb[i] = 1;
+    std::vector<int32_t> rest;
+    for (int i = 0; i < B; ++i)
+        if (!b.in_hb[i]) {
+            rest.push_back(i);
+            b.rest_items += b.grids[i]->items;
+        }
+    b.nrest = (int)rest.size();
+    b.ctr = dev_alloc_n<DevCounters>(1, s);
+    b.totals_dev = dev_alloc_n<int64_t>(B, s);
+    b.probs.resize(B);
+    for (int i = 0; i < B; ++i) {
+        const Grid &g = *b.grids[i];
+        BProb &p = b.probs[i];
+        p.G = make_dev_grid(g);
+        p.delta = fp64_mfma_delta(g);
+        p.cnt = g.cnt;
+        p.off = g.off;
+        p.pout = 0;
+        p.masks = nullptr;
+    }
+    b.probs_dev = dev_alloc_n<BProb>(B, s);
+    SJ_HIP(hipMemcpyAsync(b.probs_dev, b.probs.data(), B * sizeof(BProb), hipMemcpyHostToDevice, s));
     b.total_items = b.item_base[B];
     if (b.total_items >= (int64_t(1) << 31)) throw std::string("too many work items in one batch");
     b.sched_key = "sched/" + std::to_string(B) + "/" + std::to_string(b.total_items);
@@ -300,19 +371,26 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
     const int64_t T = std::max<int64_t>(1, b.total_items);
     unsigned long long *ka = dev_alloc_n<unsigned long long>(T, s), *kb = dev_alloc_n<unsigned long long>(T, s);
     int32_t *va = dev_alloc_n<int32_t>(T, s), *vb = dev_alloc_n<int32_t>(T, s);
+    // tile forms: d, the hit-list count's problems after the others
     int maxd = 1;
-    std::map<int, int64_t> per_d;
+    for (int i = 0; i < B; ++i) maxd = std::max(maxd, b.grids[i]->d);
+    std::map<int, int64_t> per_form;
+    std::vector<int32_t> ids(2 * (size_t)B);  // form of each problem, then the other problems' indices
     for (int i = 0; i < B; ++i) {
-        const Grid &g = *b.grids[i];
-        maxd = std::max(maxd, g.d);
-        if (g.items == 0) continue;
-        per_d[g.d] += g.items;
-        hipLaunchKernelGGL(k_item_cost, dim3((unsigned)((g.items + 255) / 256)), dim3(256), 0, s, g.item, g.ranges,
-                           (int)g.items, g.nranges, g.da >> 2, g.d, b.sym, b.item_base[i], ka, va);
+        ids[i] = b.grids[i]->d + (b.in_hb[i] ? maxd + 1 : 0);
+        if (b.grids[i]->items > 0) per_form[ids[i]] += b.grids[i]->items;
+    }
+    std::copy(rest.begin(), rest.end(), ids.begin() + B);
+    b.rest = dev_alloc_n<int32_t>(2 * (size_t)B, s);
+    SJ_HIP(hipMemcpyAsync(b.rest, ids.data(), ids.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    SJ_HIP(hipStreamSynchronize(s));
+    if (b.total_items > 0) {
+        hipLaunchKernelGGL(k_item_cost, dim3((unsigned)((b.total_items + 255) / 256)), dim3(256), 0, s, b.probs_dev,
+                           b.item_base_dev, b.rest, B, b.total_items, b.sym, ka, va);
         SJ_HIP(hipGetLastError());
     }
     int dbits = 0;
-    while ((1 << dbits) <= maxd) ++dbits;
+    while ((1 << dbits) <= 2 * maxd + 1) ++dbits;
     unsigned long long *k_sorted = ka;
     int32_t *v_sorted = va;
     radix_sort_pairs(&k_sorted, &v_sorted, k_sorted == ka ? kb : ka, v_sorted == va ? vb : va, b.total_items,
@@ -331,7 +409,7 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
     };
     for (int i = 0; i < B; ++i) {
         const Grid &g = *b.grids[i];
-        const int64_t nb = lds_form(g) ? g.nblocks : 0;
+        const int64_t nb = lds_form(g) && !b.in_hb[i] ? g.nblocks : 0;
         bbase[i + 1] = bbase[i] + nb;
         if (nb) per_d_blocks[g.d] += nb;
     }
@@ -339,14 +417,11 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
         const int64_t NB = bbase[B];
         unsigned long long *bka = dev_alloc_n<unsigned long long>(NB, s), *bkb = dev_alloc_n<unsigned long long>(NB, s);
         int32_t *bva = dev_alloc_n<int32_t>(NB, s), *bvb = dev_alloc_n<int32_t>(NB, s);
-        for (int i = 0; i < B; ++i) {
-            const Grid &g = *b.grids[i];
-            if (bbase[i + 1] == bbase[i]) continue;
-            hipLaunchKernelGGL(k_block_cost, dim3((unsigned)((g.nblocks + 255) / 256)), dim3(256), 0, s, g.blocks,
-                               g.item_base, g.item, g.ranges, g.nranges, (int)g.nblocks, g.da >> 2, g.d, b.sym,
-                               bbase[i], bka, bva);
-            SJ_HIP(hipGetLastError());
-        }
+        b.block_base_dev = dev_alloc_n<int64_t>(B + 1, s);
+        SJ_HIP(hipMemcpyAsync(b.block_base_dev, bbase.data(), (B + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(k_block_cost, dim3((unsigned)((NB + 255) / 256)), dim3(256), 0, s, b.probs_dev,
+                           b.block_base_dev, B, NB, b.sym, bka, bva);
+        SJ_HIP(hipGetLastError());
         unsigned long long *bks = bka;
         int32_t *bvs = bva;
         radix_sort_pairs(&bks, &bvs, bks == bka ? bkb : bka, bvs == bva ? bvb : bva, NB, 32 + dbits, s);
@@ -354,49 +429,23 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
         dev_free(bvs == bva ? bvb : bva, s);
         dev_free(bka, s);
         dev_free(bkb, s);
-        b.block_base_dev = dev_alloc_n<int64_t>(B + 1, s);
-        SJ_HIP(hipMemcpyAsync(b.block_base_dev, bbase.data(), (B + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
     }
     b.forms.clear();
     int64_t pos = 0, bpos = 0;
-    for (auto &kv : per_d) {  // ascending d, the key order
+    for (auto &kv : per_form) {  // ascending, the key order
         BatchForm f;
-        f.d = kv.first;
+        f.hits = kv.first > maxd;
+        f.d = f.hits ? kv.first - maxd - 1 : kv.first;
         f.lo = (int32_t)pos;
         f.hi = (int32_t)(pos + kv.second);
         f.sched = 0;
-        const int64_t nb = per_d_blocks.count(kv.first) ? per_d_blocks[kv.first] : 0;
+        const int64_t nb = !f.hits && per_d_blocks.count(f.d) ? per_d_blocks[f.d] : 0;
         f.blo = (int32_t)bpos;
         f.bhi = (int32_t)(bpos + nb);
         bpos += nb;
         b.forms.push_back(f);
         pos += kv.second;
     }
-    // in-masks of every problem (32 bytes per tile slot): the pairs pass then
-    // expands them instead of re-running the tiles (a half-stencil count
-    // records none)
-    if (!b.sym && mask_tiles > 0 && mask_tiles * 32 <= kBatchMaskBudget) {
-        try {
-            b.masks = dev_alloc_n<unsigned long long>((size_t)mask_tiles * 4, s);
-        } catch (const OomError &) {
-            b.masks = nullptr;
-        }
-    }
-    b.ctr = dev_alloc_n<DevCounters>(1, s);
-    b.totals_dev = dev_alloc_n<int64_t>(B, s);
-    b.probs.resize(B);
-    for (int i = 0; i < B; ++i) {
-        const Grid &g = *b.grids[i];
-        BProb &p = b.probs[i];
-        p.G = make_dev_grid(g);
-        p.delta = fp64_mfma_delta(g);
-        p.cnt = g.cnt;
-        p.off = g.off;
-        p.pout = 0;
-        p.masks = b.masks ? b.masks + 4 * tile_base[i] : nullptr;
-    }
-    b.probs_dev = dev_alloc_n<BProb>(B, s);
-    SJ_HIP(hipMemcpyAsync(b.probs_dev, b.probs.data(), B * sizeof(BProb), hipMemcpyHostToDevice, s));
     SJ_HIP(hipStreamSynchronize(s));
     b.totals.assign(B, 0);
     b.ms_build = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -436,6 +485,45 @@ void set_sched(Batch &b, int sched) {
     b.sched = sched;
 }
 
+// In-masks of the problems that the count's tile kernels take (32 bytes per
+// tile slot): the pairs pass then expands them instead of re-running the tiles (a
+// half-stencil count records none). `all`: every problem, else those without
+// the hit list.
+void batch_masks(Batch &b, bool all, hipStream_t s) {
+    int64_t tiles = 0;
+    for (int i = 0; i < b.B; ++i)
+        if (all || !b.in_hb[i]) tiles += b.grids[i]->tiles;
+    if (b.sym || tiles * 32 > kBatchMaskBudget) tiles = 0;
+    if (tiles > b.mask_tiles) {
+        if (b.masks) dev_free(b.masks, s);
+        b.masks = nullptr;
+        b.mask_tiles = 0;
+        try {
+            b.masks = dev_alloc_n<unsigned long long>((size_t)tiles * 4, s);
+            b.mask_tiles = tiles;
+        } catch (const OomError &) {
+            tiles = 0;
+        }
+    }
+    int64_t at = 0;
+    bool changed = false;
+    for (int i = 0; i < b.B; ++i) {
+        unsigned long long *m = nullptr;
+        if (tiles > 0 && (all || !b.in_hb[i])) {
+            // the problem's slots begin at `at`; its tile_off values at tile_base
+            m = b.masks + 4 * (at - b.tile_base[i]);
+            at += b.grids[i]->tiles;
+        }
+        changed = changed || m != b.probs[i].masks;
+        b.probs[i].masks = m;
+    }
+    b.masks_valid = tiles > 0;
+    if (changed) {
+        SJ_HIP(hipMemcpyAsync(b.probs_dev, b.probs.data(), b.B * sizeof(BProb), hipMemcpyHostToDevice, s));
+        SJ_HIP(hipStreamSynchronize(s));
+    }
+}
+
 // Count pipeline: counter reset (and, for the half stencil, the per-point
 // counts), one kernel per tile form (recording the in-masks when the batch
 // holds them), per-problem prefix sums; captured on first use per (path,
@@ -448,10 +536,12 @@ float batch_count_graph(Batch &b, sj_path path, hipStream_t s) {
         b.exec[pi] = capture(s, [&](hipStream_t cs) {
             batch_reset(b.ctr, cs);
             if (b.sym) launch_batch_zero_counts(b.probs_dev, b.B, b.max_n, cs);
+            const bool hits = pi == 1 && !b.hb.probs.empty();
             for (const BatchForm &f : b.forms)
-                launch_batch_form(false, b.sym, f, path, b.probs_dev, b.item_base_dev, b.B, b.queue, nullptr, b.ctr, cs,
-                                  b.block_base_dev, b.bqueue);
-            launch_seg_scan(b.probs_dev, b.B, b.totals_dev, cs);
+                if (!(hits && f.hits))
+                    launch_batch_form(false, b.sym, f, path, b.probs_dev, b.item_base_dev, b.B, b.queue, nullptr, b.ctr,
+                                      cs, b.block_base_dev, b.bqueue);
+            launch_seg_scan(b.probs_dev, hits ? b.rest + b.B : nullptr, hits ? b.nrest : b.B, b.totals_dev, cs);
         });
         b.graph_stream[pi] = s;
         b.graph_sched[pi] = b.sched;
@@ -461,6 +551,7 @@ float batch_count_graph(Batch &b, sj_path path, hipStream_t s) {
     SJ_HIP(hipEventCreate(&e1));
     SJ_HIP(hipEventRecord(e0, s));
     SJ_HIP(hipGraphLaunch(b.exec[pi], s));
+    if (pi == 1 && !b.hb.probs.empty()) hit_batch_count(b.hb, !b.sym, b.ctr, b.totals.data(), s);
     SJ_HIP(hipEventRecord(e1, s));
     SJ_HIP(hipEventSynchronize(e1));
     float ms = 0;
@@ -471,6 +562,8 @@ float batch_count_graph(Batch &b, sj_path path, hipStream_t s) {
 }
 
 float batch_count(Batch &b, sj_path path, hipStream_t s, HostCounters *hc) {
+    b.hits_counted = path == SJ_FP64_MFMA && !b.hb.probs.empty();
+    batch_masks(b, !b.hits_counted, s);
     if (b.tune_sched) {
         // the schedule (persistent grids or one wave per item): both timed
         // once after a warm run, the faster kept (and cached by batch shape)
@@ -499,52 +592,75 @@ float batch_count(Batch &b, sj_path path, hipStream_t s, HostCounters *hc) {
     }
     const float ms = batch_count_graph(b, path, s);
     DevCounters hb{};
-    SJ_HIP(hipMemcpyAsync(b.totals.data(), b.totals_dev, b.B * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    std::vector<int64_t> ht(b.B);
+    SJ_HIP(hipMemcpyAsync(ht.data(), b.totals_dev, b.B * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipMemcpyAsync(&hb, b.ctr, sizeof hb, hipMemcpyDeviceToHost, s));
     SJ_HIP(hipStreamSynchronize(s));
     *hc = read_counters(hb);
     for (int i = 0; i < b.B; ++i) {
+        if (!(b.hits_counted && b.in_hb[i])) b.totals[i] = ht[i];
         b.grids[i]->total = b.totals[i];
         b.grids[i]->have_counts = true;
     }
     b.counted = true;
-    b.masks_valid = b.masks != nullptr && !b.sym;
     return ms;
 }
 
+// The hit-list count's offsets into its problems' own arrays, for an emission
+// that runs their tiles again.
+void batch_offsets(Batch &b, hipStream_t s) {
+    int64_t row0 = 0;
+    for (int i : b.hb.probs) {
+        Grid &g = *b.grids[i];
+        hipLaunchKernelGGL(k_copy_offsets, dim3((unsigned)std::min<int64_t>((g.n + 256) / 256, 1024)), dim3(256), 0, s,
+                           b.hb.off + row0, g.n + 1, g.off);
+        SJ_HIP(hipGetLastError());
+        row0 += g.n;
+    }
+}
+
 // Emission of every problem's pairs into one buffer: problem i's rows at
-// [offsets[i], offsets[i + 1]). From the recorded in-masks when the batch
-// holds them (one launch over all items), else the tiles re-run in emission
-// form (one launch per tile form). Captured per (path, stream, buffer).
+// [offsets[i], offsets[i + 1]). The hit-list count's problems from its list; the
+// others from the recorded in-masks when the batch holds them (one launch over
+// all items), else their tiles re-run in emission form (one launch per tile
+// form); captured per (path, stream, buffer).
 float batch_pairs(Batch &b, sj_path path, int32_t *pairs, hipStream_t s) {
+    std::vector<int64_t> pout(b.B);
     int64_t off = 0;
     for (int i = 0; i < b.B; ++i) {
-        b.probs[i].pout = off;
+        b.probs[i].pout = pout[i] = off;
         off += b.totals[i];
     }
     SJ_HIP(hipMemcpyAsync(b.probs_dev, b.probs.data(), b.B * sizeof(BProb), hipMemcpyHostToDevice, s));
     const int pi = path == SJ_FP64_MFMA ? 1 : 0;
     const bool use_masks = b.masks_valid;
-    if (!b.pexec[pi] || b.pgraph_stream[pi] != s || b.pgraph_pairs[pi] != pairs || b.pgraph_masks[pi] != use_masks) {
-        if (b.pexec[pi]) (void)hipGraphExecDestroy(b.pexec[pi]);
-        b.pexec[pi] = nullptr;
-        b.pexec[pi] = capture(s, [&](hipStream_t cs) {
-            if (use_masks) {
-                launch_batch_emit(b.probs_dev, b.item_base_dev, b.B, b.queue, (int)b.total_items, 1, pairs, cs);
-            } else {
-                for (const BatchForm &f : b.forms)
-                    launch_batch_form(true, false, f, path, b.probs_dev, b.item_base_dev, b.B, b.queue, pairs, b.ctr, cs);
-            }
-        });
-        b.pgraph_stream[pi] = s;
-        b.pgraph_pairs[pi] = pairs;
-        b.pgraph_masks[pi] = use_masks;
-    }
     hipEvent_t e0, e1;
     SJ_HIP(hipEventCreate(&e0));
     SJ_HIP(hipEventCreate(&e1));
     SJ_HIP(hipEventRecord(e0, s));
-    SJ_HIP(hipGraphLaunch(b.pexec[pi], s));
+    // the list: kept by the count, or (half-stencil option, a list that outgrew
+    // its first guess) made again; without room for it those tiles run again too
+    const bool hits = b.hits_counted && (b.hb.valid || hit_batch_ensure(b.hb, b.ctr, b.totals, s));
+    if (b.hits_counted && !hits) batch_offsets(b, s);
+    const int mode = (use_masks ? 1 : 0) | (b.hits_counted ? 2 : 0) | (hits ? 4 : 0);
+    const bool tiles = !hits || b.rest_items > 0;  // something for the graph to launch
+    if (tiles && (!b.pexec[pi] || b.pgraph_stream[pi] != s || b.pgraph_pairs[pi] != pairs || b.pgraph_mode[pi] != mode)) {
+        if (b.pexec[pi]) (void)hipGraphExecDestroy(b.pexec[pi]);
+        b.pexec[pi] = nullptr;
+        b.pexec[pi] = capture(s, [&](hipStream_t cs) {
+            if (use_masks)
+                launch_batch_emit(b.probs_dev, b.item_base_dev, b.B, b.queue,
+                                  (int)(b.hits_counted ? b.rest_items : b.total_items), 1, pairs, cs);
+            for (const BatchForm &f : b.forms)
+                if (f.hits && b.hits_counted ? !hits : !use_masks)
+                    launch_batch_form(true, false, f, path, b.probs_dev, b.item_base_dev, b.B, b.queue, pairs, b.ctr, cs);
+        });
+        b.pgraph_stream[pi] = s;
+        b.pgraph_pairs[pi] = pairs;
+        b.pgraph_mode[pi] = mode;
+    }
+    if (tiles) SJ_HIP(hipGraphLaunch(b.pexec[pi], s));
+    if (hits) hit_batch_pairs(b.hb, pout, pairs, s);
     SJ_HIP(hipEventRecord(e1, s));
     SJ_HIP(hipEventSynchronize(e1));
     float ms = 0;

@@ -38,6 +38,7 @@
 
 #include <algorithm>
 #include <cfloat>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -86,6 +87,18 @@ struct HitOut {
     int2 *hits;                  // kHitRegions regions of `cap` entries, or null: count only
     unsigned long long *cursor;  // entries reserved in each region, kHitCursorStride apart
     unsigned long long cap;
+    int32_t row0;                // list entries are rows plus this (batched form: the problem's first row)
+};
+
+// One problem of a batch's hit-list count. Its rows are [row0, row0 + n) of
+// the batch's counts, offsets and list.
+struct HitProb {
+    HitGrid G;
+    double delta;
+    int32_t row0;
+    int32_t nbox;      // index launch: blocks that make boxes (the others: candidate items)
+    double sc;
+    int64_t pout;      // first output row of this problem's pairs
 };
 
 __device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -141,12 +154,13 @@ __device__ __forceinline__ int first_item(const Item *__restrict__ items, int a,
 // blocks after them: the candidate items of each block item and range (the
 // items that hold a row of the range; an item lies in one line, so no item
 // appears twice), and the block of each item.
-__global__ __launch_bounds__(kThreads) void k_hit_index(HitGrid G, double sc, unsigned nbox, float *__restrict__ blo,
-                                                        float *__restrict__ bhi, int2 *__restrict__ span,
-                                                        int32_t *__restrict__ item_block) {
+__device__ __forceinline__ void hit_index_block(const HitGrid &G, double sc, unsigned block, unsigned nbox) {
     __shared__ float lo[kHitMaxD][17], hi[kHitMaxD][17];
-    if (blockIdx.x >= nbox) {  // whole block
-        const int64_t t = (int64_t)(blockIdx.x - nbox) * kThreads + threadIdx.x;
+    float *__restrict__ blo = const_cast<float *>(G.blo), *__restrict__ bhi = const_cast<float *>(G.bhi);
+    int2 *__restrict__ span = const_cast<int2 *>(G.span);
+    int32_t *__restrict__ item_block = const_cast<int32_t *>(G.item_block);
+    if (block >= nbox) {  // whole block
+        const int64_t t = (int64_t)(block - nbox) * kThreads + threadIdx.x;
         if (t >= (int64_t)G.nblocks * G.nranges) return;
         const int b = (int)(t / G.nranges), o = (int)(t - (int64_t)b * G.nranges);
         const int ib = G.blocks[b] - G.item_base, ie = G.blocks[b + 1] - G.item_base;
@@ -162,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_index(HitGrid G, double sc, un
         return;
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int i0 = blockIdx.x * 16;
+    const int i0 = block * 16;
     for (int u = wv; u < 16; u += kWaves) {
         float l = -FLT_MAX, h = INFINITY;  // a padded dimension bounds nothing
         if (i0 + u < G.nitems && lane < G.d) {
@@ -189,6 +203,29 @@ __global__ __launch_bounds__(kThreads) void k_hit_index(HitGrid G, double sc, un
             bhi[(int64_t)t * G.bstride + i0 + u] = hi[t][u];
         }
     }
+}
+
+__global__ __launch_bounds__(kThreads) void k_hit_index(HitGrid G, double sc, unsigned nbox) {
+    hit_index_block(G, sc, blockIdx.x, nbox);
+}
+
+// Last problem p with base[p] <= x.
+template <typename T>
+__device__ __forceinline__ int problem_of(const T *__restrict__ base, int B, T x) {
+    int lo = 0, hi = B;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (base[mid] <= x) lo = mid;
+        else hi = mid;
+    }
+    return uniform_i32(lo);
+}
+
+__global__ __launch_bounds__(kThreads) void k_hit_index_batch(const HitProb *__restrict__ P,
+                                                              const int64_t *__restrict__ first, int B) {
+    const int p = problem_of<int64_t>(first, B, blockIdx.x);
+    const HitGrid G = P[p].G;
+    hit_index_block(G, P[p].sc, blockIdx.x - (unsigned)first[p], P[p].nbox);
 }
 
 // ------------------------------------------------------------- tile parts --
@@ -331,7 +368,7 @@ __device__ __forceinline__ void hit_push(const HitOut &R, HitRun &H, int region,
     }
     if (mine) {
         const unsigned long long e = H.at + lane_rank(m);
-        if (e < R.cap) R.hits[region * R.cap + e] = make_int2(q, c);
+        if (e < R.cap) R.hits[region * R.cap + e] = make_int2(R.row0 + q, R.row0 + c);
     }
     H.at += k;
     H.left -= k;
@@ -513,14 +550,13 @@ constexpr int hit_k(int s, int g) {
 }
 
 template <int KS>
-__global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64(HitGrid G, HitOut R, double delta, int nseg) {
+__device__ __forceinline__ void hit_f64_block(const HitGrid &G, const HitOut &R, double delta, int bi, int seg,
+                                              int nseg) {
     __shared__ double A[4 * KS * 64];
     __shared__ double4_t qn[4 * 4];  // [tile][row group g]: |q|^2 of rows g + 4r
     __shared__ BlockShared S;
     const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i32(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const int lb = xcd_block(blockIdx.x, gridDim.x);
-    const int bi = lb / nseg, seg = lb - bi * nseg;
     const int ib = uniform_i32(G.blocks[bi] - G.item_base), ie = uniform_i32(G.blocks[bi + 1] - G.item_base);
     const int nt = ie - ib;
     // the block's rows are consecutive: only the last item can be short
@@ -577,6 +613,29 @@ __global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64(HitGrid G
         __syncthreads();
     }
     hit_finish(R, S, C, W, q0, nrows, seg, true);
+}
+
+template <int KS>
+__global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64(HitGrid G, HitOut R, double delta, int nseg) {
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    const int bi = lb / nseg;
+    hit_f64_block<KS>(G, R, delta, bi, lb - bi * nseg, nseg);
+}
+
+// The block items of many problems (queue: global block indices, longest
+// first; block_base: the problems' first).
+template <int KS>
+__global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64_batch(const HitProb *__restrict__ P,
+                                                                              const int64_t *__restrict__ block_base,
+                                                                              int B, const int32_t *__restrict__ queue,
+                                                                              HitOut R, int nseg) {
+    const int pos = blockIdx.x / nseg;
+    const int gb = uniform_i32(queue[pos]);
+    const int p = problem_of<int64_t>(block_base, B, gb);
+    const HitGrid G = P[p].G;
+    R.row0 = P[p].row0;
+    R.cnt += R.row0;
+    hit_f64_block<KS>(G, R, P[p].delta, gb - (int)block_base[p], blockIdx.x - pos * nseg, nseg);
 }
 
 // ---------------------------------------------------------- low precision --
@@ -939,17 +998,46 @@ struct EmitOut {
     double *d2;
     int32_t *big;  // [0]: number, then (point, item) of the larger ones
     int32_t per;   // queries of an item that one wave takes (a power of two up to 16)
+    int32_t row0;  // the bins hold rows plus this
 };
 
-__global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
+// What a launch emits: one grid's items, or (P) the items of many problems,
+// item_base their first.
+struct EmitSrc {
+    HitGrid G;
+    EmitOut E;
+    const HitProb *P;
+    const int64_t *item_base;
+    int B;
+};
+
+// The problem of global item `it`: its grid and outputs; returns the item's
+// index in it.
+__device__ __forceinline__ int emit_problem(const EmitSrc &S, int it, HitGrid &G, EmitOut &E) {
+    const int p = problem_of<int64_t>(S.item_base, S.B, it);
+    G = S.P[p].G;
+    E.row0 = S.P[p].row0;
+    E.off += E.row0;
+    E.base = E.off[0] - S.P[p].pout;
+    E.qlo = 0;
+    E.qhi = INT_MAX;
+    return it - (int)S.item_base[p];
+}
+
+template <bool BATCH>
+__global__ __launch_bounds__(kThreads) void k_hit_emit(EmitSrc Src) {
     __shared__ ListMap maps[kWaves];
     __shared__ uint4 keys[kWaves][kWaveBin / 4 + 1];  // positions, or the bitmap
     __shared__ unsigned short before[kWaves][kWinBits / 32];
     const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
     const int64_t w = (int64_t)blockIdx.x * kWaves + wv;
-    const int parts = kTileQ / E.per;
-    const int it = (int)(E.item_lo + w / parts), part = (int)(w % parts);
-    if (it >= E.item_hi) return;
+    const int parts = kTileQ / Src.E.per;
+    const int item = uniform_i32((int)(Src.E.item_lo + w / parts)), part = uniform_i32((int)(w % parts));
+    if (item >= Src.E.item_hi) return;
+    HitGrid G = Src.G;
+    EmitOut E = Src.E;
+    int it = item;
+    if (BATCH) it = emit_problem(Src, item, G, E);
     ListMap &M = maps[wv];
     const Item I = G.items[it];
     const int qb = max(I.qbegin + part * E.per, E.qlo), nq = min(min(I.qend, I.qbegin + (part + 1) * E.per), E.qhi) - qb;
@@ -959,7 +1047,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
     const int64_t offs = E.off[qb + min(lane, nq)];
     const int32_t pqs = G.perm[qb + min(lane, nq - 1)];
     const int64_t o_first = readlane_i64(offs, 0);
-    int nxt = E.bin[o_first + min((int64_t)lane, readlane_i64(offs, 1) - o_first - 1)];
+    int nxt = E.bin[o_first + min((int64_t)lane, readlane_i64(offs, 1) - o_first - 1)] - E.row0;
     const int total = list_map(G, it, lane, M);
     unsigned *ks = reinterpret_cast<unsigned *>(keys[wv]);
     auto settle = [] {
@@ -991,7 +1079,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
             for (int u = 0; u < per; ++u) ks[u * 64 + lane] = 0;
             settle();
             for (int e = lane; e < m; e += 64) {
-                const int p = list_pos(M, e == m - 1 ? q : m <= 64 ? cur : E.bin[o0 + e]) - w0;
+                const int p = list_pos(M, e == m - 1 ? q : m <= 64 ? cur : E.bin[o0 + e] - E.row0) - w0;
                 if (p >= 0 && p < kWinBits) atomicOr(ks + (p >> 5), 1u << (p & 31));
             }
             settle();
@@ -1009,7 +1097,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
             for (int u = 0; u < per; ++u) before[wv][lane * per + u] += (unsigned short)excl;
             settle();
             for (int e = lane; e < m; e += 64) {
-                const int c = e == m - 1 ? q : m <= 64 ? cur : E.bin[o0 + e];
+                const int c = e == m - 1 ? q : m <= 64 ? cur : E.bin[o0 + e] - E.row0;
                 const int p = list_pos(M, c) - w0;
                 if (p >= 0 && p < kWinBits) {
                     const int rank = before[wv][p >> 5] + __popc(ks[p >> 5] & ((1u << (p & 31)) - 1u));
@@ -1026,14 +1114,14 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
         const int cur = nxt;
         if (i + 1 < nq) {  // the next query's neighbours, in flight during this one
             const int64_t o1 = o0 + m64;
-            nxt = E.bin[o1 + min((int64_t)lane, readlane_i64(offs, i + 2) - o1 - 1)];
+            nxt = E.bin[o1 + min((int64_t)lane, readlane_i64(offs, i + 2) - o1 - 1)] - E.row0;
         }
         const int32_t pq = __builtin_amdgcn_readlane(pqs, i);
         if (m64 > kWaveBin) {
             if (lane == 0) {
                 const int s = atomicAdd(E.big, 1);
                 E.big[2 + 2 * s] = q;
-                E.big[3 + 2 * s] = it;
+                E.big[3 + 2 * s] = item;
             }
             continue;
         }
@@ -1058,12 +1146,12 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
         } else {
             for (int e = lane; e < ((m + 3) & ~3); e += 64) {
                 unsigned k = 0xffffffffu;
-                if (e < m) k = (unsigned)list_pos(M, e < m - 1 ? E.bin[o0 + e] : q);
+                if (e < m) k = (unsigned)list_pos(M, e < m - 1 ? E.bin[o0 + e] - E.row0 : q);
                 ks[e] = k;
             }
             settle();
             for (int e = lane; e < m; e += 64) {
-                const int c = e < m - 1 ? E.bin[o0 + e] : q;
+                const int c = e < m - 1 ? E.bin[o0 + e] - E.row0 : q;
                 put(o0 - E.base + rank_of(ks[e], m), pq, q, c, G.perm[c]);
             }
         }
@@ -1072,15 +1160,20 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit(HitGrid G, EmitOut E) {
 
 // Points with many neighbours: one block per point, the list positions of
 // the neighbours as bits of an LDS window, which then leave in order.
-__global__ __launch_bounds__(kThreads) void k_hit_emit_big(HitGrid G, EmitOut E) {
+template <bool BATCH>
+__global__ __launch_bounds__(kThreads) void k_hit_emit_big(EmitSrc Src) {
     __shared__ ListMap M;
     __shared__ unsigned bits[kBigBits / 32];
     __shared__ int wsum[kWaves];
     __shared__ int total_pos;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nbig = E.big[0];
+    const int nbig = Src.E.big[0];
     for (int s = blockIdx.x; s < nbig; s += gridDim.x) {
-        const int q = E.big[2 + 2 * s], it = E.big[3 + 2 * s];
+        HitGrid G = Src.G;
+        EmitOut E = Src.E;
+        const int q = E.big[2 + 2 * s];
+        int it = E.big[3 + 2 * s];
+        if (BATCH) it = emit_problem(Src, it, G, E);
         __syncthreads();
         if (tid < 64) list_map(G, it, lane, M);
         if (tid == 0) {
@@ -1099,7 +1192,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit_big(HitGrid G, EmitOut E)
             for (int e = tid; e < kBigBits / 32; e += kThreads) bits[e] = 0;
             __syncthreads();
             for (int64_t e = tid; e < m; e += kThreads) {
-                const int c = e < m - 1 ? E.bin[o0 + e] : q;
+                const int c = e < m - 1 ? E.bin[o0 + e] - E.row0 : q;
                 const int64_t p = (int64_t)list_pos(M, c) - w0;
                 if (p >= 0 && p < kBigBits) atomicOr(&bits[p >> 5], 1u << (p & 31));
             }
@@ -1147,6 +1240,48 @@ __global__ __launch_bounds__(kThreads) void k_hit_emit_big(HitGrid G, EmitOut E)
     }
 }
 
+// Sort key of each block item of a batch: its K-step count above, then
+// descending cost (its list's length; the blocks of one form have the same
+// number of K-steps); value = global block index.
+__global__ __launch_bounds__(kThreads) void k_hit_cost(const HitProb *__restrict__ P,
+                                                       const int64_t *__restrict__ block_base, int B, int64_t nb,
+                                                       unsigned long long *__restrict__ key, int32_t *__restrict__ val) {
+    const int64_t gb = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (gb >= nb) return;
+    int lo = 0, hi = B;  // the problem (not wave-uniform here)
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (block_base[mid] <= gb) lo = mid;
+        else hi = mid;
+    }
+    const HitGrid &G = P[lo].G;
+    const int b = (int)(gb - block_base[lo]);
+    const int64_t it = G.blocks[b] - G.item_base;
+    unsigned long long c = 0;
+    for (int o = 0; o < G.nranges; ++o) {
+        const Range r = G.ranges[it * G.nranges + o];
+        c += (unsigned long long)max(0, r.end - r.begin);
+    }
+    c = (c + 63) / 64;
+    const unsigned long long cap = (1ull << 27) - 1;
+    key[gb] = ((unsigned long long)(G.da >> 2) << 27) | (cap - (c < cap ? c : cap));
+    val[gb] = (int32_t)gb;
+}
+
+// Totals of a batch's problems, then the entries reserved in the fullest region.
+__global__ __launch_bounds__(kThreads) void k_hit_totals(const HitProb *__restrict__ P, const int64_t *__restrict__ off,
+                                                         int64_t rows, int B,
+                                                         const unsigned long long *__restrict__ cursor,
+                                                         int64_t *__restrict__ out) {
+    const int k = blockIdx.x * kThreads + threadIdx.x;
+    if (k < B) out[k] = off[k + 1 < B ? P[k + 1].row0 : rows] - off[P[k].row0];
+    if (k == B) {
+        unsigned long long m = 0;
+        for (int r = 0; r < kHitRegions; ++r) m = max(m, cursor[r * kHitCursorStride]);
+        out[B] = (int64_t)m;
+    }
+}
+
 // Calls f with the compile-time K-step count `ks` (LO .. HI).
 template <int LO, int HI, typename F>
 void by_k_steps(int ks, F f) {
@@ -1157,6 +1292,8 @@ void by_k_steps(int ks, F f) {
         else by_k_steps<LO + 1, HI>(ks, f);
     }
 }
+
+double hit_scale(const Grid &g) { return std::ldexp(1.0, -std::ilogb(g.eps)); }
 
 HitGrid hit_grid(const Grid &g) {
     HitGrid G{};
@@ -1180,7 +1317,7 @@ HitGrid hit_grid(const Grid &g) {
     G.nblocks = (int32_t)g.nblocks;
     G.item_base = g.item_base;
     G.boxes = g.sc != -1;
-    const double sc = std::ldexp(1.0, -std::ilogb(g.eps));
+    const double sc = hit_scale(g);
     G.sc = sc;
     G.eps_s = g.eps * sc;
     G.eps2_s = g.eps2 * sc * sc;
@@ -1211,10 +1348,16 @@ size_t hit_index_bytes(int64_t items, int64_t nblocks, int nranges, int d) {
 // n = 30000, d = 5, 1.3e8: 559 and 514; n = 9001, d = 23 index-free, 4.9e8: 1169
 // and 502), eps far enough from the ends of the range for the boxes'
 // power-of-two scale.
+static bool hits_fit(const Grid &g) {
+    return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && g.n >= 8 * g.items &&
+           g.eps >= 0x1p-500 && g.eps <= 0x1p500;
+}
+static double hits_work(const Grid &g) { return (double)g.cand_items * (g.da >> 2); }
+constexpr double kHitWork = 0x1p24;
+
 bool hits_usable(const Grid &g, sj_path path) {
-    return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && (path == SJ_FP64_MFMA || path == SJ_FP32_MFMA || path == SJ_BF16X3_MFMA) &&
-           g.n >= 8 * g.items && (double)g.cand_items * (g.da >> 2) >= 0x1p24 && g.eps >= 0x1p-500 &&
-           g.eps <= 0x1p500;
+    return hits_fit(g) && hits_work(g) >= kHitWork &&
+           (path == SJ_FP64_MFMA || path == SJ_FP32_MFMA || path == SJ_BF16X3_MFMA);
 }
 
 size_t hits_lean_bytes(int64_t n, int32_t d) {
@@ -1223,11 +1366,9 @@ size_t hits_lean_bytes(int64_t n, int32_t d) {
     return hit_index_bytes(items, items, 27, d) + 8 * 256;
 }
 
-void hits_prepare(Grid &g, hipStream_t s) {
-    if (g.hit_index) return;
+// Lays the grid's index out at p.
+static void hit_layout(Grid &g, char *p) {
     const size_t dims = (size_t)((g.d + 3) & ~3);
-    char *p = static_cast<char *>(dev_alloc(hit_index_bytes(g.items, g.nblocks, g.nranges, g.d), s));
-    g.hit_index = p;
     g.hit_blo = reinterpret_cast<float *>(p);
     p += align_up(dims * g.items * sizeof(float));
     g.hit_bhi = reinterpret_cast<float *>(p);
@@ -1235,11 +1376,17 @@ void hits_prepare(Grid &g, hipStream_t s) {
     g.hit_item_block = reinterpret_cast<int32_t *>(p);
     p += align_up(g.items * sizeof(int32_t));
     g.hit_span = reinterpret_cast<int2 *>(p);
-    const double sc = std::ldexp(1.0, -std::ilogb(g.eps));
-    const unsigned nbox = (unsigned)((g.items + 15) / 16);
-    const int64_t t = g.nblocks * g.nranges;
-    hipLaunchKernelGGL(k_hit_index, dim3(nbox + (unsigned)((t + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                       hit_grid(g), sc, nbox, g.hit_blo, g.hit_bhi, g.hit_span, g.hit_item_block);
+}
+
+static unsigned box_blocks(const Grid &g) { return (unsigned)((g.items + 15) / 16); }
+static unsigned span_blocks(const Grid &g) { return (unsigned)((g.nblocks * g.nranges + kThreads - 1) / kThreads); }
+
+void hits_prepare(Grid &g, hipStream_t s) {
+    if (g.hit_index) return;
+    g.hit_index = dev_alloc(hit_index_bytes(g.items, g.nblocks, g.nranges, g.d), s);
+    hit_layout(g, static_cast<char *>(g.hit_index));
+    const unsigned nbox = box_blocks(g);
+    hipLaunchKernelGGL(k_hit_index, dim3(nbox + span_blocks(g)), dim3(kThreads), 0, s, hit_grid(g), hit_scale(g), nbox);
     SJ_HIP(hipGetLastError());
 }
 
@@ -1257,11 +1404,11 @@ void hits_free_list(Grid &g, hipStream_t s) {
 // Entries per region for `most` of them in the fullest (0: a first guess of
 // 256 pairs a point, of which half are listed), or 0 when the list would
 // exceed the budget.
-static unsigned long long region_cap(const Grid &g, unsigned long long most) {
-    const unsigned long long waves = (unsigned long long)g.nblocks * kWaves;
-    if (!most) most = (128ull * (unsigned long long)g.n + waves * kHitChunk) / kHitRegions + 16 * kHitChunk;
+static unsigned long long region_cap(int64_t rows, int64_t nblocks, unsigned long long most, int64_t budget) {
+    const unsigned long long waves = (unsigned long long)nblocks * kWaves;
+    if (!most) most = (128ull * (unsigned long long)rows + waves * kHitChunk) / kHitRegions + 16 * kHitChunk;
     most = (most + kHitChunk - 1) / kHitChunk * kHitChunk;
-    return most * kHitRegions * sizeof(int2) <= (unsigned long long)kMaskBudget ? most : 0;
+    return most * kHitRegions * sizeof(int2) <= (unsigned long long)budget ? most : 0;
 }
 
 // Enqueues the count: counts into cnt (n + 1 entries, zeroed here), pairs into
@@ -1275,7 +1422,7 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
     R.cnt = cnt;
     R.ctr = ro.ctr;
     if (record) {  // (a former list is dropped)
-        const unsigned long long cap = region_cap(g, most);
+        const unsigned long long cap = region_cap(g.n, g.nblocks, most, kMaskBudget);
         if (g.hit_bin) dev_free(g.hit_bin, s);
         g.hit_bin = nullptr;
         if (cap > g.hit_cap) {
@@ -1324,7 +1471,7 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
 bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
     unsigned long long most = g.hit_most;
     for (int tries = 0; tries < 2; ++tries) {
-        if (!region_cap(g, most)) return false;
+        if (!region_cap(g.n, g.nblocks, most, kMaskBudget)) return false;
         int32_t *cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
         RefineOut again;
         again.ctr = ro.ctr;
@@ -1347,41 +1494,60 @@ bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
     return false;
 }
 
+// How the list is ordered by point (see k_hit_part): the buckets, or (too
+// many points or pairs for them) the pairs one by one.
+struct BinPlan {
+    int sh, nbuckets;
+    bool parts;
+    int64_t entries;  // each listed pair twice
+    size_t nfill;     // counters, zeroed by the caller
+};
+static BinPlan bin_plan(int64_t rows, int64_t total) {
+    BinPlan b;
+    b.sh = 6;
+    while ((rows >> b.sh) >= kBuckets) ++b.sh;
+    b.nbuckets = (int)std::min<int64_t>((rows + (int64_t(1) << b.sh) - 1) >> b.sh, INT_MAX);
+    b.entries = total - rows;
+    b.parts = b.sh <= 13 && b.entries * (int64_t)sizeof(uint2) <= kMaskBudget;
+    b.nfill = b.parts ? (size_t)b.nbuckets : (size_t)rows;
+    return b;
+}
+static void make_bins(const BinPlan &b, const int2 *hits, const unsigned long long *cursor, unsigned long long cap,
+                      unsigned long long most, const int64_t *off, int64_t rows, int32_t *fill, int32_t *bin,
+                      hipStream_t s) {
+    if (!b.parts) {
+        hipLaunchKernelGGL(k_hit_bin, dim3(256, kHitRegions), dim3(kThreads), 0, s, hits, cursor, cap, off, fill, bin);
+        SJ_HIP(hipGetLastError());
+        return;
+    }
+    uint2 *part = dev_alloc_n<uint2>((size_t)std::max<int64_t>(b.entries, 1), s);
+    const int64_t slabs = (int64_t)(most + kSlab - 1) / kSlab;
+    hipLaunchKernelGGL(k_hit_part, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(slabs, 128)), kHitRegions),
+                       dim3(kPartThreads), 0, s, hits, cursor, cap, off, b.sh, b.nbuckets,
+                       reinterpret_cast<unsigned *>(fill), part);
+    SJ_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_hit_place, dim3((unsigned)b.nbuckets), dim3(kThreads), sizeof(unsigned) << b.sh, s, part, off,
+                       rows, b.sh, bin);
+    SJ_HIP(hipGetLastError());
+    dev_free(part, s);
+}
+
 // Pairs of the chunk from the list (valid): the bins are made on the first
 // call and kept for the chunks that follow.
 void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, bool zero_ctr,
                 RefineOut &ro, hipStream_t s) {
     ro.kt.start(ro.timed, s);
-    int sh = 6;
-    while ((g.n >> sh) >= kBuckets) ++sh;
-    const int nbuckets = (int)((g.n + (int64_t(1) << sh) - 1) >> sh);
-    const int64_t entries = g.total - g.n;  // each listed pair twice
-    const bool parts = sh <= 13 && entries * (int64_t)sizeof(uint2) <= kMaskBudget;
-    const size_t nfill = g.hit_bin ? 0 : parts ? (size_t)nbuckets : (size_t)g.n;
     // more than kWaveBin neighbours: at most written / kWaveBin points
     const size_t nbig = (size_t)(p.written / kWaveBin) + 1;
+    const BinPlan bp = bin_plan(g.n, g.total);
+    const size_t nfill = g.hit_bin ? 0 : bp.nfill;
     int32_t *work = dev_alloc_n<int32_t>(2 + 2 * nbig + nfill, s);
     int32_t *fill = work + 2 + 2 * nbig;
     fill_zero_many({{work, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}, {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
                    s);
     if (!g.hit_bin) {
         g.hit_bin = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(g.total, 1), s);
-        if (parts) {
-            uint2 *part = dev_alloc_n<uint2>((size_t)std::max<int64_t>(entries, 1), s);
-            const int64_t slabs = (int64_t)(g.hit_most + kSlab - 1) / kSlab;
-            hipLaunchKernelGGL(k_hit_part, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(slabs, 128)), kHitRegions),
-                               dim3(kPartThreads), 0, s, g.hits, g.hit_cursor, g.hit_cap, g.off, sh, nbuckets,
-                               reinterpret_cast<unsigned *>(fill), part);
-            SJ_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_hit_place, dim3((unsigned)nbuckets), dim3(kThreads), sizeof(unsigned) << sh, s, part,
-                               g.off, g.n, sh, g.hit_bin);
-            SJ_HIP(hipGetLastError());
-            dev_free(part, s);
-        } else {
-            hipLaunchKernelGGL(k_hit_bin, dim3(256, kHitRegions), dim3(kThreads), 0, s, g.hits, g.hit_cursor,
-                               g.hit_cap, g.off, fill, g.hit_bin);
-            SJ_HIP(hipGetLastError());
-        }
+        make_bins(bp, g.hits, g.hit_cursor, g.hit_cap, g.hit_most, g.off, g.n, fill, g.hit_bin, s);
     }
     const int nitems = (int)(p.item_hi - p.item_lo);
     if (nitems > 0) {
@@ -1401,15 +1567,218 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
         E.per = kTileQ;
         while (E.per > 1 && (int64_t)nitems * (kTileQ / E.per) < 16384) E.per /= 2;
         const int64_t waves = (int64_t)nitems * (kTileQ / E.per);
-        hipLaunchKernelGGL(k_hit_emit, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, G, E);
+        EmitSrc src{G, E, nullptr, nullptr, 0};
+        hipLaunchKernelGGL(k_hit_emit<false>, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, src);
         SJ_HIP(hipGetLastError());
         if (p.written > kWaveBin) {
-            hipLaunchKernelGGL(k_hit_emit_big, dim3((unsigned)std::min<size_t>(nbig, 1024)), dim3(kThreads), 0, s, G, E);
+            hipLaunchKernelGGL(k_hit_emit_big<false>, dim3((unsigned)std::min<size_t>(nbig, 1024)), dim3(kThreads), 0, s,
+                               src);
             SJ_HIP(hipGetLastError());
         }
     }
     dev_free(work, s);
     ro.kt.stop(s);
+}
+
+// ------------------------------------------------------------------ batch --
+// The hit-list count of a batch's problems: those whose grids it takes, if
+// together they have the work. One index launch, one count launch per K-step
+// count over their block items (longest first), one list, and one ordering and
+// emission for all of them (256 problems of 1e3 to 2e5 uniform points, d = 2, 3,
+// 4, 8, 16: count at d = 8 and 16 218 -> 74 ms, the whole call 243 -> 86 ms); their
+// rows follow each other in the counts,
+// offsets and list (entries are rows of all these problems together).
+void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s) {
+    double work = 0;
+    for (size_t i = 0; i < grids.size(); ++i) {
+        const Grid &g = *grids[i];
+        if (!hits_fit(g) || !m64_in_range(g)) continue;
+        hb.probs.push_back((int)i);
+        work += hits_work(g);
+    }
+    if (work < kHitWork) hb.probs.clear();
+    if (hb.probs.empty()) return;
+    const int P = (int)hb.probs.size();
+    // K-step counts grouped: the block queue is made form by form, in this order
+    std::stable_sort(hb.probs.begin(), hb.probs.end(), [&](int a, int b) { return grids[a]->da < grids[b]->da; });
+    size_t bytes = 0;
+    for (int i : hb.probs) bytes += hit_index_bytes(grids[i]->items, grids[i]->nblocks, grids[i]->nranges, grids[i]->d);
+    hb.index = dev_alloc(bytes, s);
+    std::vector<HitProb> hp(P);
+    std::vector<int64_t> bbase(P + 1, 0), ibase(P + 1, 0), first(P + 1, 0);
+    char *at = static_cast<char *>(hb.index);
+    hb.rows = 0;
+    for (int k = 0; k < P; ++k) {
+        Grid &g = *grids[hb.probs[k]];
+        hit_layout(g, at);
+        at += hit_index_bytes(g.items, g.nblocks, g.nranges, g.d);
+        HitProb &x = hp[k];
+        x.G = hit_grid(g);
+        x.delta = fp64_mfma_delta(g);
+        x.row0 = (int32_t)hb.rows;
+        x.nbox = (int32_t)box_blocks(g);
+        x.sc = hit_scale(g);
+        x.pout = 0;
+        hb.rows += g.n;
+        bbase[k + 1] = bbase[k] + g.nblocks;
+        ibase[k + 1] = ibase[k] + g.items;
+        first[k + 1] = first[k] + box_blocks(g) + span_blocks(g);
+        if (hb.forms.empty() || hb.forms.back().ks != g.da >> 2) hb.forms.push_back({g.da >> 2, (int32_t)bbase[k], 0});
+        hb.forms.back().hi = (int32_t)bbase[k + 1];
+    }
+    hb.blocks = bbase[P];
+    hb.items = ibase[P];
+    // one upload: the problems, then the three prefix arrays
+    const size_t pb = align_up(P * sizeof(HitProb)), nb = align_up((P + 1) * sizeof(int64_t));
+    std::vector<char> host(pb + 3 * nb);
+    std::memcpy(host.data(), hp.data(), P * sizeof(HitProb));
+    std::memcpy(host.data() + pb, bbase.data(), (P + 1) * sizeof(int64_t));
+    std::memcpy(host.data() + pb + nb, ibase.data(), (P + 1) * sizeof(int64_t));
+    std::memcpy(host.data() + pb + 2 * nb, first.data(), (P + 1) * sizeof(int64_t));
+    hb.dev = dev_alloc(host.size(), s);
+    SJ_HIP(hipMemcpyAsync(hb.dev, host.data(), host.size(), hipMemcpyHostToDevice, s));
+    SJ_HIP(hipStreamSynchronize(s));
+    hb.host_probs.assign(host.begin(), host.begin() + pb);
+    char *d = static_cast<char *>(hb.dev);
+    hb.block_base = reinterpret_cast<int64_t *>(d + pb);
+    hb.item_base = reinterpret_cast<int64_t *>(d + pb + nb);
+    const HitProb *dp = reinterpret_cast<const HitProb *>(d);
+    hipLaunchKernelGGL(k_hit_index_batch, dim3((unsigned)first[P]), dim3(kThreads), 0, s, dp,
+                       reinterpret_cast<const int64_t *>(d + pb + 2 * nb), P);
+    SJ_HIP(hipGetLastError());
+    // the queue: block items of each form by descending cost
+    unsigned long long *ka = dev_alloc_n<unsigned long long>(hb.blocks, s);
+    unsigned long long *kb = dev_alloc_n<unsigned long long>(hb.blocks, s);
+    int32_t *va = dev_alloc_n<int32_t>(hb.blocks, s), *vb = dev_alloc_n<int32_t>(hb.blocks, s);
+    hipLaunchKernelGGL(k_hit_cost, dim3((unsigned)((hb.blocks + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, dp,
+                       hb.block_base, P, hb.blocks, ka, va);
+    SJ_HIP(hipGetLastError());
+    unsigned long long *ks = ka;
+    int32_t *vs = va;
+    radix_sort_pairs(&ks, &vs, kb, vb, hb.blocks, 32, s);  // cost below the K-step count
+    hb.queue = vs;
+    dev_free(vs == va ? vb : va, s);
+    dev_free(ka, s);
+    dev_free(kb, s);
+    hb.cnt = dev_alloc_n<int32_t>((size_t)hb.rows + 1, s);
+    hb.off = dev_alloc_n<int64_t>((size_t)hb.rows + 1, s);
+    hb.cursor = dev_alloc_n<unsigned long long>(kHitRegions * kHitCursorStride, s);
+}
+
+void hit_batch_free(HitBatch &hb, hipStream_t s) {
+    void *bufs[] = {hb.index, hb.dev, hb.queue, hb.cnt, hb.off, hb.cursor, hb.hits, hb.bin};
+    for (void *p : bufs)
+        if (p) dev_free(p, s);
+    hb = HitBatch{};
+}
+
+// Counts, offsets and totals (totals[i] for problem i of the batch) of these
+// problems, and with `record` the list; counters are added to ctr.
+void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *totals, hipStream_t s) {
+    hb.valid = false;
+    if (hb.bin) dev_free(hb.bin, s);
+    hb.bin = nullptr;
+    if (record) {
+        const unsigned long long cap = region_cap(hb.rows, hb.blocks, hb.most, kHitBatchBudget);
+        if (cap > hb.cap) {
+            if (hb.hits) dev_free(hb.hits, s);
+            hb.hits = nullptr;
+            hb.cap = 0;
+            try {
+                hb.hits = dev_alloc_n<int2>((size_t)(cap * kHitRegions), s);
+                hb.cap = cap;
+            } catch (const OomError &) {  // the pairs call evaluates its tiles again
+            }
+        }
+    }
+    HitOut R{};
+    R.cnt = hb.cnt;
+    R.ctr = ctr;
+    if (record && hb.hits) {
+        R.hits = static_cast<int2 *>(hb.hits);
+        R.cursor = hb.cursor;
+        R.cap = hb.cap;
+    }
+    fill_zero_many({{hb.cnt, ((size_t)hb.rows + 1) * sizeof(int32_t)},
+                    {hb.cursor, kHitRegions * kHitCursorStride * sizeof(unsigned long long)}},
+                   s);
+    const HitProb *dp = static_cast<const HitProb *>(hb.dev);
+    const int P = (int)hb.probs.size();
+    for (const HitBatch::Form &f : hb.forms) {
+        const int nb = f.hi - f.lo;
+        const int nseg = (int)std::max<int64_t>(1, std::min<int64_t>(16, 4096 / nb));
+        by_k_steps<2, 16>(f.ks, [&](auto ks) {
+            hipLaunchKernelGGL(k_hit_f64_batch<decltype(ks)::value>, dim3((unsigned)(nb * nseg)), dim3(kThreads), 0, s,
+                               dp, hb.block_base, P, hb.queue + f.lo, R, nseg);
+        });
+        SJ_HIP(hipGetLastError());
+    }
+    exclusive_scan_i32_to_i64(hb.cnt, hb.off, hb.rows + 1, s);
+    hb.listed = R.hits != nullptr;
+    // totals and the fullest region: one copy
+    int64_t *out = dev_alloc_n<int64_t>(P + 1, s);
+    hipLaunchKernelGGL(k_hit_totals, dim3((unsigned)((P + 1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, dp,
+                       hb.off, hb.rows, P, hb.cursor, out);
+    SJ_HIP(hipGetLastError());
+    std::vector<int64_t> h(P + 1);
+    SJ_HIP(hipMemcpyAsync(h.data(), out, (P + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    SJ_HIP(hipStreamSynchronize(s));
+    dev_free(out, s);
+    hb.total = 0;
+    for (int k = 0; k < P; ++k) {
+        totals[hb.probs[k]] = h[k];
+        hb.total += h[k];
+    }
+    if (hb.listed) {
+        hb.most = (unsigned long long)h[P];
+        hb.valid = hb.most <= hb.cap;
+    }
+}
+
+// A valid list for the pairs call, the count run again where it kept none.
+bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &totals, hipStream_t s) {
+    for (int tries = 0; tries < 2 && !hb.valid; ++tries) {
+        if (!region_cap(hb.rows, hb.blocks, hb.most, kHitBatchBudget)) return false;
+        hit_batch_count(hb, true, ctr, totals.data(), s);
+        if (!hb.listed) return false;
+    }
+    return hb.valid;
+}
+
+// Pairs of these problems from the list, problem i's at pout[i].
+void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pairs, hipStream_t s) {
+    const int P = (int)hb.probs.size();
+    HitProb *hp = reinterpret_cast<HitProb *>(hb.host_probs.data());
+    for (int k = 0; k < P; ++k) hp[k].pout = pout[hb.probs[k]];
+    SJ_HIP(hipMemcpyAsync(hb.dev, hp, P * sizeof(HitProb), hipMemcpyHostToDevice, s));
+    const BinPlan bp = bin_plan(hb.rows, hb.total);
+    const size_t nbig = (size_t)(hb.total / kWaveBin) + 1;
+    int32_t *work = dev_alloc_n<int32_t>(2 + 2 * nbig + bp.nfill, s);
+    int32_t *fill = work + 2 + 2 * nbig;
+    fill_zero_many({{work, sizeof(int32_t)}, {fill, (hb.bin ? 0 : bp.nfill) * sizeof(int32_t)}}, s);
+    if (!hb.bin) {
+        hb.bin = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(hb.total, 1), s);
+        make_bins(bp, static_cast<const int2 *>(hb.hits), hb.cursor, hb.cap, hb.most, hb.off, hb.rows, fill, hb.bin, s);
+    }
+    EmitSrc src{};
+    src.P = static_cast<const HitProb *>(hb.dev);
+    src.item_base = hb.item_base;
+    src.B = P;
+    src.E.off = hb.off;
+    src.E.bin = hb.bin;
+    src.E.item_hi = (int32_t)hb.items;
+    src.E.pairs = reinterpret_cast<int2 *>(pairs);
+    src.E.big = work;
+    src.E.per = kTileQ;
+    while (src.E.per > 1 && hb.items * (kTileQ / src.E.per) < 16384) src.E.per /= 2;
+    const int64_t waves = hb.items * (kTileQ / src.E.per);
+    hipLaunchKernelGGL(k_hit_emit<true>, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, src);
+    SJ_HIP(hipGetLastError());
+    if (hb.total > kWaveBin) {
+        hipLaunchKernelGGL(k_hit_emit_big<true>, dim3((unsigned)std::min<size_t>(nbig, 1024)), dim3(kThreads), 0, s, src);
+        SJ_HIP(hipGetLastError());
+    }
+    dev_free(work, s);
 }
 
 }  // namespace sj

@@ -161,6 +161,7 @@ struct BatchForm {
     int32_t d;
     int32_t lo, hi;
     int32_t sched;
+    bool hits;         // problems of the hit-list count (their FP64 MFMA count is not this form's)
     int32_t blo, bhi;  // FP64 MFMA count, d = 5 .. 16: its block items' positions in the block queue
 };
 
@@ -380,7 +381,8 @@ void launch_batch_zero_counts(const BProb *probs, int B, int64_t max_n, hipStrea
 void launch_sym_cand(const Grid &g, unsigned long long *acc, hipStream_t s);
 void launch_batch_emit(const BProb *probs, const int64_t *item_base, int B, const int32_t *queue, int total,
                        int sched, int32_t *pairs, hipStream_t s);
-void launch_seg_scan(const BProb *probs, int B, int64_t *totals, hipStream_t s);
+// ids: the problems to scan (null: all B).
+void launch_seg_scan(const BProb *probs, const int32_t *ids, int B, int64_t *totals, hipStream_t s);
 DevGrid make_dev_grid(const Grid &g);
 double fp64_mfma_delta(const Grid &g);
 
@@ -414,6 +416,35 @@ bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s);
 void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, bool zero_ctr, RefineOut &ro,
                 hipStream_t s);
 void hits_free_list(Grid &g, hipStream_t s);
+
+// The hit-list count of a batch (FP64 MFMA): the problems it takes, by
+// K-step count, with one index, block queue and list for all of them.
+struct HitBatch {
+    struct Form {
+        int32_t ks, lo, hi;  // K-steps; queue positions
+    };
+    std::vector<int> probs;  // problem indices (empty: not used)
+    std::vector<Form> forms;
+    std::vector<char> host_probs;  // the problems as the device has them
+    void *index = nullptr;         // boxes and candidate items of every problem
+    void *dev = nullptr;           // problems and prefix arrays
+    int64_t *block_base = nullptr, *item_base = nullptr;
+    int32_t *queue = nullptr;
+    int32_t *cnt = nullptr;        // rows + 1
+    int64_t *off = nullptr;        // rows + 1
+    unsigned long long *cursor = nullptr;
+    void *hits = nullptr;
+    int32_t *bin = nullptr;
+    int64_t rows = 0, blocks = 0, items = 0, total = 0;
+    unsigned long long cap = 0, most = 0;
+    bool listed = false, valid = false;
+};
+constexpr int64_t kHitBatchBudget = int64_t(64) << 30;  // largest list of a batch (bytes)
+void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s);
+void hit_batch_free(HitBatch &hb, hipStream_t s);
+void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *totals, hipStream_t s);
+bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &totals, hipStream_t s);
+void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pairs, hipStream_t s);
 
 }  // namespace sj
 

@@ -1631,10 +1631,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 8))
 // One block per problem: exclusive scan of its counts (n + 1 entries, the
 // last taken as 0) into its prefix array, and its total.
 __global__ __launch_bounds__(kThreads) void k_seg_scan(const BProb *__restrict__ probs,
-                                                       int64_t *__restrict__ totals) {
+                                                       const int32_t *__restrict__ ids, int64_t *__restrict__ totals) {
     __shared__ int64_t wsum[kWaves];
     __shared__ int64_t carry;
-    const BProb P = probs[blockIdx.x];
+    const int pi = ids ? ids[blockIdx.x] : (int)blockIdx.x;
+    const BProb P = probs[pi];
     const int64_t n1 = P.G.n + 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) carry = 0;
@@ -1656,7 +1657,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_scan(const BProb *__restrict__
         if (tid == kThreads - 1) carry = pre + x;
         __syncthreads();
     }
-    if (tid == 0) totals[blockIdx.x] = carry;
+    if (tid == 0) totals[pi] = carry;
 }
 
 __global__ void k_batch_reset(DevCounters *ctr) { *ctr = DevCounters{}; }
@@ -1920,9 +1921,9 @@ void launch_batch_emit(const BProb *probs, const int64_t *item_base, int B, cons
 DevGrid make_dev_grid(const Grid &g) { return dev_grid(g); }
 double fp64_mfma_delta(const Grid &g) { return m64_delta(g); }
 
-void launch_seg_scan(const BProb *probs, int B, int64_t *totals, hipStream_t s) {
+void launch_seg_scan(const BProb *probs, const int32_t *ids, int B, int64_t *totals, hipStream_t s) {
     if (B <= 0) return;
-    hipLaunchKernelGGL(k_seg_scan, dim3(B), dim3(kThreads), 0, s, probs, totals);
+    hipLaunchKernelGGL(k_seg_scan, dim3(B), dim3(kThreads), 0, s, probs, ids, totals);
     SJ_HIP(hipGetLastError());
 }
 

@@ -83,3 +83,40 @@ def test_long_bins_and_list_growth(path):
 def test_units_far_from_one(path, scale):
     X = gen.gaussian_mixture(6001, 9, clusters=4, seed=4) * scale
     _same(X, _eps(X / scale, 25) * scale, path)
+
+
+@pytest.mark.parametrize("symmetric", [0, 1])
+@pytest.mark.parametrize("dims", [(8, 16, 5), (2, 8, 3, 16, 20)])
+def test_batch_lists_equal_mask_expansion(symmetric, dims):
+    """A batch with (and without) problems that stay on the per-wave tiles:
+    pairs, offsets and totals of the hit-list count equal those that the
+    vector-ALU path's masks give, in order; repeated counts; and a count on one
+    path with the pairs asked for on the other."""
+    import torch
+    from paper_2209_11287_amd import (selfjoin_batch_build, selfjoin_batch_count, selfjoin_batch_free,
+                                      selfjoin_batch_pairs)
+    rng = np.random.default_rng(11)
+    sizes = [0, 1, 65, 3000, 4511, 2500, 700]
+    X = [rng.random((sizes[k % 7], dims[k % len(dims)])) for k in range(12)]
+    X.append(rng.random((2500, dims[0])) * 1e-3)  # every pair within eps: the list outgrows its first guess
+    eps = [0.1 * x.shape[1] ** 0.5 for x in X]
+    pts = [torch.from_numpy(x).to("cuda:0") for x in X]
+
+    def run(count_path, pairs_path, sym):
+        b = selfjoin_batch_build(pts, eps, symmetric=sym)
+        t0, _ = selfjoin_batch_count(b, count_path)
+        t1, _ = selfjoin_batch_count(b, count_path)
+        buf = torch.full((sum(t1) + 7, 2), -1, dtype=torch.int32, device="cuda:0")
+        offs, _ = selfjoin_batch_pairs(b, pairs_path, buf)
+        again = torch.full_like(buf, -1)
+        selfjoin_batch_pairs(b, pairs_path, again)
+        selfjoin_batch_free(b)
+        assert t0 == t1 and torch.equal(buf, again)
+        return t1, offs, buf.cpu().numpy()
+
+    want = run("fp64_valu", "fp64_valu", 0)
+    for cp, pp in (("fp64_mfma", "fp64_mfma"), ("fp64_mfma", "fp64_valu"), ("fp64_valu", "fp64_mfma")):
+        log(f"[hits] batch dims={dims} symmetric={symmetric} count {cp} pairs {pp}")
+        got = run(cp, pp, symmetric)
+        assert got[0] == want[0] and got[1] == want[1]
+        assert np.array_equal(got[2], want[2])
