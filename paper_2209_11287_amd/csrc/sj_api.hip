@@ -57,50 +57,95 @@ constexpr int32_t kKnnMax = 64;                  // largest k of selfjoin_knn
 constexpr int64_t kKnnBudget = int64_t(1) << 26;  // default pairs held at once (1 GiB with d2)
 
 // k nearest within eps for sorted queries [qlo, qhi) of one pair chunk, one
-// wave per query: k rounds, each taking the smallest (d2, index) key above
-// the previous round's over the query's pairs (the point itself skipped).
-// Rows are written in the input order; unused slots get -1 / +inf.
-__global__ void k_knn_select(const int2 *__restrict__ pairs, const double *__restrict__ d2,
-                             const int64_t *__restrict__ off, int64_t base, const int32_t *__restrict__ perm,
-                             int64_t qlo, int64_t qhi, int32_t k, int32_t *__restrict__ nbr,
-                             double *__restrict__ nbr_d2, int32_t *__restrict__ nfound) {
-    const int lane = threadIdx.x & 63;
-    const int64_t q = qlo + (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+// wave per query, ordered by (d2, index), the point itself skipped.
+// Up to kKnnRank pairs: they sit in LDS and every lane counts, for its pair,
+// the smaller distances (and, where some distances are equal, the smaller
+// indices among those): a pair's rank is its place in the row. About four
+// instructions per pair and 64 pairs, where a round of the selection below
+// takes about 100 and waits for its loads (500k points, 33 pairs each, k = 10:
+// 1.11 ms by rounds).
+// More pairs: k rounds, each taking the smallest key above the previous
+// round's.
+constexpr int kKnnRank = 256;
+constexpr int kKnnWaves = 4;
+
+__global__ __launch_bounds__(64 * kKnnWaves) void k_knn_select(
+    const int2 *__restrict__ pairs, const double *__restrict__ d2, const int64_t *__restrict__ off, int64_t base,
+    const int32_t *__restrict__ perm, int64_t qlo, int64_t qhi, int32_t k, int32_t *__restrict__ nbr,
+    double *__restrict__ nbr_d2, int32_t *__restrict__ nfound) {
+    __shared__ double2 kd[kKnnWaves][kKnnRank / 2];
+    __shared__ int32_t kj[kKnnWaves][kKnnRank];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t q = qlo + (int64_t)blockIdx.x * kKnnWaves + wv;
     if (q >= qhi) return;  // whole wave
     const int64_t b = off[q] - base, e = off[q + 1] - base;
     const int32_t self = perm[q];
     int64_t row = (int64_t)self * k;
-    double pd = -1.0;  // previous key (d2 >= 0)
-    int32_t pj = -1;
     int found = 0;
-    for (; found < k; ++found) {
-        double bd = INFINITY;
-        int32_t bj = INT_MAX;
-        for (int64_t p = b + lane; p < e; p += 64) {
-            const int32_t j = pairs[p].y;
-            if (j == self) continue;
-            const double x = d2[p];
-            const bool above = x > pd || (x == pd && j > pj);
-            if (above && (x < bd || (x == bd && j < bj))) {
-                bd = x;
-                bj = j;
+    if (e - b <= kKnnRank) {
+        const int m = (int)(e - b);
+        double *const d = reinterpret_cast<double *>(kd[wv]);
+        // the point itself (and the filling up) is NaN: below nothing
+        for (int p = lane; p < ((m + 3) & ~3); p += 64) {
+            const int32_t j = p < m ? pairs[b + p].y : self;
+            d[p] = j == self ? NAN : d2[b + p];
+            kj[wv][p] = j;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int p0 = 0; p0 < m; p0 += 64) {
+            const int p = min(p0 + lane, m - 1);
+            const double x = d[p];
+            const int32_t j = kj[wv][p];
+            int less = 0, upto = 0;  // smaller distances; smaller or equal ones
+#pragma unroll 2
+            for (int f = 0; f < (m + 3) >> 2; ++f) {
+                const double2 u = kd[wv][2 * f], v = kd[wv][2 * f + 1];
+                less += (u.x < x) + (u.y < x) + (v.x < x) + (v.y < x);
+                upto += (u.x <= x) + (u.y <= x) + (v.x <= x) + (v.y <= x);
+            }
+            const bool mine = p0 + lane < m && j != self;
+            if (__ballot(mine && upto > less + 1))  // equal distances: by index
+                for (int f = 0; f < m; ++f) less += d[f] == x && kj[wv][f] < j;
+            if (mine && less < k) {
+                nbr[row + less] = j;
+                if (nbr_d2) nbr_d2[row + less] = x;
             }
         }
-        for (int sh = 32; sh > 0; sh >>= 1) {
-            const double od = __shfl_xor(bd, sh);
-            const int32_t oj = __shfl_xor(bj, sh);
-            if (od < bd || (od == bd && oj < bj)) {
-                bd = od;
-                bj = oj;
+        found = min(k, m - 1);
+    } else {
+        double pd = -1.0;  // previous key (d2 >= 0)
+        int32_t pj = -1;
+        for (; found < k; ++found) {
+            double bd = INFINITY;
+            int32_t bj = INT_MAX;
+            for (int64_t p = b + lane; p < e; p += 64) {
+                const int32_t j = pairs[p].y;
+                if (j == self) continue;
+                const double x = d2[p];
+                const bool above = x > pd || (x == pd && j > pj);
+                if (above && (x < bd || (x == bd && j < bj))) {
+                    bd = x;
+                    bj = j;
+                }
             }
+            for (int sh = 32; sh > 0; sh >>= 1) {
+                const double od = __shfl_xor(bd, sh);
+                const int32_t oj = __shfl_xor(bj, sh);
+                if (od < bd || (od == bd && oj < bj)) {
+                    bd = od;
+                    bj = oj;
+                }
+            }
+            if (bj == INT_MAX) break;  // wave-uniform after the reduction
+            if (lane == 0) {
+                nbr[row + found] = bj;
+                if (nbr_d2) nbr_d2[row + found] = bd;
+            }
+            pd = bd;
+            pj = bj;
         }
-        if (bj == INT_MAX) break;  // wave-uniform after the reduction
-        if (lane == 0) {
-            nbr[row + found] = bj;
-            if (nbr_d2) nbr_d2[row + found] = bd;
-        }
-        pd = bd;
-        pj = bj;
     }
     for (int r = found + lane; r < k; r += 64) {
         nbr[row + r] = -1;
@@ -607,7 +652,7 @@ sj_status selfjoin_knn(sj_grid *gh, sj_path path, int32_t k, int64_t pair_budget
         re.ctr = ctr.p;
         refine_pairs(g, run, p, cursor, pairs.p, pd2.p, re, s);
         const int64_t nq = p.next - cursor;
-        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((nq + kKnnWaves - 1) / kKnnWaves)), dim3(64 * kKnnWaves), 0, s,
                            reinterpret_cast<const int2 *>(pairs.p), pd2.p, g.off, p.base, g.perm, cursor, p.next, k,
                            nbr, nbr_d2, nfound);
         SJ_HIP(hipGetLastError());
