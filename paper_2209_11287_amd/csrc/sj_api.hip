@@ -33,17 +33,19 @@ __global__ void k_total_to_ctr(const int64_t *total, const unsigned long long *c
 }
 
 // Core flags in the input order and their number (one counter atomic per
-// block).
-__global__ void k_core_flags(const int32_t *__restrict__ cnt, const int32_t *__restrict__ perm, int64_t n,
-                             int32_t min_pts, uint8_t *__restrict__ is_core, unsigned long long *__restrict__ ncore) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool core = false;
-    if (i < n) {
-        core = cnt[i] >= min_pts;
+// block, 1024 blocks: atomics on one address take about 13 ns each, one after the
+// other, and a block for every 256 points made 100 us of them at 2M points).
+__global__ __launch_bounds__(256) void k_core_flags(const int32_t *__restrict__ cnt, const int32_t *__restrict__ perm,
+                                                    int64_t n, int32_t min_pts, uint8_t *__restrict__ is_core,
+                                                    unsigned long long *__restrict__ ncore) {
+    unsigned c = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const bool core = cnt[i] >= min_pts;
         is_core[perm[i]] = core ? 1 : 0;
+        c += core;
     }
     __shared__ unsigned part[256 / 64];
-    const unsigned c = (unsigned)__popcll(__ballot(core));
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -681,7 +683,7 @@ sj_status selfjoin_core_points(sj_grid *gh, sj_path path, int32_t min_pts, uint8
     if (g.n > 0) {
         DevBuf<unsigned long long> dc(1, s);
         fill_zero(dc.p, sizeof(unsigned long long), s);
-        hipLaunchKernelGGL(k_core_flags, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, g.cnt, g.perm, g.n,
+        hipLaunchKernelGGL(k_core_flags, dim3((unsigned)std::min<int64_t>((g.n + 255) / 256, 1024)), dim3(256), 0, s, g.cnt, g.perm, g.n,
                            min_pts, is_core, dc.p);
         SJ_HIP(hipGetLastError());
         SJ_HIP(hipMemcpyAsync(&hc, dc.p, sizeof hc, hipMemcpyDeviceToHost, s));

@@ -73,28 +73,48 @@ struct BuildReadback {
     int32_t err;
     int32_t pad;
     double nmax;
-    unsigned long long acc[3];  // item candidates, tiles, united candidates
+    unsigned long long cand;   // candidate pairs of the items
+    unsigned long long tiles;  // in-mask tile slots
 };
 
-__global__ void k_build_readback(const int32_t *__restrict__ counters, const int32_t *__restrict__ err,
-                                 const double *__restrict__ nmax, const unsigned long long *__restrict__ acc,
-                                 BuildReadback *__restrict__ out) {
-    BuildReadback r;
-    for (int i = 0; i < 4; ++i) r.c[i] = counters[i];
-    r.err = *err;
-    r.pad = 0;
-    r.nmax = *nmax;
-    for (int i = 0; i < 3; ++i) r.acc[i] = acc[i];
-    *out = r;
+// Gathers them in one block: the tables' sizes, and the sums and maximum over
+// the other kernels' per-block partials (a single-address atomic per block
+// takes about 13 ns of its own each).
+__global__ __launch_bounds__(kThreads) void k_build_readback(const int32_t *__restrict__ counters,
+                                                             const int32_t *__restrict__ err,
+                                                             const double *__restrict__ nmax_part, int64_t n_nmax,
+                                                             const unsigned long long *__restrict__ cand_part,
+                                                             int n_cand, const int64_t *__restrict__ tile_off,
+                                                             double *__restrict__ nmax_out,
+                                                             BuildReadback *__restrict__ out) {
+    __shared__ double smax[kThreads];
+    __shared__ unsigned long long ssum[kThreads];
+    double m = 0.0;
+    unsigned long long c = 0;
+    for (int64_t i = threadIdx.x; i < n_nmax; i += kThreads) m = fmax(m, nmax_part[i]);
+    for (int i = threadIdx.x; i < n_cand; i += kThreads) c += cand_part[i];
+    smax[threadIdx.x] = m;
+    ssum[threadIdx.x] = c;
+    __syncthreads();
+    for (int w = kThreads / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) {
+            smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + w]);
+            ssum[threadIdx.x] += ssum[threadIdx.x + w];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        BuildReadback r;
+        for (int i = 0; i < 4; ++i) r.c[i] = counters[i];
+        r.err = *err;
+        r.pad = 0;
+        r.nmax = smax[0];
+        r.cand = ssum[0];
+        r.tiles = (unsigned long long)tile_off[r.c[2]];
+        *nmax_out = smax[0];
+        *out = r;
+    }
 }
-
-void fill_ones(void *p, size_t bytes, hipStream_t s) {
-    if (!bytes) return;
-    unsigned blocks = (unsigned)std::min<size_t>((bytes + kThreads - 1) / kThreads, 4096);
-    hipLaunchKernelGGL(k_fill_u8, dim3(blocks), dim3(kThreads), 0, s, (unsigned char *)p, bytes, (unsigned char)0xff);
-    SJ_HIP(hipGetLastError());
-}
-
 
 // ---------------------------------------------------------------- bbox ----
 // Each block reduces a contiguous run of rows. Threads walk the run's
@@ -106,7 +126,7 @@ void fill_ones(void *p, size_t bytes, hipStream_t s) {
 template <bool MOM>
 __global__ void k_bbox_partial(const double *__restrict__ X, int64_t n, int d, int64_t rows_per_block,
                                double *__restrict__ pmin, double *__restrict__ pmax, double *__restrict__ psum,
-                               double *__restrict__ psq, int *__restrict__ bad) {
+                               double *__restrict__ psq, double *__restrict__ pbad) {
     __shared__ double smin[kThreads], smax[kThreads];
     __shared__ double ssum[MOM ? kThreads : 1], ssq[MOM ? kThreads : 1];
     const int S = (kThreads / d) * d;
@@ -137,8 +157,8 @@ __global__ void k_bbox_partial(const double *__restrict__ X, int64_t n, int d, i
         ssum[tid] = s1;
         ssq[tid] = s2;
     }
-    if (nonfinite) atomicOr(bad, 1);
-    __syncthreads();
+    nonfinite = __syncthreads_or(nonfinite);
+    if (tid == 0) pbad[blockIdx.x] = nonfinite ? 1.0 : 0.0;
     if (tid < d) {
         double a = INFINITY, b = -INFINITY, c1 = 0.0, c2 = 0.0;
         for (int t = tid; t < S; t += d) {
@@ -159,12 +179,21 @@ __global__ void k_bbox_partial(const double *__restrict__ X, int64_t n, int d, i
 }
 
 // One block per dimension j: out[j] = min, out[d + j] = max and, with the
-// moments (psum non-null), out[2d + j], out[3d + j] = their sums.
+// moments (psum non-null), out[2d + j], out[3d + j] = their sums; one more block:
+// *bad = whether any block met a non-finite value.
 __global__ void k_bbox_final(const double *__restrict__ pmin, const double *__restrict__ pmax,
-                             const double *__restrict__ psum, const double *__restrict__ psq, int nb, int d,
-                             double *__restrict__ out) {
+                             const double *__restrict__ psum, const double *__restrict__ psq,
+                             const double *__restrict__ pbad, int nb, int d, double *__restrict__ out,
+                             double *__restrict__ bad) {
     __shared__ double smin[kThreads], smax[kThreads], s1[kThreads], s2[kThreads];
     const int j = blockIdx.x;
+    if (j == d) {
+        int any = 0;
+        for (int t = threadIdx.x; t < nb; t += blockDim.x) any |= pbad[t] != 0.0;
+        any = __syncthreads_or(any);
+        if (threadIdx.x == 0) *bad = any ? 1.0 : 0.0;
+        return;
+    }
     double a = INFINITY, b = -INFINITY, c1 = 0.0, c2 = 0.0;
     for (int t = threadIdx.x; t < nb; t += blockDim.x) {
         a = fmin(a, pmin[(int64_t)t * d + j]);
@@ -517,9 +546,11 @@ constexpr int kScanItems = 16;
 constexpr int kScanTile = kThreads * kScanItems;
 
 template <typename Tin, typename Tacc>
-__global__ void k_scan_sums(const Tin *__restrict__ in, int64_t n, Tacc *__restrict__ sums) {
+__global__ void k_scan_sums(const Tin *__restrict__ in, int64_t n, Tacc *__restrict__ sums,
+                            const int32_t *__restrict__ limit) {
     __shared__ Tacc part[kThreads / 64];
     const int64_t t0 = (int64_t)blockIdx.x * kScanTile;
+    if (limit && t0 > *limit) return;  // entries past *limit are not wanted
     Tacc acc = 0;
     if (sizeof(Tin) == 4 && t0 + kScanTile <= n) {
         // whole tile: 16-byte loads, each wave reading 1 KB runs (the tile
@@ -552,7 +583,9 @@ __global__ void k_scan_sums(const Tin *__restrict__ in, int64_t n, Tacc *__restr
 // scanned across the wave and the block.
 template <typename Tin, typename Tacc>
 __global__ void k_scan_tiles(const Tin *__restrict__ in, Tacc *__restrict__ out, int64_t n,
-                             const Tacc *__restrict__ carry, const Tacc *__restrict__ sums) {
+                             const Tacc *__restrict__ carry, const Tacc *__restrict__ sums,
+                             const int32_t *__restrict__ limit) {
+    if (limit && (int64_t)blockIdx.x * kScanTile > *limit) return;
     __shared__ Tacc wsum[kThreads / 64];
     __shared__ Tacc csum[kThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -634,33 +667,35 @@ __global__ void k_scan_tiles(const Tin *__restrict__ in, Tacc *__restrict__ out,
     }
 }
 
+// limit (device, nullable): only the entries up to *limit are wanted.
 template <typename Tin, typename Tacc>
-void exclusive_scan(const Tin *in, Tacc *out, int64_t n, hipStream_t s) {
+void exclusive_scan(const Tin *in, Tacc *out, int64_t n, hipStream_t s, const int32_t *limit = nullptr) {
     if (n <= 0) return;
     const int64_t tiles = (n + kScanTile - 1) / kScanTile;
     if (tiles == 1) {
         hipLaunchKernelGGL((k_scan_tiles<Tin, Tacc>), dim3(1), dim3(kThreads), 0, s, in, out, n,
-                           (const Tacc *)nullptr, (const Tacc *)nullptr);
+                           (const Tacc *)nullptr, (const Tacc *)nullptr, limit);
         SJ_HIP(hipGetLastError());
         return;
     }
     if (tiles <= 8192) {  // two launches: tile sums, then tiles that add up the sums before them
         Tacc *sums = dev_alloc_n<Tacc>(tiles, s);
-        hipLaunchKernelGGL((k_scan_sums<Tin, Tacc>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, n, sums);
+        hipLaunchKernelGGL((k_scan_sums<Tin, Tacc>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, n, sums, limit);
         SJ_HIP(hipGetLastError());
         hipLaunchKernelGGL((k_scan_tiles<Tin, Tacc>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, out, n,
-                           (const Tacc *)nullptr, (const Tacc *)sums);
+                           (const Tacc *)nullptr, (const Tacc *)sums, limit);
         SJ_HIP(hipGetLastError());
         dev_free(sums, s);
         return;
     }
     Tacc *sums = dev_alloc_n<Tacc>(tiles, s);
     Tacc *sums_ex = dev_alloc_n<Tacc>(tiles, s);
-    hipLaunchKernelGGL((k_scan_sums<Tin, Tacc>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, n, sums);
+    hipLaunchKernelGGL((k_scan_sums<Tin, Tacc>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, n, sums,
+                       (const int32_t *)nullptr);
     SJ_HIP(hipGetLastError());
     exclusive_scan<Tacc, Tacc>(sums, sums_ex, tiles, s);
     hipLaunchKernelGGL((k_scan_tiles<Tin, Tacc>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, out, n,
-                       (const Tacc *)sums_ex, (const Tacc *)nullptr);
+                       (const Tacc *)sums_ex, (const Tacc *)nullptr, (const int32_t *)nullptr);
     SJ_HIP(hipGetLastError());
     dev_free(sums, s);
     dev_free(sums_ex, s);
@@ -685,21 +720,6 @@ __device__ __forceinline__ void block_max_out(double v, double *__restrict__ par
         double m = part[0];
         for (int w = 1; w < kThreads / 64; ++w) m = fmax(m, part[w]);
         part_out[blockIdx.x] = m;
-    }
-}
-
-// One block: maximum of `nb` partials into *out.
-__global__ void k_max_final(const double *__restrict__ part, int64_t nb, double *__restrict__ out) {
-    double v = 0.0;
-    for (int64_t i = threadIdx.x; i < nb; i += blockDim.x) v = fmax(v, part[i]);
-    __shared__ double red[kThreads / 64];
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = red[0];
-        for (int w = 1; w < kThreads / 64; ++w) m = fmax(m, red[w]);
-        *out = m;
     }
 }
 
@@ -861,37 +881,322 @@ __global__ void k_gather4(const double *__restrict__ X, const int32_t *__restric
     block_max_out(mx, nmax_part);
 }
 
-// ----------------------------------------------------------- cell table ----
-// Sorted keys carry `sb` sub-cell bits below the cell key.
-__global__ void k_cell_flags(const unsigned long long *__restrict__ key, int64_t n, int sb,
-                             int32_t *__restrict__ flag) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) flag[i] = (i == 0 || (key[i] >> sb) != (key[i - 1] >> sb)) ? 1 : 0;
+// --------------------------------------------------------------- tables ----
+// Division by a value that does not change, by its reciprocal: floor(2^64 / m)
+// underestimates the quotient of a 64-bit value by at most two.
+struct FastDiv {
+    unsigned long long m, inv;
+};
+FastDiv fast_div(unsigned long long m) {
+    // floor(2^64 / m) for m >= 2 (2^64 - 1 = q m + r: one more when r = m - 1)
+    const unsigned long long q = ~0ull / m, r = ~0ull % m;
+    return FastDiv{m, m == 1 ? 0ull : (r == m - 1 ? q + 1 : q)};
+}
+__device__ __forceinline__ unsigned long long div_by(unsigned long long v, const FastDiv &d) {
+    if (d.m == 1) return v;
+    unsigned long long q = __umul64hi(v, d.inv), r = v - q * d.m;
+    if (r >= d.m) {
+        ++q;
+        r -= d.m;
+    }
+    if (r >= d.m) ++q;
+    return q;
 }
 
-__global__ void k_cell_write(const unsigned long long *__restrict__ key, int sb, const int32_t *__restrict__ flag,
-                             const int32_t *__restrict__ cid, int64_t n, int64_t *__restrict__ cell_key,
-                             int32_t *__restrict__ cell_start, int32_t *__restrict__ ncells) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (flag[i]) {
-        cell_key[cid[i]] = (int64_t)(key[i] >> sb);
-        cell_start[cid[i]] = (int32_t)i;
+// The cells, lines, work items and block items of the sorted keys (`sb`
+// sub-cell bits below the cell key), in two passes over the keys in place of a
+// flag pass, a scan and a write pass for each of the four tables (17 launches;
+// at 20,000 points they were a third of the build, at 2M about 110 us).
+// A position starts a cell where its cell key differs from the one before, a
+// line where the key without the last indexed coordinate does; in a line of L
+// points, ceil(L / 16) items start at multiples of 16 points from the line's
+// start and ceil(L / 64) block items at multiples of 64. A stretch of positions
+// is summarised by its cells and lines, the rows before its first line start
+// and from its last one, and the items and blocks of the lines between: that
+// summary composes (a line cut by a boundary is closed when its two parts
+// meet), so a pass over tiles gives each tile the state it starts with.
+constexpr int kTabSteps = 16;  // most steps of 64 positions per wave
+constexpr int64_t kTabDirect = 8192;               // tiles up to which each joins those before it by itself
+
+struct TabSum {
+    int32_t cells, lines;
+    int32_t pre, suf;  // rows before the first line start (all, without one); from the last one
+    int32_t items, blocks;
+};
+
+__host__ __device__ __forceinline__ TabSum tab_empty() { return TabSum{0, 0, 0, 0, 0, 0}; }
+
+__device__ __forceinline__ TabSum tab_join(const TabSum &a, const TabSum &b) {
+    TabSum r;
+    r.cells = a.cells + b.cells;
+    r.lines = a.lines + b.lines;
+    r.pre = a.lines ? a.pre : a.pre + b.pre;
+    r.suf = b.lines ? b.suf : a.suf + b.pre;  // (a without a line start: not used)
+    r.items = a.items + b.items;
+    r.blocks = a.blocks + b.blocks;
+    if (a.lines && b.lines) {
+        const int len = a.suf + b.pre;
+        r.items += (len + kTileQ - 1) / kTileQ;
+        r.blocks += (len + kBlockItems * kTileQ - 1) / (kBlockItems * kTileQ);
     }
-    if (i == n - 1) {
-        const int32_t c = cid[i] + flag[i];
-        *ncells = c;
-        cell_start[c] = (int32_t)n;
+    return r;
+}
+
+struct TabMasks {
+    unsigned long long cell, line;  // which of 64 consecutive positions start one
+};
+
+// The keys of 64 positions as their masks: each lane has its own key and line,
+// the one before comes from its neighbour (lane 0: from the step before).
+struct TabScan {
+    unsigned long long cell, line;  // last position so far (none: ~0)
+};
+
+__device__ __forceinline__ unsigned long long shfl_up_u64(unsigned long long v) {
+    const unsigned lo = __shfl_up((unsigned)v, 1), hi = __shfl_up((unsigned)(v >> 32), 1);
+    return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ unsigned long long last_u64(unsigned long long v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), 63);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+__device__ __forceinline__ TabScan tab_before(const unsigned long long *__restrict__ key, int64_t i0, int sb,
+                                              const FastDiv &ml) {
+    TabScan t{~0ull, ~0ull};
+    if (i0 > 0) {
+        t.cell = key[i0 - 1] >> sb;
+        t.line = div_by(t.cell, ml);
+    }
+    return t;
+}
+
+// v: the lane's key (any value past n).
+__device__ __forceinline__ TabMasks tab_masks(TabScan &t, unsigned long long v, bool in, int sb, const FastDiv &ml,
+                                              int lane) {
+    const unsigned long long c = v >> sb, l = div_by(c, ml);
+    unsigned long long pc = shfl_up_u64(c), pl = shfl_up_u64(l);
+    if (lane == 0) {
+        pc = t.cell;
+        pl = t.line;
+    }
+    t.cell = last_u64(c);
+    t.line = last_u64(l);
+    return TabMasks{__ballot(in && c != pc), __ballot(in && l != pl)};
+}
+
+// Summary of 64 positions (fewer at the end: `rows`).
+__device__ __forceinline__ TabSum tab_of(const TabMasks &m, int rows) {
+    TabSum r = tab_empty();
+    r.cells = __popcll(m.cell);
+    r.lines = __popcll(m.line);
+    if (!m.line) {
+        r.pre = rows;
+        return r;
+    }
+    r.pre = __builtin_ctzll(m.line);
+    const int last = 63 - __builtin_clzll(m.line);
+    r.suf = rows - last;
+    unsigned long long left = m.line & (m.line - 1);
+    for (int at = r.pre; left; left &= left - 1) {  // lines within (at most 64 rows: one block each)
+        const int nx = __builtin_ctzll(left);
+        r.items += (nx - at + kTileQ - 1) / kTileQ;
+        ++r.blocks;
+        at = nx;
+    }
+    return r;
+}
+
+__global__ __launch_bounds__(kThreads) void k_table_sums(const unsigned long long *__restrict__ key, int64_t n, int sb,
+                                                         FastDiv ml, int steps, TabSum *__restrict__ wave_sums,
+                                                         TabSum *__restrict__ tile_sums) {
+    __shared__ TabSum part[kThreads / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t w = (int64_t)blockIdx.x * (kThreads / 64) + wv;
+    const int64_t w0 = w * 64 * steps;
+    TabSum r = tab_empty();
+    if (w0 < n) {
+        TabScan t = tab_before(key, w0, sb, ml);
+        for (int s0 = 0; s0 < steps; s0 += 4) {
+            unsigned long long v[4];  // four steps' loads in flight together
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = key[min(w0 + 64 * (s0 + u) + lane, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t i0 = w0 + 64 * (s0 + u);
+                if (s0 + u >= steps || i0 >= n) break;
+                r = tab_join(r, tab_of(tab_masks(t, v[u], i0 + lane < n, sb, ml, lane), (int)min<int64_t>(64, n - i0)));
+            }
+        }
+    }
+    if (lane == 0) {
+        wave_sums[w] = r;
+        part[wv] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        TabSum t = part[0];
+        for (int k = 1; k < kThreads / 64; ++k) t = tab_join(t, part[k]);
+        tile_sums[blockIdx.x] = t;
     }
 }
 
-// Line of a cell: its key without the last indexed coordinate.
-__global__ void k_line_flags(const int64_t *__restrict__ cell_key, const int32_t *__restrict__ ncells_p,
-                             int64_t m_last, int32_t *__restrict__ lflag) {
-    const int64_t ncells = *ncells_p;
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncells) return;
-    lflag[c] = (c == 0 || cell_key[c] / m_last != cell_key[c - 1] / m_last) ? 1 : 0;
+// Ordered join of the entries [0, m) of sums over the block's threads; the
+// result in every thread.
+__device__ __forceinline__ TabSum tab_block_join(const TabSum *__restrict__ sums, int64_t m) {
+    __shared__ TabSum part[kThreads];
+    const int64_t per = (m + kThreads - 1) / kThreads;
+    const int64_t a = min(m, per * threadIdx.x), b = min(m, a + per);
+    TabSum r = tab_empty();
+    for (int64_t i = a; i < b; ++i) r = tab_join(r, sums[i]);
+    part[threadIdx.x] = r;
+    __syncthreads();
+    for (int w = 1; w < kThreads; w <<= 1) {
+        if ((threadIdx.x & (2 * w - 1)) == 0) part[threadIdx.x] = tab_join(part[threadIdx.x], part[threadIdx.x + w]);
+        __syncthreads();
+    }
+    return part[0];
+}
+
+// Exclusive joins of the tile sums (one block; many tiles).
+__global__ __launch_bounds__(kThreads) void k_table_scan(const TabSum *__restrict__ tile_sums, int64_t tiles,
+                                                         TabSum *__restrict__ base) {
+    __shared__ TabSum part[kThreads];
+    __shared__ TabSum carry;
+    if (threadIdx.x == 0) carry = tab_empty();
+    for (int64_t t0 = 0; t0 < tiles; t0 += kThreads) {
+        const int64_t t = t0 + threadIdx.x;
+        part[threadIdx.x] = t < tiles ? tile_sums[t] : tab_empty();
+        __syncthreads();
+        for (int w = 1; w < kThreads; w <<= 1) {  // inclusive
+            TabSum v = part[threadIdx.x];
+            if ((int)threadIdx.x >= w) v = tab_join(part[threadIdx.x - w], v);
+            __syncthreads();
+            part[threadIdx.x] = v;
+            __syncthreads();
+        }
+        if (t < tiles) base[t] = threadIdx.x ? tab_join(carry, part[threadIdx.x - 1]) : carry;
+        __syncthreads();
+        if (threadIdx.x == 0) carry = tab_join(carry, part[kThreads - 1]);
+        __syncthreads();
+    }
+}
+
+struct Tables {
+    int64_t *cell_key;
+    int32_t *cell_start;  // + end
+    int32_t *line_first;  // first cell of each line, + end
+    int32_t *line_row;    // first row of each line, + end
+    int32_t *line_table;  // dense line key -> line id + 1 (0: empty), or null
+    Item *items;
+    int32_t *bflag;       // per item: starts a block item
+    int32_t *blocks;      // first item of each block item, + end
+    int32_t *counters;    // ncells, nlines, nitems, nblocks
+};
+
+__global__ __launch_bounds__(kThreads) void k_table_write(const unsigned long long *__restrict__ key, int64_t n, int sb,
+                                                          FastDiv ml, int steps, const TabSum *__restrict__ wave_sums,
+                                                          const TabSum *__restrict__ tile_sums,
+                                                          const TabSum *__restrict__ base, Tables T) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int kW = kThreads / 64;
+    TabSum S = base ? base[blockIdx.x] : tab_block_join(tile_sums, blockIdx.x);
+    for (int w = 0; w < wv; ++w) S = tab_join(S, wave_sums[(int64_t)blockIdx.x * kW + w]);
+    const int64_t w0 = ((int64_t)blockIdx.x * kW + wv) * 64 * steps;
+    if (w0 >= n) return;
+    // running state: cells, lines, items and blocks of the closed lines, start of the open line
+    int cells = S.cells, lines = S.lines, items = S.items, blocks = S.blocks;
+    int64_t open = S.lines ? w0 - S.suf : 0;
+    const unsigned long long le = lane == 63 ? ~0ull : (2ull << lane) - 1ull;  // positions up to the lane's
+    TabScan ts = tab_before(key, w0, sb, ml);
+    auto key_at = [&](int64_t i0) { return key[min(i0 + lane, n - 1)]; };
+    // the keys two steps ahead are in flight while a step is written
+    unsigned long long k1 = key_at(w0), k2 = key_at(w0 + 64);
+    TabMasks nx = tab_masks(ts, k1, w0 + lane < n, sb, ml, lane);
+    for (int st = 0; st < steps; ++st) {
+        const int64_t i0 = w0 + 64 * st;
+        if (i0 >= n) break;
+        const TabMasks m = nx;
+        const unsigned long long own = k1;
+        k1 = k2;
+        k2 = key_at(i0 + 128);
+        nx = tab_masks(ts, k1, i0 + 64 + lane < n, sb, ml, lane);  // the next 64 (items end there)
+        const int64_t i = i0 + lane;
+        const bool in = i < n;
+        const unsigned long long mle = m.line & le, mlt = m.line & (le >> 1);
+        const int ci = cells + __popcll(m.cell & le) - 1;   // the lane's cell
+        const int li = lines + __popcll(mle) - 1;           // and line
+        const int64_t start = mle ? i0 + (63 - __builtin_clzll(mle)) : open;
+        // items and blocks of the lines closed at or before the lane
+        int ic = items, bc = blocks;
+        if (m.line) {
+            const bool here = (m.line >> lane) & 1ull;
+            const int64_t before = mlt ? i0 + (63 - __builtin_clzll(mlt)) : open;
+            const int len = here && li > 0 ? (int)(i - before) : 0;
+            int a = (len + kTileQ - 1) / kTileQ, b = (len + kBlockItems * kTileQ - 1) / (kBlockItems * kTileQ);
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(a, o), y = __shfl_up(b, o);
+                if (lane >= o) {
+                    a += x;
+                    b += y;
+                }
+            }
+            ic += a;
+            bc += b;
+        }
+        if (in && ((m.cell >> lane) & 1ull)) {
+            const unsigned long long k = own >> sb;
+            T.cell_key[ci] = (int64_t)k;
+            T.cell_start[ci] = (int32_t)i;
+            if ((m.line >> lane) & 1ull) {
+                T.line_first[li] = ci;
+                T.line_row[li] = (int32_t)i;
+                if (T.line_table) T.line_table[div_by(k, ml)] = li + 1;
+            }
+        }
+        const unsigned at = (unsigned)(i - start);  // the lane's place in its line
+        if (in && at % kTileQ == 0) {
+            const int it = ic + (int)(at / kTileQ);
+            // the item's end: 16 points on, or the next line
+            const unsigned long long cl = m.cell, cn = nx.cell;
+            const int sh = lane + 1;
+            // starts among the next 63 positions: bit u = position i + 1 + u
+            const unsigned long long ln = (sh < 64 ? m.line >> sh : 0ull) | (nx.line << (63 - lane));
+            const unsigned long long ce = (sh < 64 ? cl >> sh : 0ull) | (cn << (63 - lane));
+            int len = ln ? min(kTileQ, 1 + __builtin_ctzll(ln)) : kTileQ;
+            len = (int)min<int64_t>(len, n - i);
+            Item r;
+            r.qbegin = (int32_t)i;
+            r.qend = (int32_t)i + len;
+            r.cell_first = ci;
+            r.cell_last = ci + __popcll(ce & ((1ull << (len - 1)) - 1ull));
+            T.items[it] = r;
+            const bool bs = at % (kBlockItems * kTileQ) == 0;
+            T.bflag[it] = bs;
+            if (bs) T.blocks[bc + (int)(at / (kBlockItems * kTileQ))] = it;
+        }
+        if (i == n - 1) {
+            const int L = (int)(i - start) + 1;
+            const int ni = ic + (L + kTileQ - 1) / kTileQ;
+            const int nb = bc + (L + kBlockItems * kTileQ - 1) / (kBlockItems * kTileQ);
+            T.cell_start[ci + 1] = (int32_t)n;
+            T.line_first[li + 1] = ci + 1;
+            T.line_row[li + 1] = (int32_t)n;
+            T.blocks[nb] = ni;
+            T.counters[0] = ci + 1;
+            T.counters[1] = li + 1;
+            T.counters[2] = ni;
+            T.counters[3] = nb;
+        }
+        cells += __popcll(m.cell);
+        lines += __popcll(m.line);
+        if (m.line) {
+            items = __shfl(ic, 63);
+            blocks = __shfl(bc, 63);
+            open = i0 + (63 - __builtin_clzll(m.line));
+        }
+    }
 }
 
 // Per line: first cell, and the number of work items (ceil(points / kTileQ)).
@@ -1021,7 +1326,7 @@ __device__ __forceinline__ Range line_segment(const int64_t *__restrict__ cell_k
     Range r{0, 0};
     int64_t a = 0, b = ncells;
     if (line_of_key) {
-        const int32_t lid = line_of_key[base / mlast];
+        const int32_t lid = line_of_key[base / mlast] - 1;  // 0: an empty line
         if (lid < 0) return r;
         a = line_first[lid];
         b = line_first[lid + 1];
@@ -1052,6 +1357,19 @@ __device__ __forceinline__ int64_t neighbour_line(const int64_t *cc, int o, cons
     return base;
 }
 
+// Block sum into part[blockIdx.x].
+__device__ __forceinline__ void block_sum_out(unsigned long long v, unsigned long long *__restrict__ part_out) {
+    __shared__ unsigned long long part[kThreads / 64];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int w = 0; w < kThreads / 64; ++w) t += part[w];
+        part_out[blockIdx.x] = t;
+    }
+}
+
 // Block sum then one atomic per block.
 __device__ __forceinline__ void block_add(unsigned long long v, unsigned long long *out) {
     __shared__ unsigned long long part[kThreads / 64];
@@ -1065,61 +1383,121 @@ __device__ __forceinline__ void block_add(unsigned long long v, unsigned long lo
     }
 }
 
-// Ranges of every work item (grid-stride over item x offset), plus the
-// number of candidate pairs the items see. A range starts as the cells
-// c_first - 1 .. c_last + 1 of a neighbour line. With sub-cell bits a point's
-// position along the line is p = c_last * 2^sb + sub = floor(t 2^sb) (clamped,
-// monotone), t = fl(fl(x - lo) / w); a pair within eps differs by less than
-// w on the last indexed dimension, so by at most 2^sb in p. The range is cut
-// to positions [p(first query) - 2^sb - 1, p(last query) + 2^sb + 1] (the
-// item's queries are in key order) by two binary searches over the sorted
-// keys.
-__global__ void k_item_ranges(const Item *__restrict__ items, const int32_t *__restrict__ nitems_p,
-                              const int64_t *__restrict__ cell_key, const int32_t *__restrict__ cell_start,
-                              const int32_t *__restrict__ ncells_p, RangeGeom geo,
-                              const int32_t *__restrict__ line_of_key, const int32_t *__restrict__ line_first,
-                              const unsigned long long *__restrict__ skey, Range *__restrict__ ranges,
-                              unsigned long long *__restrict__ cand_items) {
-    const int64_t total = (int64_t)(*nitems_p) * geo.nranges;
-    const int64_t ncells = *ncells_p;
-    const int kl = geo.k - 1;
-    const int64_t mlast = geo.m[kl];
+// Ranges of every work item, the number of candidate pairs the items see (per
+// block, into cand_part) and, with `tiles`, each item's in-mask tile slots (see
+// k_item_tiles). A range is the rows of a neighbour line whose last coordinate is
+// in c_first - 1 .. c_last + 1. With sub-cell bits a point's position along the
+// line is p = c_last * 2^sb + sub = floor(t 2^sb) (clamped, monotone), t = fl(fl(x
+// - lo) / w); a pair within eps differs by less than w on the last indexed
+// dimension, so by at most 2^sb in p, and the range is cut to positions [p(first
+// query) - 2^sb - 1, p(last query) + 2^sb + 1] (the item's queries are in key
+// order). Both bounds are keys of the neighbour line, found by one search over its
+// rows (over all rows without the line table).
+// A block takes 64 consecutive items, lane i item i, its waves taking the
+// neighbour lines in turn (`split` blocks share the items' lines when there are
+// few items): the lanes of a wave then search one line, mostly, for places 16
+// rows apart, so their probes share cache lines. With a line per lane the searches
+// were bound by the 64 lines that every load touched (uniform 4-d set of 2M
+// points: 241 us).
+struct ItemGeom {
+    int k, nranges, sb;
+    FastDiv last;                      // cells of the last indexed dimension
+    FastDiv lead[kMaxIndexDims];       // strides of the leading ones, in lines
+    int64_t m[kMaxIndexDims];
+};
+
+constexpr int kMaxRanges = 27;
+
+__global__ __launch_bounds__(kThreads) void k_item_ranges(const Item *__restrict__ items,
+                                                          const int32_t *__restrict__ nitems_p, ItemGeom geo,
+                                                          const int32_t *__restrict__ line_table,
+                                                          const int32_t *__restrict__ line_row,
+                                                          const unsigned long long *__restrict__ skey, int64_t n,
+                                                          int split, Range *__restrict__ ranges,
+                                                          int32_t *__restrict__ tiles,
+                                                          unsigned long long *__restrict__ cand_part) {
+    __shared__ Range out[64 * kMaxRanges];
+    __shared__ int lens[kThreads];
+    const int I = *nitems_p;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int kl = geo.k - 1, nr = geo.nranges;
+    const int64_t mlast = (int64_t)geo.last.m, span = int64_t(1) << geo.sb;
+    constexpr int kW = kThreads / 64;
     unsigned long long acc = 0;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t it = t / geo.nranges;
-        const int o = (int)(t - it * geo.nranges);
-        const Item I = items[it];
-        // keys of the item's first and last query (read ahead of the searches)
-        const unsigned long long kf = geo.sb > 0 ? skey[I.qbegin] : 0ull;
-        const unsigned long long kb = geo.sb > 0 ? skey[I.qend - 1] : 0ull;
-        int64_t c0[kMaxIndexDims], c1[kMaxIndexDims];
-        decode_key(cell_key[I.cell_first], geo, c0);
-        decode_key(cell_key[I.cell_last], geo, c1);
-        const int64_t base = neighbour_line(c0, o, geo);
-        Range r{0, 0};
-        if (base >= 0) {
-            const int64_t lo_c = c0[kl] > 0 ? c0[kl] - 1 : 0;
-            const int64_t hi_c = c1[kl] < mlast - 1 ? c1[kl] + 1 : c1[kl];
-            r = line_segment(cell_key, cell_start, ncells, line_of_key, line_first, base, mlast, lo_c, hi_c);
-            if (geo.sb > 0 && r.end > r.begin) {
-                const unsigned long long sub = (1ull << geo.sb) - 1ull;
-                const int64_t pf = (int64_t)((((kf >> geo.sb) % (unsigned long long)mlast) << geo.sb) | (kf & sub));
-                const int64_t pb = (int64_t)((((kb >> geo.sb) % (unsigned long long)mlast) << geo.sb) | (kb & sub));
-                const int64_t span = int64_t(1) << geo.sb, pmax = mlast * span - 1;
-                const int64_t plo = max(pf - span - 1, int64_t(0)), phi = min(pb + span + 1, pmax);
-                const unsigned long long klo = ((unsigned long long)base << geo.sb) + (unsigned long long)plo;
-                const unsigned long long khi = ((unsigned long long)base << geo.sb) + (unsigned long long)phi;
-                int64_t x0, x1;  // first key >= klo, first key > khi
-                bounds2<unsigned long long>(skey, r.begin, r.end, klo, khi, x0, x1);
+    const int part = blockIdx.x % split;
+    for (int64_t t0 = (int64_t)(blockIdx.x / split) * 64; t0 < I; t0 += (int64_t)(gridDim.x / split) * 64) {
+        const int64_t it = t0 + lane;
+        const bool have = it < I;
+        int nq = 0, len = 0;
+        unsigned long long line = 0;
+        int64_t plo = 0, phi = -1;
+        if (have) {
+            const Item q = items[it];
+            nq = q.qend - q.qbegin;
+            const unsigned long long kf = skey[q.qbegin], kb = skey[q.qend - 1];
+            const unsigned long long cf = kf >> geo.sb, cb = kb >> geo.sb;
+            line = div_by(cf, geo.last);
+            const int64_t first = (int64_t)(cf - line * geo.last.m), lastc = (int64_t)(cb - line * geo.last.m);
+            plo = max(first - 1, int64_t(0)) * span;
+            phi = (min(lastc + 1, mlast - 1) + 1) * span - 1;
+            if (geo.sb > 0) {
+                const int64_t sub = span - 1;
+                plo = max(plo, first * span + (int64_t)(kf & (unsigned long long)sub) - span - 1);
+                phi = min(phi, lastc * span + (int64_t)(kb & (unsigned long long)sub) + span + 1);
+            }
+        }
+        for (int o = part * kW + wv; o < nr; o += split * kW) {
+            Range r{0, 0};
+            // the neighbour line
+            unsigned long long left = line;
+            int64_t nl = 0;
+            int oo = o;
+            bool in = have;
+            for (int j = 0; j < kl; ++j) {
+                const unsigned long long c = div_by(left, geo.lead[j]);
+                left -= c * geo.lead[j].m;
+                const int64_t cj = (int64_t)c + oo % 3 - 1;
+                oo /= 3;
+                in = in && cj >= 0 && cj < geo.m[j];
+                nl += cj * (int64_t)geo.lead[j].m;
+            }
+            int64_t a = 0, b = n;
+            if (in && line_table) {
+                const int32_t id = line_table[nl];
+                in = id > 0;
+                if (in) {
+                    a = line_row[id - 1];
+                    b = line_row[id];
+                }
+            }
+            if (in) {
+                const unsigned long long base = ((unsigned long long)nl * geo.last.m) << geo.sb;
+                int64_t x0, x1;
+                bounds2<unsigned long long>(skey, a, b, base + (unsigned long long)plo, base + (unsigned long long)phi,
+                                            x0, x1);
                 r.begin = (int32_t)x0;
                 r.end = (int32_t)x1;
             }
+            len += r.end - r.begin;
+            if (split == 1) out[lane * nr + o] = r;
+            else if (have) ranges[it * nr + o] = r;
         }
-        ranges[t] = r;
-        acc += (unsigned long long)(I.qend - I.qbegin) * (unsigned long long)(r.end - r.begin);
+        acc += (unsigned long long)nq * (unsigned long long)len;
+        if (split == 1) {
+            lens[threadIdx.x] = len;
+            __syncthreads();
+            const int m = (int)min<int64_t>(64, I - t0) * nr;
+            for (int e = threadIdx.x; e < m; e += kThreads) ranges[t0 * nr + e] = out[e];
+            if (tiles && wv == 0 && have) {
+                int c = len;
+                for (int w = 1; w < kW; ++w) c += lens[64 * w + lane];
+                tiles[it] = (((c + 15) >> 4) + 15) & ~15;
+            }
+            __syncthreads();
+        }
     }
-    block_add(acc, cand_items);
+    if (tiles && split == 1 && blockIdx.x == 0 && threadIdx.x == 0) tiles[I] = 0;  // the scan ends with the total
+    block_sum_out(acc, cand_part);
 }
 
 // d > 4: the ranges of every item become the union of its block item's
@@ -1131,7 +1509,7 @@ __global__ void k_item_ranges(const Item *__restrict__ items, const int32_t *__r
 // Also the candidate pairs the items then see.
 __global__ void k_unite_ranges(const Item *__restrict__ items, const int32_t *__restrict__ nitems_p,
                                const int32_t *__restrict__ bflag, int nranges, const Range *__restrict__ in,
-                               Range *__restrict__ out, unsigned long long *__restrict__ cand_items) {
+                               Range *__restrict__ out, unsigned long long *__restrict__ cand_part) {
     const int64_t I = *nitems_p;
     unsigned long long acc = 0;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < I * nranges;
@@ -1155,7 +1533,7 @@ __global__ void k_unite_ranges(const Item *__restrict__ items, const int32_t *__
         const Item m = items[it];
         acc += (unsigned long long)(m.qend - m.qbegin) * (unsigned long long)(u.end - u.begin);
     }
-    block_add(acc, cand_items);
+    block_sum_out(acc, cand_part);
 }
 
 // Mask slots of each work item: its candidates (the ranges in order) form one
@@ -1175,11 +1553,6 @@ __global__ void k_item_tiles(const Range *__restrict__ ranges, const int32_t *__
         }
     const int64_t nt = (c + 15) / 16;
     tiles[it] = (int32_t)((nt + 15) / 16 * 16);
-}
-
-__global__ void k_tiles_total(const int64_t *__restrict__ tile_off, const int32_t *__restrict__ nitems_p,
-                              unsigned long long *__restrict__ out) {
-    *out = (unsigned long long)tile_off[*nitems_p];
 }
 
 // C_ref = sum over non-empty cells c of |c| * (points in the 3^k cells around
@@ -1207,14 +1580,6 @@ __global__ void k_cell_cref(const int64_t *__restrict__ cell_key, const int32_t 
     block_add(acc, cref);
 }
 
-// Dense map line key -> compact line id (-1 for empty lines).
-__global__ void k_line_table(const int64_t *__restrict__ cell_key, const int32_t *__restrict__ line_first,
-                             const int32_t *__restrict__ nlines_p, int64_t m_last, int32_t *__restrict__ table) {
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= *nlines_p) return;
-    table[cell_key[line_first[l]] / m_last] = (int32_t)l;
-}
-
 RangeGeom range_geom(const Grid &g) {
     RangeGeom rg{};
     rg.k = g.k;
@@ -1225,6 +1590,19 @@ RangeGeom range_geom(const Grid &g) {
     }
     rg.sb = g.sub_bits;
     return rg;
+}
+
+ItemGeom item_geom(const Grid &g) {
+    ItemGeom ig{};
+    ig.k = g.k;
+    ig.nranges = g.nranges;
+    ig.sb = g.sub_bits;
+    ig.last = fast_div((unsigned long long)g.m[g.k - 1]);
+    for (int j = 0; j < g.k; ++j) {
+        ig.m[j] = g.m[j];
+        if (j < g.k - 1) ig.lead[j] = fast_div((unsigned long long)(g.stride[j] / g.m[g.k - 1]));
+    }
+    return ig;
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + kThreads - 1) / kThreads); }
@@ -1426,31 +1804,29 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
         const int64_t rows_per_block = std::max<int64_t>(1024, (n + 2047) / 2048);
         const int nb = (int)std::max<int64_t>(1, (n + rows_per_block - 1) / rows_per_block);
         const int parts = mom ? 4 : 2;
-        double *part = dev_alloc_n<double>((size_t)parts * nb * d, s);
+        double *part = dev_alloc_n<double>((size_t)parts * nb * d + nb, s);
         double *pmin = part, *pmax = part + (size_t)nb * d;
         double *psum = mom ? part + 2 * (size_t)nb * d : nullptr;
         double *psq = mom ? part + 3 * (size_t)nb * d : nullptr;
         const size_t nbox = (size_t)(mom ? 4 : 2) * d;
         double *box = dev_alloc_n<double>(nbox + 1, s);
-        int *bad = reinterpret_cast<int *>(box + nbox);
-        fill_zero(bad, sizeof(int), s);
+        double *pbad = part + (size_t)parts * nb * d;
         if (mom)
             hipLaunchKernelGGL(k_bbox_partial<true>, dim3(nb), dim3(kThreads), 0, s, points, n, d, rows_per_block,
-                               pmin, pmax, psum, psq, bad);
+                               pmin, pmax, psum, psq, pbad);
         else
             hipLaunchKernelGGL(k_bbox_partial<false>, dim3(nb), dim3(kThreads), 0, s, points, n, d, rows_per_block,
-                               pmin, pmax, psum, psq, bad);
+                               pmin, pmax, psum, psq, pbad);
         SJ_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_bbox_final, dim3(d), dim3(kThreads), 0, s, pmin, pmax, psum, psq, nb, d, box);
+        hipLaunchKernelGGL(k_bbox_final, dim3(d + 1), dim3(kThreads), 0, s, pmin, pmax, psum, psq, pbad, nb, d, box,
+                           box + nbox);
         SJ_HIP(hipGetLastError());
         std::vector<double> hb(nbox + 1);
         SJ_HIP(hipMemcpyAsync(hb.data(), box, (nbox + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
         SJ_HIP(hipStreamSynchronize(s));
         dev_free(part, s);
         dev_free(box, s);
-        int badflag;
-        std::memcpy(&badflag, &hb[nbox], sizeof(int));
-        if (badflag) throw std::string("non-finite coordinate in points");
+        if (hb[nbox] != 0.0) throw std::string("non-finite coordinate in points");
         for (int j = 0; j < d; ++j) {
             g.lo[j] = hb[j];
             g.hi[j] = hb[d + j];
@@ -1530,23 +1906,30 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     g.npc = d > 4 ? g.da / 4 - 1 : 0;
     if (g.npc > 0) g.pn = dev_alloc_n<double>(rows * g.npc, s);
     g.dev_nmax = dev_alloc_n<double>(1, s);
-    int32_t *counters = dev_alloc_n<int32_t>(4, s);                    // ncells, nlines, nitems
-    unsigned long long *acc = dev_alloc_n<unsigned long long>(3, s);  // item candidates, tiles, united candidates
-    // padding rows, nmax (n = 0), counters: one launch
+    int32_t *counters = dev_alloc_n<int32_t>(4, s);  // ncells, nlines, nitems, nblocks
+    // dense line table when the leading indexed dimensions span few lines
+    int64_t nline_keys = 1;
+    for (int j = 0; j < g.k - 1; ++j) nline_keys *= g.m[j];
+    if (n > 0 && nline_keys <= (g.lean ? kLeanLineTable : (int64_t(1) << 24)))
+        g.line_table = dev_alloc_n<int32_t>((size_t)nline_keys, s);
+    // padding rows, nmax (n = 0), counters, line table: one launch
     fill_zero_many({{g.xs + (size_t)n * g.dp, (size_t)kRowPad * g.dp * sizeof(double)},
                     {g.xa + (size_t)n * g.da, (size_t)kRowPad * g.da * sizeof(double)},
                     {g.nrm + n, (size_t)kRowPad * sizeof(double)},
                     {g.pn ? g.pn + (size_t)n * g.npc : nullptr, (size_t)kRowPad * g.npc * sizeof(double)},
                     {g.dev_nmax, sizeof(double)},
                     {counters, 4 * sizeof(int32_t)},
-                    {acc, 3 * sizeof(unsigned long long)}},
+                    {g.line_table, g.line_table ? (size_t)nline_keys * sizeof(int32_t) : 0}},
                    s);
+    double *nmax_part = nullptr;
+    int64_t n_nmax = 0;
     if (n > 0) {
         const bool lds_rows = d >= 16 && d <= kGatherLdsD;
         const unsigned nb = d <= 4 ? std::min(blocks_for(4 * n), 4096u)
                             : lds_rows ? (unsigned)((n + kGatherRows - 1) / kGatherRows)
                                        : blocks_for(n);
-        double *part = dev_alloc_n<double>(nb, s);
+        double *part = nmax_part = dev_alloc_n<double>(nb, s);
+        n_nmax = nb;
         if (d <= 4) {
             Mid4 mid{};
             for (int j = 0; j < d; ++j) mid.m[j] = g.mid[j];
@@ -1570,91 +1953,73 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
                                    g.nrm, g.pn, part);
         }
         SJ_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_max_final, dim3(1), dim3(kThreads), 0, s, part, (int64_t)nb, g.dev_nmax);
-        SJ_HIP(hipGetLastError());
-        dev_free(part, s);
     }
 
-    // ---- G4: cell table, lines, work items ----
-    // flags / scan scratch, reused for cells (n), lines (<= n) and items (<= n + n/16 + 1)
-    int32_t *flag = dev_alloc_n<int32_t>(n + n / kTileQ + 2, s);
-    int32_t *cid = dev_alloc_n<int32_t>(n + n / kTileQ + 2, s);
+    // ---- G4 + G5: cells, lines, work items, and the items' neighbour ranges
+    // (tables sized by upper bounds) ----
+    const int64_t items_ub = n + n / kTileQ + 1;  // lines <= cells <= n
     g.cell_key = dev_alloc_n<int64_t>(n + 1, s);
     g.cell_start = dev_alloc_n<int32_t>(n + 2, s);
-    int32_t *line_first = dev_alloc_n<int32_t>(n + 2, s);
-    int32_t *nitem = dev_alloc_n<int32_t>(n + 1, s);
-    int32_t *item_off = dev_alloc_n<int32_t>(n + 1, s);
-    if (n > 0) {
-        hipLaunchKernelGGL(k_cell_flags, dim3(blocks_for(n)), dim3(kThreads), 0, s, key_a, n, g.sub_bits, flag);
-        SJ_HIP(hipGetLastError());
-        exclusive_scan<int32_t, int32_t>(flag, cid, n, s);
-        hipLaunchKernelGGL(k_cell_write, dim3(blocks_for(n)), dim3(kThreads), 0, s, key_a, g.sub_bits, flag, cid, n,
-                           g.cell_key, g.cell_start, counters + 0);
-        SJ_HIP(hipGetLastError());
-        // lines (cells grid-stride bounded by n)
-        hipLaunchKernelGGL(k_line_flags, dim3(blocks_for(n)), dim3(kThreads), 0, s, g.cell_key, counters + 0,
-                           (int64_t)g.m[g.k - 1], flag);
-        SJ_HIP(hipGetLastError());
-        exclusive_scan<int32_t, int32_t>(flag, cid, n, s);  // entries past ncells are ignored
-        hipLaunchKernelGGL(k_line_write, dim3(blocks_for(n)), dim3(kThreads), 0, s, flag, cid, g.cell_start,
-                           counters + 0, line_first, counters + 1);
-        SJ_HIP(hipGetLastError());
-        fill_zero(nitem, (size_t)(n + 1) * sizeof(int32_t), s);
-        hipLaunchKernelGGL(k_line_items, dim3(blocks_for(n)), dim3(kThreads), 0, s, line_first, g.cell_start,
-                           counters + 1, nitem);
-        SJ_HIP(hipGetLastError());
-    }
-    // ---- G5: work items and their neighbour ranges (tables sized by upper bounds) ----
-    const int64_t items_ub = n + n / kTileQ + 1;  // lines <= cells <= n
-    g.tile_off = dev_alloc_n<int64_t>((size_t)items_ub + 1, s);
+    g.line_first = dev_alloc_n<int32_t>(n + 2, s);  // kept by the grid (lazy C_ref)
+    int32_t *line_row = dev_alloc_n<int32_t>(n + 2, s);
+    int32_t *bflag = dev_alloc_n<int32_t>((size_t)items_ub + 1, s);
     int32_t *item_tiles = dev_alloc_n<int32_t>((size_t)items_ub + 1, s);
+    g.tile_off = dev_alloc_n<int64_t>((size_t)items_ub + 1, s);
     g.item = dev_alloc_n<Item>((size_t)items_ub, s);
     g.blocks = dev_alloc_n<int32_t>((size_t)items_ub + 1, s);
     g.ranges = dev_alloc_n<Range>((size_t)items_ub * g.nranges, s);
-    g.line_first = line_first;
-    line_first = nullptr;  // kept by the grid (lazy C_ref)
+    unsigned long long *cand_part = nullptr;
+    int n_cand = 0;
     if (n > 0) {
-        exclusive_scan<int32_t, int32_t>(nitem, item_off, n, s);  // entries past nlines are ignored
-        hipLaunchKernelGGL(k_items_total, dim3(1), dim3(1), 0, s, nitem, item_off, counters + 1, counters + 2);
+        // about 2048 blocks, at most kTabSteps steps a wave
+        const int steps = (int)std::max<int64_t>(1, std::min<int64_t>(kTabSteps, (n + 256 * 2048 - 1) / (256 * 2048)));
+        const int64_t tile = (int64_t)kThreads * steps, tiles = (n + tile - 1) / tile;
+        const FastDiv ml = fast_div((unsigned long long)g.m[g.k - 1]);
+        TabSum *wave_sums = dev_alloc_n<TabSum>((size_t)tiles * (kThreads / 64), s);
+        TabSum *tile_sums = dev_alloc_n<TabSum>((size_t)tiles, s);
+        TabSum *tile_base = tiles > kTabDirect ? dev_alloc_n<TabSum>((size_t)tiles, s) : nullptr;
+        hipLaunchKernelGGL(k_table_sums, dim3((unsigned)tiles), dim3(kThreads), 0, s, key_a, n, g.sub_bits, ml, steps,
+                           wave_sums, tile_sums);
         SJ_HIP(hipGetLastError());
-        // dense line table when the leading indexed dimensions span few lines
-        int64_t nline_keys = 1;
-        for (int j = 0; j < g.k - 1; ++j) nline_keys *= g.m[j];
-        if (nline_keys <= (g.lean ? kLeanLineTable : (int64_t(1) << 24))) {
-            g.line_table = dev_alloc_n<int32_t>((size_t)nline_keys, s);
-            fill_ones(g.line_table, (size_t)nline_keys * sizeof(int32_t), s);
-            hipLaunchKernelGGL(k_line_table, dim3(blocks_for(n)), dim3(kThreads), 0, s, g.cell_key, g.line_first,
-                               counters + 1, (int64_t)g.m[g.k - 1], g.line_table);
+        if (tile_base) {
+            hipLaunchKernelGGL(k_table_scan, dim3(1), dim3(kThreads), 0, s, tile_sums, tiles, tile_base);
             SJ_HIP(hipGetLastError());
         }
-        hipLaunchKernelGGL(k_items, dim3(blocks_for(items_ub)), dim3(kThreads), 0, s, g.line_first, item_off,
-                           g.cell_start, counters + 1, counters + 2, g.item, flag);
+        const Tables T{g.cell_key, g.cell_start, g.line_first, line_row, g.line_table, g.item, bflag, g.blocks, counters};
+        hipLaunchKernelGGL(k_table_write, dim3((unsigned)tiles), dim3(kThreads), 0, s, key_a, n, g.sub_bits, ml, steps,
+                           wave_sums, tile_sums, tile_base, T);
         SJ_HIP(hipGetLastError());
-        // block items (groups of up to kBlockItems items of one line)
-        exclusive_scan<int32_t, int32_t>(flag, cid, items_ub, s);
-        hipLaunchKernelGGL(k_blocks, dim3(blocks_for(items_ub)), dim3(kThreads), 0, s, flag, cid, counters + 2,
-                           g.blocks, counters + 3);
-        SJ_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_item_ranges, dim3(2048), dim3(kThreads), 0, s, g.item, counters + 2, g.cell_key,
-                           g.cell_start, counters + 0, range_geom(g), g.line_table, g.line_first, key_a,
-                           g.ranges, acc);
+        dev_free(wave_sums, s);
+        dev_free(tile_sums, s);
+        if (tile_base) dev_free(tile_base, s);
+        // few items: their neighbour lines are split over more blocks
+        const int64_t groups = (items_ub + 63) / 64;
+        const int split = groups >= 512 || g.nranges <= kThreads / 64
+                              ? 1
+                              : (g.nranges + kThreads / 64 - 1) / (kThreads / 64);
+        n_cand = (int)std::min<int64_t>(groups, 2048) * split;
+        cand_part = dev_alloc_n<unsigned long long>((size_t)n_cand, s);
+        const bool own_tiles = d > 4 || split > 1;  // tile slots: from the united (or complete) ranges
+        hipLaunchKernelGGL(k_item_ranges, dim3(n_cand), dim3(kThreads), 0, s, g.item, counters + 2, item_geom(g),
+                           g.line_table, line_row, key_a, n, split, g.ranges, own_tiles ? nullptr : item_tiles,
+                           cand_part);
         SJ_HIP(hipGetLastError());
         if (d > 4) {  // block items share one candidate list
             Range *united = dev_alloc_n<Range>((size_t)items_ub * g.nranges, s);
-            hipLaunchKernelGGL(k_unite_ranges, dim3(2048), dim3(kThreads), 0, s, g.item, counters + 2, flag,
-                               g.nranges, g.ranges, united, acc + 2);
+            hipLaunchKernelGGL(k_unite_ranges, dim3(n_cand), dim3(kThreads), 0, s, g.item, counters + 2, bflag,
+                               g.nranges, g.ranges, united, cand_part);
             SJ_HIP(hipGetLastError());
             dev_free(g.ranges, s);
             g.ranges = united;
             g.united = true;
         }
+        if (own_tiles) {
+            hipLaunchKernelGGL(k_item_tiles, dim3(blocks_for(items_ub + 1)), dim3(kThreads), 0, s, g.ranges,
+                               counters + 2, g.nranges, item_tiles);
+            SJ_HIP(hipGetLastError());
+        }
         // tile offsets of the items (for the per-tile in-masks of the count pass)
-        hipLaunchKernelGGL(k_item_tiles, dim3(blocks_for(items_ub + 1)), dim3(kThreads), 0, s, g.ranges,
-                           counters + 2, g.nranges, item_tiles);
-        SJ_HIP(hipGetLastError());
-        exclusive_scan<int32_t, int64_t>(item_tiles, g.tile_off, items_ub + 1, s);
-        hipLaunchKernelGGL(k_tiles_total, dim3(1), dim3(1), 0, s, g.tile_off, counters + 2, acc + 1);
-        SJ_HIP(hipGetLastError());
+        exclusive_scan<int32_t, int64_t>(item_tiles, g.tile_off, items_ub + 1, s, counters + 2);
     }
     // ---- one host sync: table sizes, candidates of the items, nmax (gathered
     // on the device into one block, so that one copy brings them all) ----
@@ -1662,14 +2027,14 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     BuildReadback *rb_dev = nullptr;
     if (n > 0) {
         rb_dev = dev_alloc_n<BuildReadback>(1, s);
-        hipLaunchKernelGGL(k_build_readback, dim3(1), dim3(1), 0, s, counters, os_err, g.dev_nmax, acc, rb_dev);
+        hipLaunchKernelGGL(k_build_readback, dim3(1), dim3(kThreads), 0, s, counters, os_err, nmax_part, n_nmax,
+                           cand_part, n_cand, g.tile_off, g.dev_nmax, rb_dev);
         SJ_HIP(hipGetLastError());
         SJ_HIP(hipMemcpyAsync(&rb, rb_dev, sizeof rb, hipMemcpyDeviceToHost, s));
     }
     const int32_t *hc = rb.c;
     const int32_t herr = rb.err;
     const double hn = rb.nmax;
-    const unsigned long long *hacc = rb.acc;
     if (ev1) {
         SJ_HIP(hipEventRecord(ev1, s));
         SJ_HIP(hipEventSynchronize(ev1));
@@ -1686,19 +2051,18 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     g.nblocks = hc[3];
     g.nmax = hn;
     g.cand_ref = -1;  // computed on request (grid_cref)
-    g.cand_items = (int64_t)(g.united ? hacc[2] : hacc[0]);
-    g.tiles = (int64_t)hacc[1];
+    g.cand_items = (int64_t)rb.cand;
+    g.tiles = (int64_t)rb.tiles;
 
     if (rb_dev) dev_free(rb_dev, s);
-    dev_free(acc, s);
+    if (nmax_part) dev_free(nmax_part, s);
+    if (cand_part) dev_free(cand_part, s);
     dev_free(item_tiles, s);
+    dev_free(bflag, s);
+    dev_free(line_row, s);
     dev_free(key_a, s);
     dev_free(key_b, s);
-    dev_free(flag, s);
-    dev_free(cid, s);
     dev_free(counters, s);
-    dev_free(nitem, s);
-    dev_free(item_off, s);
 }
 
 int64_t grid_cref(Grid &g, hipStream_t s) {

@@ -2011,11 +2011,11 @@ void refine_count(Grid &g, sj_path path, int32_t *cnt_sorted, RefineOut &ro, hip
     const bool sym = ro.sym && (path == SJ_FP64_VALU || path == SJ_FP64_MFMA);
     ro.cand_eval = g.cand_items;
     if (ro.hits) {
-        if (sym) {
+        if (sym && ro.timed) {
             fill_zero(ro.ctr, sizeof(DevCounters), s);
             launch_sym_cand(g, &ro.ctr->spare[0], s);
         }
-        hits_count(g, path, cnt_sorted, ro.record_hits, 0, !sym, ro, s);
+        hits_count(g, path, cnt_sorted, ro.record_hits, 0, !(sym && ro.timed), ro, s);
         return;
     }
     fill_zero(ro.ctr, sizeof(DevCounters), s);
@@ -2024,7 +2024,7 @@ void refine_count(Grid &g, sj_path path, int32_t *cnt_sorted, RefineOut &ro, hip
     R.ctr = ro.ctr;
     R.item_lo = 0;
     R.masks = ro.masks;
-    if (sym) launch_sym_cand(g, &ro.ctr->spare[0], s);
+    if (sym && ro.timed) launch_sym_cand(g, &ro.ctr->spare[0], s);  // a statistic
     if (path == SJ_FP64_VALU) {
         ro.kt.start(ro.timed, s);
         if (sym) launch_v64<MODE_SYM>(g, R, (int)g.items, s);
