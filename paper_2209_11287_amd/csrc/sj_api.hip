@@ -11,6 +11,7 @@
 #include <new>
 #include <string>
 #include <unordered_map>
+#include <vector>
 
 #include "sj_internal.h"
 
@@ -24,13 +25,21 @@ __global__ void k_set_i32(int32_t *p, int32_t v) { *p = v; }
 // The count's total (the last entry of the offsets' exclusive scan) beside
 // its counters, so that one copy brings both to the host, and with a hit list
 // the entries reserved in its fullest region.
-__global__ void k_total_to_ctr(const int64_t *total, const unsigned long long *cursor, DevCounters *ctr) {
-    ctr->spare[1] = (unsigned long long)*total;
-    if (!cursor) return;
-    unsigned long long m = 0;
-    for (int r = 0; r < kHitRegions; ++r) m = max(m, cursor[r * kHitCursorStride]);
-    ctr->spare[0] = m;
+__global__ void k_total_to_ctr(const int64_t *total, const unsigned long long *cursor, const DevCounters *ctr,
+                               DevCounters *out) {
+    DevCounters c = *ctr;
+    c.spare[1] = (unsigned long long)*total;
+    if (cursor) {
+        unsigned long long m = 0;
+        for (int r = 0; r < kHitRegions; ++r) m = max(m, cursor[r * kHitCursorStride]);
+        c.spare[0] = m;
+    }
+    *out = c;
 }
+
+__global__ void k_copy_u64(const unsigned long long *v, unsigned long long *out) { *out = *v; }
+
+__global__ void k_copy_ctr(const DevCounters *ctr, DevCounters *out) { *out = *ctr; }
 
 // Core flags in the input order and their number (one counter atomic per
 // block, 1024 blocks: atomics on one address take about 13 ns each, one after the
@@ -286,6 +295,68 @@ static void cache_free(void *p, hipStream_t s) {
     c.live.erase(it);
 }
 
+namespace {
+std::unordered_map<int, std::vector<hipEvent_t>> g_events;  // by device
+std::vector<void *> g_host;
+}  // namespace
+
+hipEvent_t event_get() {
+    int dev = 0;
+    SJ_HIP(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto &v = g_events[dev];
+        if (!v.empty()) {
+            hipEvent_t e = v.back();
+            v.pop_back();
+            return e;
+        }
+    }
+    hipEvent_t e = nullptr;
+    SJ_HIP(hipEventCreate(&e));
+    return e;
+}
+
+void event_put(hipEvent_t e) {
+    int dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess) {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto &v = g_events[dev];
+        if (v.size() < kEventPool) {
+            v.push_back(e);
+            return;
+        }
+    }
+    (void)hipEventDestroy(e);
+}
+
+HostBuf::HostBuf() {
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (!g_host.empty()) {
+            p_ = g_host.back();
+            g_host.pop_back();
+            return;
+        }
+    }
+    if (hipHostMalloc(&p_, kHostBlock, hipHostMallocPortable) != hipSuccess || !p_) {
+        (void)hipGetLastError();
+        throw OomError{kHostBlock};
+    }
+}
+
+HostBuf::~HostBuf() {
+    if (armed_) (void)hipStreamSynchronize(s_);
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (g_host.size() < kHostPool) {
+            g_host.push_back(p_);
+            return;
+        }
+    }
+    (void)hipHostFree(p_);
+}
+
 void set_error(const std::string &msg) { g_err = msg; }
 const char *last_error() { return g_err.c_str(); }
 
@@ -305,23 +376,30 @@ struct DevBuf {
 // Device time between two events recorded on one stream.
 struct CallTimer {
     hipEvent_t a = nullptr, b = nullptr;
+    bool ended = false;
     explicit CallTimer(bool on, hipStream_t s) {
         if (!on) return;
-        SJ_HIP(hipEventCreate(&a));
-        SJ_HIP(hipEventCreate(&b));
+        a = event_get();
+        b = event_get();
         SJ_HIP(hipEventRecord(a, s));
     }
+    // Marks the end of the call's work (before a wait that the call makes anyway).
+    void end(hipStream_t s) {
+        if (a) SJ_HIP(hipEventRecord(b, s));
+        ended = true;
+    }
+    // Waits for the end mark.
     float stop(hipStream_t s) {
         if (!a) return 0.f;
-        SJ_HIP(hipEventRecord(b, s));
+        if (!ended) end(s);
         SJ_HIP(hipEventSynchronize(b));
         float ms = 0;
         SJ_HIP(hipEventElapsedTime(&ms, a, b));
         return ms;
     }
     ~CallTimer() {
-        if (a) (void)hipEventDestroy(a);
-        if (b) (void)hipEventDestroy(b);
+        if (a) event_put(a);
+        if (b) event_put(b);
     }
 };
 
@@ -335,8 +413,10 @@ struct CountRun {
 };
 
 // Computes per-query counts with `path` (range-checked) into the handle's
-// cache (sorted order), their exclusive prefix sums and the total.
-static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipStream_t s) {
+// cache (sorted order), their exclusive prefix sums and the total; with
+// per_point also the counts in the input order. tm: the call ends with this.
+static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipStream_t s,
+                           int32_t *per_point = nullptr, CallTimer *tm = nullptr) {
     if (!g.cnt) {
         g.cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
         g.off = dev_alloc_n<int64_t>((size_t)g.n + 1, s);
@@ -365,13 +445,31 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     if (g.n > 0) refine_count(g, path, g.cnt, ro, s);
     else fill_zero(g.ctr, sizeof(DevCounters), s);
     exclusive_scan_i32_to_i64(g.cnt, g.off, g.n + 1, s);
-    // the total and the counters: one copy, one sync
     const bool listed = ro.record_hits && g.hits;
-    hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, listed ? g.hit_cursor : nullptr, g.ctr);
-    SJ_HIP(hipGetLastError());
+    const unsigned long long *cursor = listed ? g.hit_cursor : nullptr;
+    if (per_point && g.n > 0) {
+        hipLaunchKernelGGL(k_scatter_counts, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, g.cnt, g.perm,
+                           g.n, per_point);
+        SJ_HIP(hipGetLastError());
+    }
+    // the total and the counters, one wait (a lean call, which allocates
+    // nothing, copies them)
     DevCounters hctr{};
-    SJ_HIP(hipMemcpyAsync(&hctr, g.ctr, sizeof hctr, hipMemcpyDeviceToHost, s));
-    SJ_HIP(hipStreamSynchronize(s));
+    if (g.lean) {
+        hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, cursor, g.ctr, g.ctr);
+        SJ_HIP(hipGetLastError());
+        SJ_HIP(hipMemcpyAsync(&hctr, g.ctr, sizeof hctr, hipMemcpyDeviceToHost, s));
+        SJ_HIP(hipStreamSynchronize(s));
+    } else {
+        HostBuf hb;
+        hb.arm(s);
+        hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, cursor, g.ctr, hb.as<DevCounters>());
+        SJ_HIP(hipGetLastError());
+        if (tm) tm->end(s);
+        SJ_HIP(hipStreamSynchronize(s));
+        hb.settled();
+        hctr = *hb.as<DevCounters>();
+    }
     const int64_t total = (int64_t)hctr.spare[1];
     g.total = total;
     g.masks_valid = ro.masks != nullptr;
@@ -614,12 +712,7 @@ sj_status selfjoin_count(sj_grid *gh, sj_path path, int32_t *per_point, int64_t 
     const sj_path run = path_for(g, path);
     CallTimer tm(stats != nullptr, s);
     CountRun cr;
-    compute_counts(g, run, stats != nullptr, cr, s);
-    if (per_point && g.n > 0) {
-        hipLaunchKernelGGL(k_scatter_counts, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, g.cnt, g.perm,
-                           g.n, per_point);
-        SJ_HIP(hipGetLastError());
-    }
+    compute_counts(g, run, stats != nullptr, cr, s, per_point, &tm);
     *total = g.total;
     if (stats) fill_stats(stats, g, g.total, cr, run, tm.stop(s), 0.f, nullptr, 0.0);
     return SJ_OK;
@@ -682,12 +775,17 @@ sj_status selfjoin_core_points(sj_grid *gh, sj_path path, int32_t min_pts, uint8
     unsigned long long hc = 0;
     if (g.n > 0) {
         DevBuf<unsigned long long> dc(1, s);
+        HostBuf hb;
         fill_zero(dc.p, sizeof(unsigned long long), s);
         hipLaunchKernelGGL(k_core_flags, dim3((unsigned)std::min<int64_t>((g.n + 255) / 256, 1024)), dim3(256), 0, s, g.cnt, g.perm, g.n,
                            min_pts, is_core, dc.p);
         SJ_HIP(hipGetLastError());
-        SJ_HIP(hipMemcpyAsync(&hc, dc.p, sizeof hc, hipMemcpyDeviceToHost, s));
+        hb.arm(s);
+        hipLaunchKernelGGL(k_copy_u64, dim3(1), dim3(1), 0, s, dc.p, hb.as<unsigned long long>());
+        SJ_HIP(hipGetLastError());
         SJ_HIP(hipStreamSynchronize(s));
+        hb.settled();
+        hc = *hb.as<unsigned long long>();
     }
     *ncore = (int64_t)hc;
     return SJ_OK;
@@ -732,8 +830,18 @@ sj_status selfjoin_pairs(sj_grid *gh, sj_path path, int64_t cursor, int32_t *pai
     *next_cursor = p.next;
     if (stats) {
         DevCounters h{};
-        SJ_HIP(hipMemcpyAsync(&h, ctr.p, sizeof h, hipMemcpyDeviceToHost, s));
-        const float ms = tm.stop(s);  // synchronises the stream
+        float ms = 0.f;
+        if (re.counted) {
+            HostBuf hb;
+            hb.arm(s);
+            hipLaunchKernelGGL(k_copy_ctr, dim3(1), dim3(1), 0, s, ctr.p, hb.as<DevCounters>());
+            SJ_HIP(hipGetLastError());
+            ms = tm.stop(s);  // waits for the stream's work so far
+            hb.settled();
+            h = *hb.as<DevCounters>();
+        } else {
+            ms = tm.stop(s);
+        }
         const HostCounters he = read_counters(h);
         double brel = re.band_rel;
         if (is_lowp(run)) {
@@ -825,14 +933,9 @@ sj_status selfjoin_count_noalloc(const double *points, int64_t n, int32_t d, dou
     build_grid(g, points, n, d, eps, 0, s);
     const sj_path run = path_for(g, path);
     CountRun cr;
-    compute_counts(g, run, false, cr, s);
-    if (per_point && g.n > 0) {
-        hipLaunchKernelGGL(k_scatter_counts, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, g.cnt, g.perm,
-                           g.n, per_point);
-        SJ_HIP(hipGetLastError());
-    }
-    // the next call may reuse the scratch as soon as this one returns
-    SJ_HIP(hipStreamSynchronize(s));
+    // waits for the stream: the next call may reuse the scratch as soon as
+    // this one returns
+    compute_counts(g, run, false, cr, s, per_point);
     *total = g.total;
     return SJ_OK;
     SJ_API_END

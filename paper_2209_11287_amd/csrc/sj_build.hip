@@ -18,6 +18,7 @@
 #include <cmath>
 #include <cstring>
 #include <initializer_list>
+#include <memory>
 #include <utility>
 #include <vector>
 
@@ -1783,16 +1784,19 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     const size_t rows = (size_t)n + kRowPad;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;  // device time of the build (not in a lean build)
     if (!g.lean) {
-        SJ_HIP(hipEventCreate(&ev0));
-        SJ_HIP(hipEventCreate(&ev1));
+        ev0 = event_get();
+        ev1 = event_get();
     }
     struct EvGuard {
         hipEvent_t &a, &b;
         ~EvGuard() {
-            if (a) (void)hipEventDestroy(a);
-            if (b) (void)hipEventDestroy(b);
+            if (a) event_put(a);
+            if (b) event_put(b);
         }
     } evg{ev0, ev1};
+    // the two read-backs land in pinned memory (a lean build, which allocates
+    // nothing, copies them)
+    std::unique_ptr<HostBuf> host(g.lean ? nullptr : new HostBuf());
     if (ev0) SJ_HIP(hipEventRecord(ev0, s));
 
     // ---- G1: bounding box, finiteness and (d > 4) moments (one host sync) ----
@@ -1809,7 +1813,7 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
         double *psum = mom ? part + 2 * (size_t)nb * d : nullptr;
         double *psq = mom ? part + 3 * (size_t)nb * d : nullptr;
         const size_t nbox = (size_t)(mom ? 4 : 2) * d;
-        double *box = dev_alloc_n<double>(nbox + 1, s);
+        double *box = host ? host->as<double>() : dev_alloc_n<double>(nbox + 1, s);
         double *pbad = part + (size_t)parts * nb * d;
         if (mom)
             hipLaunchKernelGGL(k_bbox_partial<true>, dim3(nb), dim3(kThreads), 0, s, points, n, d, rows_per_block,
@@ -1818,14 +1822,20 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
             hipLaunchKernelGGL(k_bbox_partial<false>, dim3(nb), dim3(kThreads), 0, s, points, n, d, rows_per_block,
                                pmin, pmax, psum, psq, pbad);
         SJ_HIP(hipGetLastError());
+        if (host) host->arm(s);
         hipLaunchKernelGGL(k_bbox_final, dim3(d + 1), dim3(kThreads), 0, s, pmin, pmax, psum, psq, pbad, nb, d, box,
                            box + nbox);
         SJ_HIP(hipGetLastError());
         std::vector<double> hb(nbox + 1);
-        SJ_HIP(hipMemcpyAsync(hb.data(), box, (nbox + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
+        if (!host) SJ_HIP(hipMemcpyAsync(hb.data(), box, (nbox + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
         SJ_HIP(hipStreamSynchronize(s));
         dev_free(part, s);
-        dev_free(box, s);
+        if (host) {
+            host->settled();
+            std::copy(box, box + nbox + 1, hb.begin());
+        } else {
+            dev_free(box, s);
+        }
         if (hb[nbox] != 0.0) throw std::string("non-finite coordinate in points");
         for (int j = 0; j < d; ++j) {
             g.lo[j] = hb[j];
@@ -2026,15 +2036,13 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     BuildReadback rb{};
     BuildReadback *rb_dev = nullptr;
     if (n > 0) {
-        rb_dev = dev_alloc_n<BuildReadback>(1, s);
+        rb_dev = host ? host->as<BuildReadback>() : dev_alloc_n<BuildReadback>(1, s);
+        if (host) host->arm(s);
         hipLaunchKernelGGL(k_build_readback, dim3(1), dim3(kThreads), 0, s, counters, os_err, nmax_part, n_nmax,
                            cand_part, n_cand, g.tile_off, g.dev_nmax, rb_dev);
         SJ_HIP(hipGetLastError());
-        SJ_HIP(hipMemcpyAsync(&rb, rb_dev, sizeof rb, hipMemcpyDeviceToHost, s));
+        if (!host) SJ_HIP(hipMemcpyAsync(&rb, rb_dev, sizeof rb, hipMemcpyDeviceToHost, s));
     }
-    const int32_t *hc = rb.c;
-    const int32_t herr = rb.err;
-    const double hn = rb.nmax;
     if (ev1) {
         SJ_HIP(hipEventRecord(ev1, s));
         SJ_HIP(hipEventSynchronize(ev1));
@@ -2044,6 +2052,14 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     } else {
         SJ_HIP(hipStreamSynchronize(s));
     }
+    if (host) {
+        host->settled();
+        if (rb_dev) rb = *rb_dev;
+        rb_dev = nullptr;
+    }
+    const int32_t *hc = rb.c;
+    const int32_t herr = rb.err;
+    const double hn = rb.nmax;
     dev_free(os_hist, s);
     if (herr) throw HipError{hipErrorLaunchFailure, "radix sort: a tile's look-back did not complete"};
     g.cells = hc[0];

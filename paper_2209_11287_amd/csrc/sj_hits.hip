@@ -1534,8 +1534,7 @@ static void make_bins(const BinPlan &b, const int2 *hits, const unsigned long lo
 
 // Pairs of the chunk from the list (valid): the bins are made on the first
 // call and kept for the chunks that follow.
-void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, bool zero_ctr,
-                RefineOut &ro, hipStream_t s) {
+void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s) {
     ro.kt.start(ro.timed, s);
     // more than kWaveBin neighbours: at most written / kWaveBin points
     const size_t nbig = (size_t)(p.written / kWaveBin) + 1;
@@ -1543,8 +1542,7 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
     const size_t nfill = g.hit_bin ? 0 : bp.nfill;
     int32_t *work = dev_alloc_n<int32_t>(2 + 2 * nbig + nfill, s);
     int32_t *fill = work + 2 + 2 * nbig;
-    fill_zero_many({{work, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}, {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
-                   s);
+    fill_zero_many({{work, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}}, s);
     if (!g.hit_bin) {
         g.hit_bin = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(g.total, 1), s);
         make_bins(bp, g.hits, g.hit_cursor, g.hit_cap, g.hit_most, g.off, g.n, fill, g.hit_bin, s);

@@ -97,6 +97,41 @@ T *dev_alloc_n(size_t n, hipStream_t s) {
     return static_cast<T *>(dev_alloc(n * sizeof(T) + 16, s));
 }
 
+// Timing events, kept per device for reuse (creating and destroying a pair
+// costs a call more than recording it): at most kEventPool of them.
+constexpr size_t kEventPool = 64;
+hipEvent_t event_get();
+void event_put(hipEvent_t e);
+
+// A block of pinned host memory that a kernel writes a call's results into, so
+// that the host reads them after its one wait, with no copy (each a blit kernel of
+// about 8 us beside its launch). Blocks come from a pool of at most kHostPool,
+// shared by all threads. `arm` before the kernel that writes it is launched,
+// `settled` once the stream has been waited for; a block still armed at the end of its scope (an
+// error on the way) waits too, so that no kernel writes a block handed on.
+constexpr size_t kHostPool = 64;
+constexpr size_t kHostBlock = 16384;  // 4 doubles for each of 256 dimensions, and more
+class HostBuf {
+public:
+    HostBuf();  // throws OomError
+    ~HostBuf();
+    HostBuf(const HostBuf &) = delete;
+    HostBuf &operator=(const HostBuf &) = delete;
+    template <typename T>
+    T *as() const {
+        return static_cast<T *>(p_);
+    }
+    void arm(hipStream_t s) {
+        s_ = s;
+        armed_ = true;
+    }
+    void settled() { armed_ = false; }  // the stream has been waited for
+private:
+    void *p_ = nullptr;
+    hipStream_t s_ = nullptr;
+    bool armed_ = false;
+};
+
 // Device counters of one refine launch (zeroed before it). Non-negative
 // doubles are kept as their bit patterns, whose integer order is theirs.
 struct DevCounters {
@@ -306,8 +341,8 @@ struct KernelTimer {
     void start(bool enable, hipStream_t s) {
         on = enable;
         if (!on) return;
-        SJ_HIP(hipEventCreate(&a));
-        SJ_HIP(hipEventCreate(&b));
+        a = event_get();
+        b = event_get();
         SJ_HIP(hipEventRecord(a, s));
     }
     void stop(hipStream_t s) {
@@ -318,16 +353,17 @@ struct KernelTimer {
         float v = 0.f;
         SJ_HIP(hipEventSynchronize(b));
         SJ_HIP(hipEventElapsedTime(&v, a, b));
-        (void)hipEventDestroy(a);
-        (void)hipEventDestroy(b);
-        on = false;
+        put();
         return v;
     }
-    ~KernelTimer() {
-        if (on) {
-            (void)hipEventDestroy(a);
-            (void)hipEventDestroy(b);
-        }
+    ~KernelTimer() { put(); }
+
+private:
+    void put() {
+        if (a) event_put(a);
+        if (b) event_put(b);
+        a = b = nullptr;
+        on = false;
     }
 };
 
@@ -338,6 +374,7 @@ struct RefineOut {
     unsigned long long *masks = nullptr;   // per-tile in-masks to record (FP64 count), nullable
     bool hits = false;         // run the hit-list count
     bool record_hits = false;  // and keep its list
+    bool counted = false;      // pairs: a tile kernel ran and its counters are in ctr (else all zero)
     bool record_lp = false;  // low-precision count: record its in-masks (layout and buffer on the grid)
     double band_rel = 0;     // largest band half-width / eps^2
     int64_t cand_eval = 0;
@@ -413,8 +450,7 @@ size_t hits_lean_bytes(int64_t n, int32_t d);
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
                 RefineOut &ro, hipStream_t s);
 bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s);
-void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, bool zero_ctr, RefineOut &ro,
-                hipStream_t s);
+void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s);
 void hits_free_list(Grid &g, hipStream_t s);
 
 // The hit-list count of a batch (FP64 MFMA): the problems it takes, by

@@ -2139,12 +2139,14 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
     R.item_lo = (int32_t)p.item_lo;
     R.ctr = ro.ctr;
     if (g.hits_valid && g.hits_lowp == is_lowp(path)) {
-        hits_pairs(g, p, qlo, pairs, d2, true, ro, s);
+        hits_pairs(g, p, qlo, pairs, d2, ro, s);
         return;
     }
-    fill_zero(ro.ctr, sizeof(DevCounters), s);
     const int nitems = (int)(p.item_hi - p.item_lo);
-    if ((path == SJ_FP64_VALU || path == SJ_FP64_MFMA) && g.masks_valid && g.masks) {
+    const bool expand = (path == SJ_FP64_VALU || path == SJ_FP64_MFMA) && g.masks_valid && g.masks;
+    ro.counted = !expand;
+    if (!expand) fill_zero(ro.ctr, sizeof(DevCounters), s);
+    if (expand) {
         ro.kt.start(ro.timed, s);
         const unsigned blocks = (unsigned)((nitems + kWaves - 1) / kWaves);
         if (blocks) {
@@ -2161,7 +2163,7 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
         }
         ro.kt.stop(s);
     } else if (hits_usable(g, path) && hits_ensure(g, path, ro, s)) {
-        hits_pairs(g, p, qlo, pairs, d2, false, ro, s);
+        hits_pairs(g, p, qlo, pairs, d2, ro, s);
     } else if (path == SJ_FP64_VALU) {
         ro.kt.start(ro.timed, s);
         launch_v64<MODE_EMIT>(g, R, nitems, s);
