@@ -1308,8 +1308,7 @@ struct MaskBatch {
     int32_t c[4];          // sorted index of the candidate
 };
 
-// D2 (distances requested; 4: d <= 4): the sorted indices (rows for the exact
-// chain; the input index is looked up per pair); otherwise the input indices.
+// D2 (distances requested; 4: d <= 4): the sorted indices too.
 template <int D2>
 __device__ __forceinline__ void mask_batch_load(MaskBatch &B, CandList &L, const unsigned long long *mb,
                                                 const DevGrid &G, int gi, int lane) {
@@ -1321,7 +1320,7 @@ __device__ __forceinline__ void mask_batch_load(MaskBatch &B, CandList &L, const
         int idx[1];
         cand_chunk<1>(L, c, P, idx);
         if (D2) B.c[q] = idx[0];
-        else B.pc[q] = G.perm[idx[0]];
+        B.pc[q] = G.perm[idx[0]];
     }
 }
 
@@ -1420,8 +1419,12 @@ __device__ __forceinline__ void emit_group(unsigned long long w, const MaskBatch
     const unsigned p01 = i01 - c01, p23 = i23 - c23;
     wave_lds_sync();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) stage[64 * q + lane] = D2 ? cur.c[q] : cur.pc[q];
+    for (int q = 0; q < 4; ++q) {
+        stage[64 * q + lane] = cur.pc[q];
+        if (D2) stage[256 + 64 * q + lane] = cur.c[q];
+    }
     int32_t *const own = slot + kSlot * g;
+    uint8_t *const own8 = reinterpret_cast<uint8_t *>(slot) + kSlot * g;  // D2: places in the group
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int sh = 16 * (r & 1);
@@ -1429,12 +1432,22 @@ __device__ __forceinline__ void emit_group(unsigned long long w, const MaskBatch
         if (__ballot(T != 0u) == 0ull) continue;
         wave_lds_sync();
         unsigned yy = ((r < 2 ? y01 : y23) >> sh) & 0xFFFFu;
-        int32_t *at = own + (((r < 2 ? p01 : p23) >> sh) & 0xFFFFu);
-        const int32_t *const tile = stage + 16 * j;
-        while (yy) {
-            const int col = __builtin_ctz(yy);
-            yy &= yy - 1u;
-            *at++ = tile[col];
+        const unsigned rank = ((r < 2 ? p01 : p23) >> sh) & 0xFFFFu;
+        if (D2) {
+            uint8_t *at = own8 + rank;
+            while (yy) {
+                const int col = __builtin_ctz(yy);
+                yy &= yy - 1u;
+                *at++ = (uint8_t)(16 * j + col);
+            }
+        } else {
+            int32_t *at = own + rank;
+            const int32_t *const tile = stage + 16 * j;
+            while (yy) {
+                const int col = __builtin_ctz(yy);
+                yy &= yy - 1u;
+                *at++ = tile[col];
+            }
         }
         wave_lds_sync();
         double2 a0, a1;
@@ -1445,14 +1458,13 @@ __device__ __forceinline__ void emit_group(unsigned long long w, const MaskBatch
         for (unsigned m = 0; m < T; m += 16) {
             const unsigned k = m + j;
             if (k < T) {
-                const int32_t v = own[k];
+                const int32_t v = D2 ? own8[k] : own[k];
                 const int64_t pos = base[r] + k;
-                if (D2 == 4) {
-                    reinterpret_cast<int2 *>(R.pairs)[pos] = make_int2(pq[r], G.perm[v]);
-                    R.d2[pos] = exact_d2_4(a0, a1, G.xs + 4 * (int64_t)v);
-                } else if (D2) {
-                    reinterpret_cast<int2 *>(R.pairs)[pos] = make_int2(pq[r], G.perm[v]);
-                    R.d2[pos] = exact_d2(G.xs + (int64_t)(q0 + g + 4 * r) * G.dp, G.xs + (int64_t)v * G.dp, G.d);
+                if (D2) {
+                    const int32_t c = stage[256 + v];
+                    reinterpret_cast<int2 *>(R.pairs)[pos] = make_int2(pq[r], stage[v]);
+                    R.d2[pos] = D2 == 4 ? exact_d2_4(a0, a1, G.xs + 4 * (int64_t)c)
+                                        : exact_d2(G.xs + (int64_t)(q0 + g + 4 * r) * G.dp, G.xs + (int64_t)c * G.dp, G.d);
                 } else {
                     reinterpret_cast<int2 *>(R.pairs)[pos] = make_int2(pq[r], v);
                 }
@@ -1521,23 +1533,30 @@ __device__ __forceinline__ void mask_item(const DevGrid &G, const RefOut &R, con
     }
 }
 
-// Seven waves per SIMD (72 VGPRs; no spill without distances, 20 KB of LDS
-// per block) hide more of the group loads than six (~5 %).
-// D2 = 4 (distances, d <= 4): the query rows come from LDS and a candidate row in
-// two 16-byte loads beside the lookup of its index, all in flight together; with
-// a loop over d and both rows read per dimension (D2 = 1) 130M pairs of a skewed
-// 4-d set took 2.24 ms, against 0.57 ms without distances.
+// Seven waves per SIMD without distances (72 VGPRs, no spill, 20 KB of LDS per
+// block) hide more of the group loads than six (~5 %).
+// With distances a group's candidates sit in LDS twice, as input and as sorted
+// indices, and the slots hold one-byte places in the group: the input index,
+// gathered per pair, touched a cache line per lane like each half of the
+// candidate's row does. D2 = 4 (d <= 4) reads the query rows from LDS and a
+// candidate row in two 16-byte loads. The bound is that gather of rows; five
+// waves (88 VGPRs) because at seven 21 registers spill, and scratch goes through
+// the same unit: a join of 2M skewed 4-d points with distances (130M pairs) takes
+// 3.47 ms with the gathered index, 3.18 with places at seven waves, 2.91 at six,
+// 2.77 at five; 2M uniform 2-d points 1.66, 1.66, 1.51 and 1.43 ms. Rows staged
+// in LDS whole (no gather, 40 KB per block) win 6 % where most candidates are
+// pairs and lose 15 % on the skewed set, where few are.
 template <int D2>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_mask_emit(DevGrid G,
-                                                                                                 RefOut R,
-                                                                                                 const unsigned long long *masks) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D2 ? 5 : 7, 8))) void k_mask_emit(
+    DevGrid G, RefOut R, const unsigned long long *masks) {
+    constexpr int kStage = D2 ? 512 : 256, kOut = D2 ? kSlot : 4 * kSlot;  // words per wave
     const int wv = uniform_i32(threadIdx.x >> 6);
     const int it = uniform_i32(R.item_lo + xcd_block(blockIdx.x, gridDim.x) * kWaves + wv);
-    __shared__ int32_t stage[kWaves * 256];
-    __shared__ int32_t slot[kWaves * 4 * kSlot];
+    __shared__ int32_t stage[kWaves * kStage];
+    __shared__ int32_t slot[kWaves * kOut];
     __shared__ double2 qrow[D2 == 4 ? kWaves * 32 : 1];
     if (it >= G.nitems) return;
-    mask_item<D2>(G, R, masks, it, stage + 256 * wv, slot + 4 * kSlot * wv, qrow + (D2 == 4 ? 32 * wv : 0));
+    mask_item<D2>(G, R, masks, it, stage + kStage * wv, slot + kOut * wv, qrow + (D2 == 4 ? 32 * wv : 0));
 }
 
 // ------------------------------------------------------------------ batch --
