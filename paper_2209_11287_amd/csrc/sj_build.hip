@@ -325,26 +325,35 @@ __global__ void k_rs_scatter(const unsigned long long *__restrict__ kin, const i
 // ------------------------------------------------------ one-sweep sort ----
 // The build's sort of (cell key, point index): LSD radix sort, 8-bit digits,
 // one launch per digit. The key kernel also counts every digit of every key
-// (all passes' digit histograms in one read). A pass kernel takes one tile
-// of kOsTile keys (tile numbers handed out in launch order by a counter, so
-// every tile's predecessors have started), ranks its keys stably by digit
-// (wave-wide digit match, as in k_rs_scatter), publishes its per-digit counts
-// and finds the counts of all tiles before it by looking back over their
-// published words (decoupled look-back; each word = flag + count, read and
-// written as one 64-bit atomic). The tile's keys are reordered by digit in
-// LDS first, so the stores of one digit's run are contiguous.
+// (all passes' digit histograms in one read). A pass kernel takes one tile of
+// keys (tile numbers handed out in launch order by a counter, so every tile's
+// predecessors have started), publishes its per-digit counts, ranks its keys
+// stably by digit (wave-wide digit match; each wave ranks a run of its own
+// against its own counts in LDS) and finds the counts of all tiles before it by
+// looking back over their published words (decoupled look-back, kOsLook words
+// per step in flight; each word = flag + count, read and written as one 64-bit
+// atomic). The tile's keys are reordered by digit in LDS first, so the stores
+// of one digit's run are contiguous.
 // Keys of at most 32 bits travel packed with their index in one 64-bit word
 // (key in the high half); the last pass then writes the key and the index
 // to separate arrays. Wider keys travel as (64-bit key, 32-bit index).
+// What bounds a pass is the serial chain of a tile (load, rank, look back,
+// store) while few tiles are in flight: ranked a row of 256 keys at a time by
+// the whole block (two barriers per row) and looking back one word at a time, a
+// pass took 13 us at 20k keys, 33 us at 2M; in this form 11 and 25 us. Tiles of 4
+// keys per thread shorten the chain further (7 us at 20k), but leave more to
+// look back over and shorter runs to store: joins of 20k, 100k, 260k, 500k and
+// 2M points take 224, 261, 310, 660 and 970 us with them, 232, 266, 312, 652 and
+// 886 us with 16 per thread, so small tiles end at 2^18 keys.
 // A look-back that does not see its predecessor's word after kOsSpin polls
 // sets *err (the host reports it) instead of waiting on; with tile numbers
 // handed out in order it cannot happen.
-constexpr int kOsItems = 16;
-constexpr int kOsTile = kThreads * kOsItems;
+constexpr int kOsLarge = 16, kOsSmall = 4;  // keys per thread
 constexpr int kOsMaxPasses = 8;
 constexpr unsigned long long kOsAgg = 1ull << 32;     // word flag: the tile's own count
 constexpr unsigned long long kOsIncl = 2ull << 32;    // word flag: count of this tile and all before it
 constexpr int kOsSpin = 1 << 16;
+constexpr int kOsLook = 8;  // words per look-back step
 
 enum { OS_PACKED = 0, OS_PACKED_SPLIT = 1, OS_WIDE = 2 };
 
@@ -387,7 +396,14 @@ __global__ __launch_bounds__(kThreads) void k_keys_hist(const double *__restrict
         if (h[t]) atomicAdd(&hist[t], h[t]);
 }
 
-template <int MODE>
+// Orders a wave's LDS accesses before its next ones.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int MODE, int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long *__restrict__ kin,
                                                        const int32_t *__restrict__ vin,
                                                        unsigned long long *__restrict__ kout,
@@ -395,39 +411,38 @@ __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long 
                                                        const int32_t *__restrict__ hist,
                                                        unsigned long long *__restrict__ status,
                                                        int32_t *__restrict__ tile_ctr, int32_t *__restrict__ err) {
+    constexpr int kOsTile = kThreads * ITEMS;
     __shared__ unsigned long long skey[kOsTile];
     __shared__ int32_t sval[MODE == OS_WIDE ? kOsTile : 1];
     __shared__ int32_t dcnt[256];   // the tile's keys per digit
     __shared__ int32_t dexc[256];   // their exclusive prefix: first LDS slot of each digit
     __shared__ int32_t gbase[256];  // first output position of the tile's keys of each digit
-    __shared__ int32_t run[256];
-    __shared__ int32_t wcnt[kThreads / 64][256];
-    __shared__ int32_t wpre[kThreads / 64][256];
+    __shared__ int32_t wcnt[kThreads / 64][256];  // a wave's keys per digit, then their first LDS slot
     __shared__ int32_t wsum[kThreads / 64];
     __shared__ int32_t tile_sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int dshift = (MODE == OS_WIDE ? 0 : 32) + shift;
     if (tid == 0) tile_sh = atomicAdd(tile_ctr, 1);
     dcnt[tid] = 0;
-    run[tid] = 0;
 #pragma unroll
     for (int w = 0; w < kThreads / 64; ++w) wcnt[w][tid] = 0;
     __syncthreads();
     const int tile = tile_sh;
     const int64_t t0 = (int64_t)tile * kOsTile;
-    // the tile's keys, all loads in flight together
-    unsigned long long kk[kOsItems];
-    int32_t vv[kOsItems];
+    // the wave's keys (ITEMS runs of 64), all loads in flight together
+    const int64_t w0 = t0 + (int64_t)wave * 64 * ITEMS + lane;
+    unsigned long long kk[ITEMS];
+    int32_t vv[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kOsItems; ++r) {
-        const int64_t i = t0 + (int64_t)r * kThreads + tid;
+    for (int r = 0; r < ITEMS; ++r) {
+        const int64_t i = w0 + 64 * r;
         kk[r] = i < n ? kin[i] : 0ull;
         if (MODE == OS_WIDE) vv[r] = i < n ? vin[i] : 0;
     }
     // digit counts of the tile
 #pragma unroll
-    for (int r = 0; r < kOsItems; ++r)
-        if (t0 + (int64_t)r * kThreads + tid < n) atomicAdd(&dcnt[(int)((kk[r] >> dshift) & 255u)], 1);
+    for (int r = 0; r < ITEMS; ++r)
+        if (w0 + 64 * r < n) atomicAdd(&dcnt[(int)((kk[r] >> dshift) & 255u)], 1);
     __syncthreads();
     // publish them at once (the first tile publishes its inclusive count)
     const int agg = dcnt[tid];
@@ -460,12 +475,13 @@ __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long 
         gbase[tid] = yo + yi - y;  // completed by the look-back below
     }
     __syncthreads();
-    // stable ranks, round by round (round r = keys t0 + 256 r ..): digit match
-    // within the wave, per-wave counts combined per digit in LDS
+    // stable ranks within the wave, run by run: digit match, and the wave's
+    // own counts in LDS, so no barrier until all its keys are ranked
     const unsigned long long lt = lane ? ((~0ull) >> (64u - (unsigned)lane)) : 0ull;
+    int rk[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kOsItems; ++r) {
-        const bool valid = t0 + (int64_t)r * kThreads + tid < n;
+    for (int r = 0; r < ITEMS; ++r) {
+        const bool valid = w0 + 64 * r < n;
         const unsigned digit = valid ? (unsigned)((kk[r] >> dshift) & 255u) : 0u;
         unsigned long long peers = __ballot(valid);
 #pragma unroll
@@ -474,22 +490,27 @@ __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long 
             const unsigned long long m = __ballot(bit);
             peers &= bit ? m : ~m;
         }
-        const int rank = __popcll(peers & lt);
-        if (valid && rank == 0) wcnt[wave][digit] = __popcll(peers);
-        __syncthreads();
-        {
-            int acc = run[tid];
+        const int before = wcnt[wave][digit];
+        wave_lds_fence();
+        rk[r] = before + __popcll(peers & lt);
+        if (valid && (peers & lt) == 0ull) wcnt[wave][digit] = before + __popcll(peers);
+        wave_lds_fence();
+    }
+    __syncthreads();
+    {
+        int acc = dexc[tid];
 #pragma unroll
-            for (int w = 0; w < kThreads / 64; ++w) {
-                wpre[w][tid] = acc;
-                acc += wcnt[w][tid];
-                wcnt[w][tid] = 0;
-            }
-            run[tid] = acc;
+        for (int w = 0; w < kThreads / 64; ++w) {
+            const int c = wcnt[w][tid];
+            wcnt[w][tid] = acc;
+            acc += c;
         }
-        __syncthreads();
-        if (valid) {
-            const int slot = dexc[digit] + wpre[wave][digit] + rank;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        if (w0 + 64 * r < n) {
+            const int slot = wcnt[wave][(int)((kk[r] >> dshift) & 255u)] + rk[r];
             skey[slot] = kk[r];
             if (MODE == OS_WIDE) sval[slot] = vv[r];
         }
@@ -498,20 +519,34 @@ __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long 
     if (tile > 0) {
         int excl = 0, spins = 0;
         for (int k = tile - 1; k >= 0;) {
-            const unsigned long long w =
-                __hip_atomic_load(&status[(int64_t)k * 256 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned long long f = w & ~0xffffffffull;
-            if (f == 0ull) {
+            unsigned long long w[kOsLook];  // the nearest words, in flight together
+#pragma unroll
+            for (int b = 0; b < kOsLook; ++b)
+                w[b] = __hip_atomic_load(&status[(int64_t)max(k - b, 0) * 256 + tid], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+            bool open = true;  // no unpublished word, no inclusive count yet
+            int took = 0;
+#pragma unroll
+            for (int b = 0; b < kOsLook; ++b) {
+                const unsigned long long f = w[b] & ~0xffffffffull;
+                open = open && f != 0ull && k - b >= 0;
+                if (open) {
+                    excl += (int)(uint32_t)w[b];
+                    ++took;
+                    if (f == kOsIncl) {
+                        open = false;
+                        took = k + 1;  // ends the look-back
+                    }
+                }
+            }
+            k -= took;
+            if (took == 0) {
                 if (++spins > kOsSpin) {
                     atomicOr(err, 1);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
-                continue;
             }
-            excl += (int)(uint32_t)w;
-            if (f == kOsIncl) break;
-            --k;
         }
         __hip_atomic_store(&status[(int64_t)tile * 256 + tid], kOsIncl | (unsigned long long)(uint32_t)(excl + agg),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -521,7 +556,7 @@ __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long 
     // stores in LDS order: each digit's run of the tile is contiguous
     const int cnt = (int)min<int64_t>(kOsTile, n - t0);
 #pragma unroll
-    for (int r = 0; r < kOsItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int sidx = r * kThreads + tid;
         if (sidx < cnt) {
             const unsigned long long k = skey[sidx];
@@ -538,6 +573,26 @@ __global__ __launch_bounds__(kThreads) void k_onesweep(const unsigned long long 
             }
         }
     }
+}
+
+// Small tiles for few keys (both sides measured above). The static scratch is
+// sized for the status words of 8 passes over large tiles: there, small tiles
+// only where their words fit that.
+bool onesweep_small(int64_t n, int passes, bool lean) {
+    if (n > (1 << 18)) return false;
+    const int64_t tiles = (n + kThreads * kOsSmall - 1) / (kThreads * kOsSmall);
+    return !lean || passes * tiles <= kOsMaxPasses * ((n + kThreads * kOsLarge - 1) / (kThreads * kOsLarge));
+}
+
+int64_t onesweep_tiles(int64_t n, bool small) {
+    const int64_t tile = kThreads * (small ? kOsSmall : kOsLarge);
+    return std::max<int64_t>(1, (n + tile - 1) / tile);
+}
+
+template <int MODE, class... A>
+void launch_onesweep(bool small, int64_t tiles, hipStream_t s, A... a) {
+    if (small) hipLaunchKernelGGL((k_onesweep<MODE, kOsSmall>), dim3((unsigned)tiles), dim3(kThreads), 0, s, a...);
+    else hipLaunchKernelGGL((k_onesweep<MODE, kOsLarge>), dim3((unsigned)tiles), dim3(kThreads), 0, s, a...);
 }
 
 // ---------------------------------------------------------------- scans ----
@@ -1858,7 +1913,8 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     const int sort_bits = g.key_bits + g.sub_bits;
     const int passes = (sort_bits + 7) / 8;
     const bool packed = passes > 0 && sort_bits <= 32;
-    const int64_t os_tiles = std::max<int64_t>(1, (n + kOsTile - 1) / kOsTile);
+    const bool os_small = onesweep_small(n, passes, g.lean);
+    const int64_t os_tiles = onesweep_tiles(n, os_small);
     int32_t *os_hist = dev_alloc_n<int32_t>(kOsMaxPasses * 256 + kOsMaxPasses + 1, s);  // hists, tile counters, err
     int32_t *os_ctr = os_hist + kOsMaxPasses * 256;
     int32_t *os_err = os_ctr + kOsMaxPasses;
@@ -1890,14 +1946,14 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
             const bool last = p == passes - 1;
             unsigned long long *st = os_status + (size_t)p * os_tiles * 256;
             if (!packed)
-                hipLaunchKernelGGL(k_onesweep<OS_WIDE>, dim3((unsigned)os_tiles), dim3(kThreads), 0, s, key_a, val_a,
-                                   key_b, val_b, n, 8 * p, os_hist + 256 * p, st, os_ctr + p, os_err);
+                launch_onesweep<OS_WIDE>(os_small, os_tiles, s, key_a, val_a, key_b, val_b, n, 8 * p,
+                                         os_hist + 256 * p, st, os_ctr + p, os_err);
             else if (!last)
-                hipLaunchKernelGGL(k_onesweep<OS_PACKED>, dim3((unsigned)os_tiles), dim3(kThreads), 0, s, key_a,
-                                   val_a, key_b, val_b, n, 8 * p, os_hist + 256 * p, st, os_ctr + p, os_err);
+                launch_onesweep<OS_PACKED>(os_small, os_tiles, s, key_a, val_a, key_b, val_b, n, 8 * p,
+                                           os_hist + 256 * p, st, os_ctr + p, os_err);
             else
-                hipLaunchKernelGGL(k_onesweep<OS_PACKED_SPLIT>, dim3((unsigned)os_tiles), dim3(kThreads), 0, s,
-                                   key_a, val_a, key_b, val_b, n, 8 * p, os_hist + 256 * p, st, os_ctr + p, os_err);
+                launch_onesweep<OS_PACKED_SPLIT>(os_small, os_tiles, s, key_a, val_a, key_b, val_b, n, 8 * p,
+                                                 os_hist + 256 * p, st, os_ctr + p, os_err);
             SJ_HIP(hipGetLastError());
             std::swap(key_a, key_b);
             // packed passes carry the index in the key word; the last one
@@ -2716,7 +2772,8 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
     unsigned long long *kb = static_cast<unsigned long long *>(scratch((size_t)(N + 1) * 8));
     int32_t *va = static_cast<int32_t *>(scratch((size_t)(N + 1) * 4));
     int32_t *vb = static_cast<int32_t *>(scratch((size_t)(N + 1) * 4));
-    const int64_t os_tiles = std::max<int64_t>(1, (N + kOsTile - 1) / kOsTile);
+    const bool os_small = onesweep_small(N, passes, false);
+    const int64_t os_tiles = onesweep_tiles(N, os_small);
     int32_t *os_hist = static_cast<int32_t *>(scratch((kOsMaxPasses * 256 + kOsMaxPasses + 1) * sizeof(int32_t)));
     int32_t *os_ctr = os_hist + kOsMaxPasses * 256;
     int32_t *os_err = os_ctr + kOsMaxPasses;
@@ -2738,8 +2795,8 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
     }
     for (int ps = 0; ps < passes && N > 0; ++ps) {
         unsigned long long *st = os_status + (size_t)ps * os_tiles * 256;
-        hipLaunchKernelGGL(k_onesweep<OS_WIDE>, dim3((unsigned)os_tiles), dim3(kThreads), 0, s, ka, va, kb, vb, N,
-                           8 * ps, os_hist + 256 * ps, st, os_ctr + ps, os_err);
+        launch_onesweep<OS_WIDE>(os_small, os_tiles, s, ka, va, kb, vb, N, 8 * ps, os_hist + 256 * ps, st,
+                                 os_ctr + ps, os_err);
         SJ_HIP(hipGetLastError());
         std::swap(ka, kb);
         std::swap(va, vb);

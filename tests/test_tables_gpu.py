@@ -59,3 +59,19 @@ def test_several_steps_per_wave(n, d):
     X = gen.make("expo", n, d, seed=7)
     eps = 0.2 / 40 * (1.0 / n) ** (1.0 / d) * 8
     _check(X, eps, "expo", pairs=False)
+
+
+@pytest.mark.parametrize("d", [2, 6])  # keys packed with their index; wide keys
+@pytest.mark.parametrize("n", [63, 64, 65, 255, 257, 1023, 1024, 1025, 4095, 4096, 4097, 8193, (1 << 18) - 1,
+                               1 << 18, (1 << 18) + 1])
+def test_sort_tile_edges(n, d):
+    """Whole and ragged tiles of both sizes, one digit holding most keys."""
+    import oracle
+    rng = np.random.default_rng(n + d)
+    X = rng.random((n, d))
+    X[: n // 2, 1:] *= 1e-3
+    eps = 0.25 * n ** -0.5
+    log(f"[sort] n={n} d={d}")
+    total, pp, _, _ = oracle.grid_count(X, eps)
+    g = gpu_join(X, eps, "fp64_mfma", want_pairs=False)
+    assert g["total"] == total and np.array_equal(g["per_point"], pp)
