@@ -48,7 +48,10 @@ __global__ void k_item_cost(const BProb *__restrict__ probs, const int64_t *__re
     const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gi >= total) return;
     const int p = problem_of(item_base, B, gi);
-    const DevGrid &G = probs[p].G;
+    DevGrid G = probs[p].G;
+    G.ranges = global_ptr(G.ranges);
+    G.items = global_ptr(G.items);
+    G.blocks = global_ptr(G.blocks);
     const int64_t it = gi - item_base[p];
     // half stencil: the ranges as the count cuts them (from the first query on)
     const int32_t cut = sym ? G.items[it].qbegin : INT32_MIN;
@@ -72,7 +75,10 @@ __global__ void k_block_cost(const BProb *__restrict__ probs, const int64_t *__r
     const int64_t gb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gb >= total) return;
     const int p = problem_of(block_base, B, gb);
-    const DevGrid &G = probs[p].G;
+    DevGrid G = probs[p].G;
+    G.ranges = global_ptr(G.ranges);
+    G.items = global_ptr(G.items);
+    G.blocks = global_ptr(G.blocks);
     const int b = (int)(gb - block_base[p]);
     const int64_t it0 = G.blocks[b] - G.item_base;
     const int ni = G.blocks[b + 1] - G.blocks[b];

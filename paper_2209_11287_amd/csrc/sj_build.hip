@@ -2207,9 +2207,10 @@ __global__ void k_seg_bbox_partial(const SegProb *__restrict__ P, const SegBlk *
     double mn = INFINITY, mx = -INFINITY, s1 = 0.0, s2 = 0.0;
     int nonfinite = 0;
     if (tid < S && b.r0 < b.r1) {
-        const double x0 = q.X[tid % d];
+        const double *X = global_ptr(q.X);
+        const double x0 = X[tid % d];
         for (int64_t e = b.r0 * d + tid; e < b.r1 * d; e += S) {
-            const double v = q.X[e];
+            const double v = X[e];
             nonfinite |= !isfinite(v);
             mn = fmin(mn, v);
             mx = fmax(mx, v);
@@ -2300,7 +2301,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_keys_hist(const SegProb *__res
     for (int64_t i = b.r0 + threadIdx.x; i < b.r1; i += kThreads) {
         unsigned long long kk = 0, sub = 0;
         for (int j = 0; j < geo.k; ++j) {
-            const double t = __ddiv_rn(__dsub_rn(q.X[i * geo.d + j], geo.lo[j]), geo.w);
+            const double t = __ddiv_rn(__dsub_rn(global_ptr(q.X)[i * geo.d + j], geo.lo[j]), geo.w);
             double c = floor(t);
             c = !(c >= 0.0) ? 0.0 : (c > (double)(geo.m[j] - 1) ? (double)(geo.m[j] - 1) : c);
             const int64_t ci = (int64_t)c;
@@ -2343,7 +2344,7 @@ __global__ void k_seg_gather(const SegProb *__restrict__ P, const SegBlk *__rest
             const int32_t loc = val[pos] - (int32_t)q.pt_off;
             perm_all[pos] = loc;
             skey[pos] = key[pos] & ((1ull << keybits) - 1ull);
-            const double *src = q.X + (int64_t)loc * d;
+            const double *src = global_ptr(q.X) + (int64_t)loc * d;
             for (int t = 0; t < d; ++t) ps[t] = src[t];
             for (int t = 0; t < d; ++t) {
                 const int u = fo[t];

@@ -101,6 +101,22 @@ struct HitProb {
     int64_t pout;      // first output row of this problem's pairs
 };
 
+__device__ __forceinline__ HitGrid hit_grid(const HitProb &P) {
+    HitGrid G = P.G;
+    G.xs = global_ptr(G.xs);
+    G.xa = global_ptr(G.xa);
+    G.nrm = global_ptr(G.nrm);
+    G.perm = global_ptr(G.perm);
+    G.items = global_ptr(G.items);
+    G.ranges = global_ptr(G.ranges);
+    G.blocks = global_ptr(G.blocks);
+    G.item_block = global_ptr(G.item_block);
+    G.span = global_ptr(G.span);
+    G.blo = global_ptr(G.blo);
+    G.bhi = global_ptr(G.bhi);
+    return G;
+}
+
 __device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // The oracle's chain: ascending dimensions from +0.0, fl(a - b) then fma.
@@ -224,7 +240,7 @@ __device__ __forceinline__ int problem_of(const T *__restrict__ base, int B, T x
 __global__ __launch_bounds__(kThreads) void k_hit_index_batch(const HitProb *__restrict__ P,
                                                               const int64_t *__restrict__ first, int B) {
     const int p = problem_of<int64_t>(first, B, blockIdx.x);
-    const HitGrid G = P[p].G;
+    const HitGrid G = hit_grid(P[p]);
     hit_index_block(G, P[p].sc, blockIdx.x - (unsigned)first[p], P[p].nbox);
 }
 
@@ -638,7 +654,7 @@ __global__ __launch_bounds__(kThreads, KS <= 8 ? 4 : 3) void k_hit_f64_batch(con
     const int pos = blockIdx.x / nseg;
     const int gb = uniform_i32(queue[pos]);
     const int p = problem_of<int64_t>(block_base, B, gb);
-    const HitGrid G = P[p].G;
+    const HitGrid G = hit_grid(P[p]);
     R.row0 = P[p].row0;
     R.cnt += R.row0;
     hit_f64_block<KS>(G, R, P[p].delta, gb - (int)block_base[p], blockIdx.x - pos * nseg, nseg);
@@ -1022,7 +1038,7 @@ struct EmitSrc {
 // index in it.
 __device__ __forceinline__ int emit_problem(const EmitSrc &S, int it, HitGrid &G, EmitOut &E) {
     const int p = problem_of<int64_t>(S.item_base, S.B, it);
-    G = S.P[p].G;
+    G = hit_grid(S.P[p]);
     E.row0 = S.P[p].row0;
     E.off += E.row0;
     E.base = E.off[0] - S.P[p].pout;
@@ -1261,7 +1277,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_cost(const HitProb *__restrict
         if (block_base[mid] <= gb) lo = mid;
         else hi = mid;
     }
-    const HitGrid &G = P[lo].G;
+    const HitGrid G = hit_grid(P[lo]);
     const int b = (int)(gb - block_base[lo]);
     const int64_t it = G.blocks[b] - G.item_base;
     unsigned long long c = 0;

@@ -179,6 +179,17 @@ struct DevGrid {
     const int64_t *tile_off;
 };
 
+// A device pointer read from a record in memory, known to point to global
+// memory. Of such a pointer the compiler knows nothing, and its accesses become
+// flat ones, which count on the LDS counter too and return in no order: every LDS
+// wait then waits for all loads in flight, and every load for all before it, so
+// a prefetch hides nothing. The batched kernels' pointers all come that way (256
+// mixed problems: 86.5 -> 84.7 ms).
+template <class T>
+__device__ __forceinline__ T *global_ptr(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)reinterpret_cast<uintptr_t>(p);
+}
+
 // One problem of a batch, as the batch kernels see it.
 struct BProb {
     DevGrid G;

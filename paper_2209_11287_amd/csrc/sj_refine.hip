@@ -1578,6 +1578,24 @@ __device__ __forceinline__ int batch_problem(const int64_t *__restrict__ item_ba
     return uniform_i32(lo);
 }
 
+__device__ __forceinline__ BProb batch_load(const BProb *__restrict__ probs, int p) {
+    BProb P = probs[p];
+    DevGrid &G = P.G;
+    G.xs = global_ptr(G.xs);
+    G.xa = global_ptr(G.xa);
+    G.nrm = global_ptr(G.nrm);
+    G.pn = global_ptr(G.pn);
+    G.perm = global_ptr(G.perm);
+    G.ranges = global_ptr(G.ranges);
+    G.items = global_ptr(G.items);
+    G.blocks = global_ptr(G.blocks);
+    G.tile_off = global_ptr(G.tile_off);
+    P.cnt = global_ptr(P.cnt);
+    P.off = global_ptr(P.off);
+    P.masks = global_ptr(P.masks);
+    return P;
+}
+
 __device__ __forceinline__ RefOut batch_out(const BProb &P, int32_t *pairs, DevCounters *ctr, int mode) {
     RefOut R{};
     R.cnt = P.cnt;
@@ -1603,7 +1621,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
     for (int w = lo + uniform_i32(blockIdx.x * kWaves + wv); w < hi; w += W) {
         const int gi = queue[w];
         const int p = batch_problem(item_base, B, gi);
-        const BProb &P = probs[p];
+        const BProb P = batch_load(probs, p);
         const RefOut R = batch_out(P, pairs, ctr, MODE);
         const int it = uniform_i32(gi - (int)item_base[p]);
         m64_item<KS, SLOT, MODE>(P.G, R, P.delta, it, KS > 4 ? tqbuf + wv * (KS > 4 ? KS - 1 : 1) * 16 : nullptr);
@@ -1622,7 +1640,7 @@ __global__ __launch_bounds__(kThreads) void k_batch_v64(const BProb *__restrict_
     for (int w = lo + uniform_i32(blockIdx.x * kWaves + wv); w < hi; w += W) {
         const int gi = queue[w];
         const int p = batch_problem(item_base, B, gi);
-        const BProb &P = probs[p];
+        const BProb P = batch_load(probs, p);
         const RefOut R = batch_out(P, pairs, ctr, MODE);
         const int it = uniform_i32(gi - (int)item_base[p]);
         v64_item<D, MODE>(P.G, R, it, D == 0 ? qbuf + wv * 16 * kV64LdsD : nullptr,
@@ -1641,7 +1659,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
     for (int w = lo + (int)blockIdx.x; w < hi; w += (int)gridDim.x) {  // block-uniform
         const int gb = bqueue[w];
         const int p = batch_problem(block_base, B, gb);
-        const BProb &P = probs[p];
+        const BProb P = batch_load(probs, p);
         const RefOut R = batch_out(P, nullptr, ctr, SYM ? MODE_SYM : MODE_COUNT);
         m64_block_count<KS, SLOT, SYM>(P.G, R, P.delta, uniform_i32(gb - (int)block_base[p]), lds);
     }
@@ -1652,7 +1670,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
 // problems blockIdx.y, blockIdx.y + gridDim.y, ..., each swept along x.
 __global__ __launch_bounds__(kThreads) void k_batch_zero_cnt(const BProb *__restrict__ probs, int B) {
     for (int p = (int)blockIdx.y; p < B; p += (int)gridDim.y) {
-        int32_t *const c = probs[p].cnt;
+        int32_t *const c = global_ptr(probs[p].cnt);
         const int64_t n = probs[p].G.n;
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
             c[i] = 0;
@@ -1671,7 +1689,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 8))
     for (int w = lo + uniform_i32(blockIdx.x * kWaves + wv); w < hi; w += W) {
         const int gi = queue[w];
         const int p = batch_problem(item_base, B, gi);
-        const BProb &P = probs[p];
+        const BProb P = batch_load(probs, p);
         const RefOut R = batch_out(P, pairs, nullptr, MODE_EMIT);
         const int it = uniform_i32(gi - (int)item_base[p]);
         mask_item<0>(P.G, R, P.masks, it, stage + 256 * wv, slot + 4 * kSlot * wv);
@@ -1685,7 +1703,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_scan(const BProb *__restrict__
     __shared__ int64_t wsum[kWaves];
     __shared__ int64_t carry;
     const int pi = ids ? ids[blockIdx.x] : (int)blockIdx.x;
-    const BProb P = probs[pi];
+    const BProb P = batch_load(probs, pi);
     const int64_t n1 = P.G.n + 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) carry = 0;
