@@ -1434,6 +1434,21 @@ static unsigned long long region_cap(int64_t rows, int64_t nblocks, unsigned lon
     return most * kHitRegions * sizeof(int2) <= (unsigned long long)budget ? most : 0;
 }
 
+// Blocks per block item: its walk is dealt to them, a round of kRound items each
+// in turn. Few block items: so many that the chip is filled, whatever their
+// length. Otherwise up to 2^15 blocks in all, each with four rounds at least:
+// about 1280 blocks run at once, and with 2922 of equal length a third of the
+// last turn stays empty. Uniform points, 187k: d = 16 (40 rounds) 10.45 ms with one
+// block per block item, 9.85 so; d = 8 (7 rounds) 1.87 and 1.74. With one round at
+// least, d = 8 takes 1.70 ms, but Gaussian mixtures, 200k points, d = 64 (2 rounds),
+// lose the start of each block: 1.89 ms against 1.75.
+int hit_segments(const Grid &g) {
+    const int64_t rounds = (int64_t)((double)g.cand_items / ((double)g.n * kTileQ * kRound));
+    const int64_t fill = std::min<int64_t>(16, 4096 / g.nblocks);
+    const int64_t even = std::min<int64_t>(32768 / g.nblocks, rounds / 4);
+    return (int)std::max<int64_t>(1, std::max(fill, std::min<int64_t>(even, 64)));
+}
+
 // Enqueues the count: counts into cnt (n + 1 entries, zeroed here), pairs into
 // the grid's list when `record`; ro.ctr zeroed here unless it already counts. most: entries per region
 // that a former run of this count reserved (0: not known).
@@ -1465,8 +1480,7 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
                     {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
                    s);
     const HitGrid G = hit_grid(g);
-    // few blocks: their walks are split so that the chip is filled
-    const int nseg = (int)std::max<int64_t>(1, std::min<int64_t>(16, 4096 / g.nblocks));
+    const int nseg = hit_segments(g);
     const dim3 grid((unsigned)(g.nblocks * nseg));
     ro.kt.start(ro.timed, s);
     if (path == SJ_FP64_MFMA) {
