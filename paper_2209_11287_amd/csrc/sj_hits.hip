@@ -13,8 +13,8 @@
 //    of its own rows the pairs (q, c > q). A pair within eps is a candidate of
 //    both of its points, so either side may evaluate it.
 //  - Box filter. Every work item (up to 16 consecutive rows) has a bounding
-//    box over all d dimensions; an item whose box is more than eps from the
-//    block's box has no pair with it. In clustered data the grid's candidates
+//    box over all d dimensions; an item has no pair with a query tile whose box
+//    is more than eps from its own, and runs only against the others. In clustered data the grid's candidates
 //    are mostly other clusters: on a 1M-point mixture of 100 clusters in 64
 //    dimensions the lists hold 77k candidates a point, its cluster 10k.
 //  - Hit list. A pair within eps is appended to a list (i, c) of sorted
@@ -26,8 +26,7 @@
 // and 50 neighbours, d = 16: count kernel 9.3 -> 4.2 ms, pairs 0.95 -> 1.6 ms;
 // d = 64: count 144 -> 16.2 ms (10.7 ms of it FP64 MFMA). Index-free count of
 // 65536 points, d = 16: 4.29 -> 1.46 ms (0.88 ms of MFMA). Uniform, 2M points,
-// d = 5: 8.7 -> 3.9 ms. Of the tile loop's time about 85 % is MFMA; the rest of
-// the kernel is the walk (box tests between barriers) and the hits.
+// d = 5: 8.7 -> 3.9 ms.
 //
 // The box test is safe in FP32: boxes hold the centred coordinates times a
 // power of two that puts eps in [1, 2), rounded outward and widened by one more
@@ -525,8 +524,10 @@ __device__ __forceinline__ void hit_finish(const HitOut &R, BlockShared &S, HitC
 // (one item ahead), the A operand (-2 q, zero past d) of all four tiles sits in
 // LDS, so a candidate row is read once per 64 queries, nothing in the loop
 // waits on another wave, and the four tiles' chains are independent. Bound by
-// the FP64 matrix unit: KS MFMAs of 64 cycles per tile against about 30 vector
-// instructions. K order: two K-steps share one 16-byte load of the row (lane g
+// the FP64 matrix unit: KS MFMAs of 64 cycles per tile and about 16 vector
+// instructions, which the counters show on top of them rather than beside them
+// (256 problems, d = 16: 112M cycles per SIMD of MFMA and 27M of vector issue in
+// 151M). K order: two K-steps share one 16-byte load of the row (lane g
 // holds dimensions 8p + 2g and 8p + 2g + 1 of K-step pair p), a last single
 // K-step dimension 4 (KS - 1) + g.
 // The accumulator starts at |q|^2 (+inf for absent rows), so D = |q|^2 - 2 q.c
@@ -1450,8 +1451,9 @@ int hit_segments(const Grid &g) {
 }
 
 // Enqueues the count: counts into cnt (n + 1 entries, zeroed here), pairs into
-// the grid's list when `record`; ro.ctr zeroed here unless it already counts. most: entries per region
-// that a former run of this count reserved (0: not known).
+// the grid's list when `record`; ro.ctr zeroed here unless it already counts.
+// most: entries per region that a former run of this count reserved (0: not
+// known).
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
                 RefineOut &ro, hipStream_t s) {
     hits_prepare(g, s);
