@@ -120,3 +120,21 @@ def test_batch_lists_equal_mask_expansion(symmetric, dims):
         got = run(cp, pp, symmetric)
         assert got[0] == want[0] and got[1] == want[1]
         assert np.array_equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("n,d", [(140001, 5), (150016, 7)])
+def test_long_walks_dealt_to_several_blocks(n, d):
+    """Enough block items and rounds that the walks are split for evenness; per-point counts and the pair list
+    against the vector-ALU path, which walks no hit list."""
+    import torch
+
+    rng = np.random.default_rng(n)
+    X = rng.random((n, d))
+    eps = 0.5 * (8.0 / n) ** (1.0 / d)
+    log(f"[hits] long walks n={n} d={d} eps={eps}")
+    got = gpu_join(X, eps, "fp64_mfma", index_dims=-1)
+    want = gpu_join(X, eps, "fp64_valu", index_dims=-1)
+    assert got["total"] == want["total"]
+    assert np.array_equal(got["per_point"], want["per_point"])
+    assert np.array_equal(got["pairs"], want["pairs"])
+    torch.cuda.synchronize()
