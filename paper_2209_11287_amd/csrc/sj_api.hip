@@ -214,6 +214,8 @@ void release_cache(DevCache &c) {
 }  // namespace
 
 thread_local AllocScope *tl_scope = nullptr;
+thread_local size_t tl_fail_bytes = 0;
+thread_local int32_t tl_fail_skip = 0;
 
 AllocScope::AllocScope(const AllocHook &h) : hook(h.alloc ? &h : nullptr), prev(tl_scope) { tl_scope = this; }
 AllocScope::AllocScope(Arena *a) : arena(a), prev(tl_scope) { tl_scope = this; }
@@ -231,6 +233,10 @@ void *dev_alloc(size_t bytes, hipStream_t s) {
         a.used = off + bytes;
         a.peak = std::max(a.peak, a.used);
         return a.base + off;
+    }
+    if (tl_fail_bytes && bytes >= tl_fail_bytes && tl_fail_skip-- == 0) {
+        tl_fail_bytes = 0;
+        throw OomError{bytes};
     }
     if (sc && sc->hook) {
         void *p = sc->hook->alloc(bytes, static_cast<void *>(s), sc->hook->ctx);
@@ -359,19 +365,6 @@ HostBuf::~HostBuf() {
 
 void set_error(const std::string &msg) { g_err = msg; }
 const char *last_error() { return g_err.c_str(); }
-
-// A device buffer released (in stream order) when it goes out of scope.
-template <typename T>
-struct DevBuf {
-    T *p = nullptr;
-    hipStream_t s = nullptr;
-    DevBuf(size_t n, hipStream_t st) : p(dev_alloc_n<T>(n, st)), s(st) {}
-    ~DevBuf() {
-        if (p) dev_free(p, s);
-    }
-    DevBuf(const DevBuf &) = delete;
-    DevBuf &operator=(const DevBuf &) = delete;
-};
 
 // Device time between two events recorded on one stream.
 struct CallTimer {
@@ -655,6 +648,11 @@ void probe_peaks(int64_t bytes, sj_peaks &out, hipStream_t s);
 }  // namespace sj
 
 extern "C" {
+
+void sj_test_fail_alloc(size_t bytes, int32_t skip) {
+    tl_fail_bytes = bytes;
+    tl_fail_skip = skip;
+}
 
 sj_status selfjoin_build_grid(const double *points, int64_t n, int32_t d, double eps, const sj_opts *opts,
                               void *stream, sj_grid **out) {

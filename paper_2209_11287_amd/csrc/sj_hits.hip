@@ -1559,16 +1559,15 @@ static void make_bins(const BinPlan &b, const int2 *hits, const unsigned long lo
         SJ_HIP(hipGetLastError());
         return;
     }
-    uint2 *part = dev_alloc_n<uint2>((size_t)std::max<int64_t>(b.entries, 1), s);
+    DevBuf<uint2> part((size_t)std::max<int64_t>(b.entries, 1), s);
     const int64_t slabs = (int64_t)(most + kSlab - 1) / kSlab;
     hipLaunchKernelGGL(k_hit_part, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(slabs, 128)), kHitRegions),
                        dim3(kPartThreads), 0, s, hits, cursor, cap, off, b.sh, b.nbuckets,
-                       reinterpret_cast<unsigned *>(fill), part);
+                       reinterpret_cast<unsigned *>(fill), part.p);
     SJ_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_hit_place, dim3((unsigned)b.nbuckets), dim3(kThreads), sizeof(unsigned) << b.sh, s, part, off,
+    hipLaunchKernelGGL(k_hit_place, dim3((unsigned)b.nbuckets), dim3(kThreads), sizeof(unsigned) << b.sh, s, part.p, off,
                        rows, b.sh, bin);
     SJ_HIP(hipGetLastError());
-    dev_free(part, s);
 }
 
 // Pairs of the chunk from the list (valid): the bins are made on the first
@@ -1579,12 +1578,13 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
     const size_t nbig = (size_t)(p.written / kWaveBin) + 1;
     const BinPlan bp = bin_plan(g.n, g.total);
     const size_t nfill = g.hit_bin ? 0 : bp.nfill;
-    int32_t *work = dev_alloc_n<int32_t>(2 + 2 * nbig + nfill, s);
-    int32_t *fill = work + 2 + 2 * nbig;
-    fill_zero_many({{work, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}}, s);
-    if (!g.hit_bin) {
-        g.hit_bin = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(g.total, 1), s);
-        make_bins(bp, g.hits, g.hit_cursor, g.hit_cap, g.hit_most, g.off, g.n, fill, g.hit_bin, s);
+    DevBuf<int32_t> work(2 + 2 * nbig + nfill, s);
+    int32_t *fill = work.p + 2 + 2 * nbig;
+    fill_zero_many({{work.p, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}}, s);
+    if (!g.hit_bin) {  // the grid's once they are made: a call that fails on the way leaves none
+        DevBuf<int32_t> bin((size_t)std::max<int64_t>(g.total, 1), s);
+        make_bins(bp, g.hits, g.hit_cursor, g.hit_cap, g.hit_most, g.off, g.n, fill, bin.p, s);
+        g.hit_bin = bin.release();
     }
     const int nitems = (int)(p.item_hi - p.item_lo);
     if (nitems > 0) {
@@ -1598,7 +1598,7 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
         E.item_hi = (int32_t)p.item_hi;
         E.pairs = reinterpret_cast<int2 *>(pairs);
         E.d2 = d2;
-        E.big = work;
+        E.big = work.p;
         const HitGrid G = hit_grid(g);
         // a wave's queries run one after the other: few items are spread over more waves
         E.per = kTileQ;
@@ -1613,7 +1613,6 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
             SJ_HIP(hipGetLastError());
         }
     }
-    dev_free(work, s);
     ro.kt.stop(s);
 }
 
@@ -1790,12 +1789,13 @@ void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pa
     SJ_HIP(hipMemcpyAsync(hb.dev, hp, P * sizeof(HitProb), hipMemcpyHostToDevice, s));
     const BinPlan bp = bin_plan(hb.rows, hb.total);
     const size_t nbig = (size_t)(hb.total / kWaveBin) + 1;
-    int32_t *work = dev_alloc_n<int32_t>(2 + 2 * nbig + bp.nfill, s);
-    int32_t *fill = work + 2 + 2 * nbig;
-    fill_zero_many({{work, sizeof(int32_t)}, {fill, (hb.bin ? 0 : bp.nfill) * sizeof(int32_t)}}, s);
+    DevBuf<int32_t> work(2 + 2 * nbig + bp.nfill, s);
+    int32_t *fill = work.p + 2 + 2 * nbig;
+    fill_zero_many({{work.p, sizeof(int32_t)}, {fill, (hb.bin ? 0 : bp.nfill) * sizeof(int32_t)}}, s);
     if (!hb.bin) {
-        hb.bin = dev_alloc_n<int32_t>((size_t)std::max<int64_t>(hb.total, 1), s);
-        make_bins(bp, static_cast<const int2 *>(hb.hits), hb.cursor, hb.cap, hb.most, hb.off, hb.rows, fill, hb.bin, s);
+        DevBuf<int32_t> bin((size_t)std::max<int64_t>(hb.total, 1), s);
+        make_bins(bp, static_cast<const int2 *>(hb.hits), hb.cursor, hb.cap, hb.most, hb.off, hb.rows, fill, bin.p, s);
+        hb.bin = bin.release();
     }
     EmitSrc src{};
     src.P = static_cast<const HitProb *>(hb.dev);
@@ -1805,7 +1805,7 @@ void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pa
     src.E.bin = hb.bin;
     src.E.item_hi = (int32_t)hb.items;
     src.E.pairs = reinterpret_cast<int2 *>(pairs);
-    src.E.big = work;
+    src.E.big = work.p;
     src.E.per = kTileQ;
     while (src.E.per > 1 && hb.items * (kTileQ / src.E.per) < 16384) src.E.per /= 2;
     const int64_t waves = hb.items * (kTileQ / src.E.per);
@@ -1815,7 +1815,6 @@ void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pa
         hipLaunchKernelGGL(k_hit_emit_big<true>, dim3((unsigned)std::min<size_t>(nbig, 1024)), dim3(kThreads), 0, s, src);
         SJ_HIP(hipGetLastError());
     }
-    dev_free(work, s);
 }
 
 }  // namespace sj

@@ -97,6 +97,24 @@ T *dev_alloc_n(size_t n, hipStream_t s) {
     return static_cast<T *>(dev_alloc(n * sizeof(T) + 16, s));
 }
 
+// A device buffer released (in stream order) when it goes out of scope.
+template <typename T>
+struct DevBuf {
+    T *p = nullptr;
+    hipStream_t s = nullptr;
+    DevBuf(size_t n, hipStream_t st) : p(dev_alloc_n<T>(n, st)), s(st) {}
+    ~DevBuf() {
+        if (p) dev_free(p, s);
+    }
+    T *release() {
+        T *q = p;
+        p = nullptr;
+        return q;
+    }
+    DevBuf(const DevBuf &) = delete;
+    DevBuf &operator=(const DevBuf &) = delete;
+};
+
 // Timing events, kept per device for reuse (creating and destroying a pair
 // costs a call more than recording it): at most kEventPool of them.
 constexpr size_t kEventPool = 64;
@@ -494,6 +512,11 @@ bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &tota
 void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pairs, hipStream_t s);
 
 }  // namespace sj
+
+// For tests of what follows a failed allocation: the next device allocation of
+// at least `bytes` on the calling thread fails, after `skip` of them that do
+// not; once, and not in the static scratch. bytes 0 takes it back.
+extern "C" void sj_test_fail_alloc(size_t bytes, int32_t skip);
 
 struct sj_grid {
     sj::Grid g;
