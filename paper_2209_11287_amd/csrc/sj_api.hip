@@ -425,11 +425,14 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     g.masks_valid = false;
     g.lp_masks_valid = false;
     g.hits_valid = false;
-    ro.hits = hits_usable(g, path) && (!g.lean || g.lean_hits);
+    ro.hits = hits_usable(g, path) && (!g.lean || g.lean_hits) && hits_prepare(g, s);
     ro.record_hits = ro.hits && !sym && !g.lean;
     ro.record_lp = is_lowp(path) && !g.lean && !ro.hits;
     if (fp64 && !ro.hits && !sym && !g.lean && !g.masks && g.tiles > 0 && g.tiles * 32 <= kMaskBudget)
-        g.masks = dev_alloc_n<unsigned long long>((size_t)g.tiles * 4, s);
+        try {
+            g.masks = dev_alloc_n<unsigned long long>((size_t)g.tiles * 4, s);
+        } catch (const OomError &) {  // the pairs call evaluates its tiles again
+        }
     ro.masks = fp64 && !sym && !ro.hits ? g.masks : nullptr;
     ro.sym = sym;
     if (sym && !ro.hits && g.n > 0) fill_zero(g.cnt, (size_t)g.n * sizeof(int32_t), s);

@@ -144,7 +144,7 @@ float time_count(const double *pts, int64_t n, int d, double eps, int k, int sc,
         int32_t *cnt = dev_alloc_n<int32_t>((size_t)n + 1, s);
         RefineOut ro;
         ro.timed = true;
-        ro.hits = hits_usable(g, SJ_FP64_MFMA);
+        ro.hits = hits_usable(g, SJ_FP64_MFMA) && hits_prepare(g, s);
         ro.ctr = dev_alloc_n<DevCounters>(1, s);
         refine_count(g, SJ_FP64_MFMA, cnt, ro, s);  // warm
         ro.kt.ms();
@@ -646,7 +646,8 @@ float batch_pairs(Batch &b, sj_path path, int32_t *pairs, hipStream_t s) {
     SJ_HIP(hipEventRecord(e0, s));
     // the list: kept by the count, or (half-stencil option, a list that outgrew
     // its first guess) made again; without room for it those tiles run again too
-    const bool hits = b.hits_counted && (b.hb.valid || hit_batch_ensure(b.hb, b.ctr, b.totals, s));
+    const bool hits = b.hits_counted && (b.hb.valid || hit_batch_ensure(b.hb, b.ctr, b.totals, s)) &&
+                      hit_batch_bins(b.hb, s);
     if (b.hits_counted && !hits) batch_offsets(b, s);
     const int mode = (use_masks ? 1 : 0) | (b.hits_counted ? 2 : 0) | (hits ? 4 : 0);
     const bool tiles = !hits || b.rest_items > 0;  // something for the graph to launch

@@ -40,6 +40,7 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <type_traits>
 
 #include "sj_internal.h"
@@ -1405,13 +1406,20 @@ static void hit_layout(Grid &g, char *p) {
 static unsigned box_blocks(const Grid &g) { return (unsigned)((g.items + 15) / 16); }
 static unsigned span_blocks(const Grid &g) { return (unsigned)((g.nblocks * g.nranges + kThreads - 1) / kThreads); }
 
-void hits_prepare(Grid &g, hipStream_t s) {
-    if (g.hit_index) return;
-    g.hit_index = dev_alloc(hit_index_bytes(g.items, g.nblocks, g.nranges, g.d), s);
+// Makes the grid's index on the first such count; false when there is no
+// memory for it (the count then runs the tiles of all candidates).
+bool hits_prepare(Grid &g, hipStream_t s) {
+    if (g.hit_index) return true;
+    try {
+        g.hit_index = dev_alloc(hit_index_bytes(g.items, g.nblocks, g.nranges, g.d), s);
+    } catch (const OomError &) {
+        return false;
+    }
     hit_layout(g, static_cast<char *>(g.hit_index));
     const unsigned nbox = box_blocks(g);
     hipLaunchKernelGGL(k_hit_index, dim3(nbox + span_blocks(g)), dim3(kThreads), 0, s, hit_grid(g), hit_scale(g), nbox);
     SJ_HIP(hipGetLastError());
+    return true;
 }
 
 void hits_free_list(Grid &g, hipStream_t s) {
@@ -1450,13 +1458,13 @@ int hit_segments(const Grid &g) {
     return (int)std::max<int64_t>(1, std::max(fill, std::min<int64_t>(even, 64)));
 }
 
-// Enqueues the count: counts into cnt (n + 1 entries, zeroed here), pairs into
-// the grid's list when `record`; ro.ctr zeroed here unless it already counts.
+// Enqueues the count (hits_prepare has made the index): counts into cnt (n + 1
+// entries, zeroed here), pairs into the grid's list when `record` and there is
+// memory for it; ro.ctr zeroed here unless it already counts.
 // most: entries per region that a former run of this count reserved (0: not
 // known).
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
                 RefineOut &ro, hipStream_t s) {
-    hits_prepare(g, s);
     g.hits_valid = false;
     HitOut R{};
     R.cnt = cnt;
@@ -1467,11 +1475,15 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
         g.hit_bin = nullptr;
         if (cap > g.hit_cap) {
             hits_free_list(g, s);
-            g.hits = dev_alloc_n<int2>((size_t)(cap * kHitRegions), s);
-            g.hit_cap = cap;
+            try {
+                DevBuf<unsigned long long> cursor(kHitRegions * kHitCursorStride, s);
+                g.hits = dev_alloc_n<int2>((size_t)(cap * kHitRegions), s);
+                g.hit_cursor = cursor.release();
+                g.hit_cap = cap;
+            } catch (const OomError &) {  // the count goes on without a list
+            }
         }
         if (g.hits) {
-            if (!g.hit_cursor) g.hit_cursor = dev_alloc_n<unsigned long long>(kHitRegions * kHitCursorStride, s);
             R.hits = g.hits;
             R.cursor = g.hit_cursor;
             R.cap = g.hit_cap;
@@ -1506,16 +1518,21 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
 
 // A list for a pairs call whose count kept none (half-stencil option, a count
 // on another path, or a list that outgrew its first guess): the count run
-// again, its counts dropped. False when the list would exceed the budget.
+// again, its counts dropped. False when the list would exceed the budget or
+// there is no memory for it; ro.ctr may then hold this count's counters.
 bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
+    if (!hits_prepare(g, s)) return false;
     unsigned long long most = g.hit_most;
     for (int tries = 0; tries < 2; ++tries) {
         if (!region_cap(g.n, g.nblocks, most, kMaskBudget)) return false;
-        int32_t *cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
         RefineOut again;
         again.ctr = ro.ctr;
-        hits_count(g, path, cnt, true, most, true, again, s);
-        dev_free(cnt, s);
+        try {
+            DevBuf<int32_t> cnt((size_t)g.n + 1, s);
+            hits_count(g, path, cnt.p, true, most, true, again, s);
+        } catch (const OomError &) {
+            return false;
+        }
         if (!g.hits) return false;
         unsigned long long cur[kHitRegions * kHitCursorStride];
         SJ_HIP(hipMemcpyAsync(cur, g.hit_cursor, sizeof cur, hipMemcpyDeviceToHost, s));
@@ -1571,20 +1588,26 @@ static void make_bins(const BinPlan &b, const int2 *hits, const unsigned long lo
 }
 
 // Pairs of the chunk from the list (valid): the bins are made on the first
-// call and kept for the chunks that follow.
-void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s) {
-    ro.kt.start(ro.timed, s);
+// call and kept for the chunks that follow. False (and nothing written) when
+// there is no memory for them.
+bool hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s) {
     // more than kWaveBin neighbours: at most written / kWaveBin points
     const size_t nbig = (size_t)(p.written / kWaveBin) + 1;
     const BinPlan bp = bin_plan(g.n, g.total);
     const size_t nfill = g.hit_bin ? 0 : bp.nfill;
-    DevBuf<int32_t> work(2 + 2 * nbig + nfill, s);
-    int32_t *fill = work.p + 2 + 2 * nbig;
-    fill_zero_many({{work.p, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}}, s);
-    if (!g.hit_bin) {  // the grid's once they are made: a call that fails on the way leaves none
-        DevBuf<int32_t> bin((size_t)std::max<int64_t>(g.total, 1), s);
-        make_bins(bp, g.hits, g.hit_cursor, g.hit_cap, g.hit_most, g.off, g.n, fill, bin.p, s);
-        g.hit_bin = bin.release();
+    std::unique_ptr<DevBuf<int32_t>> work;
+    try {
+        work.reset(new DevBuf<int32_t>(2 + 2 * nbig + nfill, s));
+        int32_t *fill = work->p + 2 + 2 * nbig;
+        ro.kt.start(ro.timed, s);
+        fill_zero_many({{work->p, sizeof(int32_t)}, {fill, nfill * sizeof(int32_t)}}, s);
+        if (!g.hit_bin) {  // the grid's once they are made: a call that fails on the way leaves none
+            DevBuf<int32_t> bin((size_t)std::max<int64_t>(g.total, 1), s);
+            make_bins(bp, g.hits, g.hit_cursor, g.hit_cap, g.hit_most, g.off, g.n, fill, bin.p, s);
+            g.hit_bin = bin.release();
+        }
+    } catch (const OomError &) {
+        return false;
     }
     const int nitems = (int)(p.item_hi - p.item_lo);
     if (nitems > 0) {
@@ -1598,7 +1621,7 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
         E.item_hi = (int32_t)p.item_hi;
         E.pairs = reinterpret_cast<int2 *>(pairs);
         E.d2 = d2;
-        E.big = work.p;
+        E.big = work->p;
         const HitGrid G = hit_grid(g);
         // a wave's queries run one after the other: few items are spread over more waves
         E.per = kTileQ;
@@ -1614,6 +1637,7 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
         }
     }
     ro.kt.stop(s);
+    return true;
 }
 
 // ------------------------------------------------------------------ batch --
@@ -1624,7 +1648,7 @@ void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
 // 4, 8, 16: count at d = 8 and 16 218 -> 74 ms, the whole call 243 -> 86 ms); their
 // rows follow each other in the counts,
 // offsets and list (entries are rows of all these problems together).
-void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s) {
+static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s) {
     double work = 0;
     for (size_t i = 0; i < grids.size(); ++i) {
         const Grid &g = *grids[i];
@@ -1683,19 +1707,15 @@ void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t
                        reinterpret_cast<const int64_t *>(d + pb + 2 * nb), P);
     SJ_HIP(hipGetLastError());
     // the queue: block items of each form by descending cost
-    unsigned long long *ka = dev_alloc_n<unsigned long long>(hb.blocks, s);
-    unsigned long long *kb = dev_alloc_n<unsigned long long>(hb.blocks, s);
-    int32_t *va = dev_alloc_n<int32_t>(hb.blocks, s), *vb = dev_alloc_n<int32_t>(hb.blocks, s);
+    DevBuf<unsigned long long> ka(hb.blocks, s), kb(hb.blocks, s);
+    DevBuf<int32_t> va(hb.blocks, s), vb(hb.blocks, s);
     hipLaunchKernelGGL(k_hit_cost, dim3((unsigned)((hb.blocks + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, dp,
-                       hb.block_base, P, hb.blocks, ka, va);
+                       hb.block_base, P, hb.blocks, ka.p, va.p);
     SJ_HIP(hipGetLastError());
-    unsigned long long *ks = ka;
-    int32_t *vs = va;
-    radix_sort_pairs(&ks, &vs, kb, vb, hb.blocks, 32, s);  // cost below the K-step count
-    hb.queue = vs;
-    dev_free(vs == va ? vb : va, s);
-    dev_free(ka, s);
-    dev_free(kb, s);
+    unsigned long long *ks = ka.p;
+    int32_t *vs = va.p;
+    radix_sort_pairs(&ks, &vs, kb.p, vb.p, hb.blocks, 32, s);  // cost below the K-step count
+    hb.queue = vs == va.p ? va.release() : vb.release();
     hb.cnt = dev_alloc_n<int32_t>((size_t)hb.rows + 1, s);
     hb.off = dev_alloc_n<int64_t>((size_t)hb.rows + 1, s);
     hb.cursor = dev_alloc_n<unsigned long long>(kHitRegions * kHitCursorStride, s);
@@ -1706,6 +1726,15 @@ void hit_batch_free(HitBatch &hb, hipStream_t s) {
     for (void *p : bufs)
         if (p) dev_free(p, s);
     hb = HitBatch{};
+}
+
+// Without memory for the index no problem takes the hit list.
+void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s) {
+    try {
+        hit_batch_make(hb, grids, s);
+    } catch (const OomError &) {
+        hit_batch_free(hb, s);
+    }
 }
 
 // Counts, offsets and totals (totals[i] for problem i of the batch) of these
@@ -1781,22 +1810,31 @@ bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &tota
     return hb.valid;
 }
 
-// Pairs of these problems from the list, problem i's at pout[i].
+// The list's bins (valid list); false when there is no memory for them.
+bool hit_batch_bins(HitBatch &hb, hipStream_t s) {
+    if (hb.bin) return true;
+    const BinPlan bp = bin_plan(hb.rows, hb.total);
+    try {
+        DevBuf<int32_t> fill(bp.nfill, s);
+        DevBuf<int32_t> bin((size_t)std::max<int64_t>(hb.total, 1), s);
+        fill_zero(fill.p, bp.nfill * sizeof(int32_t), s);
+        make_bins(bp, static_cast<const int2 *>(hb.hits), hb.cursor, hb.cap, hb.most, hb.off, hb.rows, fill.p, bin.p, s);
+        hb.bin = bin.release();
+    } catch (const OomError &) {
+        return false;
+    }
+    return true;
+}
+
+// Pairs of these problems from the bins, problem i's at pout[i].
 void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pairs, hipStream_t s) {
     const int P = (int)hb.probs.size();
     HitProb *hp = reinterpret_cast<HitProb *>(hb.host_probs.data());
     for (int k = 0; k < P; ++k) hp[k].pout = pout[hb.probs[k]];
     SJ_HIP(hipMemcpyAsync(hb.dev, hp, P * sizeof(HitProb), hipMemcpyHostToDevice, s));
-    const BinPlan bp = bin_plan(hb.rows, hb.total);
     const size_t nbig = (size_t)(hb.total / kWaveBin) + 1;
-    DevBuf<int32_t> work(2 + 2 * nbig + bp.nfill, s);
-    int32_t *fill = work.p + 2 + 2 * nbig;
-    fill_zero_many({{work.p, sizeof(int32_t)}, {fill, (hb.bin ? 0 : bp.nfill) * sizeof(int32_t)}}, s);
-    if (!hb.bin) {
-        DevBuf<int32_t> bin((size_t)std::max<int64_t>(hb.total, 1), s);
-        make_bins(bp, static_cast<const int2 *>(hb.hits), hb.cursor, hb.cap, hb.most, hb.off, hb.rows, fill, bin.p, s);
-        hb.bin = bin.release();
-    }
+    DevBuf<int32_t> work(2 + 2 * nbig, s);
+    fill_zero(work.p, sizeof(int32_t), s);
     EmitSrc src{};
     src.P = static_cast<const HitProb *>(hb.dev);
     src.item_base = hb.item_base;

@@ -368,6 +368,7 @@ struct KernelTimer {
     hipEvent_t a = nullptr, b = nullptr;
     bool on = false;
     void start(bool enable, hipStream_t s) {
+        put();
         on = enable;
         if (!on) return;
         a = event_get();
@@ -476,10 +477,11 @@ void lowp_measure(Grid &g, sj_path path, double *max_err, double *max_band, int6
 // Hit-list count (sj_hits.hip).
 bool hits_usable(const Grid &g, sj_path path);
 size_t hits_lean_bytes(int64_t n, int32_t d);
+bool hits_prepare(Grid &g, hipStream_t s);
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
                 RefineOut &ro, hipStream_t s);
 bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s);
-void hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s);
+bool hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s);
 void hits_free_list(Grid &g, hipStream_t s);
 
 // The hit-list count of a batch (FP64 MFMA): the problems it takes, by
@@ -509,6 +511,7 @@ void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t
 void hit_batch_free(HitBatch &hb, hipStream_t s);
 void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *totals, hipStream_t s);
 bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &totals, hipStream_t s);
+bool hit_batch_bins(HitBatch &hb, hipStream_t s);
 void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pairs, hipStream_t s);
 
 }  // namespace sj

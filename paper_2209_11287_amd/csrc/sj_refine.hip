@@ -2187,13 +2187,14 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
     R.d2 = d2;
     R.item_lo = (int32_t)p.item_lo;
     R.ctr = ro.ctr;
-    if (g.hits_valid && g.hits_lowp == is_lowp(path)) {
-        hits_pairs(g, p, qlo, pairs, d2, ro, s);
-        return;
-    }
+    const bool listed = g.hits_valid && g.hits_lowp == is_lowp(path);
+    if (listed && hits_pairs(g, p, qlo, pairs, d2, ro, s)) return;
     const int nitems = (int)(p.item_hi - p.item_lo);
     const bool expand = (path == SJ_FP64_VALU || path == SJ_FP64_MFMA) && g.masks_valid && g.masks;
     ro.counted = !expand;
+    if (!expand && !listed && hits_usable(g, path) && hits_ensure(g, path, ro, s) &&
+        hits_pairs(g, p, qlo, pairs, d2, ro, s))
+        return;
     if (!expand) fill_zero(ro.ctr, sizeof(DevCounters), s);
     if (expand) {
         ro.kt.start(ro.timed, s);
@@ -2211,8 +2212,6 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
             SJ_HIP(hipGetLastError());
         }
         ro.kt.stop(s);
-    } else if (hits_usable(g, path) && hits_ensure(g, path, ro, s)) {
-        hits_pairs(g, p, qlo, pairs, d2, ro, s);
     } else if (path == SJ_FP64_VALU) {
         ro.kt.start(ro.timed, s);
         launch_v64<MODE_EMIT>(g, R, nitems, s);

@@ -123,3 +123,86 @@ def test_batch_pairs_after_failed_bins(what):
         else:
             assert k == 0
     selfjoin_batch_free(b)
+
+
+@pytest.mark.parametrize("path", ["fp64_mfma", "fp32_mfma", "bf16x3_mfma"])
+def test_single_goes_on_without_the_list(path):
+    """No memory for the list at the count, nor at the pairs call that would
+    make it; then for the bins of a list that the pairs call has made: the tiles
+    run again, and the statistics are theirs alone."""
+    import torch
+
+    import oracle
+    from paper_2209_11287_amd import SelfJoin, selfjoin_pairs
+    X, eps = _points()
+    total, pp, want = oracle.grid_pairs(X, eps)[:3]
+    xt = torch.from_numpy(X).to("cuda:0")
+    log(f"[failed alloc] no list path={path} total={total}")
+
+    def pairs(sj, **fail):
+        buf = torch.full((total, 2), -1, dtype=torch.int32, device="cuda:0")
+        if fail:
+            _fail(**fail)
+        r = selfjoin_pairs(sj.grid, path, 0, buf)
+        _fail(0)
+        assert r[0] == total and np.array_equal(pair_keys(buf.cpu().numpy()), pair_keys(want))
+        return r[2]
+
+    big = 1 << 22  # only the list is larger
+    sj = SelfJoin(xt, eps)
+    _fail(big)
+    t, per_point, _ = sj.count(path, per_point=True)
+    _fail(0)
+    assert t == total and np.array_equal(per_point.cpu().numpy(), pp)
+    tiles = pairs(sj, nbytes=big)  # no list again
+    after_list = pairs(sj, nbytes=8 * (total - len(X)), skip=1)  # the list, then no parts
+    assert (after_list["rechecked"], after_list["rechecked_in"]) == (tiles["rechecked"], tiles["rechecked_in"])
+    pairs(sj)
+    pairs(sj)
+    sj.close()
+
+
+def test_single_goes_on_without_the_index():
+    import torch
+
+    import oracle
+    from paper_2209_11287_amd import SelfJoin
+    X, eps = _points(9007, 48)
+    total, pp, want = oracle.grid_pairs(X, eps)[:3]
+    log(f"[failed alloc] no index total={total}")
+    sj = SelfJoin(torch.from_numpy(X).to("cuda:0"), eps)
+    _fail(2 * 48 * 4 * (len(X) // 16))  # the boxes
+    t, per_point, _ = sj.count("fp64_mfma", per_point=True)
+    _fail(0)
+    assert t == total and np.array_equal(per_point.cpu().numpy(), pp)
+    assert np.array_equal(pair_keys(sj.all_pairs("fp64_mfma").cpu().numpy()), pair_keys(want))
+    sj.close()
+
+
+@pytest.mark.parametrize("symmetric", [0, 1])
+@pytest.mark.parametrize("pairs_path", ["fp64_mfma", "fp64_valu"])
+def test_batch_goes_on_without_the_list(symmetric, pairs_path):
+    """No memory for the batch's list at the count and at the pairs call: the
+    tiles of its problems run again; with memory the list is made."""
+    import torch
+
+    from paper_2209_11287_amd import (selfjoin_batch_build, selfjoin_batch_count, selfjoin_batch_free,
+                                      selfjoin_batch_pairs)
+    sets, want = _batch()
+    b = selfjoin_batch_build([torch.from_numpy(X).to("cuda:0") for X, _ in sets], [e for _, e in sets],
+                             symmetric=symmetric)
+    big = 1 << 22
+    log(f"[failed alloc] batch without list symmetric={symmetric} pairs {pairs_path}")
+    if not symmetric:
+        _fail(big)
+    totals, _ = selfjoin_batch_count(b, "fp64_mfma")
+    _fail(0)
+    assert [int(t) for t in totals] == [len(w) for w in want]
+    for fail in (True, False):
+        buf = torch.full((sum(totals), 2), -1, dtype=torch.int32, device="cuda:0")
+        if fail:
+            _fail(big)
+        offsets, _ = selfjoin_batch_pairs(b, pairs_path, buf)
+        _fail(0)
+        _check_batch(offsets, buf, want)
+    selfjoin_batch_free(b)
