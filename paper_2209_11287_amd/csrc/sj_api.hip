@@ -410,11 +410,10 @@ struct CountRun {
 // per_point also the counts in the input order. tm: the call ends with this.
 static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipStream_t s,
                            int32_t *per_point = nullptr, CallTimer *tm = nullptr) {
-    if (!g.cnt) {
-        g.cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
-        g.off = dev_alloc_n<int64_t>((size_t)g.n + 1, s);
-        g.ctr = dev_alloc_n<DevCounters>(1, s);
-    }
+    g.have_counts = false;  // until this pass is through
+    if (!g.cnt) g.cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
+    if (!g.off) g.off = dev_alloc_n<int64_t>((size_t)g.n + 1, s);
+    if (!g.ctr) g.ctr = dev_alloc_n<DevCounters>(1, s);
     RefineOut ro;
     ro.timed = timed;
     ro.ctr = g.ctr;

@@ -568,6 +568,7 @@ float batch_count_graph(Batch &b, sj_path path, hipStream_t s) {
 }
 
 float batch_count(Batch &b, sj_path path, hipStream_t s, HostCounters *hc) {
+    b.counted = false;  // until this pass is through
     b.hits_counted = path == SJ_FP64_MFMA && !b.hb.probs.empty();
     batch_masks(b, !b.hits_counted, s);
     if (b.tune_sched) {

@@ -206,3 +206,23 @@ def test_batch_goes_on_without_the_list(symmetric, pairs_path):
         _fail(0)
         _check_batch(offsets, buf, want)
     selfjoin_batch_free(b)
+
+
+def test_count_after_a_failed_count():
+    """The offsets could not be allocated: the next count makes them."""
+    import torch
+
+    import oracle
+    from paper_2209_11287_amd import SelfJoin, SelfJoinError
+    X, eps = _points(5000, 4)
+    total, pp, want = oracle.grid_pairs(X, eps)[:3]
+    log(f"[failed alloc] offsets total={total}")
+    sj = SelfJoin(torch.from_numpy(X).to("cuda:0"), eps)
+    _fail(8 * len(X))
+    with pytest.raises(SelfJoinError):
+        sj.count("fp64_valu")
+    _fail(0)
+    t, per_point, _ = sj.count("fp64_valu", per_point=True)
+    assert t == total and np.array_equal(per_point.cpu().numpy(), pp)
+    assert np.array_equal(pair_keys(sj.all_pairs("fp64_valu").cpu().numpy()), pair_keys(want))
+    sj.close()
