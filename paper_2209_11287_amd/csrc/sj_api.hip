@@ -312,6 +312,7 @@ hipEvent_t event_get() {
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto &v = g_events[dev];
+        v.reserve(kEventPool);  // event_put, which destructors call, then allocates nothing
         if (!v.empty()) {
             hipEvent_t e = v.back();
             v.pop_back();
@@ -327,9 +328,9 @@ void event_put(hipEvent_t e) {
     int dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) {
         std::lock_guard<std::mutex> lk(g_mu);
-        auto &v = g_events[dev];
-        if (v.size() < kEventPool) {
-            v.push_back(e);
+        auto it = g_events.find(dev);
+        if (it != g_events.end() && it->second.size() < kEventPool) {
+            it->second.push_back(e);
             return;
         }
     }
@@ -339,6 +340,7 @@ void event_put(hipEvent_t e) {
 HostBuf::HostBuf() {
     {
         std::lock_guard<std::mutex> lk(g_mu);
+        g_host.reserve(kHostPool);  // the destructor then allocates nothing
         if (!g_host.empty()) {
             p_ = g_host.back();
             g_host.pop_back();
