@@ -426,8 +426,12 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     g.masks_valid = false;
     g.lp_masks_valid = false;
     g.hits_valid = false;
-    ro.hits = hits_usable(g, path) && (!g.lean || g.lean_hits) && hits_prepare(g, s);
-    ro.record_hits = ro.hits && !sym && !g.lean;
+    ro.record_hits = !sym && !g.lean && hits_usable(g, path, HitUse::PAIRS) && hits_prepare(g, s);
+    // without a list: where no in-masks would be kept either
+    const bool no_masks = g.lean || (fp64 && g.tiles * 32 > kMaskBudget);
+    ro.hits = ro.record_hits || (sym && hits_usable(g, path, HitUse::HALF) && hits_prepare(g, s)) ||
+              (!sym && no_masks && (!g.lean || g.lean_hits) && hits_usable(g, path, HitUse::COUNT) &&
+               hits_prepare(g, s));
     ro.record_lp = is_lowp(path) && !g.lean && !ro.hits;
     if (fp64 && !ro.hits && !sym && !g.lean && !g.masks && g.tiles > 0 && g.tiles * 32 <= kMaskBudget)
         try {

@@ -144,7 +144,7 @@ float time_count(const double *pts, int64_t n, int d, double eps, int k, int sc,
         int32_t *cnt = dev_alloc_n<int32_t>((size_t)n + 1, s);
         RefineOut ro;
         ro.timed = true;
-        ro.hits = hits_usable(g, SJ_FP64_MFMA) && hits_prepare(g, s);
+        ro.hits = hits_usable(g, SJ_FP64_MFMA, HitUse::PAIRS) && hits_prepare(g, s);
         ro.ctr = dev_alloc_n<DevCounters>(1, s);
         refine_count(g, SJ_FP64_MFMA, cnt, ro, s);  // warm
         ro.kt.ms();
@@ -343,7 +343,7 @@ void batch_build(Batch &b, int B, const double *const *points, const int64_t *n,
         b.grids[i]->off = b.off_all + at;
         at += b.grids[i]->n + 1;
     }
-    hit_batch_build(b.hb, b.grids, s);
+    hit_batch_build(b.hb, b.grids, b.sym, s);
     b.in_hb.assign(B, 0);
     for (int i : b.hb.probs) b.in_hb[i] = 1;
     std::vector<int32_t> rest;

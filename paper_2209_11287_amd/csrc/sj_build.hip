@@ -76,6 +76,7 @@ struct BuildReadback {
     double nmax;
     unsigned long long cand;   // candidate pairs of the items
     unsigned long long tiles;  // in-mask tile slots
+    PairSample sample;         // d = 5 .. 64
 };
 
 // Gathers them in one block: the tables' sizes, and the sums and maximum over
@@ -85,22 +86,32 @@ __global__ __launch_bounds__(kThreads) void k_build_readback(const int32_t *__re
                                                              const int32_t *__restrict__ err,
                                                              const double *__restrict__ nmax_part, int64_t n_nmax,
                                                              const unsigned long long *__restrict__ cand_part,
-                                                             int n_cand, const int64_t *__restrict__ tile_off,
+                                                             int n_cand, const PairSample *__restrict__ sample_part,
+                                                             int n_sample, const int64_t *__restrict__ tile_off,
                                                              double *__restrict__ nmax_out,
                                                              BuildReadback *__restrict__ out) {
     __shared__ double smax[kThreads];
     __shared__ unsigned long long ssum[kThreads];
+    __shared__ PairSample ssam[kThreads];
     double m = 0.0;
     unsigned long long c = 0;
+    PairSample ps{0, 0};
     for (int64_t i = threadIdx.x; i < n_nmax; i += kThreads) m = fmax(m, nmax_part[i]);
     for (int i = threadIdx.x; i < n_cand; i += kThreads) c += cand_part[i];
+    for (int i = threadIdx.x; i < n_sample; i += kThreads) {
+        ps.pairs += sample_part[i].pairs;
+        ps.hits += sample_part[i].hits;
+    }
     smax[threadIdx.x] = m;
     ssum[threadIdx.x] = c;
+    ssam[threadIdx.x] = ps;
     __syncthreads();
     for (int w = kThreads / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) {
             smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + w]);
             ssum[threadIdx.x] += ssum[threadIdx.x + w];
+            ssam[threadIdx.x].pairs += ssam[threadIdx.x + w].pairs;
+            ssam[threadIdx.x].hits += ssam[threadIdx.x + w].hits;
         }
         __syncthreads();
     }
@@ -112,6 +123,7 @@ __global__ __launch_bounds__(kThreads) void k_build_readback(const int32_t *__re
         r.nmax = smax[0];
         r.cand = ssum[0];
         r.tiles = (unsigned long long)tile_off[r.c[2]];
+        r.sample = ssam[0];
         *nmax_out = smax[0];
         *out = r;
     }
@@ -1592,13 +1604,113 @@ __global__ void k_unite_ranges(const Item *__restrict__ items, const int32_t *__
     block_sum_out(acc, cand_part);
 }
 
+// A sample of the result's size: kSampleWaves waves, each with one work item of
+// its share of them, and 64 of the item's (query, candidate) pairs drawn evenly,
+// by a hash of the wave and lane; a pair within eps stands for its share of the
+// candidate pairs. 65536 distances: about 2 % of error where one pair in 25 is
+// within eps (where the choice between a list and in-masks lies), and enough
+// to size a list where few are. Only a guess: no result depends on it.
+constexpr int kSampleWaves = 1024;
+constexpr int kSampleBlocks = kSampleWaves / (kThreads / 64);
+
+__device__ __forceinline__ unsigned mix32(unsigned x) {  // a bijection that spreads every bit
+    x ^= x >> 16;
+    x *= 0x45d9f3bu;
+    x ^= x >> 15;
+    x *= 0x2c1b3c6du;
+    x ^= x >> 16;
+    return x;
+}
+
+// Wave w's part of `waves`. ranges: the first item's; rows of xs are the items' rows.
+__device__ __forceinline__ PairSample sample_pairs(const double *__restrict__ xs, int dp, double eps2,
+                                                   const Item *__restrict__ items, int64_t nitems,
+                                                   const Range *__restrict__ ranges, int nranges, unsigned w,
+                                                   unsigned waves) {
+    const int lane = threadIdx.x & 63;
+    const int64_t lo = nitems * w / waves, hi = nitems * (w + 1) / waves;
+    if (hi <= lo) return PairSample{0, 0};  // whole wave
+    const int64_t it = lo + mix32(w + 0x9e3779b9u) % (unsigned)(hi - lo);
+    const Item I = items[it];
+    const int nq = I.qend - I.qbegin;
+    int rb = 0, len = 0;
+    if (lane < nranges) {
+        const Range r = ranges[it * nranges + lane];
+        rb = r.begin;
+        len = max(0, r.end - r.begin);
+    }
+    int incl = len;
+    for (int o = 1; o < 32; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, 31);
+    if (nq <= 0 || total <= 0) return PairSample{0, 0};
+    const unsigned h = mix32(w * 64 + lane), g = mix32(h ^ 0x85ebca6bu);
+    const int q = I.qbegin + (int)(((h >> 8) * (unsigned long long)nq) >> 24);
+    const int pos = (int)((g * (unsigned long long)(unsigned)total) >> 32);
+    int o = 0;  // the range that holds list position pos
+    for (int k = 0; k < nranges; ++k) o += __shfl(incl, k) <= pos;
+    const int c = __shfl(rb, o) + pos - (__shfl(incl, o) - __shfl(len, o));
+    const double *__restrict__ a = xs + (int64_t)q * dp, *__restrict__ b = xs + (int64_t)c * dp;
+    double acc = 0.0;
+    for (int t0 = 0; t0 < dp; t0 += 16) {  // (whole rows: zero from d to dp)
+        double2 x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int t = min(t0 + 2 * u, dp - 2);
+            x[u] = *reinterpret_cast<const double2 *>(a + t);
+            y[u] = *reinterpret_cast<const double2 *>(b + t);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (t0 + 2 * u < dp) {
+                const double d0 = x[u].x - y[u].x, d1 = x[u].y - y[u].y;
+                acc += d0 * d0 + d1 * d1;
+            }
+        if (!__ballot(acc <= eps2)) break;
+    }
+    const unsigned hits = (unsigned)__popcll(__ballot(acc <= eps2));
+    // the share of the wave's items: (hi - lo) nq total pairs, hits of 64 drawn within eps
+    const unsigned long long all = (unsigned long long)((hi - lo) * nq) * (unsigned)total;
+    return PairSample{(all >> 6) * hits + (((all & 63u) * hits) >> 6), hits};
+}
+
+struct SampleArgs {
+    const double *xs;
+    const Item *items;
+    double eps2;
+    int32_t dp;
+    int32_t first;     // blocks from here on sample
+    PairSample *part;  // per sampling block
+};
+
 // Mask slots of each work item: its candidates (the ranges in order) form one
 // packed list of ceil(sum of range lengths / 16) tiles, and its in-masks take
 // whole groups of 16 tile slots (64 words of 64 bits per group); entry nitems
-// is 0 so that an exclusive scan ends with the total.
-__global__ void k_item_tiles(const Range *__restrict__ ranges, const int32_t *__restrict__ nitems_p, int nranges,
-                             int32_t *__restrict__ tiles) {
+// is 0 so that an exclusive scan ends with the total. Blocks from S.first on draw
+// the sample of pairs instead.
+__global__ __launch_bounds__(kThreads) void k_item_tiles(const Range *__restrict__ ranges,
+                                                         const int32_t *__restrict__ nitems_p, int nranges,
+                                                         int32_t *__restrict__ tiles, SampleArgs S) {
     const int64_t I = *nitems_p;
+    if ((int)blockIdx.x >= S.first) {  // whole block
+        __shared__ PairSample part[kThreads / 64];
+        const unsigned b = blockIdx.x - S.first;
+        const PairSample v = sample_pairs(S.xs, S.dp, S.eps2, S.items, I, ranges, nranges,
+                                          b * (kThreads / 64) + (threadIdx.x >> 6), kSampleWaves);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            PairSample t{0, 0};
+            for (int k = 0; k < kThreads / 64; ++k) {
+                t.pairs += part[k].pairs;
+                t.hits += part[k].hits;
+            }
+            S.part[b] = t;
+        }
+        return;
+    }
     const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (it > I) return;
     int64_t c = 0;
@@ -2035,7 +2147,8 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     g.blocks = dev_alloc_n<int32_t>((size_t)items_ub + 1, s);
     g.ranges = dev_alloc_n<Range>((size_t)items_ub * g.nranges, s);
     unsigned long long *cand_part = nullptr;
-    int n_cand = 0;
+    PairSample *sample_part = nullptr;
+    int n_cand = 0, n_sample = 0;
     if (n > 0) {
         // about 2048 blocks, at most kTabSteps steps a wave
         const int steps = (int)std::max<int64_t>(1, std::min<int64_t>(kTabSteps, (n + 256 * 2048 - 1) / (256 * 2048)));
@@ -2080,8 +2193,14 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
             g.united = true;
         }
         if (own_tiles) {
-            hipLaunchKernelGGL(k_item_tiles, dim3(blocks_for(items_ub + 1)), dim3(kThreads), 0, s, g.ranges,
-                               counters + 2, g.nranges, item_tiles);
+            SampleArgs sa{g.xs, g.item, g.eps2, g.dp, (int32_t)blocks_for(items_ub + 1), nullptr};
+            if (d > 4 && d <= kHitMaxD) {
+                n_sample = kSampleBlocks;
+                sample_part = dev_alloc_n<PairSample>((size_t)n_sample, s);
+                sa.part = sample_part;
+            }
+            hipLaunchKernelGGL(k_item_tiles, dim3((unsigned)(sa.first + n_sample)), dim3(kThreads), 0, s, g.ranges,
+                               counters + 2, g.nranges, item_tiles, sa);
             SJ_HIP(hipGetLastError());
         }
         // tile offsets of the items (for the per-tile in-masks of the count pass)
@@ -2095,7 +2214,7 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
         rb_dev = host ? host->as<BuildReadback>() : dev_alloc_n<BuildReadback>(1, s);
         if (host) host->arm(s);
         hipLaunchKernelGGL(k_build_readback, dim3(1), dim3(kThreads), 0, s, counters, os_err, nmax_part, n_nmax,
-                           cand_part, n_cand, g.tile_off, g.dev_nmax, rb_dev);
+                           cand_part, n_cand, sample_part, n_sample, g.tile_off, g.dev_nmax, rb_dev);
         SJ_HIP(hipGetLastError());
         if (!host) SJ_HIP(hipMemcpyAsync(&rb, rb_dev, sizeof rb, hipMemcpyDeviceToHost, s));
     }
@@ -2125,10 +2244,13 @@ void build_grid(Grid &g, const double *points, int64_t n, int d, double eps, int
     g.cand_ref = -1;  // computed on request (grid_cref)
     g.cand_items = (int64_t)rb.cand;
     g.tiles = (int64_t)rb.tiles;
+    g.sample = rb.sample;
+    g.samples = 64 * std::min<int64_t>(g.items, kSampleWaves);
 
     if (rb_dev) dev_free(rb_dev, s);
     if (nmax_part) dev_free(nmax_part, s);
     if (cand_part) dev_free(cand_part, s);
+    if (sample_part) dev_free(sample_part, s);
     dev_free(item_tiles, s);
     dev_free(bflag, s);
     dev_free(line_row, s);
@@ -2174,6 +2296,7 @@ struct SegProb {
     int64_t pn_off;          // first element of its prefix norms
     int64_t range_base;      // first range slot of its items
     int32_t d, dp, da, npc, nranges, mid_off;
+    double eps2;
     KeyGeom key;
     RangeGeom rg;
 };
@@ -2574,6 +2697,61 @@ __global__ void k_seg_item_tiles(const SegProb *__restrict__ P, int B, Item *__r
     items[it] = m;
 }
 
+// The sample of each problem with d = 5 .. 64, a part per wave: a wave for every
+// 16 points, at most kSegSampleWaves (16384 distances, 5 % of error where one
+// pair in 40 is within eps; 1024 waves for each of 512 problems of 1000 points
+// took 0.3 ms). The items in the problem's local positions.
+constexpr int kSegSampleWaves = 256;
+
+__host__ __device__ __forceinline__ int seg_sample_waves(int64_t n, int d) {
+    if (d <= 4 || d > kHitMaxD || n <= 0) return 0;
+    return (int)(n / 16 + 1 < kSegSampleWaves ? n / 16 + 1 : kSegSampleWaves);
+}
+
+__global__ __launch_bounds__(kThreads) void k_seg_sample(const SegProb *__restrict__ P, int B,
+                                                         const Item *__restrict__ items,
+                                                         const int64_t *__restrict__ it_off,
+                                                         const Range *__restrict__ ranges,
+                                                         const double *__restrict__ xs_all,
+                                                         PairSample *__restrict__ part) {
+    const int w = (int)(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
+    for (int p = (int)blockIdx.y; p < B; p += (int)gridDim.y) {
+        const SegProb &q = P[p];
+        const int waves = seg_sample_waves(q.n, q.d);
+        if (w >= waves) continue;
+        const PairSample v = sample_pairs(xs_all + q.xs_off, q.dp, q.eps2, items + it_off[p],
+                                          it_off[p + 1] - it_off[p], ranges + q.range_base, q.nranges, w, waves);
+        if ((threadIdx.x & 63) == 0) part[(int64_t)p * kSegSampleWaves + w] = v;
+    }
+}
+
+// The parts of each problem (one block), summed.
+__global__ __launch_bounds__(kThreads) void k_seg_sample_sum(const SegProb *__restrict__ P,
+                                                             const PairSample *__restrict__ part,
+                                                             PairSample *__restrict__ out) {
+    __shared__ PairSample red[kThreads / 64];
+    const int p = blockIdx.x;
+    PairSample t{0, 0};
+    const int waves = seg_sample_waves(P[p].n, P[p].d);
+    for (int i = threadIdx.x; i < waves; i += kThreads) {
+        t.pairs += part[(int64_t)p * kSegSampleWaves + i].pairs;
+        t.hits += part[(int64_t)p * kSegSampleWaves + i].hits;
+    }
+    for (int sh = 32; sh > 0; sh >>= 1) {
+        t.pairs += __shfl_xor(t.pairs, sh);
+        t.hits += __shfl_xor(t.hits, sh);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) {
+            t.pairs += red[w].pairs;
+            t.hits += red[w].hits;
+        }
+        out[p] = t;
+    }
+}
+
 // The united ranges of every problem with d > 4 (as k_unite_ranges, at the
 // problem's range slots; blocks never cross a line, hence never a problem);
 // others copied.
@@ -2743,6 +2921,7 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
         q.npc = g->npc;
         q.nranges = g->nranges;
         q.mid_off = (int32_t)mid_all.size();
+        q.eps2 = g->eps2;
         for (int j = 0; j < x.d; ++j) {
             mid_all.push_back(g->mid[j]);
             fo_all.push_back(g->fo[j]);
@@ -2829,12 +3008,14 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
     unsigned long long *os_status =
         static_cast<unsigned long long *>(scratch((size_t)passes * os_tiles * 256 * sizeof(unsigned long long)));
     unsigned long long *nmax_bits = static_cast<unsigned long long *>(scratch((size_t)B * 8));
-    unsigned long long *cand = static_cast<unsigned long long *>(scratch((size_t)B * 8));
+    // candidate pairs, then the samples: one copy to the host
+    unsigned long long *cand = static_cast<unsigned long long *>(scratch((size_t)B * (8 + sizeof(PairSample))));
+    PairSample *sample = reinterpret_cast<PairSample *>(cand + B);
     int32_t *counters = static_cast<int32_t *>(scratch(4 * sizeof(int32_t)));  // ncells, nlines, nitems
     fill_zero_many({{os_hist, (kOsMaxPasses * 256 + kOsMaxPasses + 1) * sizeof(int32_t)},
                     {os_status, (size_t)passes * os_tiles * 256 * sizeof(unsigned long long)},
                     {nmax_bits, (size_t)B * 8},
-                    {cand, (size_t)B * 8},
+                    {cand, (size_t)B * (8 + sizeof(PairSample))},
                     {counters, 4 * sizeof(int32_t)}},
                    s);
     if (!blk.empty()) {
@@ -2915,19 +3096,30 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
     hipLaunchKernelGGL(k_seg_item_tiles, dim3(blocks_for(items_ub + 1)), dim3(kThreads), 0, s, P, B, items,
                        counters + 2, it_off, ranges, item_tiles, cand);
     SJ_HIP(hipGetLastError());
+    int sample_waves = 0;
+    for (const SegInput &x : in) sample_waves = std::max(sample_waves, seg_sample_waves(x.n, x.d));
+    if (sample_waves > 0) {
+        PairSample *part = static_cast<PairSample *>(scratch((size_t)B * kSegSampleWaves * sizeof(PairSample)));
+        const unsigned nb = (unsigned)((sample_waves + kThreads / 64 - 1) / (kThreads / 64));
+        hipLaunchKernelGGL(k_seg_sample, dim3(nb, (unsigned)std::min(B, 32768)), dim3(kThreads), 0, s, P, B, items,
+                           it_off, ranges, xs_all, part);
+        SJ_HIP(hipGetLastError());
+        hipLaunchKernelGGL(k_seg_sample_sum, dim3((unsigned)B), dim3(kThreads), 0, s, P, part, sample);
+        SJ_HIP(hipGetLastError());
+    }
     exclusive_scan<int32_t, int64_t>(item_tiles, tile_off, items_ub + 1, s);
     int64_t *ptiles = static_cast<int64_t *>(scratch((B + 1) * sizeof(int64_t)));
     hipLaunchKernelGGL(k_seg_tiles, dim3(blocks_for(B + 1)), dim3(kThreads), 0, s, it_off, B, tile_off, ptiles);
     SJ_HIP(hipGetLastError());
     // ---- one host sync: per-problem items, tiles, norms, candidates ----
     std::vector<int64_t> h_it(B + 1), h_tiles(B + 1), h_bl(B + 1);
-    std::vector<unsigned long long> h_nmax(B), h_cand(B);
+    std::vector<unsigned long long> h_nmax(B), h_cand(3 * (size_t)B);
     int32_t herr = 0;
     SJ_HIP(hipMemcpyAsync(h_it.data(), it_off, (B + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipMemcpyAsync(h_tiles.data(), ptiles, (B + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipMemcpyAsync(h_bl.data(), bl_off, (B + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipMemcpyAsync(h_nmax.data(), nmax_bits, B * 8, hipMemcpyDeviceToHost, s));
-    SJ_HIP(hipMemcpyAsync(h_cand.data(), cand, B * 8, hipMemcpyDeviceToHost, s));
+    SJ_HIP(hipMemcpyAsync(h_cand.data(), cand, B * (8 + sizeof(PairSample)), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipMemcpyAsync(&herr, os_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipStreamSynchronize(s));
     for (void *q : tmp) dev_free(q, s);
@@ -2951,6 +3143,8 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
         g.nmax = nm;
         g.cand_items = (int64_t)h_cand[p];
         g.cand_ref = -1;
+        g.sample = PairSample{h_cand[B + 2 * (size_t)p], h_cand[B + 2 * (size_t)p + 1]};
+        g.samples = 64 * std::min<int64_t>(g.items, seg_sample_waves(g.n, g.d));
         g.blocks = blocks + h_bl[p];  // global item indices: item_base below
         g.nblocks = h_bl[p + 1] - h_bl[p];
         g.item_base = (int32_t)h_it[p];

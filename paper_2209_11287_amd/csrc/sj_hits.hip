@@ -40,6 +40,7 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <type_traits>
 
@@ -1362,6 +1363,24 @@ size_t hit_index_bytes(int64_t items, int64_t nblocks, int nranges, int d) {
 
 }  // namespace
 
+// Blocks per block item: its walk is dealt to them, a round of kRound items each
+// in turn. Few block items: so many that the chip is filled, whatever their
+// length. Otherwise up to 2^15 blocks in all, each with four rounds at least:
+// about 1280 blocks run at once, and with 2922 of equal length a third of the
+// last turn stays empty. Uniform points, 187k: d = 16 (40 rounds) 10.45 ms with one
+// block per block item, 9.85 so; d = 8 (7 rounds) 1.87 and 1.74. With one round at
+// least, d = 8 takes 1.70 ms, but Gaussian mixtures, 200k points, d = 64 (2 rounds),
+// lose the start of each block: 1.89 ms against 1.75.
+static int hit_segments(const Grid &g) {
+    const int64_t rounds = (int64_t)((double)g.cand_items / ((double)g.n * kTileQ * kRound));
+    const int64_t fill = std::min<int64_t>(16, 4096 / g.nblocks);
+    const int64_t even = std::min<int64_t>(32768 / g.nblocks, rounds / 4);
+    return (int)std::max<int64_t>(1, std::max(fill, std::min<int64_t>(even, 64)));
+}
+
+thread_local int32_t tl_hits_always = 0;
+thread_local unsigned long long tl_hits_first = 0;
+
 // The grids and paths this count takes: block items with one candidate list
 // (d > 4), d <= 64 (whole rows in a wave's lanes; more dimensions stay on the
 // per-wave tiles), work items at least half full (an item is a tile here, and
@@ -1372,7 +1391,7 @@ size_t hit_index_bytes(int64_t items, int64_t nblocks, int nranges, int d) {
 // n = 2048, d = 8, 8.4e6: 315 and 333; n = 5000, d = 6, 2.3e7: 530 and 493;
 // n = 30000, d = 5, 1.3e8: 559 and 514; n = 9001, d = 23 index-free, 4.9e8: 1169
 // and 502), eps far enough from the ends of the range for the boxes'
-// power-of-two scale.
+// power-of-two scale, and few enough pairs (hits_pay).
 static bool hits_fit(const Grid &g) {
     return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && g.n >= 8 * g.items &&
            g.eps >= 0x1p-500 && g.eps <= 0x1p500;
@@ -1380,9 +1399,84 @@ static bool hits_fit(const Grid &g) {
 static double hits_work(const Grid &g) { return (double)g.cand_items * (g.da >> 2); }
 constexpr double kHitWork = 0x1p24;
 
-bool hits_usable(const Grid &g, sj_path path) {
-    return hits_fit(g) && hits_work(g) >= kHitWork &&
-           (path == SJ_FP64_MFMA || path == SJ_FP32_MFMA || path == SJ_BF16X3_MFMA);
+// The upper end: a pair costs this count more than a candidate's mask bit costs
+// the tiles of all candidates. With C candidates and s pairs a point (s from the
+// build's sample) the tiles saved weigh C (2 KS + 1), KS the K-steps of 4
+// dimensions, and a pair `per_pair` of that: in a join (use = PAIRS) 240 in FP64,
+// where both ways take about the same (count and pairs, ms, tiles with in-masks
+// against list; 200k points): uniform d = 5, C = 9730, s = 198 1.76 and 1.59, s =
+// 398 2.58 and 2.76; d = 8, C = 74503, s = 201 11.7 and 5.0; mixture d = 8, C =
+// 1752, s = 49 0.55 and 0.56, s = 97 0.61 and 0.83; d = 16, C = 2325, s = 50 0.82
+// and 0.61, s = 99 0.85 and 0.90. The tiles of FP32 and split BF16 are dearer: 140
+// and 60 (mixture d = 16, s = 197: 1.55 and 1.61, 2.38 and 1.77). A point's pairs
+// past 300 cost more each, for the ordering (uniform d = 6, C = 34453, s = 403 5.5
+// and 4.1, C = 53866, s = 804 9.0 and 12.4; mixture of 1M points, d = 16, s = 394
+// 11.7 and 21.0). Few items with 2 or 3 K-steps leave the per-wave tiles idle
+// (uniform, 30k points, d = 5, s = 200 0.60 and 0.43); with more they do not
+// (mixture, 30k, d = 16, s = 50 0.20 and 0.25). A batch of 16 (uniform, d = 5, 62500
+// points each, s = 101 4.2 and 3.9, s = 201 6.2 and 6.7): 200, and the idle tiles
+// by all its items. A count alone (COUNT: no list, no in-masks) only bears the pairs'
+// atomics: 30 (mixture d = 8, C = 2112, s = 389 0.84 and 0.91); against the
+// half-stencil tiles (HALF) 130 (mixture d = 16, s = 99 0.53 and 0.44, s = 197 0.53
+// and 0.56).
+static bool hits_pay(const Grid &g, sj_path path, HitUse use, int64_t batch_items = 0) {
+    if (tl_hits_always) return true;
+    const int ks = path == SJ_FP64_MFMA ? g.da >> 2 : g.dp >> 2;
+    const double per_pair = use == HitUse::COUNT   ? 30
+                            : use == HitUse::HALF  ? 130
+                            : batch_items > 0      ? 200
+                            : path == SJ_FP64_MFMA ? 240
+                            : path == SJ_FP32_MFMA ? 140
+                                                   : 60;
+    const double pairs = (double)g.sample.pairs;
+    double gain = (double)g.cand_items * (2 * ks + 1), cost = per_pair * pairs;
+    if (use == HitUse::PAIRS) {
+        cost *= std::max(1.0, pairs / (300.0 * (double)g.n));
+        const double items = (double)(batch_items > 0 ? batch_items : g.items);
+        if (ks < 4) gain *= std::min(8.0, std::max(1.0, 16384.0 / items));
+    }
+    return gain >= cost;
+}
+
+// Pairs of the result that the list is laid out for: the sample's, and what
+// its spread may hide.
+static double pairs_up(const Grid &g) {
+    const double pairs = (double)g.sample.pairs, hits = (double)g.sample.hits, cand = (double)g.cand_items;
+    const double each = std::max(cand / (double)std::max<int64_t>(g.samples, 1), hits > 0 ? pairs / hits : 0.0);
+    return std::min(cand, 1.15 * pairs + 3.0 * std::sqrt(hits + 1.0) * each);
+}
+
+// Entries of a list of `listed` pairs that `waves` waves write: each may leave
+// the rest of its last run unused.
+static double list_entries(double listed, double waves) {
+    return listed + (double)kHitChunk * std::min(waves, listed + 1.0);
+}
+
+// Entries per region to begin with: twice the pairs that are expected (the
+// regions fill unevenly). Past the budget the budget: the cursors count on, so
+// that a count that overflows still tells the need.
+static unsigned long long region_first(double listed, double waves, int64_t budget) {
+    if (tl_hits_first) return tl_hits_first;
+    const double most = list_entries(2.0 * listed, waves) / kHitRegions + 16 * kHitChunk;
+    const unsigned long long lim = (unsigned long long)budget / (kHitRegions * sizeof(int2)) / kHitChunk;
+    return std::min((unsigned long long)(most / kHitChunk) + 1, lim) * kHitChunk;
+}
+
+// Entries per region for `most` of them in the fullest, 0 past the budget.
+static unsigned long long region_cap(unsigned long long most, int64_t budget) {
+    most = (most + kHitChunk - 1) / kHitChunk * kHitChunk;
+    return most * kHitRegions * sizeof(int2) <= (unsigned long long)budget ? most : 0;
+}
+
+static double listed_up(const Grid &g) { return std::max(0.0, 0.5 * (pairs_up(g) - (double)g.n)); }
+
+bool hits_usable(const Grid &g, sj_path path, HitUse use) {
+    if (path != SJ_FP64_MFMA && path != SJ_FP32_MFMA && path != SJ_BF16X3_MFMA) return false;
+    if (!hits_fit(g) || hits_work(g) < kHitWork || !hits_pay(g, path, use)) return false;
+    if (use != HitUse::PAIRS) return true;
+    // a join whose list would not fit keeps in-masks, if they do
+    const double waves = (double)g.nblocks * hit_segments(g) * kWaves;
+    return list_entries(listed_up(g), waves) * sizeof(int2) <= (double)kMaskBudget;
 }
 
 size_t hits_lean_bytes(int64_t n, int32_t d) {
@@ -1433,31 +1527,6 @@ void hits_free_list(Grid &g, hipStream_t s) {
     g.hits_valid = false;
 }
 
-// Entries per region for `most` of them in the fullest (0: a first guess of
-// 256 pairs a point, of which half are listed), or 0 when the list would
-// exceed the budget.
-static unsigned long long region_cap(int64_t rows, int64_t nblocks, unsigned long long most, int64_t budget) {
-    const unsigned long long waves = (unsigned long long)nblocks * kWaves;
-    if (!most) most = (128ull * (unsigned long long)rows + waves * kHitChunk) / kHitRegions + 16 * kHitChunk;
-    most = (most + kHitChunk - 1) / kHitChunk * kHitChunk;
-    return most * kHitRegions * sizeof(int2) <= (unsigned long long)budget ? most : 0;
-}
-
-// Blocks per block item: its walk is dealt to them, a round of kRound items each
-// in turn. Few block items: so many that the chip is filled, whatever their
-// length. Otherwise up to 2^15 blocks in all, each with four rounds at least:
-// about 1280 blocks run at once, and with 2922 of equal length a third of the
-// last turn stays empty. Uniform points, 187k: d = 16 (40 rounds) 10.45 ms with one
-// block per block item, 9.85 so; d = 8 (7 rounds) 1.87 and 1.74. With one round at
-// least, d = 8 takes 1.70 ms, but Gaussian mixtures, 200k points, d = 64 (2 rounds),
-// lose the start of each block: 1.89 ms against 1.75.
-int hit_segments(const Grid &g) {
-    const int64_t rounds = (int64_t)((double)g.cand_items / ((double)g.n * kTileQ * kRound));
-    const int64_t fill = std::min<int64_t>(16, 4096 / g.nblocks);
-    const int64_t even = std::min<int64_t>(32768 / g.nblocks, rounds / 4);
-    return (int)std::max<int64_t>(1, std::max(fill, std::min<int64_t>(even, 64)));
-}
-
 // Enqueues the count (hits_prepare has made the index): counts into cnt (n + 1
 // entries, zeroed here), pairs into the grid's list when `record` and there is
 // memory for it; ro.ctr zeroed here unless it already counts.
@@ -1465,12 +1534,15 @@ int hit_segments(const Grid &g) {
 // known).
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
                 RefineOut &ro, hipStream_t s) {
+    const int nseg = hit_segments(g);
     g.hits_valid = false;
     HitOut R{};
     R.cnt = cnt;
     R.ctr = ro.ctr;
     if (record) {  // (a former list is dropped)
-        const unsigned long long cap = region_cap(g.n, g.nblocks, most, kMaskBudget);
+        const unsigned long long cap =
+            most ? region_cap(most, kMaskBudget)
+                 : region_first(listed_up(g), (double)g.nblocks * nseg * kWaves, kMaskBudget);
         if (g.hit_bin) dev_free(g.hit_bin, s);
         g.hit_bin = nullptr;
         if (cap > g.hit_cap) {
@@ -1494,7 +1566,6 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
                     {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
                    s);
     const HitGrid G = hit_grid(g);
-    const int nseg = hit_segments(g);
     const dim3 grid((unsigned)(g.nblocks * nseg));
     ro.kt.start(ro.timed, s);
     if (path == SJ_FP64_MFMA) {
@@ -1524,7 +1595,7 @@ bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
     if (!hits_prepare(g, s)) return false;
     unsigned long long most = g.hit_most;
     for (int tries = 0; tries < 2; ++tries) {
-        if (!region_cap(g.n, g.nblocks, most, kMaskBudget)) return false;
+        if (most && !region_cap(most, kMaskBudget)) return false;
         RefineOut again;
         again.ctr = ro.ctr;
         try {
@@ -1648,15 +1719,28 @@ bool hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double
 // 4, 8, 16: count at d = 8 and 16 218 -> 74 ms, the whole call 243 -> 86 ms); their
 // rows follow each other in the counts,
 // offsets and list (entries are rows of all these problems together).
-static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s) {
+static int hit_batch_segments(int64_t blocks) { return (int)std::max<int64_t>(1, std::min<int64_t>(16, 4096 / blocks)); }
+
+static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, bool sym, hipStream_t s) {
     double work = 0;
+    std::map<int, int64_t> blocks;  // by K-step count
+    hb.listed_up = 0;
+    int64_t items = 1;
+    for (const Grid *g : grids) items += g->items;
     for (size_t i = 0; i < grids.size(); ++i) {
         const Grid &g = *grids[i];
         if (!hits_fit(g) || !m64_in_range(g)) continue;
+        if (!hits_pay(g, SJ_FP64_MFMA, sym ? HitUse::HALF : HitUse::PAIRS, items)) continue;
         hb.probs.push_back((int)i);
         work += hits_work(g);
+        blocks[g.da >> 2] += g.nblocks;
+        hb.listed_up += listed_up(g);
     }
+    hb.waves = 0;
+    for (const auto &kv : blocks) hb.waves += (double)kv.second * hit_batch_segments(kv.second) * kWaves;
     if (work < kHitWork) hb.probs.clear();
+    // (a list that would not fit: in-masks, if they do)
+    if (!sym && list_entries(hb.listed_up, hb.waves) * sizeof(int2) > (double)kHitBatchBudget) hb.probs.clear();
     if (hb.probs.empty()) return;
     const int P = (int)hb.probs.size();
     // K-step counts grouped: the block queue is made form by form, in this order
@@ -1729,9 +1813,9 @@ void hit_batch_free(HitBatch &hb, hipStream_t s) {
 }
 
 // Without memory for the index no problem takes the hit list.
-void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s) {
+void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, bool sym, hipStream_t s) {
     try {
-        hit_batch_make(hb, grids, s);
+        hit_batch_make(hb, grids, sym, s);
     } catch (const OomError &) {
         hit_batch_free(hb, s);
     }
@@ -1744,7 +1828,8 @@ void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *total
     if (hb.bin) dev_free(hb.bin, s);
     hb.bin = nullptr;
     if (record) {
-        const unsigned long long cap = region_cap(hb.rows, hb.blocks, hb.most, kHitBatchBudget);
+        const unsigned long long cap = hb.most ? region_cap(hb.most, kHitBatchBudget)
+                                               : region_first(hb.listed_up, hb.waves, kHitBatchBudget);
         if (cap > hb.cap) {
             if (hb.hits) dev_free(hb.hits, s);
             hb.hits = nullptr;
@@ -1771,7 +1856,7 @@ void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *total
     const int P = (int)hb.probs.size();
     for (const HitBatch::Form &f : hb.forms) {
         const int nb = f.hi - f.lo;
-        const int nseg = (int)std::max<int64_t>(1, std::min<int64_t>(16, 4096 / nb));
+        const int nseg = hit_batch_segments(nb);
         by_k_steps<2, 16>(f.ks, [&](auto ks) {
             hipLaunchKernelGGL(k_hit_f64_batch<decltype(ks)::value>, dim3((unsigned)(nb * nseg)), dim3(kThreads), 0, s,
                                dp, hb.block_base, P, hb.queue + f.lo, R, nseg);
@@ -1803,7 +1888,7 @@ void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *total
 // A valid list for the pairs call, the count run again where it kept none.
 bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &totals, hipStream_t s) {
     for (int tries = 0; tries < 2 && !hb.valid; ++tries) {
-        if (!region_cap(hb.rows, hb.blocks, hb.most, kHitBatchBudget)) return false;
+        if (hb.most && !region_cap(hb.most, kHitBatchBudget)) return false;
         hit_batch_count(hb, true, ctr, totals.data(), s);
         if (!hb.listed) return false;
     }
@@ -1856,3 +1941,8 @@ void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pa
 }
 
 }  // namespace sj
+
+extern "C" void sj_test_hits(int32_t always, unsigned long long first) {
+    sj::tl_hits_always = always;
+    sj::tl_hits_first = first;
+}

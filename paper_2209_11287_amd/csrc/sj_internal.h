@@ -162,6 +162,13 @@ struct DevCounters {
     unsigned long long spare[2];
 };
 
+// A sample of candidate pairs drawn by the build (d = 5 .. 64): the pairs within
+// eps that it stands for (ordered, the points' own included), and the number
+// of drawn ones.
+struct PairSample {
+    unsigned long long pairs, hits;
+};
+
 // Candidate range of a work item: the union of the neighbouring cells of its
 // first and last cell along one offset of the leading indexed dimensions.
 struct Range {
@@ -249,6 +256,8 @@ struct Grid {
     int64_t nblocks = 0;
     int64_t cand_ref = -1;   // C_ref (lazily computed; -1 = not yet)
     int64_t cand_items = 0;  // candidate pairs the work items evaluate
+    PairSample sample{0, 0}; // guess of the result's size (d = 5 .. 64)
+    int64_t samples = 0;     // pairs it drew
     double nmax = 0;       // max squared norm of the centred rows of xa
     // Dimension order of the distance tiles (xa, the low-precision tiles):
     // column t holds input dimension fo[t]. For d > 4 (unless dim_order = 1)
@@ -475,7 +484,10 @@ void lowp_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_t 
 void lowp_measure(Grid &g, sj_path path, double *max_err, double *max_band, int64_t *viol, hipStream_t s);
 
 // Hit-list count (sj_hits.hip).
-bool hits_usable(const Grid &g, sj_path path);
+// What a hit-list count is asked for: counts and, by a pairs call, the list;
+// counts alone; counts that the half-stencil tiles would give otherwise.
+enum class HitUse { PAIRS, COUNT, HALF };
+bool hits_usable(const Grid &g, sj_path path, HitUse use);
 size_t hits_lean_bytes(int64_t n, int32_t d);
 bool hits_prepare(Grid &g, hipStream_t s);
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
@@ -504,10 +516,11 @@ struct HitBatch {
     int32_t *bin = nullptr;
     int64_t rows = 0, blocks = 0, items = 0, total = 0;
     unsigned long long cap = 0, most = 0;
+    double listed_up = 0, waves = 0;  // pairs that the list is laid out for; waves that write it
     bool listed = false, valid = false;
 };
 constexpr int64_t kHitBatchBudget = int64_t(64) << 30;  // largest list of a batch (bytes)
-void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, hipStream_t s);
+void hit_batch_build(HitBatch &hb, const std::vector<Grid *> &grids, bool sym, hipStream_t s);
 void hit_batch_free(HitBatch &hb, hipStream_t s);
 void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *totals, hipStream_t s);
 bool hit_batch_ensure(HitBatch &hb, DevCounters *ctr, std::vector<int64_t> &totals, hipStream_t s);
@@ -520,6 +533,11 @@ void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pa
 // at least `bytes` on the calling thread fails, after `skip` of them that do
 // not; once, and not in the static scratch. bytes 0 takes it back.
 extern "C" void sj_test_fail_alloc(size_t bytes, int32_t skip);
+
+// For tests of the hit-list count, on the calling thread: always = 1 takes it
+// whatever the number of pairs (where grid, path and work allow it); first > 0
+// = entries per region of a list's first layout. 0, 0 takes it back.
+extern "C" void sj_test_hits(int32_t always, unsigned long long first);
 
 struct sj_grid {
     sj::Grid g;

@@ -2192,7 +2192,7 @@ void refine_pairs(Grid &g, sj_path path, const ChunkPlan &p, int64_t qlo, int32_
     const int nitems = (int)(p.item_hi - p.item_lo);
     const bool expand = (path == SJ_FP64_VALU || path == SJ_FP64_MFMA) && g.masks_valid && g.masks;
     ro.counted = !expand;
-    if (!expand && !listed && hits_usable(g, path) && hits_ensure(g, path, ro, s) &&
+    if (!expand && !listed && hits_usable(g, path, HitUse::PAIRS) && hits_ensure(g, path, ro, s) &&
         hits_pairs(g, p, qlo, pairs, d2, ro, s))
         return;
     if (!expand) fill_zero(ro.ctr, sizeof(DevCounters), s);
