@@ -75,8 +75,12 @@ constexpr int64_t kKnnBudget = int64_t(1) << 26;  // default pairs held at once 
 // instructions per pair and 64 pairs, where a round of the selection below
 // takes about 100 and waits for its loads (500k points, 33 pairs each, k = 10:
 // 1.11 ms by rounds).
-// More pairs: k rounds, each taking the smallest key above the previous
-// round's.
+// More pairs, or few neighbours wanted of many: k rounds, each taking the
+// smallest key above the previous round's. With m pairs in c = ceil(m / 64)
+// parts, ranks take 0.015 c m / 4 ms for 500k points and rounds 0.05 k (c + 1)
+// (whole calls by ranks and by rounds: 100 pairs, k = 1 1.28 and 0.79 ms, k = 4
+// 1.28 and 1.23; 200 pairs, k = 1 3.73 and 1.48, k = 6 3.74 and 2.64; 32 pairs, k =
+// 1 0.47 and 0.45).
 constexpr int kKnnRank = 256;
 constexpr int kKnnWaves = 4;
 
@@ -93,8 +97,9 @@ __global__ __launch_bounds__(64 * kKnnWaves) void k_knn_select(
     const int32_t self = perm[q];
     int64_t row = (int64_t)self * k;
     int found = 0;
-    if (e - b <= kKnnRank) {
-        const int m = (int)(e - b);
+    const int m = __builtin_amdgcn_readfirstlane((int)min(e - b, (int64_t)(kKnnRank + 1)));
+    const int chunks = (m + 63) >> 6;
+    if (m <= kKnnRank && chunks * ((m + 3) >> 2) <= 3 * min(k, m) * (chunks + 1)) {
         double *const d = reinterpret_cast<double *>(kd[wv]);
         // the point itself (and the filling up) is NaN: below nothing
         for (int p = lane; p < ((m + 3) & ~3); p += 64) {
