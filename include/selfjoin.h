@@ -172,13 +172,18 @@ typedef struct {
                             -1 until selfjoin_grid_info has computed it */
     int64_t cand_eval;   /* candidate pairs the path evaluated, tile padding
                             excluded (a half-stencil count: the pairs after
-                            each work item's first query) */
+                            each work item's first query; a count that keeps a
+                            hit list, d = 5 .. 64: each unordered pair of block
+                            items once, and a block item's rows with
+                            themselves; tiles left early count) */
     int64_t pairs;       /* |R| for count; pairs written for pairs */
     int64_t rechecked;   /* pairs of this call's tile kernels whose fast value
                             fell inside the error band and were re-evaluated
                             with the exact FP64 chain (0 on the FP64 VALU
-                            path, and for pairs expanded from the in-masks a
-                            count recorded) */
+                            path, and for pairs expanded from the in-masks or
+                            the hit list a count recorded; a hit-list count
+                            meets each unordered pair once, so it re-evaluates
+                            it once) */
     int64_t rechecked_in; /* of those, the pairs found within eps */
     double band_rel;     /* largest band half-width used, divided by eps^2 */
     double ms;           /* device time of the whole call (ms) */

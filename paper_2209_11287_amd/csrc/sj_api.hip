@@ -409,7 +409,7 @@ struct CountRun {
     HostCounters hc;
     double band_rel = 0;
     float ms_refine = 0;
-    int64_t cand_eval = -1;  // half-stencil count: the candidate pairs it evaluated
+    int64_t cand_eval = -1;  // half-stencil or hit-list count: the candidate pairs it evaluated
 };
 
 // Computes per-query counts with `path` (range-checked) into the handle's
@@ -494,7 +494,7 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
         cr.band_rel = g.eps2 > 0 ? cr.hc.max_delta / (g.eps2 * sc * sc) : 0.0;
     }
     cr.ms_refine = ro.kt.ms();
-    cr.cand_eval = sym ? (int64_t)hctr.spare[0] : -1;
+    cr.cand_eval = ro.hits ? cr.hc.met : sym ? (int64_t)hctr.spare[0] : -1;
     g.have_counts = true;
 }
 

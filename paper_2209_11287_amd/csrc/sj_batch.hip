@@ -219,7 +219,8 @@ struct Batch {
     bool counted = false;
     bool sym = false;                     // half-stencil count (sj_opts.symmetric): no in-masks
     int64_t max_n = 0;                    // largest problem
-    int64_t sym_cand = -1;                // candidate pairs the half-stencil count evaluates (on first use)
+    int64_t sym_cand[2] = {-1, -1};       // candidate pairs the half-stencil tiles evaluate (on first use): of all
+                                          // problems, of those without the hit list
     double ms_build = 0;                  // wall time of the grid builds and the queue
     // graphs per path: the count pipeline, and the pairs launch (per output buffer)
     hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -768,29 +769,27 @@ sj_status selfjoin_batch_count(sj_batch *bh, sj_path path, int64_t *totals, sj_s
     Batch &b = bh->b;
     HostCounters hc;
     const float ms = batch_count(b, path, s, &hc);
-    int64_t sum = 0, cev = 0;
+    int64_t sum = 0, cev = hc.met;  // (the hit list's problems)
     for (int i = 0; i < b.B; ++i) {
         totals[i] = b.totals[i];
         sum += b.totals[i];
-        cev += b.grids[i]->cand_items;
     }
     if (stats && b.sym) {
-        if (b.sym_cand < 0) {  // ranges cut at each item's first query (once per batch)
-            unsigned long long *acc = dev_alloc_n<unsigned long long>(1, s);
+        int64_t &cand = b.sym_cand[b.hits_counted ? 1 : 0];
+        if (cand < 0) {  // ranges cut at each item's first query (once per batch)
+            DevBuf<unsigned long long> acc(1, s);
             unsigned long long h = 0;
-            try {
-                fill_zero(acc, sizeof h, s);
-                for (const Grid *g : b.grids) launch_sym_cand(*g, acc, s);
-                SJ_HIP(hipMemcpyAsync(&h, acc, sizeof h, hipMemcpyDeviceToHost, s));
-                SJ_HIP(hipStreamSynchronize(s));
-            } catch (...) {
-                dev_free(acc, s);
-                throw;
-            }
-            dev_free(acc, s);
-            b.sym_cand = (int64_t)h;
+            fill_zero(acc.p, sizeof h, s);
+            for (int i = 0; i < b.B; ++i)
+                if (!(b.hits_counted && b.in_hb[i])) launch_sym_cand(*b.grids[i], acc.p, s);
+            SJ_HIP(hipMemcpyAsync(&h, acc.p, sizeof h, hipMemcpyDeviceToHost, s));
+            SJ_HIP(hipStreamSynchronize(s));
+            cand = (int64_t)h;
         }
-        cev = b.sym_cand;
+        cev += cand;
+    } else {
+        for (int i = 0; i < b.B; ++i)
+            if (!(b.hits_counted && b.in_hb[i])) cev += b.grids[i]->cand_items;
     }
     if (stats) {
         std::memset(stats, 0, sizeof *stats);

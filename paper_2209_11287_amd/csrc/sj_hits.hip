@@ -251,16 +251,17 @@ struct BlockShared {
     int2 surv[kSurv];     // surviving items: first row, rows | own block << 8 | query tiles near it << 16
     int pre[28], first[28];
     int wcount[kWaves];
+    unsigned wmet[kWaves];
     int cntq[64];         // pairs of the block's rows as query
     float4_t alo[kHitMaxD], ahi[kHitMaxD];  // the four query tiles' boxes
 };
 
 // Walks a block's candidate items, kRound at a time, and keeps those of the
-// block's half whose boxes are near enough. State is block-uniform except
-// `dropped` (per thread).
+// block's half whose boxes are near enough. State is block-uniform except, per
+// thread, the rows of its half's items and the tiles that their boxes dropped.
 struct Walk {
     int total, pos, step;
-    unsigned dropped;
+    unsigned met, dropped;
 };
 
 __device__ __forceinline__ Walk walk_init(const HitGrid &G, BlockShared &S, int bi, int ib, int ie, int seg, int nseg) {
@@ -292,7 +293,7 @@ __device__ __forceinline__ Walk walk_init(const HitGrid &G, BlockShared &S, int 
     W.total = S.wcount[0];
     W.pos = seg * kRound;
     W.step = nseg * kRound;
-    W.dropped = 0;
+    W.met = W.dropped = 0;
     __syncthreads();
     return W;
 }
@@ -320,6 +321,7 @@ __device__ __forceinline__ int walk_fill(const HitGrid &G, BlockShared &S, Walk 
             ok = b == bi || ((bi < b) == (((bi + b) & 1) == 0));
             if (ok) {
                 const Item I = G.items[it];
+                W.met += (unsigned)(I.qend - I.qbegin);
                 unsigned near = (1u << nt) - 1u;  // query tiles
                 if (G.boxes && b != bi) {
                     float s[4] = {0.f, 0.f, 0.f, 0.f};
@@ -509,14 +511,28 @@ __device__ __forceinline__ void hit_finish(const HitOut &R, BlockShared &S, HitC
         const int v = S.cntq[tid] + (seg == 0 ? 1 : 0);
         if (v) atomicAdd(R.cnt + q0 + tid, v);
     }
-    unsigned long long dr = count_dropped ? W.dropped : 0;
-    for (int sh = 32; sh > 0; sh >>= 1) dr += __shfl_xor(dr, sh);
+    unsigned dr = W.dropped, met = W.met;
+    for (int sh = 32; sh > 0; sh >>= 1) {
+        dr += __shfl_xor(dr, sh);
+        met += __shfl_xor(met, sh);
+    }
     if (lane == 0) {
-        if (dr) atomicAdd(&R.ctr->pruned, dr);
+        S.wcount[tid >> 6] = (int)dr;
+        S.wmet[tid >> 6] = met;
         if (C.band) {
             atomicAdd(&R.ctr->rechecked, C.band);
             atomicAdd(&R.ctr->rechecked_in, C.band_in);
         }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long d = 0, m = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            d += (unsigned)S.wcount[w];
+            m += S.wmet[w];
+        }
+        if (m) atomicAdd(&R.ctr->met, m * (unsigned long long)nrows);
+        if (d && count_dropped) atomicAdd(&R.ctr->pruned, d);
     }
 }
 
@@ -1529,11 +1545,11 @@ void hits_free_list(Grid &g, hipStream_t s) {
 
 // Enqueues the count (hits_prepare has made the index): counts into cnt (n + 1
 // entries, zeroed here), pairs into the grid's list when `record` and there is
-// memory for it; ro.ctr zeroed here unless it already counts.
+// memory for it; ro.ctr zeroed here.
 // most: entries per region that a former run of this count reserved (0: not
 // known).
-void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
-                RefineOut &ro, hipStream_t s) {
+void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, RefineOut &ro,
+                hipStream_t s) {
     const int nseg = hit_segments(g);
     g.hits_valid = false;
     HitOut R{};
@@ -1563,7 +1579,7 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
     }
     fill_zero_many({{cnt, ((size_t)g.n + 1) * sizeof(int32_t)},
                     {R.cursor, R.cursor ? kHitRegions * kHitCursorStride * sizeof(unsigned long long) : 0},
-                    {zero_ctr ? ro.ctr : nullptr, sizeof(DevCounters)}},
+                    {ro.ctr, sizeof(DevCounters)}},
                    s);
     const HitGrid G = hit_grid(g);
     const dim3 grid((unsigned)(g.nblocks * nseg));
@@ -1600,7 +1616,7 @@ bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
         again.ctr = ro.ctr;
         try {
             DevBuf<int32_t> cnt((size_t)g.n + 1, s);
-            hits_count(g, path, cnt.p, true, most, true, again, s);
+            hits_count(g, path, cnt.p, true, most, again, s);
         } catch (const OomError &) {
             return false;
         }

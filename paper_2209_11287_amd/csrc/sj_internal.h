@@ -159,6 +159,7 @@ struct DevCounters {
     unsigned long long max_delta;     // largest band half-width used (bits)
     unsigned long long max_err;       // measure: largest |fast - exact| (bits)
     unsigned long long violations;    // measure: errors above their band
+    unsigned long long met;           // hit-list count: candidate pairs of the halves it takes
     unsigned long long spare[2];
 };
 
@@ -424,7 +425,7 @@ struct RefineOut {
 // Host copy of a launch's counters (one device-to-host copy with the
 // caller's other readbacks).
 struct HostCounters {
-    int64_t rechecked = 0, rechecked_in = 0, pruned = 0, violations = 0;
+    int64_t rechecked = 0, rechecked_in = 0, pruned = 0, violations = 0, met = 0;
     double max_delta = 0, max_err = 0;
 };
 HostCounters read_counters(const DevCounters &c);
@@ -490,8 +491,8 @@ enum class HitUse { PAIRS, COUNT, HALF };
 bool hits_usable(const Grid &g, sj_path path, HitUse use);
 size_t hits_lean_bytes(int64_t n, int32_t d);
 bool hits_prepare(Grid &g, hipStream_t s);
-void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, bool zero_ctr,
-                RefineOut &ro, hipStream_t s);
+void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, RefineOut &ro,
+                hipStream_t s);
 bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s);
 bool hits_pairs(Grid &g, const ChunkPlan &p, int64_t qlo, int32_t *pairs, double *d2, RefineOut &ro, hipStream_t s);
 void hits_free_list(Grid &g, hipStream_t s);

@@ -2013,6 +2013,7 @@ HostCounters read_counters(const DevCounters &c) {
     h.rechecked_in = (int64_t)c.rechecked_in;
     h.pruned = (int64_t)c.pruned;
     h.violations = (int64_t)c.violations;
+    h.met = (int64_t)c.met;
     std::memcpy(&h.max_delta, &c.max_delta, sizeof(double));
     std::memcpy(&h.max_err, &c.max_err, sizeof(double));
     return h;
@@ -2060,11 +2061,7 @@ void refine_count(Grid &g, sj_path path, int32_t *cnt_sorted, RefineOut &ro, hip
     const bool sym = ro.sym && (path == SJ_FP64_VALU || path == SJ_FP64_MFMA);
     ro.cand_eval = g.cand_items;
     if (ro.hits) {
-        if (sym && ro.timed) {
-            fill_zero(ro.ctr, sizeof(DevCounters), s);
-            launch_sym_cand(g, &ro.ctr->spare[0], s);
-        }
-        hits_count(g, path, cnt_sorted, ro.record_hits, 0, !(sym && ro.timed), ro, s);
+        hits_count(g, path, cnt_sorted, ro.record_hits, 0, ro, s);
         return;
     }
     fill_zero(ro.ctr, sizeof(DevCounters), s);
