@@ -1407,10 +1407,13 @@ thread_local unsigned long long tl_hits_first = 0;
 // n = 2048, d = 8, 8.4e6: 315 and 333; n = 5000, d = 6, 2.3e7: 530 and 493;
 // n = 30000, d = 5, 1.3e8: 559 and 514; n = 9001, d = 23 index-free, 4.9e8: 1169
 // and 502), eps far enough from the ends of the range for the boxes'
-// power-of-two scale, and few enough pairs (hits_pay).
+// power-of-two scale, few enough pairs (hits_pay), and a block for each block
+// item within one launch (below 2^32 threads).
+constexpr int64_t kHitMaxBlocks = ((int64_t(1) << 32) - 1) / kThreads;
+
 static bool hits_fit(const Grid &g) {
     return g.united && g.blocks && g.items > 0 && g.d > 4 && g.d <= kHitMaxD && g.n >= 8 * g.items &&
-           g.eps >= 0x1p-500 && g.eps <= 0x1p500;
+           g.nblocks <= kHitMaxBlocks && g.eps >= 0x1p-500 && g.eps <= 0x1p500;
 }
 static double hits_work(const Grid &g) { return (double)g.cand_items * (g.da >> 2); }
 constexpr double kHitWork = 0x1p24;
@@ -1753,7 +1756,10 @@ static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, bool 
         hb.listed_up += listed_up(g);
     }
     hb.waves = 0;
-    for (const auto &kv : blocks) hb.waves += (double)kv.second * hit_batch_segments(kv.second) * kWaves;
+    for (const auto &kv : blocks) {
+        hb.waves += (double)kv.second * hit_batch_segments(kv.second) * kWaves;
+        if (kv.second > kHitMaxBlocks) work = 0;
+    }
     if (work < kHitWork) hb.probs.clear();
     // (a list that would not fit: in-masks, if they do)
     if (!sym && list_entries(hb.listed_up, hb.waves) * sizeof(int2) > (double)kHitBatchBudget) hb.probs.clear();
