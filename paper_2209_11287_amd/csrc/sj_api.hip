@@ -576,11 +576,14 @@ ScratchDev &scratch_for_current_device() {
 }
 
 // Upper bound of the scratch bytes a lean build + count of n points in d
-// dimensions takes: the sum of every allocation the two make (the arena
-// releases nothing), each with its 16-byte tail and 256-byte alignment.
-// Table sizes use the build's own upper bounds (items <= n + n/16 + 1,
-// 3^(k-1) ranges per item with k <= min(d, 4)); each exclusive scan of L
-// entries is charged L/256 + 4096 bytes of tile sums.
+// dimensions takes (the arena releases nothing): each term at least the
+// allocations named beside it, with their 16-byte tails and 256-byte alignment.
+// It also is the limit that callers know, so a term stays when its buffer
+// goes: the spare one below is two arrays of the points' number. Table sizes use
+// the build's own upper bounds (items <= n + n/16 + 1, 3^(k-1) ranges per item
+// with k <= min(d, 4)); each exclusive scan of L entries is charged L/256 + 4096
+// bytes of tile sums. A hit-list count's index is asked for on top
+// (hits_lean_bytes).
 size_t lean_need(int64_t n, int32_t d) {
     const size_t N = (size_t)n;
     const size_t dp = (size_t)((d + 3) & ~3);
@@ -597,11 +600,13 @@ size_t lean_need(int64_t n, int32_t d) {
     need += 2 * A(8 * N) + 2 * A(4 * N);                                             // keys, indices
     need += A((8 * 256 + 9) * 4) + A(8 * sort_tiles * 256 * 8);                     // radix sort
     const size_t npc = d > 4 ? da / 4 - 1 : 0;
-    need += A(rows * dp * 8) + A(rows * da * 8) + A(rows * 8) + A(rows * npc * 8) + 3 * A(16);  // rows, norms
-    need += A(std::max<size_t>(4096, N / 256 + 1) * 8);                              // norm maxima
-    need += 2 * A((N + N / kTileQ + 2) * 4);                                         // flags, ids
-    need += A(8 * (N + 1)) + 4 * A(4 * (N + 2)) + 3 * scan(N + 1);                   // cells, lines
-    need += A(8 * (items_ub + 1)) + 2 * A(4 * (items_ub + 1)) + A(16 * items_ub);    // items
+    need += A(rows * dp * 8) + A(rows * da * 8) + A(rows * 8) + A(rows * npc * 8) + 3 * A(16);  // rows, norms, counters
+    need += A(std::max<size_t>(4096, N / 256 + 1) * 8);  // norm maxima (d = 16 ..: N / 32 of them, the rest spare)
+    need += 2 * A((N + N / kTileQ + 2) * 4);                                         // block flags, first rows of lines
+    need += A(8 * (N + 1)) + 2 * A(4 * (N + 2));                                     // cell keys and starts, lines
+    need += 2 * A(4 * (N + 2)) + 3 * scan(N + 1);  // spare: the tables' sums (24 bytes a wave and a tile of them),
+                                                   // candidate and sample parts, the box's flags, the read-back
+    need += A(8 * (items_ub + 1)) + 2 * A(4 * (items_ub + 1)) + A(16 * items_ub);    // items, tile slots, blocks
     need += A(8 * items_ub * nr) * (d > 4 ? 2 : 1) + A(4 * (size_t)kLeanLineTable) + 2 * scan(items_ub + 1);
     need += A(4 * (N + 1)) + A(8 * (N + 1)) + A(sizeof(DevCounters)) + scan(N + 1);  // counts
     return need;
