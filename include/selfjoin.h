@@ -332,7 +332,7 @@ void selfjoin_free_grid(sj_grid *g, void *stream);
  * cannot: its address is private to the library).
  * Limit: inputs whose worst-case need exceeds the array return
  * SJ_ERR_CAPACITY before any device work (about n <= 1.29M at d = 2, 647k
- * at d = 4, 175k at d = 64, 50k at d = 256; selfjoin_last_error states the
+ * at d = 4, 151k at d = 64, 47k at d = 256; selfjoin_last_error states the
  * need).
  * Errors: SJ_ERR_INVALID (bad argument or non-finite coordinate),
  * SJ_ERR_UNSUPPORTED (low-precision path with d > 64), SJ_ERR_CAPACITY,
