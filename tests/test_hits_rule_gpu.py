@@ -152,3 +152,31 @@ def test_large_set_keeps_its_list():
     assert torch.equal(c - q, k % 3 - 1)
     del q, c, k, at, pp
     torch.cuda.empty_cache()
+
+
+# The list count's own tests with the rule set aside (in-masks would be taken for
+# some of their sets).
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("d", [5, 7, 8, 9, 12, 13, 16, 17, 20, 25, 31, 32, 36, 41, 47, 48, 53, 60, 63, 64])
+def test_every_k_step_count_in_a_list(path, d):
+    from tests import test_hits_gpu as t
+    with _hits():
+        t.test_every_k_step_count(path, d)
+
+
+@pytest.mark.parametrize("path", PATHS)
+def test_skewed_and_far_units_in_a_list(path):
+    from tests import test_hits_gpu as t
+    with _hits():
+        t.test_chunks_and_skewed_points(path)
+        for scale in (2.0 ** -400, 1e100):
+            t.test_units_far_from_one(path, scale)
+
+
+@pytest.mark.parametrize("symmetric", [0, 1])
+@pytest.mark.parametrize("dims", [(8, 16, 5), (2, 8, 3, 16, 20)])
+def test_batch_in_a_list(symmetric, dims):
+    from tests import test_hits_gpu as t
+    with _hits():
+        t.test_batch_lists_equal_mask_expansion(symmetric, dims)
