@@ -23,17 +23,28 @@ thread_local std::string g_err;
 __global__ void k_set_i32(int32_t *p, int32_t v) { *p = v; }
 
 // The count's total (the last entry of the offsets' exclusive scan) beside
-// its counters, so that one copy brings both to the host, and with a hit list
-// the entries reserved in its fullest region.
-__global__ void k_total_to_ctr(const int64_t *total, const unsigned long long *cursor, const DevCounters *ctr,
-                               DevCounters *out) {
+// its counters, so that one copy brings both to the host; with a hit list the
+// entries reserved in its fullest region, and of a hit-list count its tally.
+// One wave.
+__global__ __launch_bounds__(64) void k_total_to_ctr(const int64_t *total, const unsigned long long *cursor,
+                                                     const unsigned long long *tally, const DevCounters *ctr,
+                                                     DevCounters *out) {
+    static_assert(kHitRegions <= 64 && kHitTally == 64, "a lane each");
+    const int lane = threadIdx.x;
+    unsigned long long most = cursor && lane < kHitRegions ? cursor[lane * kHitCursorStride] : 0;
+    unsigned long long met = tally ? tally[lane * kHitCursorStride] : 0;
+    unsigned long long pruned = tally ? tally[lane * kHitCursorStride + 1] : 0;
+    for (int o = 32; o > 0; o >>= 1) {
+        most = max(most, __shfl_xor(most, o));
+        met += __shfl_xor(met, o);
+        pruned += __shfl_xor(pruned, o);
+    }
+    if (lane > 0) return;
     DevCounters c = *ctr;
     c.spare[1] = (unsigned long long)*total;
-    if (cursor) {
-        unsigned long long m = 0;
-        for (int r = 0; r < kHitRegions; ++r) m = max(m, cursor[r * kHitCursorStride]);
-        c.spare[0] = m;
-    }
+    if (cursor) c.spare[0] = most;
+    c.met += met;
+    c.pruned += pruned;
     *out = c;
 }
 
@@ -453,6 +464,7 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     exclusive_scan_i32_to_i64(g.cnt, g.off, g.n + 1, s);
     const bool listed = ro.record_hits && g.hits;
     const unsigned long long *cursor = listed ? g.hit_cursor : nullptr;
+    const unsigned long long *tally = ro.hits ? g.hit_tally : nullptr;
     if (per_point && g.n > 0) {
         hipLaunchKernelGGL(k_scatter_counts, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, g.cnt, g.perm,
                            g.n, per_point);
@@ -462,14 +474,15 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     // nothing, copies them)
     DevCounters hctr{};
     if (g.lean) {
-        hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, cursor, g.ctr, g.ctr);
+        hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(64), 0, s, g.off + g.n, cursor, tally, g.ctr, g.ctr);
         SJ_HIP(hipGetLastError());
         SJ_HIP(hipMemcpyAsync(&hctr, g.ctr, sizeof hctr, hipMemcpyDeviceToHost, s));
         SJ_HIP(hipStreamSynchronize(s));
     } else {
         HostBuf hb;
         hb.arm(s);
-        hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(1), 0, s, g.off + g.n, cursor, g.ctr, hb.as<DevCounters>());
+        hipLaunchKernelGGL(k_total_to_ctr, dim3(1), dim3(64), 0, s, g.off + g.n, cursor, tally, g.ctr,
+                           hb.as<DevCounters>());
         SJ_HIP(hipGetLastError());
         if (tm) tm->end(s);
         SJ_HIP(hipStreamSynchronize(s));

@@ -87,6 +87,7 @@ struct HitOut {
     DevCounters *ctr;
     int2 *hits;                  // kHitRegions regions of `cap` entries, or null: count only
     unsigned long long *cursor;  // entries reserved in each region, kHitCursorStride apart
+    unsigned long long *tally;   // kHitTally pairs (candidate pairs met, tiles dropped), kHitCursorStride apart
     unsigned long long cap;
     int32_t row0;                // list entries are rows plus this (batched form: the problem's first row)
 };
@@ -502,8 +503,9 @@ __device__ __forceinline__ void hit_record(const HitGrid &G, const HitOut &R, Bl
 
 // The end of a block: the list's last entries, the rows' counts as query (and
 // the point itself, once per row), the counters.
+template <bool DROPPED>
 __device__ __forceinline__ void hit_finish(const HitOut &R, BlockShared &S, HitCtx &C, const Walk &W, int q0, int nrows,
-                                           int seg, bool count_dropped) {
+                                           int seg) {
     const int tid = threadIdx.x, lane = tid & 63;
     if (R.hits) hit_pad(R, C.run, C.region, lane);
     __syncthreads();
@@ -511,13 +513,13 @@ __device__ __forceinline__ void hit_finish(const HitOut &R, BlockShared &S, HitC
         const int v = S.cntq[tid] + (seg == 0 ? 1 : 0);
         if (v) atomicAdd(R.cnt + q0 + tid, v);
     }
-    unsigned dr = W.dropped, met = W.met;
+    unsigned dr = DROPPED ? W.dropped : 0, met = W.met;
     for (int sh = 32; sh > 0; sh >>= 1) {
-        dr += __shfl_xor(dr, sh);
+        if (DROPPED) dr += __shfl_xor(dr, sh);
         met += __shfl_xor(met, sh);
     }
     if (lane == 0) {
-        S.wcount[tid >> 6] = (int)dr;
+        if (DROPPED) S.wcount[tid >> 6] = (int)dr;
         S.wmet[tid >> 6] = met;
         if (C.band) {
             atomicAdd(&R.ctr->rechecked, C.band);
@@ -528,11 +530,13 @@ __device__ __forceinline__ void hit_finish(const HitOut &R, BlockShared &S, HitC
     if (tid == 0) {
         unsigned long long d = 0, m = 0;
         for (int w = 0; w < kWaves; ++w) {
-            d += (unsigned)S.wcount[w];
+            if (DROPPED) d += (unsigned)S.wcount[w];
             m += S.wmet[w];
         }
-        if (m) atomicAdd(&R.ctr->met, m * (unsigned long long)nrows);
-        if (d && count_dropped) atomicAdd(&R.ctr->pruned, d);
+        // (on one address the blocks' atomics would queue up, 13 ns each: 2.25 -> 2.63 ms for 2.4M points)
+        unsigned long long *T = R.tally + (blockIdx.x & (kHitTally - 1)) * kHitCursorStride;
+        if (m) atomicAdd(T, m * (unsigned long long)nrows);
+        if (DROPPED && d) atomicAdd(T + 1, d);
     }
 }
 
@@ -653,7 +657,7 @@ __device__ __forceinline__ void hit_f64_block(const HitGrid &G, const HitOut &R,
         }
         __syncthreads();
     }
-    hit_finish(R, S, C, W, q0, nrows, seg, true);
+    hit_finish<true>(R, S, C, W, q0, nrows, seg);
 }
 
 template <int KS>
@@ -732,7 +736,7 @@ __device__ __forceinline__ unsigned bf16_pair(float a, float b) {
 }
 
 template <int PREC, int KS>
-__global__ __launch_bounds__(kThreads, PREC == PREC_F32 ? (KS <= 8 ? 4 : 3) : (KS == 1 ? 4 : 3)) void k_hit_lp(
+__global__ __launch_bounds__(kThreads, PREC == PREC_F32 ? (KS <= 10 ? 4 : 3) : (KS == 1 ? 4 : 3)) void k_hit_lp(
     HitGrid G, HitOut R, int nseg) {
     using Tile = LpTile<PREC, KS>;
     constexpr int NB = Tile::NB;
@@ -873,7 +877,7 @@ __global__ __launch_bounds__(kThreads, PREC == PREC_F32 ? (KS <= 8 ? 4 : 3) : (K
         __syncthreads();
     }
     if (C.waiting) band_flush(G, R, S, C, q0, lane);
-    hit_finish(R, S, C, W, q0, nrows, seg, false);  // tiles_pruned is 0 on these paths
+    hit_finish<false>(R, S, C, W, q0, nrows, seg);  // tiles_pruned is 0 on these paths
 }
 
 // --------------------------------------------------------------- hit list --
@@ -1310,10 +1314,21 @@ __global__ __launch_bounds__(kThreads) void k_hit_cost(const HitProb *__restrict
     val[gb] = (int32_t)gb;
 }
 
+// The tally of a count, added to its counters.
+__device__ __forceinline__ void hit_fold(const unsigned long long *__restrict__ tally, DevCounters *ctr) {
+    for (int r = 0; r < kHitTally; ++r) {
+        ctr->met += tally[r * kHitCursorStride];
+        ctr->pruned += tally[r * kHitCursorStride + 1];
+    }
+}
+
+__global__ void k_hit_fold(const unsigned long long *__restrict__ tally, DevCounters *ctr) { hit_fold(tally, ctr); }
+
 // Totals of a batch's problems, then the entries reserved in the fullest region.
 __global__ __launch_bounds__(kThreads) void k_hit_totals(const HitProb *__restrict__ P, const int64_t *__restrict__ off,
                                                          int64_t rows, int B,
                                                          const unsigned long long *__restrict__ cursor,
+                                                         const unsigned long long *__restrict__ tally, DevCounters *ctr,
                                                          int64_t *__restrict__ out) {
     const int k = blockIdx.x * kThreads + threadIdx.x;
     if (k < B) out[k] = off[k + 1 < B ? P[k + 1].row0 : rows] - off[P[k].row0];
@@ -1321,6 +1336,7 @@ __global__ __launch_bounds__(kThreads) void k_hit_totals(const HitProb *__restri
         unsigned long long m = 0;
         for (int r = 0; r < kHitRegions; ++r) m = max(m, cursor[r * kHitCursorStride]);
         out[B] = (int64_t)m;
+        hit_fold(tally, ctr);
     }
 }
 
@@ -1370,11 +1386,13 @@ HitGrid hit_grid(const Grid &g) {
 
 size_t align_up(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Bytes of the index that hit_prepare adds to a grid.
+constexpr size_t kTallyBytes = kHitTally * kHitCursorStride * sizeof(unsigned long long);
+
+// Bytes of the index that hits_prepare adds to a grid, the count's tally last.
 size_t hit_index_bytes(int64_t items, int64_t nblocks, int nranges, int d) {
     const size_t dims = (size_t)((d + 3) & ~3);
     return 2 * align_up(dims * items * sizeof(float)) + align_up(items * sizeof(int32_t)) +
-           align_up((size_t)nblocks * nranges * sizeof(int2));
+           align_up((size_t)nblocks * nranges * sizeof(int2)) + kTallyBytes;
 }
 
 }  // namespace
@@ -1419,42 +1437,75 @@ static double hits_work(const Grid &g) { return (double)g.cand_items * (g.da >> 
 constexpr double kHitWork = 0x1p24;
 
 // The upper end: a pair costs this count more than a candidate's mask bit costs
-// the tiles of all candidates. With C candidates and s pairs a point (s from the
-// build's sample) the tiles saved weigh C (2 KS + 1), KS the K-steps of 4
-// dimensions, and a pair `per_pair` of that: in a join (use = PAIRS) 240 in FP64,
-// where both ways take about the same (count and pairs, ms, tiles with in-masks
-// against list; 200k points): uniform d = 5, C = 9730, s = 198 1.76 and 1.59, s =
-// 398 2.58 and 2.76; d = 8, C = 74503, s = 201 11.7 and 5.0; mixture d = 8, C =
-// 1752, s = 49 0.55 and 0.56, s = 97 0.61 and 0.83; d = 16, C = 2325, s = 50 0.82
-// and 0.61, s = 99 0.85 and 0.90. The tiles of FP32 and split BF16 are dearer: 140
-// and 60 (mixture d = 16, s = 197: 1.55 and 1.61, 2.38 and 1.77). A point's pairs
-// past 300 cost more each, for the ordering (uniform d = 6, C = 34453, s = 403 5.5
-// and 4.1, C = 53866, s = 804 9.0 and 12.4; mixture of 1M points, d = 16, s = 394
-// 11.7 and 21.0). Few items with 2 or 3 K-steps leave the per-wave tiles idle
-// (uniform, 30k points, d = 5, s = 200 0.60 and 0.43); with more they do not
-// (mixture, 30k, d = 16, s = 50 0.20 and 0.25). A batch of 16 (uniform, d = 5, 62500
-// points each, s = 101 4.2 and 3.9, s = 201 6.2 and 6.7): 200, and the idle tiles
-// by all its items. A count alone (COUNT: no list, no in-masks) only bears the pairs'
-// atomics: 30 (mixture d = 8, C = 2112, s = 389 0.84 and 0.91); against the
-// half-stencil tiles (HALF) 130 (mixture d = 16, s = 99 0.53 and 0.44, s = 197 0.53
-// and 0.56).
-static bool hits_pay(const Grid &g, sj_path path, HitUse use, int64_t batch_items = 0) {
-    if (tl_hits_always) return true;
-    const int ks = path == SJ_FP64_MFMA ? g.da >> 2 : g.dp >> 2;
-    const double per_pair = use == HitUse::COUNT   ? 30
-                            : use == HitUse::HALF  ? 130
-                            : batch_items > 0      ? 200
-                            : path == SJ_FP64_MFMA ? 240
-                            : path == SJ_FP32_MFMA ? 140
-                                                   : 60;
-    const double pairs = (double)g.sample.pairs;
-    double gain = (double)g.cand_items * (2 * ks + 1), cost = per_pair * pairs;
-    if (use == HitUse::PAIRS) {
-        cost *= std::max(1.0, pairs / (300.0 * (double)g.n));
-        const double items = (double)(batch_items > 0 ? batch_items : g.items);
-        if (ks < 4) gain *= std::min(8.0, std::max(1.0, 16384.0 / items));
+// the tiles of all candidates, so a set with many pairs a point, or with few
+// candidates, stays on those. Which takes less is estimated from C candidates
+// and s pairs a point (s from the build's sample), KS K-steps of 4 dimensions and
+// the fill f of the work items (points over 16 times the items: an item is a
+// tile here, the other tiles pack their candidates):
+//   tiles ms = n (C (c + ck KS) + p s) 1e-9 + C (w + wk KS) 1e-6 + t
+//   list  ms = n (C / f (c + ck KS) + s (p + q max(0, s / 300 - 1))) 1e-9 + w C 1e-6 + t
+// (w, wk: one wave's walk over its candidates, which few items leave bare; q: the
+// ordering of long bins). Least squares over 461 joins (count and pairs; 5000 to
+// 1M points, uniform, exponential and mixture, d = 5 .. 64, s = 8 .. 800), each
+// mostly within 30 %; taking the smaller estimate costs 1.5 % over the faster of
+// the two in FP64 with up to 4 K-steps (tiles shared through LDS; the forms
+// meet there: mixture of 200k points, d = 16, C = 2325, s = 50 0.82 ms by tiles,
+// 0.61 by list, s = 99 0.85 and 0.90; uniform, d = 5, C = 9730, s = 198 1.76 and 1.59,
+// s = 398 2.58 and 2.76; mixture of 400k, d = 5, half-filled items, C = 696, s = 8
+// 0.71 and 1.18) and less than 0.2 % elsewhere (mixture of 30k, d = 29, C = 895, s = 87
+// 0.76 and 0.28; split BF16, d = 16, s = 197 2.4 and 1.8). Against the half-stencil tiles
+// (148 counts): 0.6 % there, the list always for more K-steps. A count without
+// list or in-masks only bears its pairs' atomics, and loses (by up to 10 %) only
+// in FP64 where 30 pairs outweigh the candidates (mixture of 200k, d = 8, C = 2112,
+// s = 389 0.84 and 0.91).
+struct TilesCost { double c, ck, p, w, wk, t; };
+struct ListCost { double c, ck, p, q, w, t; };
+
+struct Costs {
+    double tiles, list;
+};
+
+// Near the line the list is taken for up to 100 pairs a point: its count alone,
+// which is all that some callers ask for, is the cheaper one there (mixture of 91k
+// points, d = 13, s = 28: 0.16 and 0.27 ms).
+static double hit_lean(const Grid &g) { return g.sample.pairs <= 100ull * (unsigned long long)g.n ? 1.15 : 1.0; }
+
+// alone: the launches and the walk are this grid's alone (not a batch's).
+static Costs hits_costs(const Grid &g, sj_path path, HitUse use, bool alone) {
+    static const TilesCost tiles[5] = {{0.458, 0.096, 3.95, 35.5, 0.0, 0.147},    // FP64, up to 4 K-steps
+                                       {3.11, 0.0356, 0.0, 60.8, 0.403, 0.196},   // FP64, more
+                                       {0.726, 0.143, 9.41, 0.0, 7.13, 0.330},    // FP32
+                                       {0.360, 0.210, 24.3, 0.0, 5.46, 0.416},    // split BF16
+                                       {0.0584, 0.098, 1.23, 28.0, 0.0063, 0.108}};  // half stencil, up to 4
+    static const ListCost list[5] = {{0.107, 0.0479, 27.0, 20.8, 5.56, 0.203},
+                                     {0.329, 0.0038, 25.3, 17.9, 14.1, 0.193},
+                                     {0.215, 0.0079, 33.9, 12.0, 1.60, 0.225},
+                                     {0.241, 0.0044, 39.7, 9.19, 0.0, 0.236},
+                                     {0.136, 0.0369, 4.45, 0.0, 1.40, 0.119}};
+    const double ks = path == SJ_FP64_MFMA ? g.da >> 2 : g.dp >> 2;
+    const int k = use == HitUse::HALF ? 4 : path == SJ_FP32_MFMA ? 2 : path == SJ_BF16X3_MFMA ? 3 : ks <= 4 ? 0 : 1;
+    const double n = (double)g.n, s = (double)g.sample.pairs / n, c = (double)g.cand_items / n;
+    const double fill = n / (16.0 * (double)g.items);
+    const TilesCost &T = tiles[k];
+    const ListCost &L = list[k];
+    Costs r;
+    r.tiles = 1e-9 * n * (c * (T.c + T.ck * ks) + T.p * s);
+    r.list = 1e-9 * n * (c / fill * (L.c + L.ck * ks) + s * (L.p + L.q * std::max(0.0, s / 300.0 - 1.0)));
+    if (alone) {
+        r.tiles += 1e-6 * c * (T.w + T.wk * ks) + T.t;
+        r.list += 1e-6 * c * L.w + L.t;
     }
-    return gain >= cost;
+    return r;
+}
+
+static bool hits_pay(const Grid &g, sj_path path, HitUse use) {
+    if (tl_hits_always) return tl_hits_always > 0;
+    const int ks = path == SJ_FP64_MFMA ? g.da >> 2 : g.dp >> 2;
+    const bool few = path == SJ_FP64_MFMA && ks <= 4;
+    if (use == HitUse::COUNT) return !few || (double)g.cand_items * (2 * ks + 1) >= 30.0 * (double)g.sample.pairs;
+    if (use == HitUse::HALF && !few) return true;
+    const Costs r = hits_costs(g, path, use, true);
+    return r.list < hit_lean(g) * r.tiles;
 }
 
 // Pairs of the result that the list is laid out for: the sample's, and what
@@ -1514,6 +1565,8 @@ static void hit_layout(Grid &g, char *p) {
     g.hit_item_block = reinterpret_cast<int32_t *>(p);
     p += align_up(g.items * sizeof(int32_t));
     g.hit_span = reinterpret_cast<int2 *>(p);
+    p += align_up((size_t)g.nblocks * g.nranges * sizeof(int2));
+    g.hit_tally = reinterpret_cast<unsigned long long *>(p);
 }
 
 static unsigned box_blocks(const Grid &g) { return (unsigned)((g.items + 15) / 16); }
@@ -1548,7 +1601,7 @@ void hits_free_list(Grid &g, hipStream_t s) {
 
 // Enqueues the count (hits_prepare has made the index): counts into cnt (n + 1
 // entries, zeroed here), pairs into the grid's list when `record` and there is
-// memory for it; ro.ctr zeroed here.
+// memory for it; ro.ctr and the grid's tally zeroed here.
 // most: entries per region that a former run of this count reserved (0: not
 // known).
 void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long long most, RefineOut &ro,
@@ -1558,6 +1611,7 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
     HitOut R{};
     R.cnt = cnt;
     R.ctr = ro.ctr;
+    R.tally = g.hit_tally;
     if (record) {  // (a former list is dropped)
         const unsigned long long cap =
             most ? region_cap(most, kMaskBudget)
@@ -1582,6 +1636,7 @@ void hits_count(Grid &g, sj_path path, int32_t *cnt, bool record, unsigned long 
     }
     fill_zero_many({{cnt, ((size_t)g.n + 1) * sizeof(int32_t)},
                     {R.cursor, R.cursor ? kHitRegions * kHitCursorStride * sizeof(unsigned long long) : 0},
+                    {g.hit_tally, kTallyBytes},
                     {ro.ctr, sizeof(DevCounters)}},
                    s);
     const HitGrid G = hit_grid(g);
@@ -1624,6 +1679,8 @@ bool hits_ensure(Grid &g, sj_path path, RefineOut &ro, hipStream_t s) {
             return false;
         }
         if (!g.hits) return false;
+        hipLaunchKernelGGL(k_hit_fold, dim3(1), dim3(1), 0, s, g.hit_tally, ro.ctr);
+        SJ_HIP(hipGetLastError());
         unsigned long long cur[kHitRegions * kHitCursorStride];
         SJ_HIP(hipMemcpyAsync(cur, g.hit_cursor, sizeof cur, hipMemcpyDeviceToHost, s));
         SJ_HIP(hipStreamSynchronize(s));
@@ -1744,12 +1801,27 @@ static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, bool 
     double work = 0;
     std::map<int, int64_t> blocks;  // by K-step count
     hb.listed_up = 0;
-    int64_t items = 1;
-    for (const Grid *g : grids) items += g->items;
+    // a problem takes the form that it is clearly cheaper in; the others one
+    // form together, since each form has its launches (ms: 64 problems of 1600
+    // points, d = 5, s = 16 0.45 by tiles and 0.38 by list, 0.05 and 0.06 of it work)
+    constexpr double kBatchForm = 0.05;
+    const HitUse use = sym ? HitUse::HALF : HitUse::PAIRS;
+    double tiles = 0, list = 0;
+    std::vector<Costs> costs(grids.size(), Costs{0, 0});
     for (size_t i = 0; i < grids.size(); ++i) {
         const Grid &g = *grids[i];
         if (!hits_fit(g) || !m64_in_range(g)) continue;
-        if (!hits_pay(g, SJ_FP64_MFMA, sym ? HitUse::HALF : HitUse::PAIRS, items)) continue;
+        costs[i] = hits_costs(g, SJ_FP64_MFMA, use, false);
+        if (sym && (g.da >> 2) > 4) costs[i].list = 0;
+        if (tl_hits_always) costs[i] = tl_hits_always > 0 ? Costs{1, 0} : Costs{0, 1};
+        tiles += hit_lean(g) * costs[i].tiles;
+        list += costs[i].list;
+    }
+    for (size_t i = 0; i < grids.size(); ++i) {
+        const Grid &g = *grids[i];
+        const Costs &c = costs[i];
+        if (c.tiles == 0 && c.list == 0) continue;
+        if (!(c.list < 0.5 * c.tiles || (c.list < 2.0 * c.tiles && list < tiles + kBatchForm))) continue;
         hb.probs.push_back((int)i);
         work += hits_work(g);
         blocks[g.da >> 2] += g.nblocks;
@@ -1824,7 +1896,8 @@ static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, bool 
     hb.queue = vs == va.p ? va.release() : vb.release();
     hb.cnt = dev_alloc_n<int32_t>((size_t)hb.rows + 1, s);
     hb.off = dev_alloc_n<int64_t>((size_t)hb.rows + 1, s);
-    hb.cursor = dev_alloc_n<unsigned long long>(kHitRegions * kHitCursorStride, s);
+    hb.cursor = dev_alloc_n<unsigned long long>((kHitRegions + kHitTally) * kHitCursorStride, s);
+    hb.tally = hb.cursor + kHitRegions * kHitCursorStride;
 }
 
 void hit_batch_free(HitBatch &hb, hipStream_t s) {
@@ -1866,13 +1939,14 @@ void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *total
     HitOut R{};
     R.cnt = hb.cnt;
     R.ctr = ctr;
+    R.tally = hb.tally;
     if (record && hb.hits) {
         R.hits = static_cast<int2 *>(hb.hits);
         R.cursor = hb.cursor;
         R.cap = hb.cap;
     }
     fill_zero_many({{hb.cnt, ((size_t)hb.rows + 1) * sizeof(int32_t)},
-                    {hb.cursor, kHitRegions * kHitCursorStride * sizeof(unsigned long long)}},
+                    {hb.cursor, (kHitRegions + kHitTally) * kHitCursorStride * sizeof(unsigned long long)}},
                    s);
     const HitProb *dp = static_cast<const HitProb *>(hb.dev);
     const int P = (int)hb.probs.size();
@@ -1890,7 +1964,7 @@ void hit_batch_count(HitBatch &hb, bool record, DevCounters *ctr, int64_t *total
     // totals and the fullest region: one copy
     int64_t *out = dev_alloc_n<int64_t>(P + 1, s);
     hipLaunchKernelGGL(k_hit_totals, dim3((unsigned)((P + 1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, dp,
-                       hb.off, hb.rows, P, hb.cursor, out);
+                       hb.off, hb.rows, P, hb.cursor, hb.tally, ctr, out);
     SJ_HIP(hipGetLastError());
     std::vector<int64_t> h(P + 1);
     SJ_HIP(hipMemcpyAsync(h.data(), out, (P + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));

@@ -27,6 +27,7 @@ constexpr int64_t kMaskBudget = int64_t(16) << 30;  // largest in-mask buffer (b
 constexpr int kHitMaxD = 64;       // largest d of the hit-list count
 constexpr int kHitRegions = 16;    // regions of a hit list, each with its own cursor
 constexpr int kHitCursorStride = 16;  // cursors 128 bytes apart
+constexpr int kHitTally = 64;      // counters that a hit-list count's blocks share
 constexpr int64_t kLeanLineTable = int64_t(1) << 20;  // largest dense line table of a lean build
 
 // Thread-local error text.
@@ -159,7 +160,7 @@ struct DevCounters {
     unsigned long long max_delta;     // largest band half-width used (bits)
     unsigned long long max_err;       // measure: largest |fast - exact| (bits)
     unsigned long long violations;    // measure: errors above their band
-    unsigned long long met;           // hit-list count: candidate pairs of the halves it takes
+    unsigned long long met;           // hit-list count: candidate pairs of the halves it takes (from its tally)
     unsigned long long spare[2];
 };
 
@@ -312,6 +313,7 @@ struct Grid {
     int2 *hit_span = nullptr;
     int2 *hits = nullptr;
     unsigned long long *hit_cursor = nullptr;
+    unsigned long long *hit_tally = nullptr;  // in hit_index
     unsigned long long hit_cap = 0;
     unsigned long long hit_most = 0;  // entries the last recording count reserved in its fullest region
     int32_t *hit_bin = nullptr;
@@ -512,7 +514,7 @@ struct HitBatch {
     int32_t *queue = nullptr;
     int32_t *cnt = nullptr;        // rows + 1
     int64_t *off = nullptr;        // rows + 1
-    unsigned long long *cursor = nullptr;
+    unsigned long long *cursor = nullptr, *tally = nullptr;
     void *hits = nullptr;
     int32_t *bin = nullptr;
     int64_t rows = 0, blocks = 0, items = 0, total = 0;
@@ -535,7 +537,7 @@ void hit_batch_pairs(HitBatch &hb, const std::vector<int64_t> &pout, int32_t *pa
 // not; once, and not in the static scratch. bytes 0 takes it back.
 extern "C" void sj_test_fail_alloc(size_t bytes, int32_t skip);
 
-// For tests of the hit-list count, on the calling thread: always = 1 takes it
+// For tests of the hit-list count, on the calling thread: always = 1 takes it (-1: never)
 // whatever the number of pairs (where grid, path and work allow it); first > 0
 // = entries per region of a list's first layout. 0, 0 takes it back.
 extern "C" void sj_test_hits(int32_t always, unsigned long long first);

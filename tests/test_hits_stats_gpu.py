@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from tests.gpu_util import gpu_join, log
+from tests.test_hits_rule_gpu import _hits
 
 pytestmark = pytest.mark.gpu
 
@@ -30,7 +31,8 @@ def test_pairs_met(path, n, sc, symmetric):
     rng = np.random.default_rng(n)
     X = rng.random((n, 8))
     log(f"[hits stats] path={path} n={n} sc={sc} symmetric={symmetric}")
-    st = gpu_join(X, 0.2, path, want_pairs=False, index_dims=-1, short_circuit=sc, symmetric=symmetric)["stats"]
+    with _hits():
+        st = gpu_join(X, 0.2, path, want_pairs=False, index_dims=-1, short_circuit=sc, symmetric=symmetric)["stats"]
     assert st["cand_eval"] == _met(n)
     if sc == -1 or path != "fp64_mfma":
         assert st["tiles_pruned"] == 0
@@ -46,15 +48,16 @@ def test_batch_counts_each_form(symmetric):
     rng = np.random.default_rng(4)
     sets = [(rng.random((9001, 8)), 0.3), (rng.random((4000, 3)), 0.1), (rng.random((7000, 6)), 0.25)]
     pts = [torch.from_numpy(x).to("cuda:0") for x, _ in sets]
-    alone = {"fp64_mfma": 0, "fp64_valu": 0}
-    for (x, e), p in zip(sets, pts):
-        sj = SelfJoin(p, e, symmetric=symmetric)
-        for path in alone:
-            alone[path] += sj.count(path)[2]["cand_eval"]
-        sj.close()
-    assert alone["fp64_mfma"] != alone["fp64_valu"]  # a hit list was kept
-    b = selfjoin_batch_build(pts, [e for _, e in sets], symmetric=symmetric)
-    log(f"[hits stats] batch symmetric={symmetric}")
-    for path in ("fp64_mfma", "fp64_valu", "fp64_mfma"):
-        assert selfjoin_batch_count(b, path)[1]["cand_eval"] == alone[path]
-    selfjoin_batch_free(b)
+    with _hits():  # (a batch may choose otherwise than each problem alone)
+        alone = {"fp64_mfma": 0, "fp64_valu": 0}
+        for (x, e), p in zip(sets, pts):
+            sj = SelfJoin(p, e, symmetric=symmetric)
+            for path in alone:
+                alone[path] += sj.count(path)[2]["cand_eval"]
+            sj.close()
+        assert alone["fp64_mfma"] != alone["fp64_valu"]  # a hit list was kept
+        b = selfjoin_batch_build(pts, [e for _, e in sets], symmetric=symmetric)
+        log(f"[hits stats] batch symmetric={symmetric}")
+        for path in ("fp64_mfma", "fp64_valu", "fp64_mfma"):
+            assert selfjoin_batch_count(b, path)[1]["cand_eval"] == alone[path]
+        selfjoin_batch_free(b)
