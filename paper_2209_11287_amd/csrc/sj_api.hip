@@ -31,13 +31,16 @@ __global__ __launch_bounds__(64) void k_total_to_ctr(const int64_t *total, const
                                                      DevCounters *out) {
     static_assert(kHitRegions <= 64 && kHitTally == 64, "a lane each");
     const int lane = threadIdx.x;
-    unsigned long long most = cursor && lane < kHitRegions ? cursor[lane * kHitCursorStride] : 0;
-    unsigned long long met = tally ? tally[lane * kHitCursorStride] : 0;
-    unsigned long long pruned = tally ? tally[lane * kHitCursorStride + 1] : 0;
-    for (int o = 32; o > 0; o >>= 1) {
-        most = max(most, __shfl_xor(most, o));
-        met += __shfl_xor(met, o);
-        pruned += __shfl_xor(pruned, o);
+    unsigned long long most = 0, met = 0, pruned = 0;
+    if (tally) {
+        if (cursor && lane < kHitRegions) most = cursor[lane * kHitCursorStride];
+        met = tally[lane * kHitCursorStride];
+        pruned = tally[lane * kHitCursorStride + 1];
+        for (int o = 32; o > 0; o >>= 1) {
+            most = max(most, __shfl_xor(most, o));
+            met += __shfl_xor(met, o);
+            pruned += __shfl_xor(pruned, o);
+        }
     }
     if (lane > 0) return;
     DevCounters c = *ctr;
