@@ -127,9 +127,10 @@ typedef struct {
                                K-steps of 4 dimensions. FP64 MFMA: one check
                                after half the K-steps for d <= 16, every k
                                (default 4) K-steps beyond, or, where the count
-                               keeps a hit list (5 <= d <= 64 with enough
-                               candidates), the bounding boxes of 16-point
-                               tiles instead (any value but -1); FP64 VALU: every
+                               keeps a hit list (5 <= d <= 64, enough
+                               candidates, few pairs among them), the bounding
+                               boxes of 16-point tiles instead (any value but
+                               -1); FP64 VALU: every
                                4k (default 4) dimensions for d > 8 (the d <= 8
                                forms keep the query rows in registers and run
                                without checks) */
@@ -352,10 +353,11 @@ sj_status selfjoin_count_noalloc(const double *points, int64_t n, int32_t d, dou
  * replayed. The count pass records every problem's in-masks (up to 64 GiB;
  * beyond, the pairs launch re-runs the tiles), so the pairs launch is one
  * kernel that expands them. On SJ_FP64_MFMA the problems with 5 <= d <= 64
- * (when they hold enough candidates together) are counted on half of their
+ * that have few pairs among many candidates (by a sample that the build draws;
+ * when they hold enough candidates together) are counted on half of their
  * tiles instead, one launch per number of K-steps beside the graph, and their
- * pairs go to one list (up to 64 GiB) that the pairs call orders. With opts->tune, the tuner picks per d the
- * index_dims and the short-circuit setting (timing the FP64 MFMA count on the
+ * pairs go to one list (up to 64 GiB) that the pairs call orders. With
+ * opts->tune, the tuner picks per d the index_dims and the short-circuit setting (timing the FP64 MFMA count on the
  * largest problem of that d; cached in tune_cache), and on the first count
  * the schedule of the tile kernels: persistent grids of the resident waves
  * dealing the items round-robin, or one wave per item. Every choice is
@@ -375,11 +377,12 @@ sj_status selfjoin_batch_build(int32_t B, const double *const *points, const int
                                void *stream, sj_batch **out);
 
 /* totals : host int64[B], |R| of each problem. stats (nullable): ms =
- * ms_refine = device time of the count graph; ms_build = wall time of
- * selfjoin_batch_build (grid builds, queue, in-mask buffer); cand_eval,
- * rechecked, tiles_pruned over all problems (cand_eval of a half-stencil
- * batch: counted by one extra pass over the ranges on the first call that
- * asks for stats); cand_ref = -1. */
+ * ms_refine = device time of the count (its graph and the hit-list launches);
+ * ms_build = wall time of selfjoin_batch_build (grid builds, queues; the
+ * in-mask buffer is made by the first count); cand_eval, rechecked,
+ * tiles_pruned over all problems (cand_eval of a half-stencil batch: counted
+ * by one extra pass over the ranges on the first call that asks for stats);
+ * cand_ref = -1. */
 sj_status selfjoin_batch_count(sj_batch *b, sj_path path, int64_t *totals, sj_stats *stats,
                                void *stream);
 

@@ -1468,7 +1468,7 @@ struct Costs {
 // Near the line the list is taken for up to 100 pairs a point: its count alone,
 // which is all that some callers ask for, is the cheaper one there (mixture of 91k
 // points, d = 13, s = 28: 0.16 and 0.27 ms).
-static double hit_lean(const Grid &g) { return g.sample.pairs <= 100ull * (unsigned long long)g.n ? 1.15 : 1.0; }
+static double list_favour(const Grid &g) { return g.sample.pairs <= 100ull * (unsigned long long)g.n ? 1.15 : 1.0; }
 
 // alone: the launches and the walk are this grid's alone (not a batch's).
 static Costs hits_costs(const Grid &g, sj_path path, HitUse use, bool alone) {
@@ -1505,7 +1505,7 @@ static bool hits_pay(const Grid &g, sj_path path, HitUse use) {
     if (use == HitUse::COUNT) return !few || (double)g.cand_items * (2 * ks + 1) >= 30.0 * (double)g.sample.pairs;
     if (use == HitUse::HALF && !few) return true;
     const Costs r = hits_costs(g, path, use, true);
-    return r.list < hit_lean(g) * r.tiles;
+    return r.list < list_favour(g) * r.tiles;
 }
 
 // Pairs of the result that the list is laid out for: the sample's, and what
@@ -1814,7 +1814,7 @@ static void hit_batch_make(HitBatch &hb, const std::vector<Grid *> &grids, bool 
         costs[i] = hits_costs(g, SJ_FP64_MFMA, use, false);
         if (sym && (g.da >> 2) > 4) costs[i].list = 0;
         if (tl_hits_always) costs[i] = tl_hits_always > 0 ? Costs{1, 0} : Costs{0, 1};
-        tiles += hit_lean(g) * costs[i].tiles;
+        tiles += list_favour(g) * costs[i].tiles;
         list += costs[i].list;
     }
     for (size_t i = 0; i < grids.size(); ++i) {
