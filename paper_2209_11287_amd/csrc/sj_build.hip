@@ -95,13 +95,10 @@ __global__ __launch_bounds__(kThreads) void k_build_readback(const int32_t *__re
     __shared__ PairSample ssam[kThreads];
     double m = 0.0;
     unsigned long long c = 0;
-    PairSample ps{0, 0};
+    PairSample ps{0, 0, 0};
     for (int64_t i = threadIdx.x; i < n_nmax; i += kThreads) m = fmax(m, nmax_part[i]);
     for (int i = threadIdx.x; i < n_cand; i += kThreads) c += cand_part[i];
-    for (int i = threadIdx.x; i < n_sample; i += kThreads) {
-        ps.pairs += sample_part[i].pairs;
-        ps.hits += sample_part[i].hits;
-    }
+    for (int i = threadIdx.x; i < n_sample; i += kThreads) add_sample(ps, sample_part[i]);
     smax[threadIdx.x] = m;
     ssum[threadIdx.x] = c;
     ssam[threadIdx.x] = ps;
@@ -110,8 +107,7 @@ __global__ __launch_bounds__(kThreads) void k_build_readback(const int32_t *__re
         if ((int)threadIdx.x < w) {
             smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + w]);
             ssum[threadIdx.x] += ssum[threadIdx.x + w];
-            ssam[threadIdx.x].pairs += ssam[threadIdx.x + w].pairs;
-            ssam[threadIdx.x].hits += ssam[threadIdx.x + w].hits;
+            add_sample(ssam[threadIdx.x], ssam[threadIdx.x + w]);
         }
         __syncthreads();
     }
@@ -1629,7 +1625,7 @@ __device__ __forceinline__ PairSample sample_pairs(const double *__restrict__ xs
                                                    unsigned waves) {
     const int lane = threadIdx.x & 63;
     const int64_t lo = nitems * w / waves, hi = nitems * (w + 1) / waves;
-    if (hi <= lo) return PairSample{0, 0};  // whole wave
+    if (hi <= lo) return PairSample{0, 0, 0};  // whole wave
     const int64_t it = lo + mix32(w + 0x9e3779b9u) % (unsigned)(hi - lo);
     const Item I = items[it];
     const int nq = I.qend - I.qbegin;
@@ -1645,7 +1641,7 @@ __device__ __forceinline__ PairSample sample_pairs(const double *__restrict__ xs
         if (lane >= o) incl += y;
     }
     const int total = __builtin_amdgcn_readlane(incl, 31);
-    if (nq <= 0 || total <= 0) return PairSample{0, 0};
+    if (nq <= 0 || total <= 0) return PairSample{0, 0, 0};
     const unsigned h = mix32(w * 64 + lane), g = mix32(h ^ 0x85ebca6bu);
     const int q = I.qbegin + (int)(((h >> 8) * (unsigned long long)nq) >> 24);
     const int pos = (int)((g * (unsigned long long)(unsigned)total) >> 32);
@@ -1673,7 +1669,11 @@ __device__ __forceinline__ PairSample sample_pairs(const double *__restrict__ xs
     const unsigned hits = (unsigned)__popcll(__ballot(acc <= eps2));
     // the share of the wave's items: (hi - lo) nq total pairs, hits of 64 drawn within eps
     const unsigned long long all = (unsigned long long)((hi - lo) * nq) * (unsigned)total;
-    return PairSample{(all >> 6) * hits + (((all & 63u) * hits) >> 6), hits};
+    const unsigned long long pairs = (all >> 6) * hits + (((all & 63u) * hits) >> 6);
+    // dense where the draw shows it (8 of 64), not where one hit stands for many
+    const unsigned long long each = ((unsigned long long)(unsigned)total * hits) >> 6;  // pairs a point
+    const unsigned over = hits >= 8 && each > 300 ? (unsigned)min(768ull, (each - 300) * 256 / 300) : 0u;
+    return PairSample{pairs, (pairs >> 8) * over, hits};
 }
 
 struct SampleArgs {
@@ -1702,11 +1702,8 @@ __global__ __launch_bounds__(kThreads) void k_item_tiles(const Range *__restrict
         if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
         __syncthreads();
         if (threadIdx.x == 0) {
-            PairSample t{0, 0};
-            for (int k = 0; k < kThreads / 64; ++k) {
-                t.pairs += part[k].pairs;
-                t.hits += part[k].hits;
-            }
+            PairSample t{0, 0, 0};
+            for (int k = 0; k < kThreads / 64; ++k) add_sample(t, part[k]);
             S.part[b] = t;
         }
         return;
@@ -2731,23 +2728,15 @@ __global__ __launch_bounds__(kThreads) void k_seg_sample_sum(const SegProb *__re
                                                              PairSample *__restrict__ out) {
     __shared__ PairSample red[kThreads / 64];
     const int p = blockIdx.x;
-    PairSample t{0, 0};
+    PairSample t{0, 0, 0};
     const int waves = seg_sample_waves(P[p].n, P[p].d);
-    for (int i = threadIdx.x; i < waves; i += kThreads) {
-        t.pairs += part[(int64_t)p * kSegSampleWaves + i].pairs;
-        t.hits += part[(int64_t)p * kSegSampleWaves + i].hits;
-    }
-    for (int sh = 32; sh > 0; sh >>= 1) {
-        t.pairs += __shfl_xor(t.pairs, sh);
-        t.hits += __shfl_xor(t.hits, sh);
-    }
+    for (int i = threadIdx.x; i < waves; i += kThreads) add_sample(t, part[(int64_t)p * kSegSampleWaves + i]);
+    for (int sh = 32; sh > 0; sh >>= 1)
+        add_sample(t, PairSample{__shfl_xor(t.pairs, sh), __shfl_xor(t.dense, sh), __shfl_xor(t.hits, sh)});
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) {
-            t.pairs += red[w].pairs;
-            t.hits += red[w].hits;
-        }
+        for (int w = 1; w < kThreads / 64; ++w) add_sample(t, red[w]);
         out[p] = t;
     }
 }
@@ -3113,7 +3102,7 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
     SJ_HIP(hipGetLastError());
     // ---- one host sync: per-problem items, tiles, norms, candidates ----
     std::vector<int64_t> h_it(B + 1), h_tiles(B + 1), h_bl(B + 1);
-    std::vector<unsigned long long> h_nmax(B), h_cand(3 * (size_t)B);
+    std::vector<unsigned long long> h_nmax(B), h_cand(4 * (size_t)B);
     int32_t herr = 0;
     SJ_HIP(hipMemcpyAsync(h_it.data(), it_off, (B + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SJ_HIP(hipMemcpyAsync(h_tiles.data(), ptiles, (B + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -3143,7 +3132,7 @@ bool build_grids_segmented(const std::vector<SegInput> &in, std::vector<Grid *> 
         g.nmax = nm;
         g.cand_items = (int64_t)h_cand[p];
         g.cand_ref = -1;
-        g.sample = PairSample{h_cand[B + 2 * (size_t)p], h_cand[B + 2 * (size_t)p + 1]};
+        std::memcpy(&g.sample, &h_cand[B + 3 * (size_t)p], sizeof g.sample);
         g.samples = 64 * std::min<int64_t>(g.items, seg_sample_waves(g.n, g.d));
         g.blocks = blocks + h_bl[p];  // global item indices: item_base below
         g.nblocks = h_bl[p + 1] - h_bl[p];

@@ -1443,9 +1443,11 @@ constexpr double kHitWork = 0x1p24;
 // the fill f of the work items (points over 16 times the items: an item is a
 // tile here, the other tiles pack their candidates):
 //   tiles ms = n (C (c + ck KS) + p s) 1e-9 + C (w + wk KS) 1e-6 + t
-//   list  ms = n (C / f (c + ck KS) + s (p + q max(0, s / 300 - 1))) 1e-9 + w C 1e-6 + t
+//   list  ms = n (C / f (c + ck KS) + s (p + q min(3, max(0, s / 300 - 1)))) 1e-9 + w C 1e-6 + t
 // (w, wk: one wave's walk over its candidates, which few items leave bare; q: the
-// ordering of long bins). Least squares over 461 joins (count and pairs; 5000 to
+// ordering of long bins, by the mean s or point by point as the sample has it,
+// whichever is more: 1000 points at one place among 200k, ten times, d = 5, 1.06 ms
+// by tiles and 1.62 by list). Least squares over 461 joins (count and pairs; 5000 to
 // 1M points, uniform, exponential and mixture, d = 5 .. 64, s = 8 .. 800), each
 // mostly within 30 %; taking the smaller estimate costs 1.5 % over the faster of
 // the two in FP64 with up to 4 K-steps (tiles shared through LDS; the forms
@@ -1481,7 +1483,7 @@ static Costs hits_costs(const Grid &g, sj_path path, HitUse use, bool alone) {
                                      {0.329, 0.0038, 25.3, 17.9, 14.1, 0.193},
                                      {0.215, 0.0079, 33.9, 12.0, 1.60, 0.225},
                                      {0.241, 0.0044, 39.7, 9.19, 0.0, 0.236},
-                                     {0.136, 0.0369, 4.45, 0.0, 1.40, 0.119}};
+                                     {0.136, 0.0369, 4.45, 1.0, 1.40, 0.119}};
     const double ks = path == SJ_FP64_MFMA ? g.da >> 2 : g.dp >> 2;
     const int k = use == HitUse::HALF ? 4 : path == SJ_FP32_MFMA ? 2 : path == SJ_BF16X3_MFMA ? 3 : ks <= 4 ? 0 : 1;
     const double n = (double)g.n, s = (double)g.sample.pairs / n, c = (double)g.cand_items / n;
@@ -1490,7 +1492,8 @@ static Costs hits_costs(const Grid &g, sj_path path, HitUse use, bool alone) {
     const ListCost &L = list[k];
     Costs r;
     r.tiles = 1e-9 * n * (c * (T.c + T.ck * ks) + T.p * s);
-    r.list = 1e-9 * n * (c / fill * (L.c + L.ck * ks) + s * (L.p + L.q * std::max(0.0, s / 300.0 - 1.0)));
+    const double even = s * std::min(3.0, std::max(0.0, s / 300.0 - 1.0));
+    r.list = 1e-9 * n * (c / fill * (L.c + L.ck * ks) + s * L.p + L.q * std::max(even, (double)g.sample.dense / n));
     if (alone) {
         r.tiles += 1e-6 * c * (T.w + T.wk * ks) + T.t;
         r.list += 1e-6 * c * L.w + L.t;

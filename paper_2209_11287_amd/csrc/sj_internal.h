@@ -165,11 +165,18 @@ struct DevCounters {
 };
 
 // A sample of candidate pairs drawn by the build (d = 5 .. 64): the pairs within
-// eps that it stands for (ordered, the points' own included), and the number
-// of drawn ones.
+// eps that it stands for (ordered, the points' own included); of the points with
+// more than 300 pairs, their pairs times the excess over 300 in units of 300, at
+// most 3; and the number of drawn pairs within eps.
 struct PairSample {
-    unsigned long long pairs, hits;
+    unsigned long long pairs, dense, hits;
 };
+
+__host__ __device__ inline void add_sample(PairSample &t, const PairSample &v) {
+    t.pairs += v.pairs;
+    t.dense += v.dense;
+    t.hits += v.hits;
+}
 
 // Candidate range of a work item: the union of the neighbouring cells of its
 // first and last cell along one offset of the leading indexed dimensions.
@@ -258,7 +265,7 @@ struct Grid {
     int64_t nblocks = 0;
     int64_t cand_ref = -1;   // C_ref (lazily computed; -1 = not yet)
     int64_t cand_items = 0;  // candidate pairs the work items evaluate
-    PairSample sample{0, 0}; // guess of the result's size (d = 5 .. 64)
+    PairSample sample{0, 0, 0};  // guess of the result's size (d = 5 .. 64)
     int64_t samples = 0;     // pairs it drew
     double nmax = 0;       // max squared norm of the centred rows of xa
     // Dimension order of the distance tiles (xa, the low-precision tiles):
