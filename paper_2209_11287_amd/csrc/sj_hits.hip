@@ -1316,10 +1316,14 @@ __global__ __launch_bounds__(kThreads) void k_hit_cost(const HitProb *__restrict
 
 // The tally of a count, added to its counters.
 __device__ __forceinline__ void hit_fold(const unsigned long long *__restrict__ tally, DevCounters *ctr) {
+    unsigned long long met = 0, pruned = 0;
+#pragma unroll 16
     for (int r = 0; r < kHitTally; ++r) {
-        ctr->met += tally[r * kHitCursorStride];
-        ctr->pruned += tally[r * kHitCursorStride + 1];
+        met += tally[r * kHitCursorStride];
+        pruned += tally[r * kHitCursorStride + 1];
     }
+    ctr->met += met;
+    ctr->pruned += pruned;
 }
 
 __global__ void k_hit_fold(const unsigned long long *__restrict__ tally, DevCounters *ctr) { hit_fold(tally, ctr); }
@@ -2001,7 +2005,7 @@ bool hit_batch_bins(HitBatch &hb, hipStream_t s) {
     try {
         DevBuf<int32_t> fill(bp.nfill, s);
         DevBuf<int32_t> bin((size_t)std::max<int64_t>(hb.total, 1), s);
-        fill_zero(fill.p, bp.nfill * sizeof(int32_t), s);
+        fill_zero_many({{fill.p, bp.nfill * sizeof(int32_t)}}, s);
         make_bins(bp, static_cast<const int2 *>(hb.hits), hb.cursor, hb.cap, hb.most, hb.off, hb.rows, fill.p, bin.p, s);
         hb.bin = bin.release();
     } catch (const OomError &) {
