@@ -429,8 +429,9 @@ struct CountRun {
 // Computes per-query counts with `path` (range-checked) into the handle's
 // cache (sorted order), their exclusive prefix sums and the total; with
 // per_point also the counts in the input order. tm: the call ends with this.
+// d2: the same call emits pairs with distances.
 static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipStream_t s,
-                           int32_t *per_point = nullptr, CallTimer *tm = nullptr) {
+                           int32_t *per_point = nullptr, CallTimer *tm = nullptr, bool d2 = false) {
     g.have_counts = false;  // until this pass is through
     if (!g.cnt) g.cnt = dev_alloc_n<int32_t>((size_t)g.n + 1, s);
     if (!g.off) g.off = dev_alloc_n<int64_t>((size_t)g.n + 1, s);
@@ -445,7 +446,8 @@ static void compute_counts(Grid &g, sj_path path, bool timed, CountRun &cr, hipS
     g.masks_valid = false;
     g.lp_masks_valid = false;
     g.hits_valid = false;
-    ro.record_hits = !sym && !g.lean && hits_usable(g, path, HitUse::PAIRS) && hits_prepare(g, s);
+    ro.record_hits = !sym && !g.lean && hits_usable(g, path, d2 ? HitUse::DISTANCES : HitUse::PAIRS) &&
+                     hits_prepare(g, s);
     // without a list: where no in-masks would be kept either
     const bool no_masks = g.lean || (fp64 && g.tiles * 32 > kMaskBudget);
     ro.hits = ro.record_hits || (sym && hits_usable(g, path, HitUse::HALF) && hits_prepare(g, s)) ||
@@ -766,7 +768,7 @@ sj_status selfjoin_knn(sj_grid *gh, sj_path path, int32_t k, int64_t pair_budget
     AllocScope scope(g.hook);
     const sj_path run = path_for(g, path);  // checked before anything is allocated
     CountRun cr;
-    if (!g.have_counts) compute_counts(g, run, false, cr, s);
+    if (!g.have_counts) compute_counts(g, run, false, cr, s, nullptr, nullptr, true);
     const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(g.total, pair_budget ? pair_budget : kKnnBudget));
     DevBuf<int32_t> pairs(2 * (size_t)cap, s);
     DevBuf<double> pd2((size_t)cap, s);
@@ -846,7 +848,7 @@ sj_status selfjoin_pairs(sj_grid *gh, sj_path path, int64_t cursor, int32_t *pai
     }
     CallTimer tm(stats != nullptr, s);
     CountRun cr;
-    if (!g.have_counts) compute_counts(g, run, stats != nullptr, cr, s);
+    if (!g.have_counts) compute_counts(g, run, stats != nullptr, cr, s, nullptr, nullptr, d2 != nullptr);
     const ChunkPlan p = (cursor == 0 && capacity >= g.total) ? whole_plan(g) : plan_chunk(g, cursor, capacity, s);
     if (p.too_small) {
         *written = p.written;

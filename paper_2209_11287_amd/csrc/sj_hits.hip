@@ -1473,7 +1473,10 @@ struct Costs {
 
 // Near the line the list is taken for up to 100 pairs a point: its count alone,
 // which is all that some callers ask for, is the cheaper one there (mixture of 91k
-// points, d = 13, s = 28: 0.16 and 0.27 ms).
+// points, d = 13, s = 28: 0.16 and 0.27 ms). Where the same call emits distances, which
+// the in-masks' rows gather points for, the forms meet later (hits_pay; mixture of
+// 200k, d = 16, 10 neighbours, s = 150 3.0 ms by the list, 3.6 by in-masks, s = 220 4.2
+// and 4.7, where pairs alone take 1.57 and 1.14, 1.95 and 1.26; d = 8, s = 150 2.27 and 2.11).
 static double list_favour(const Grid &g) { return g.sample.pairs <= 100ull * (unsigned long long)g.n ? 1.15 : 1.0; }
 
 // alone: the launches and the walk are this grid's alone (not a batch's).
@@ -1512,7 +1515,7 @@ static bool hits_pay(const Grid &g, sj_path path, HitUse use) {
     if (use == HitUse::COUNT) return !few || (double)g.cand_items * (2 * ks + 1) >= 30.0 * (double)g.sample.pairs;
     if (use == HitUse::HALF && !few) return true;
     const Costs r = hits_costs(g, path, use, true);
-    return r.list < list_favour(g) * r.tiles;
+    return r.list < std::max(list_favour(g), few && use == HitUse::DISTANCES ? 1.6 : 0.0) * r.tiles;
 }
 
 // Pairs of the result that the list is laid out for: the sample's, and what
@@ -1550,7 +1553,7 @@ static double listed_up(const Grid &g) { return std::max(0.0, 0.5 * (pairs_up(g)
 bool hits_usable(const Grid &g, sj_path path, HitUse use) {
     if (path != SJ_FP64_MFMA && path != SJ_FP32_MFMA && path != SJ_BF16X3_MFMA) return false;
     if (!hits_fit(g) || hits_work(g) < kHitWork || !hits_pay(g, path, use)) return false;
-    if (use != HitUse::PAIRS) return true;
+    if (use != HitUse::PAIRS && use != HitUse::DISTANCES) return true;
     // a join whose list would not fit keeps in-masks, if they do
     const double waves = (double)g.nblocks * hit_segments(g) * kWaves;
     return list_entries(listed_up(g), waves) * sizeof(int2) <= (double)kMaskBudget;

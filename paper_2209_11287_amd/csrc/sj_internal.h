@@ -495,8 +495,9 @@ void lowp_measure(Grid &g, sj_path path, double *max_err, double *max_band, int6
 
 // Hit-list count (sj_hits.hip).
 // What a hit-list count is asked for: counts and, by a pairs call, the list;
-// counts alone; counts that the half-stencil tiles would give otherwise.
-enum class HitUse { PAIRS, COUNT, HALF };
+// the same with distances, known before the count (kNN, a pairs call without
+// one); counts alone; counts that the half-stencil tiles would give otherwise.
+enum class HitUse { PAIRS, DISTANCES, COUNT, HALF };
 bool hits_usable(const Grid &g, sj_path path, HitUse use);
 size_t hits_lean_bytes(int64_t n, int32_t d);
 bool hits_prepare(Grid &g, hipStream_t s);

@@ -119,6 +119,30 @@ def test_dense_set_keeps_in_masks():
     sj.close()
 
 
+@pytest.mark.parametrize("eps", [0.08, 0.09, 0.1])
+@pytest.mark.parametrize("path", ["fp64_mfma", "fp32_mfma"])
+def test_distances_asked_for_at_once(path, eps):
+    """A pairs call with distances (56, 148 and 303 pairs a point) and without a
+    count before it takes the list further than a count does."""
+    import torch
+
+    from paper_2209_11287_amd import SelfJoin, selfjoin_pairs
+    X = torch.from_numpy(gen.gaussian_mixture(100000, 16, seed=3)).to("cuda:0")
+    log(f"[hits rule] distances at once path={path} eps={eps}")
+    out = []
+    for counted in (True, False):
+        sj = SelfJoin(X, eps)
+        if counted:
+            total = sj.count(path)[0]
+        pairs = torch.empty((total, 2), dtype=torch.int32, device="cuda:0")
+        d2 = torch.empty(total, dtype=torch.float64, device="cuda:0")
+        assert selfjoin_pairs(sj.grid, path, 0, pairs, d2)[0] == total
+        sj.close()
+        out.append((pairs, d2))
+    (a, ad), (b, bd) = out
+    assert torch.equal(a, b) and torch.equal(ad, bd)
+
+
 def test_large_set_keeps_its_list():
     """33.6M points one unit apart on a line, 3 pairs a point: a first layout of
     256 pairs a point would pass the list's budget, the list itself does not. At
